@@ -18,13 +18,14 @@
 // M and N are multiples of the 128 x 128 block tile and K of 128 (two 64-deep tiles): the caller (muon.hip) keeps every matrix
 // in zero-padded workspace buffers, and zero rows and columns stay zero through the iteration.
 //
-// Tiling: 128 x 128 block tile with 4 waves in a 2 x 2 grid (each wave 64 x 64 = 2 x 2 accumulators of
-// v_mfma_f32_32x32x16_bf16, fp32 accumulation); where the launch has enough of them to fill the compute units,
+// Tiling: 128 x 128 block tile with 4 waves in a 2 x 2 grid (each wave 64 x 64 = 4 x 4 accumulators of
+// v_mfma_f32_16x16x32_bf16, fp32 accumulation); where the launch has enough of them to fill the compute units,
 // 256 x 256 tiles with 8 waves in a 4 x 2 grid (each 64 x 128).  One launch can cover a batch of equal-shaped
 // products.  Operand tiles, 64 deep, are loaded from global memory straight into LDS (global_load_lds_dwordx4, no
-// staging registers), swizzled against bank conflicts, double-buffered; the fragment reads of the next 16-deep
-// slice overlap the current slice's multiplications.  Workgroups are dealt to the 8 XCDs in turn, so block ids are
-// remapped to give each XCD (one L2 each) a contiguous band of output tiles.
+// staging registers), swizzled against bank conflicts, into a ring of five: see the main loop.  Workgroups are dealt
+// to the 8 XCDs in turn, so block ids are remapped to give each XCD (one L2 each) a contiguous band of output tiles.
+
+#include <utility>
 
 #include "muon_internal.h"
 
@@ -32,7 +33,7 @@ namespace adagc {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
 
@@ -105,40 +106,62 @@ __device__ __forceinline__ TilePlace place_tile(int b, int all_tiles, int M, int
 // nothing is moved across this point by the compiler's instruction scheduler
 #define ADAGC_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 
-// 16 bytes per lane from global memory straight into LDS: lane i's data lands at lds_dst + 16 i (lds_dst: the same in
-// all lanes).  The instruction takes the LDS byte address from M0, and wants one wait state after M0 is written; M0 is
-// put back afterwards, so the compiler's own uses of it are not disturbed.
+// Wait for this wave's LDS reads, then meet the workgroup's other waves.  Unlike __syncthreads this leaves the loads
+// into LDS that are still on their way alone.
+__device__ __forceinline__ void barrier_keeping_loads()
+{
+    __builtin_amdgcn_s_waitcnt(0xF | (3 << 14) | (7 << 4) | (0 << 8));
+    __builtin_amdgcn_s_barrier();
+    ADAGC_SCHED_FENCE();
+}
+
+// f(integral_constant 0), ..., f(integral_constant N-1)
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f)
+{
+    static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
+
+// 16 bytes per lane from global memory straight into LDS: lane i's data, at base + off_i bytes (base: the same in all
+// lanes), lands at lds_dst + 16 i (lds_dst: the same in all lanes).  The instruction takes the LDS byte address from
+// M0, and wants one wait state after M0 is written; M0 is put back afterwards, so the compiler's own uses of it are not
+// disturbed.
 // Written as inline assembly rather than through the compiler's builtin so that the compiler does not track these
 // loads: it would count each as outstanding in both of its memory counters ("flat" access) and, while one is, turn
 // every wait for an LDS read into a wait for all LDS reads, which serialises the fragment reads with the
 // multiplications.  The waits for these loads are explicit (ADAGC_WAIT_VMEM) wherever their data is needed.
-__device__ __forceinline__ void load_to_lds_16(const void* src, const uint16_t* lds_dst)
+__device__ __forceinline__ void load_to_lds_16(const void* base, uint32_t off, const uint16_t* lds_dst)
 {
     const uint32_t lds_addr = (uint32_t)reinterpret_cast<uintptr_t>(lds_dst);      // low half of the flat address = LDS offset
     uint32_t saved_m0;
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off\n\ts_mov_b32 m0, %0"
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b32 m0, %0"
                  : "=&s"(saved_m0)
-                 : "s"(lds_addr), "v"(src)
+                 : "s"(lds_addr), "v"(off), "s"(base)
                  : "memory");
 }
 
 // Epilogue of a workgroup: bf16(alpha acc + beta D) to Ct and C, staged through LDS so that every global access is a
 // 16-byte vector per lane along a row of the array it touches.  (In the accumulator layout a lane holds 4 consecutive
-// rows of one column and 32 lanes hold 32 columns: stored directly, that is 8 bytes per lane for Ct and D, each in a
+// rows of one column and 16 lanes hold 16 columns: stored directly, that is 8 bytes per lane for Ct and D, each in a
 // different cache line, and 2 bytes per lane for C.)
 //
 // The staging tile T holds the BT x BT result transposed, T[c][r] = result(r, c), as Ct and Dt do: row c of T is BT
 // contiguous elements of global row tile_n BT + c of Ct.  Within a row the 16-byte chunks are permuted: chunk g sits
 // at position g ^ f(c), f(c) = (c ^ (c / chunks)) mod chunks, which spreads over the LDS banks both the accumulator-
-// layout accesses (32 lanes = 32 consecutive c, one r) and the reads of the C pass (8 consecutive c at a time).
+// layout accesses (16 lanes = 16 consecutive c, one r) and the reads of the C pass (8 consecutive c at a time).
 //   1. Dt's tile is loaded into T (global_load_lds, the permutation applied on the global side);
 //   2. every lane reads the D values of its accumulator elements from T, and writes the rounded results back to the
 //      same places;
 //   3. T is written out row by row to Ct, and, gathered by columns, row by row to C.
-// Accumulator register r of lane l is element (row (r/4)*8 + (l/32)*4 + r%4, column l%32) of its 32 x 32 block.
+// Accumulator register r of lane l is element (row (l/16)*4 + r, column l%16) of its 16 x 16 block.
 // On entry no wave reads LDS any more (all are past the main loop's last barrier).
 template <int BT, int kMI, int kNI, bool SYM, int kWaves>
-__device__ __forceinline__ void store_result(uint16_t* T, const f32x16 (&acc)[kMI][kNI], int lane, int wave, int wave_row, int wave_col,
+__device__ __forceinline__ void store_result(uint16_t* T, const f32x4 (&acc)[kMI][kNI], int lane, int wave, int wave_row, int wave_col,
                                              int tile_m, int tile_n, float alpha, float beta, const uint16_t* __restrict__ Dt,
                                              int lddt, uint16_t* __restrict__ C, int ldc, uint16_t* __restrict__ Ct, int ldct)
 {
@@ -159,37 +182,33 @@ __device__ __forceinline__ void store_result(uint16_t* T, const f32x16 (&acc)[kM
             const int first = (u * kWaves + wave) * kRowsPerInst;
             const int c = first + rw_row;
             const int g = rw_pos ^ f(c);
-            load_to_lds_16(Dt + (col0_g + c) * lddt + row0_g + g * 8, T + first * BT);
+            load_to_lds_16(Dt + (col0_g + first) * lddt + row0_g, (uint32_t)(rw_row * lddt + g * 8) * 2u, T + first * BT);
         }
         ADAGC_WAIT_VMEM(0);
         __syncthreads();
     }
-    const int col_in = lane & 31;
-    const int row_in = (lane >> 5) * 4;
+    const int col_in = lane & 15;
+    const int row_in = (lane >> 4) * 4;
 #pragma unroll
     for (int i = 0; i < kMI; ++i)
 #pragma unroll
         for (int j = 0; j < kNI; ++j) {
-            const int c = wave_col + j * 32 + col_in;
+            const int c = wave_col + j * 16 + col_in;
             const int fc = f(c);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int r = wave_row + i * 32 + q * 8 + row_in;
-                u32x2v* slot = reinterpret_cast<u32x2v*>(T + c * BT + (((r >> 3) ^ fc) << 3) + (r & 7));
-                float v[4] = {alpha * acc[i][j][q * 4 + 0], alpha * acc[i][j][q * 4 + 1], alpha * acc[i][j][q * 4 + 2],
-                              alpha * acc[i][j][q * 4 + 3]};
-                if (Dt) {
-                    const u32x2v d = *slot;
-                    v[0] = fmaf(beta, bf16_lo(d.x), v[0]);
-                    v[1] = fmaf(beta, bf16_hi(d.x), v[1]);
-                    v[2] = fmaf(beta, bf16_lo(d.y), v[2]);
-                    v[3] = fmaf(beta, bf16_hi(d.y), v[3]);
-                }
-                u32x2v o;
-                o.x = f32_to_bf16_rne(v[0]) | (f32_to_bf16_rne(v[1]) << 16);
-                o.y = f32_to_bf16_rne(v[2]) | (f32_to_bf16_rne(v[3]) << 16);
-                *slot = o;
+            const int r = wave_row + i * 16 + row_in;
+            u32x2v* slot = reinterpret_cast<u32x2v*>(T + c * BT + (((r >> 3) ^ fc) << 3) + (r & 7));
+            float v[4] = {alpha * acc[i][j][0], alpha * acc[i][j][1], alpha * acc[i][j][2], alpha * acc[i][j][3]};
+            if (Dt) {
+                const u32x2v d = *slot;
+                v[0] = fmaf(beta, bf16_lo(d.x), v[0]);
+                v[1] = fmaf(beta, bf16_hi(d.x), v[1]);
+                v[2] = fmaf(beta, bf16_lo(d.y), v[2]);
+                v[3] = fmaf(beta, bf16_hi(d.y), v[3]);
             }
+            u32x2v o;
+            o.x = f32_to_bf16_rne(v[0]) | (f32_to_bf16_rne(v[1]) << 16);
+            o.y = f32_to_bf16_rne(v[2]) | (f32_to_bf16_rne(v[3]) << 16);
+            *slot = o;
         }
     __syncthreads();
     if (Ct) {
@@ -243,17 +262,14 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_bf16_kernel(
     constexpr int kWaves = kGemmThreads / 64;
     constexpr int kWM = kGemmThreads / 128;                // waves in a kWM x 2 grid
     constexpr int kTM = BT / kWM, kTN = BT / 2;            // wave tile
-    constexpr int kMI = kTM / 32, kNI = kTN / 32;          // 32 x 32 accumulators per wave
+    constexpr int kMI = kTM / 16, kNI = kTN / 16;          // 16 x 16 accumulators per wave
     constexpr int kRowsPerLoad = 64 / kVecPerRow;          // tile rows one wave-wide load covers: 8
     constexpr int kLoads = BT / kRowsPerLoad / kWaves;     // loads per wave per operand tile
     static_assert(kWaves % 2 == 0, "the swizzle of a load is taken from the wave's parity");
-    // two buffers of a P and a Q tile each; the epilogue reuses all of it as one BT x BT staging tile (or half of it)
-    __shared__ __attribute__((aligned(16))) uint16_t lds[4 * BT * kBK];
-    uint16_t* const lds_p0 = lds;
-    uint16_t* const lds_q0 = lds + BT * kBK;
-    uint16_t* const lds_p1 = lds + 2 * BT * kBK;
-    uint16_t* const lds_q1 = lds + 3 * BT * kBK;
-    static_assert(4 * BT * kBK >= BT * BT, "the staging tile of the epilogue must fit");
+    // a ring of five operand tiles; the epilogue reuses it as one BT x BT staging tile (or half of it)
+    constexpr int kTileElems = BT * kBK;
+    __shared__ __attribute__((aligned(16))) uint16_t lds[5 * kTileElems];
+    static_assert(5 * kTileElems >= BT * BT, "the staging tile of the epilogue must fit");
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -270,13 +286,13 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_bf16_kernel(
     const uint16_t* Pt = P + (size_t)tile_m * BT * ldp;
     const uint16_t* Qt = Q + (size_t)tile_n * BT * ldq;
 
-    f32x16 acc[kMI][kNI];
+    f32x4 acc[kMI][kNI];
 #pragma unroll
     for (int i = 0; i < kMI; ++i)
 #pragma unroll
         for (int j = 0; j < kNI; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+            for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
 
     // Load u of this wave covers tile rows first .. first + 7, first = (u kWaves + wave) 8; lane i writes LDS row
     // first + i / 8, position i mod 8, so it fetches vector (i mod 8) ^ ((row / 2) mod 8) of that row, and
@@ -286,94 +302,123 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_bf16_kernel(
     const int load_vec = (lane & 7) ^ ((((wave & 1) << 2) + (lane >> 4)) & 7);
     const uint32_t lane_off_p = (uint32_t)(load_row * ldp + load_vec * 8) * 2u;      // bytes
     const uint32_t lane_off_q = (uint32_t)(load_row * ldq + load_vec * 8) * 2u;
-    auto load_tile = [&](int kt, uint16_t* bp, uint16_t* bq) {
-#pragma unroll
-        for (int u = 0; u < kLoads; ++u) {
-            const int first = (u * kWaves + wave) * kRowsPerLoad;
-            const char* row0 = reinterpret_cast<const char*>(Pt + (size_t)first * ldp + kt * kBK);
-            load_to_lds_16(row0 + lane_off_p, bp + first * kBK);
-        }
-#pragma unroll
-        for (int u = 0; u < kLoads; ++u) {
-            const int first = (u * kWaves + wave) * kRowsPerLoad;
-            const char* row0 = reinterpret_cast<const char*>(Qt + (size_t)first * ldq + kt * kBK);
-            load_to_lds_16(row0 + lane_off_q, bq + first * kBK);
-        }
+    auto load_p = [&](int u, int kt, uint16_t* dst) {
+        const int first = (u * kWaves + wave) * kRowsPerLoad;
+        load_to_lds_16(Pt + (size_t)first * ldp + kt * kBK, lane_off_p, dst + first * kBK);
     };
-    // Fragment addressing: lane l holds row l mod 32 of its 32-row block and the 16-byte vector 2 kk + l / 32 of that
-    // row; a block's first row is a multiple of 32, so (row / 2) mod 8 = (l / 2) mod 8.
-    const int frag_row = lane & 31;
-    const int frag_hi = lane >> 5;
+    auto load_q = [&](int u, int kt, uint16_t* dst) {
+        const int first = (u * kWaves + wave) * kRowsPerLoad;
+        load_to_lds_16(Qt + (size_t)first * ldq + kt * kBK, lane_off_q, dst + first * kBK);
+    };
+    // Fragment addressing: lane l holds row l mod 16 of its 16-row block and the 16-byte vector 4 kk + l / 16 of that
+    // row; a block's first row is a multiple of 16, so (row / 2) mod 8 = (l / 2) mod 8.
+    const int frag_row = lane & 15;
+    const int frag_hi = lane >> 4;
     const int frag_x = (lane >> 1) & 7;
-    auto read_frags = [&](const uint16_t* bp, const uint16_t* bq, int kk, bf16x8 (&fa)[kMI], bf16x8 (&fb)[kNI]) {
-        const int pos = ((kk * 2 + frag_hi) ^ frag_x) * 8;
-#pragma unroll
-        for (int i = 0; i < kMI; ++i) fa[i] = *reinterpret_cast<const bf16x8*>(bp + (wm * kTM + i * 32 + frag_row) * kBK + pos);
-#pragma unroll
-        for (int j = 0; j < kNI; ++j) fb[j] = *reinterpret_cast<const bf16x8*>(bq + (wn * kTN + j * 32 + frag_row) * kBK + pos);
-    };
-    auto multiply = [&](const bf16x8 (&fa)[kMI], const bf16x8 (&fb)[kNI]) {
-#pragma unroll
-        for (int i = 0; i < kMI; ++i)
-#pragma unroll
-            for (int j = 0; j < kNI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+    // fragment n of slice kk, in the order p0 q0 p1 q1 ..., then what is left of the longer operand
+    auto read_frag = [&](const uint16_t* bp, const uint16_t* bq, int kk, int n, bf16x8 (&fa)[kMI], bf16x8 (&fb)[kNI]) {
+        const int pos = ((kk * 4 + frag_hi) ^ frag_x) * 8;
+        const int both = 2 * (kMI < kNI ? kMI : kNI);
+        const bool is_p = n < both ? (n & 1) == 0 : kMI > kNI;
+        const int k = n < both ? n >> 1 : n - both / 2;
+        if (is_p) fa[k] = *reinterpret_cast<const bf16x8*>(bp + (wm * kTM + k * 16 + frag_row) * kBK + pos);
+        else fb[k] = *reinterpret_cast<const bf16x8*>(bq + (wn * kTN + k * 16 + frag_row) * kBK + pos);
     };
 
-    // Software pipeline.  A 64-deep tile is four 16-deep slices; the fragments of slice s+1 are read from LDS while
-    // slice s is multiplied (two fragment register sets).  Before the last slice of tile k is multiplied, every wave
-    // has read all of tile k: after the barrier there the tile's buffer is free for the loads of tile k+2, which then
-    // have until the same point of tile k+1 to arrive, and the first slice of tile k+1 is read during the last
-    // multiplications of tile k.
+    // Main loop.  What bounds it: the matrix cores and, on ordinary data, the power the chip may draw (its clock falls
+    // to 1.65 - 1.75 GHz under this loop); the memory latency and the issue of loads have to stay out of the way.
+    //
+    // A 64-deep tile is two 32-deep slices.  While one slice is multiplied, the fragments of the next are read from LDS
+    // into a second register set and loads of later tiles are issued, one access after every few multiplications: a
+    // global load into LDS occupies the issue for about 16 clocks per wave, and with all of them in a row at the head of a
+    // tile nothing was multiplied meanwhile (16384-deep products of 4096 x 4096: 1174 TFLOP/s; spread out 1247).
+    //
+    // LDS holds five operand tiles (160 KB with 256-tiles): the current P and Q, the next P and Q, and the P after that.
+    // While tile k is multiplied, Q of tile k+1 is loaded into the place that P of tile k-1 left and P of tile k+2 into
+    // that of Q of tile k-1: half of the loads have two tiles' time to arrive, and the other half are issued first.  With
+    // two buffers of a P and a Q each, all had less than one tile's (1247 -> 1313 TFLOP/s).
+    //
+    // 16 x 16 x 32 multiplications instead of 32 x 32 x 16: half the accumulator traffic per multiplication, and so a
+    // higher clock (1313 -> 1343 TFLOP/s), and successive multiplications share an operand all the way through
+    // (rows are walked up and down in turn: 1373 -> 1381 on another card).  The results are the same bit for bit.
     bf16x8 fa0[kMI], fb0[kNI], fa1[kMI], fb1[kNI];
-    const int k_tiles = K / kBK;          // even: K is a multiple of 128
-    // slices 0 to 2 of the tile in (cur_p, cur_q); on entry set 0 holds slice 0, on exit set 1 holds slice 3, this
-    // wave's loads have arrived and all waves are past the barrier
-    auto first_three_slices = [&](const uint16_t* cur_p, const uint16_t* cur_q) {
-        read_frags(cur_p, cur_q, 1, fa1, fb1);
-        ADAGC_SCHED_FENCE();
-        multiply(fa0, fb0);
-        ADAGC_SCHED_FENCE();
-        read_frags(cur_p, cur_q, 2, fa0, fb0);
-        ADAGC_SCHED_FENCE();
-        multiply(fa1, fb1);
-        ADAGC_SCHED_FENCE();
-        read_frags(cur_p, cur_q, 3, fa1, fb1);
-        ADAGC_SCHED_FENCE();
-        multiply(fa0, fb0);
-        ADAGC_SCHED_FENCE();
-        ADAGC_WAIT_VMEM(0);
-        __syncthreads();
+    const int k_tiles = K / kBK;          // at least 2: K is a multiple of 128
+    constexpr int kL = 2 * kLoads;
+    constexpr std::integral_constant<int, 0> none{};
+    // Multiply the slice in set f, while slice kk of the tile in (bp, bq) is read into set n and loads 0 .. NL-1 of tile
+    // k's are issued (the first kLoads: Q of tile k+1 into lq, the others: P of tile k+2 into lp).
+    auto phase = [&](auto READ, const bf16x8 (&fa)[kMI], const bf16x8 (&fb)[kNI], const uint16_t* bp, const uint16_t* bq, int kk,
+                     bf16x8 (&na)[kMI], bf16x8 (&nb)[kNI], auto NL, int k, uint16_t* lp, uint16_t* lq) {
+        constexpr int kM = kMI * kNI, kR = kMI + kNI, nl = decltype(NL)::value;
+        static_for<kM>([&](auto T) __attribute__((always_inline)) {
+            constexpr int t = decltype(T)::value;
+            constexpr int j = t / kMI, i = j % 2 ? kMI - 1 - t % kMI : t % kMI;
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+            ADAGC_SCHED_FENCE();
+            if constexpr (decltype(READ)::value) {
+                static_for<kR>([&](auto N) __attribute__((always_inline)) {
+                    constexpr int n = decltype(N)::value;
+                    if constexpr (n * kM / kR == t) read_frag(bp, bq, kk, n, na, nb);
+                });
+            }
+            static_for<nl>([&](auto N) __attribute__((always_inline)) {
+                constexpr int n = decltype(N)::value;
+                if constexpr (n * kM / nl == t) {
+                    if constexpr (n < kLoads) load_q(n, k + 1, lq);
+                    else load_p(n - kLoads, k + 2, lp);
+                }
+            });
+            ADAGC_SCHED_FENCE();
+        });
     };
-    load_tile(0, lds_p0, lds_q0);
-    ADAGC_WAIT_VMEM(0);
-    __syncthreads();
-    load_tile(1, lds_p1, lds_q1);
-    read_frags(lds_p0, lds_q0, 0, fa0, fb0);
-    ADAGC_SCHED_FENCE();
-    first_three_slices(lds_p0, lds_q0);
-    for (int kt = 0; kt + 2 < k_tiles; kt += 2) {
-        // tile kt (buffer 0): slice 3 left; tile kt+1 is in buffer 1
-        load_tile(kt + 2, lds_p0, lds_q0);
-        read_frags(lds_p1, lds_q1, 0, fa0, fb0);
-        ADAGC_SCHED_FENCE();
-        multiply(fa1, fb1);
-        ADAGC_SCHED_FENCE();
-        first_three_slices(lds_p1, lds_q1);
-        // tile kt+1 (buffer 1): slice 3 left; tile kt+2 is in buffer 0
-        load_tile(kt + 3, lds_p1, lds_q1);
-        read_frags(lds_p0, lds_q0, 0, fa0, fb0);
-        ADAGC_SCHED_FENCE();
-        multiply(fa1, fb1);
-        ADAGC_SCHED_FENCE();
-        first_three_slices(lds_p0, lds_q0);
+    constexpr std::integral_constant<int, 1> yes{};
+    // Tile k, in places sp and sq of the ring; on entry slice 1 of tile k-1 is in set 1, on exit slice 1 of tile k is and
+    // all of tile k has been read by this wave.  fp, fq: the places that tile k-1 left.
+    auto tile = [&](auto NL, int k, int sp, int sq, int fp, int fq) {
+        const uint16_t *bp = lds + sp * kTileElems, *bq = lds + sq * kTileElems;
+        phase(yes, fa1, fb1, bp, bq, 0, fa0, fb0, NL, k, lds + fp * kTileElems, lds + fq * kTileElems);
+        phase(yes, fa0, fb0, bp, bq, 1, fa1, fb1, none, k, nullptr, nullptr);
+    };
+    auto two_on = [](int place) { return place >= 3 ? place - 3 : place + 2; };
+#pragma unroll
+    for (int n = 0; n < 5; ++n) {
+        if (n == 4 && k_tiles <= 2) break;
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) {
+            if (n % 2 == 0) load_p(u, n / 2, lds + n * kTileElems);
+            else load_q(u, n / 2, lds + n * kTileElems);
+        }
     }
-    // the last two tiles: k_tiles - 2 (buffer 0, slice 3 left) and k_tiles - 1 (buffer 1)
-    read_frags(lds_p1, lds_q1, 0, fa0, fb0);
+    if (k_tiles > 2) ADAGC_WAIT_VMEM(3 * kLoads);          // P and Q of tile 0 are there
+    else ADAGC_WAIT_VMEM(2 * kLoads);
+    barrier_keeping_loads();
+    static_for<kMI + kNI>([&](auto N) { read_frag(lds, lds + kTileElems, 0, decltype(N)::value, fa0, fb0); });
     ADAGC_SCHED_FENCE();
-    multiply(fa1, fb1);
-    ADAGC_SCHED_FENCE();
-    first_three_slices(lds_p1, lds_q1);
-    multiply(fa1, fb1);
+    phase(yes, fa0, fb0, lds, lds + kTileElems, 1, fa1, fb1, none, 0, nullptr, nullptr);
+    if (k_tiles > 2) ADAGC_WAIT_VMEM(kLoads);              // ... and of tile 1
+    else ADAGC_WAIT_VMEM(0);
+    barrier_keeping_loads();
+    int sp = 2, sq = 3, fp = 1, fq = 0, k = 1;
+    for (; k + 2 < k_tiles; ++k) {
+        tile(std::integral_constant<int, kL>{}, k, sp, sq, fp, fq);
+        ADAGC_WAIT_VMEM(kLoads);                           // all but P of tile k+2
+        barrier_keeping_loads();
+        fq = sp;
+        fp = sq;
+        sp = two_on(sp);
+        sq = two_on(sq);
+    }
+    if (k_tiles > 2) {
+        tile(std::integral_constant<int, kLoads>{}, k, sp, sq, fp, fq);
+        ADAGC_WAIT_VMEM(0);
+        barrier_keeping_loads();
+        sp = two_on(sp);
+        sq = two_on(sq);
+        ++k;
+    }
+    tile(none, k, sp, sq, 0, 0);
+    __syncthreads();                                       // the ring is free for the epilogue
+    phase(none, fa1, fb1, nullptr, nullptr, 0, fa0, fb0, none, 0, nullptr, nullptr);
     store_result<BT, kMI, kNI, SYM, kWaves>(lds, acc, lane, wave, wm * kTM, wn * kTN, tile_m, tile_n, alpha, beta, Dt, lddt, C, ldc, Ct,
                                             ldct);
 }

@@ -135,6 +135,25 @@ def test_batched_matrix_core_product_equals_the_single_ones(batch, M, N, K, symm
             B.adagc_muon_gemm_nt_batched(P, Q, 1.0, 0.0, None, None, buf.as_strided((batch, N, M), (N * M + 4, M, 1)))
 
 
+@pytest.mark.parametrize("batch,M,N", [(1, 256, 128), (1, 4096, 4096)])          # 128 x 128 tiles; 256 x 256 tiles
+@pytest.mark.parametrize("K", [128, 256, 384, 512, 640, 768, 1408])
+def test_matrix_core_product_at_every_place_of_the_operand_ring(batch, M, N, K):
+    """Operand tiles go through a ring of five places in LDS, two tiles per 64 of K: lengths of K that end at every place
+    of it, the shortest included.  Small integers: every sum is exact in fp32, so the result is the exact one rounded once."""
+    gen = torch.Generator(device="cpu").manual_seed(K + M)
+    P = torch.randint(-2, 3, (M, K), generator=gen).to(torch.float32)
+    Q = torch.randint(-2, 3, (N, K), generator=gen).to(torch.float32)
+    D = torch.randint(-4, 5, (M, N), generator=gen).to(torch.float32)
+    C = torch.zeros((M, N), dtype=torch.bfloat16, device=DEV)
+    Ct = torch.zeros((N, M), dtype=torch.bfloat16, device=DEV)
+    dP, dQ, dDt = (x.to(torch.bfloat16).to(DEV) for x in (P, Q, D.t().contiguous()))
+    B.adagc_muon_gemm_nt(dP, dQ, 1.0, 2.0, dDt, C, Ct)
+    torch.cuda.synchronize()
+    ref = (P @ Q.t() + 2.0 * D).to(torch.bfloat16)
+    assert torch.equal(C.cpu(), ref)
+    assert torch.equal(Ct.cpu(), ref.t())
+
+
 def test_matrix_core_product_places_every_element():
     """Index check with exactly representable data: P row i holds i+1 at column i (others 0), Q row j holds small
     integers, so C[i][j] = (i+1) * Q[j][i] exactly, and a misplaced lane or register shows as a wrong integer."""
