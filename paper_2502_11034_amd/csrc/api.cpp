@@ -47,9 +47,12 @@ struct adagc_ctx {
     struct MuonBatch {
         int mp = 0, np = 0;                  // padded extent of the wide orientation
         std::vector<int64_t> members;        // tensor indices
+        int64_t first = 0;                   // place of its first record in muon_matrices
+        int64_t largest = 0;                 // elements of its largest matrix
     };
     std::vector<adagc_matrix_shape> shapes;
     std::vector<MuonBatch> muon_batches;
+    MuonMatrix* muon_matrices = nullptr;      // device: the batches' matrices, one batch after another
     void*  muon_ws = nullptr;
     size_t muon_ws_bytes = 0;
 
@@ -89,6 +92,7 @@ void free_ctx(adagc_ctx* c)
     for (hipEvent_t e : c->upload_done)
         if (e) (void)hipEventDestroy(e);
     if (c->muon_ws) (void)hipFree(c->muon_ws);
+    if (c->muon_matrices) (void)hipFree(c->muon_matrices);
     if (c->staging) (void)hipHostFree(c->staging);
     if (c->slab) (void)hipFree(c->slab);
     delete c;
@@ -527,6 +531,38 @@ extern "C" int adagc_muon_attach(adagc_ctx* ctx, const adagc_matrix_shape* shape
             return e == hipErrorOutOfMemory ? ADAGC_ERR_OOM : ADAGC_ERR_HIP;
         }
     }
+    // the matrices' records, batch by batch, in device memory
+    int rc = ADAGC_OK;
+    try {
+        std::vector<MuonMatrix> records;
+        for (adagc_ctx::MuonBatch& bt : batches) {
+            bt.first = (int64_t)records.size();
+            bt.largest = 0;
+            for (int64_t i : bt.members) {
+                const int64_t r = shapes[i].rows, c = shapes[i].cols;
+                records.push_back(MuonMatrix{(uint32_t)i, 0u, r, c, std::sqrt(r > c ? (double)r / (double)c : 1.0)});
+                if (r * c > bt.largest) bt.largest = r * c;
+            }
+        }
+        const size_t bytes = records.size() * sizeof(MuonMatrix);
+        const hipError_t e = hipMalloc(reinterpret_cast<void**>(&ctx->muon_matrices), bytes);
+        if (e != hipSuccess) {
+            ctx->muon_matrices = nullptr;
+            (void)hipGetLastError();
+            rc = e == hipErrorOutOfMemory ? ADAGC_ERR_OOM : ADAGC_ERR_HIP;
+        } else if (hipMemcpy(ctx->muon_matrices, records.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) {
+            rc = ADAGC_ERR_HIP;
+        }
+    } catch (const std::bad_alloc&) { rc = ADAGC_ERR_OOM; }
+    if (rc != ADAGC_OK) {                 // as if the call had not been made
+        if (ctx->muon_matrices) (void)hipFree(ctx->muon_matrices);
+        (void)hipFree(ctx->muon_ws);
+        ctx->muon_matrices = nullptr;
+        ctx->muon_ws = nullptr;
+        ctx->muon_ws_bytes = 0;
+        ctx->shapes.clear();
+        return rc;
+    }
     ctx->muon_batches.swap(batches);
     return ADAGC_OK;
 }
@@ -587,17 +623,8 @@ extern "C" int adagc_muon_step(adagc_ctx* ctx, void* const* params, const void* 
         uint16_t* base = static_cast<uint16_t*>(ctx->muon_ws);
         uint16_t *x = base, *x2 = base + count * mn, *y = base + 2 * count * mn, *y2 = base + 3 * count * mn;
         uint16_t *wa = base + 4 * count * mn, *wb = wa + count * mm;
-        for (int z = 0; z < count; ++z) {
-            const int64_t i = bt.members[(size_t)z];
-            const int64_t rows = ctx->shapes[(size_t)i].rows, cols = ctx->shapes[(size_t)i].cols;
-            const bool flip = rows > cols;                  // the iteration runs on the wide orientation
-            const hipError_t g =
-                flip ? launch_muon_normalise(grads[i], momentum[i], rows, cols, np, mp, t.coef64 + i, t.sumsq + i, mu, mh->nesterov,
-                                             bf16g, y + z * mn, mp, x + z * mn, np, stream)
-                     : launch_muon_normalise(grads[i], momentum[i], rows, cols, mp, np, t.coef64 + i, t.sumsq + i, mu, mh->nesterov,
-                                             bf16g, x + z * mn, np, y + z * mn, mp, stream);
-            if (g != hipSuccess) return ADAGC_ERR_HIP;
-        }
+        if (launch_muon_normalise(t, ctx->muon_matrices + bt.first, count, mp, np, mu, mh->nesterov, bf16g, x, y, stream) != hipSuccess)
+            return ADAGC_ERR_HIP;
         bool any_tall = false, any_wide = false;
         for (int64_t i : bt.members) {
             if (ctx->shapes[(size_t)i].rows > ctx->shapes[(size_t)i].cols) any_tall = true;
@@ -623,15 +650,9 @@ extern "C" int adagc_muon_step(adagc_ctx* ctx, void* const* params, const void* 
             uint16_t* s = x; x = x2; x2 = s;
             s = y; y = y2; y2 = s;
         }
-        for (int z = 0; z < count; ++z) {
-            const int64_t i = bt.members[(size_t)z];
-            const int64_t rows = ctx->shapes[(size_t)i].rows, cols = ctx->shapes[(size_t)i].cols;
-            const bool flip = rows > cols;
-            const double scale = std::sqrt(flip ? (double)rows / (double)cols : 1.0);
-            const hipError_t g = launch_muon_apply(params[i], (flip ? y : x) + z * mn, flip ? mp : np, rows, cols, (double)h.lr,
-                                                   (double)h.weight_decay, scale, copy ? ctx->param_copies[(size_t)i] : nullptr, stream);
-            if (g != hipSuccess) return ADAGC_ERR_HIP;
-        }
+        if (launch_muon_apply(t, ctx->muon_matrices + bt.first, count, bt.largest, mp, np, x, y, (double)h.lr, (double)h.weight_decay,
+                              copy, stream) != hipSuccess)
+            return ADAGC_ERR_HIP;
     }
     if (prof) {
         if (hipEventRecord(ev[3], stream) != hipSuccess) return ADAGC_ERR_HIP;

@@ -14,14 +14,22 @@ hipError_t launch_gemm_nt_bf16(const void* P, int ldp, const void* Q, int ldq, i
                                float beta, const void* Dt, int lddt, void* C, int ldc, void* Ct, int ldct,
                                hipStream_t stream, bool symmetric = false, int batch = 1, int64_t stride_p = 0,
                                int64_t stride_q = 0, int64_t stride_dt = 0, int64_t stride_c = 0, int64_t stride_ct = 0);
-// Muon (muon.hip): momentum update with the clipped gradient and the partial sums of squares of U; X0 of one matrix
-// into the padded workspace; the parameter update.
+// One matrix of a batch, in device memory.
+struct MuonMatrix {
+    uint32_t tensor;      // its place in the list
+    uint32_t pad;
+    int64_t  rows, cols;
+    double   scale;       // sqrt(max(1, rows / cols))
+};
+
+// Muon (muon.hip): momentum update with the clipped gradient and the partial sums of squares of U; X0 of a batch's
+// matrices into the padded workspace (members: the batch's records, DEVICE); their parameter update (largest: the most
+// elements of one of them).
 hipError_t launch_muon_momentum(const DeviceTables& t, double mu, int nesterov, int grad_bf16, int grid, hipStream_t stream);
-hipError_t launch_muon_normalise(const void* g, const void* m, int64_t rows, int64_t cols, int64_t rows_p, int64_t cols_p,
-                                 const double* coef, const double* sumsq, double mu, int nesterov, int grad_bf16,
-                                 void* same, int64_t ld_same, void* trans, int64_t ld_trans, hipStream_t stream);
-hipError_t launch_muon_apply(void* theta, const void* o, int64_t ld_o, int64_t rows, int64_t cols, double lr, double wd,
-                             double scale, void* copy, hipStream_t stream);
+hipError_t launch_muon_normalise(const DeviceTables& t, const MuonMatrix* members, int count, int mp, int np, double mu, int nesterov,
+                                 int grad_bf16, uint16_t* x, uint16_t* y, hipStream_t stream);
+hipError_t launch_muon_apply(const DeviceTables& t, const MuonMatrix* members, int count, int64_t largest, int mp, int np,
+                             const uint16_t* x, const uint16_t* y, double lr, double wd, int with_copy, hipStream_t stream);
 
 }  // namespace adagc
 #endif

@@ -359,6 +359,45 @@ def test_muon_matrices_iterated_in_batches_give_the_results_of_single_ones():
         assert diff <= 0.02 * OM.update_scale(*shapes[i]) * 0.01 * 0.2
 
 
+@pytest.mark.parametrize("grad_bf16", [False, True])
+def test_muon_batch_of_matrices_end_to_end_in_flat_buffers(grad_bf16):
+    """Wide and tall matrices of one padded shape, laid end to end without gaps: every alignment and every row length modulo 4
+    in one batch, and lengths around the 4096 elements of a workgroup.  Without iterations the step is elementwise, so it must be
+    the separately allocated matrices' result up to the last bit of ||U|| (another summation order): X0 = bf16(U / ||U||) then
+    takes the neighbouring value in at most one element in 10^6 or so; 1e-3 is allowed."""
+    shapes = [(63, 65), (128, 33), (64, 64), (5, 128), (128, 127), (127, 126), (1, 97), (101, 3), (120, 128)]
+    g, m, th = _inputs(11, shapes)
+    if grad_bf16:
+        g = [torch.from_numpy(x).to(torch.bfloat16).to(torch.float32).numpy() for x in g]
+    gamma = np.array([oracle.l2_norm(x.reshape(-1)) for x in g], np.float32)
+    hp = B.make_hyper(lr=0.02, weight_decay=0.1, t_start=0)
+    mh = B.make_muon_hyper(ns_steps=0)
+    starts = np.concatenate([[0], np.cumsum([r * c for r, c in shapes])]).astype(int)
+
+    def flat(arrs, dtype=torch.float32):
+        buf = torch.from_numpy(np.concatenate([a.reshape(-1) for a in arrs])).to(dtype).to(DEV)
+        return buf, [buf[a:b] for a, b in zip(starts, starts[1:])]
+    (fth, dth), (fm, dm) = flat(th), flat(m)
+    fg, dg = flat(g, torch.bfloat16 if grad_bf16 else torch.float32)
+    fc, dc = flat([np.zeros_like(x) for x in th], torch.bfloat16)
+    ctx = B.AdaGC([r * c for r, c in shapes], B.ADAGC_OPT_MUON, B.ADAGC_GRAD_BF16 if grad_bf16 else B.ADAGC_GRAD_F32, True)
+    ctx.muon_attach(shapes)
+    ctx.set_param_copies(dc)
+    ctx.muon_step(dth, dg, dm, torch.from_numpy(gamma.copy()).to(DEV), hp, mh, 7)
+    torch.cuda.synchronize()
+    ctx.close()
+    ref = _gpu_muon(shapes, g, m, th, gamma, hp, mh, 7)
+    differ = 0
+    for i, s in enumerate(shapes):
+        a, b = to_numpy(dth[i]).reshape(s).astype(np.float64), ref[0][i].astype(np.float64)
+        step = 0.02 * OM.update_scale(*s) * 2.0 ** -7              # a bf16 step of an element of X0 (none is above 1)
+        assert (np.abs(a - b) <= step).all(), "theta of tensor %d" % i
+        differ += int((a != b).sum())
+        assert np.array_equal(to_numpy(dm[i]).reshape(s).view(np.uint32), ref[1][i].view(np.uint32)), "momentum of tensor %d" % i
+        assert torch.equal(dc[i], dth[i].to(torch.bfloat16)), "copy of tensor %d" % i
+    assert differ <= 1e-3 * starts[-1]
+
+
 def test_muon_trajectory_with_adagc_clipping():
     """Three steps with the paper's schedule in small (one warm-up step, then Eq. 3), a spike on the third step:
     norms, coefficients, flags and gamma against the C oracle's rule, the momentum against the oracle to 1e-5."""
