@@ -107,12 +107,14 @@ typedef struct {
                                      b, b+grid, ...; default: one work item per workgroup (a chunk in the
                                      norm kernel; a chunk or a part of one in the update kernel) */
     int32_t unroll;               /* 128-bit vectors per lane per array kept in flight by the update kernel:
-                                     1, 2 or 4 (default 4) */
-    int32_t nontemporal;          /* streaming (non-temporal) loads and stores: 1 = on (default), 2 = off */
+                                     1, 2 or 4 (default: AdamW 4, Lion 2) */
+    int32_t nontemporal;          /* streaming (non-temporal) loads and stores of the update kernel: 1 = on (default),
+                                     2 = off */
     int32_t schedule;             /* visiting order of the chunks, see adagc_build_visiting_order: number of
                                      contiguous parts the list is cut into (default 2; 1 = list order) */
     int32_t update_split;         /* work items of the update kernel per chunk: 1 = whole chunks, or 2, 4, ...
                                      up to chunk_elems / (unroll*1024).  Default (0): 4096-element items
+                                     for AdamW, 2048 for Lion
                                      (small items shorten the tail of the launch and give short lists more
                                      workgroups; whole chunks cost the fewest dispatches) */
     int32_t schedule_run;         /* visiting order: chunks an XCD takes in a row (default 8) */
@@ -223,8 +225,8 @@ int adagc_set_param_copies(adagc_ctx* ctx, void* const* params_bf16);
  *   step        1-based t of Alg. 1: drives the bias correction and the warm-up test
  *   stream      hipStream_t (NULL = the default stream)
  * The host pointer arrays are read during the call and may be reused afterwards.
- * Pointers aligned to 16 bytes (8 for bf16 arrays) take the vectorised path; any
- * other alignment is accepted and handled element by element.
+ * Pointers aligned to their elements (4 bytes, 2 for bf16 arrays) take the vectorised path, fastest
+ * where a tensor starts on a cache line; any other alignment is accepted and handled element by element.
  * Non-finite gradients get no special treatment: a NaN norm compares false
  * against the threshold, so the tensor is not clipped and the NaN propagates as
  * it would in plain AdamW.
@@ -265,7 +267,7 @@ int adagc_step_graph(adagc_ctx* ctx, void* const* params, const void* const* gra
  * this call allocates nothing (no hipMalloc / hipFree, no copy, no memset, no event), it only
  * launches kernels on `stream`.  The segment table, the per-chunk partial sums and the per-tensor
  * results live in a fixed array inside the library's device code, ADAGC_STATIC_MAX_* in size
- * (about 11 MB per GPU, held from the library's load until the process ends).
+ * (about 15 MB per GPU, held from the library's load until the process ends).
  *   descs, n_tensors, cfg   HOST  as for adagc_create; cfg->telemetry, cfg->update_clipping and the
  *                                 launch-tuning fields must be 0 (library defaults, chunks visited in
  *                                 list order; clip modes 0 to 3)

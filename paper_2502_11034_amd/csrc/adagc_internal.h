@@ -33,14 +33,18 @@ struct TensorArgs {
     int64_t     numel;
     uint32_t    chunk_begin; // index of this tensor's first chunk / partial slot
     uint32_t    chunk_count;
-    uint32_t    vec_ok;      // 1: all of this tensor's pointers allow 128-bit (64-bit for bf16) access
+    uint32_t    vec_ok;      // 1: every pointer is aligned to its elements, which is all that vector accesses need
     uint32_t    pad;
 };
 static_assert(sizeof(TensorArgs) == 64, "TensorArgs is one 64-byte record");
 
-struct ChunkRef {
+// One chunk, in the order in which the streaming kernels visit them: all that a workgroup needs to find its elements
+// besides the tensor's own record, in one 16-byte load.
+struct WorkRef {
     uint32_t tensor;  // owning tensor
+    uint32_t slot;    // number in list order: its slot of the partial results
     uint32_t index;   // position inside the tensor: first element = index * kChunkElems
+    uint32_t len;     // elements, 1 .. kChunkElems
 };
 
 // Scalars of the per-tensor rule (Eq. 3 / warm-up branch of Alg. 1), all widened from the
@@ -84,8 +88,8 @@ struct StepScalars {
 };
 
 struct DeviceTables {
-    const ChunkRef*   chunks;     // canonical order: tensor by tensor; slot c of `partials` belongs to chunk c
-    const uint32_t*   schedule;   // order in which the streaming kernels visit the chunks (null: list order)
+    const WorkRef*    work;       // the chunks in visiting order: the n_long that are more than one work item of the
+                                  // update kernel, then those that are one
     const TensorArgs* targs;
     double*           partials;   // one per chunk
     double*           sumsq;      // one per tensor
@@ -101,8 +105,27 @@ struct DeviceTables {
                                       // the direction (sums of squares for AGC, maxima for Clippy), or null
     double*           ucoef64;        // update clipping: per-tensor coefficient of the direction, or null
     uint32_t          n_chunks;
+    uint32_t          n_long;
     uint32_t          n_tensors;
 };
+
+// Vectors per lane and array that the update kernel keeps in flight, and the work items of a full chunk (one round of those
+// each), unless the caller chooses.  AdamW: 4, items of 4096 elements; in whole chunks a launch has too long a tail (GPT-2-small
+// shapes 639 us per step against 685, 5000-tensor lists have too few workgroups), in halves 676, as 2 and 2048 elements 637 (and
+// 1.5 % slower on lists of GBs).  Lion: 2, items of 2048 elements: it moves 10 instead of 16 bytes per element each way, and
+// more, smaller items suit it (Llama-3-8B shapes, 4 layers, two placements: 7.23 -> 6.84 ms, 6.65 -> 6.55 ms).
+constexpr int default_unroll(int optimizer) { return optimizer == ADAGC_OPT_LION ? 2 : 4; }
+constexpr int default_items(int unroll) { return kVecPerLane >= unroll ? kVecPerLane / unroll : 1; }
+
+// Chunks of at most one work item of the update kernel (items_per_chunk of them make a full chunk) are numbered after the
+// longer ones.
+__host__ __device__ inline bool is_long_chunk(int64_t len, int items_per_chunk) { return len > kChunkElems / items_per_chunk || items_per_chunk == 1; }
+
+// Work items of the update kernel: items_per_chunk for every long chunk (in groups of 8 chunks), one for each of the others.
+inline int64_t count_work_items(int64_t n_chunks, int64_t n_long, int items_per_chunk)
+{
+    return (n_long + 7) / 8 * 8 * items_per_chunk + (n_chunks - n_long);
+}
 
 // What every step entry point accepts as hyper-parameters.
 inline bool hyper_ok(const adagc_hyper& h, int optimizer)
@@ -149,7 +172,7 @@ inline void host_step_scalars(const adagc_hyper& hp, int64_t step, RuleArgs& r, 
 }
 
 // Launchers (kernels.hip).  Each only enqueues on `stream`.
-hipError_t launch_sumsq_partials(const DeviceTables& t, int grad_bf16, int nt, int grid, hipStream_t stream);
+hipError_t launch_sumsq_partials(const DeviceTables& t, int grad_bf16, int grid, hipStream_t stream);
 hipError_t launch_finalize_adagc(const DeviceTables& t, float* ema, const RuleArgs& r, hipStream_t stream);
 hipError_t launch_finalize_global(const DeviceTables& t, float* ema, const RuleArgs& r, hipStream_t stream);
 hipError_t launch_update(const DeviceTables& t, const UpdateArgs& u, int optimizer, int grad_bf16,

@@ -130,7 +130,7 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
         return ADAGC_ERR_INVALID_ARG;
     if (cfg->unroll != 0 && cfg->unroll != 1 && cfg->unroll != 2 && cfg->unroll != 4) return ADAGC_ERR_INVALID_ARG;
     {
-        const int tiles = kVecPerLane / (cfg->unroll ? cfg->unroll : 4);       // unroll*1024-element tiles per chunk
+        const int tiles = kVecPerLane / (cfg->unroll ? cfg->unroll : default_unroll(cfg->optimizer));       // unroll*1024-element tiles per chunk
         const int sp = cfg->update_split;
         if (sp < 0 || sp > tiles || (sp & (sp - 1)) != 0) return ADAGC_ERR_INVALID_ARG;
     }
@@ -179,16 +179,20 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     //    -1.9 % (AdamW, 8 B parameters), -0.4 % (Lion), -1.2 % (20 001 ragged tensors).  Fewer
     //    address fronts per array mean fewer DRAM rows open at once; runs keep each XCD on
     //    its own pages.
-    c->unroll = cfg->unroll ? cfg->unroll : 4;
+    c->unroll = cfg->unroll ? cfg->unroll : default_unroll(cfg->optimizer);
     c->nontemporal = cfg->nontemporal == 2 ? 0 : 1;
-    //  - work items of the update kernel: 4096 elements, a quarter of a chunk.  Against whole
-    //    chunks: AdamW on Llama-3-8B shapes -0.1 %, Lion -3.1 %, a 20 001-tensor ragged list
-    //    +0.2 %, 0.1-0.5 B-parameter lists -1.5...-3.7 % (shorter tail of the launch), a list of
-    //    50 chunks -25 % (more workgroups to spread over the CUs).  Halves are 0.9 % slower than
-    //    either on the 8 B list, and 1024-element items 16 % slower.
+    //  - work items of the update kernel: see default_unroll.
     // Both streaming kernels walk their work items b, b+grid, ..., so any grid size is valid.
-    c->items_per_chunk = cfg->update_split ? cfg->update_split : (kChunkElems >= 4096 ? kChunkElems / 4096 : 1);
-    const int64_t tiles = ((c->n_chunks + 7) / 8 * 8) * c->items_per_chunk;
+    c->items_per_chunk = cfg->update_split ? cfg->update_split
+                                            : default_items(c->unroll > default_unroll(cfg->optimizer) ? c->unroll
+                                                                                                       : default_unroll(cfg->optimizer));
+    auto chunk_len = [&](size_t k) {
+        const int64_t rest = c->numel[chunk_tensor[k]] - (int64_t)chunk_index[k] * kChunkElems;
+        return rest < kChunkElems ? rest : (int64_t)kChunkElems;
+    };
+    int64_t n_long = 0;
+    for (size_t k = 0; k < chunk_tensor.size(); ++k) n_long += is_long_chunk(chunk_len(k), c->items_per_chunk) ? 1 : 0;
+    const int64_t tiles = count_work_items(c->n_chunks, n_long, c->items_per_chunk);
     auto grid_for = [cfg](int64_t items) {
         int64_t want = cfg->grid_blocks > 0 ? (int64_t)cfg->grid_blocks : items;
         if (want > items) want = items;
@@ -201,8 +205,7 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     const size_t nt = (size_t)n_tensors, nc = (size_t)c->n_chunks;
     size_t off = 0;
     auto carve = [&off](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
-    const size_t o_chunks = carve(nc * sizeof(ChunkRef));
-    const size_t o_schedule = carve(nc * sizeof(uint32_t));
+    const size_t o_work = carve(nc * sizeof(WorkRef));
     const size_t o_targs = carve(nt * sizeof(TensorArgs));
     const size_t o_partials = carve(nc * sizeof(double));
     const size_t o_sumsq = carve(nt * sizeof(double));
@@ -224,25 +227,28 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     char* base = static_cast<char*>(c->slab);
     if (hipMemset(c->slab, 0, slab_bytes) != hipSuccess) { free_ctx(c); return ADAGC_ERR_HIP; }
 
-    std::vector<ChunkRef> refs;
-    try {
-        refs.resize(nc);
-    } catch (const std::bad_alloc&) { free_ctx(c); return ADAGC_ERR_OOM; }
-    for (size_t k = 0; k < nc; ++k) refs[k] = ChunkRef{chunk_tensor[k], chunk_index[k]};
-    if (hipMemcpy(base + o_chunks, refs.data(), nc * sizeof(ChunkRef), hipMemcpyHostToDevice) != hipSuccess) {
-        free_ctx(c);
-        return ADAGC_ERR_HIP;
-    }
-    // Visiting order of the streaming kernels (see adagc_build_visiting_order).
+    // The chunks in visiting order (see adagc_build_visiting_order): those of more than one work item of the update kernel,
+    // then the others in list order.
     {
-        std::vector<uint32_t> order;
+        std::vector<WorkRef> work;
         try {
-            order.resize(nc);
+            std::vector<uint32_t> longer, order;
+            longer.reserve((size_t)n_long);
+            for (size_t k = 0; k < nc; ++k)
+                if (is_long_chunk(chunk_len(k), c->items_per_chunk)) longer.push_back((uint32_t)k);
+            order.resize((size_t)n_long);
+            if (n_long > 0) {
+                rc = adagc_build_visiting_order(n_long, cfg->schedule ? cfg->schedule : 2, cfg->schedule_run ? cfg->schedule_run : 8,
+                                                order.data());
+                if (rc != ADAGC_OK) { free_ctx(c); return rc; }
+            }
+            work.reserve(nc);
+            auto append = [&](uint32_t k) { work.push_back(WorkRef{chunk_tensor[k], k, chunk_index[k], (uint32_t)chunk_len(k)}); };
+            for (uint32_t o : order) append(longer[o]);
+            for (size_t k = 0; k < nc; ++k)
+                if (!is_long_chunk(chunk_len(k), c->items_per_chunk)) append((uint32_t)k);
         } catch (const std::bad_alloc&) { free_ctx(c); return ADAGC_ERR_OOM; }
-        rc = adagc_build_visiting_order(c->n_chunks, cfg->schedule ? cfg->schedule : 2,
-                                        cfg->schedule_run ? cfg->schedule_run : 8, order.data());
-        if (rc != ADAGC_OK) { free_ctx(c); return rc; }
-        if (hipMemcpy(base + o_schedule, order.data(), nc * sizeof(uint32_t), hipMemcpyHostToDevice) != hipSuccess) {
+        if (hipMemcpy(base + o_work, work.data(), nc * sizeof(WorkRef), hipMemcpyHostToDevice) != hipSuccess) {
             free_ctx(c);
             return ADAGC_ERR_HIP;
         }
@@ -260,8 +266,7 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
 
     c->d_targs = reinterpret_cast<TensorArgs*>(base + o_targs);
     DeviceTables& t = c->tables;
-    t.chunks = reinterpret_cast<const ChunkRef*>(base + o_chunks);
-    t.schedule = reinterpret_cast<const uint32_t*>(base + o_schedule);
+    t.work = reinterpret_cast<const WorkRef*>(base + o_work);
     t.targs = c->d_targs;
     t.partials = reinterpret_cast<double*>(base + o_partials);
     t.sumsq = reinterpret_cast<double*>(base + o_sumsq);
@@ -276,6 +281,7 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     t.ustat_partials = cfg->update_clipping ? reinterpret_cast<double*>(base + o_ustat) : nullptr;
     t.ucoef64 = cfg->update_clipping ? reinterpret_cast<double*>(base + o_ucoef64) : nullptr;
     t.n_chunks = (uint32_t)c->n_chunks;
+    t.n_long = (uint32_t)n_long;
     t.n_tensors = (uint32_t)c->n_tensors;
 
     *out = c;
@@ -318,7 +324,7 @@ int prepare_tables(adagc_ctx* ctx, void* const* params, const void* const* grads
     if (copy && ctx->param_copies.size() != (size_t)ctx->n_tensors) return ADAGC_ERR_STATE;
 
     // Rebuild the per-tensor records from the caller's pointer arrays.
-    const uintptr_t grad_align = bf16g ? 8 : 16;
+    const uintptr_t grad_align = bf16g ? 2 : 4;
     for (int64_t i = 0; i < ctx->n_tensors; ++i) {
         TensorArgs& a = ctx->scratch_args[(size_t)i];
         a.param = params[i];
@@ -330,8 +336,8 @@ int prepare_tables(adagc_ctx* ctx, void* const* params, const void* const* grads
         a.numel = ctx->numel[(size_t)i];
         a.chunk_begin = (uint32_t)ctx->chunk_begin[(size_t)i];
         a.chunk_count = (uint32_t)(ctx->chunk_begin[(size_t)i + 1] - ctx->chunk_begin[(size_t)i]);
-        a.vec_ok = (aligned(a.param, 16) && aligned(a.exp_avg, 16) && aligned(a.grad, grad_align) &&
-                    (!adamw || aligned(a.exp_avg_sq, 16)) && (!copy || aligned(a.param_copy, 8)))
+        a.vec_ok = (aligned(a.param, 4) && aligned(a.exp_avg, 4) && aligned(a.grad, grad_align) &&
+                    (!adamw || aligned(a.exp_avg_sq, 4)) && (!copy || aligned(a.param_copy, 2)))
                        ? 1u : 0u;
         a.pad = 0;
     }
@@ -394,7 +400,7 @@ extern "C" int adagc_step(adagc_ctx* ctx, void* const* params, const void* const
         if (prof && (hipEventRecord(ev[1], stream) != hipSuccess || hipEventRecord(ev[2], stream) != hipSuccess))
             return ADAGC_ERR_HIP;
     } else {
-        if (launch_sumsq_partials(ctx->tables, bf16g, ctx->nontemporal, ctx->grid_norm, stream) != hipSuccess) return ADAGC_ERR_HIP;
+        if (launch_sumsq_partials(ctx->tables, bf16g, ctx->grid_norm, stream) != hipSuccess) return ADAGC_ERR_HIP;
         if (prof && hipEventRecord(ev[1], stream) != hipSuccess) return ADAGC_ERR_HIP;
         const hipError_t e = global_rule ? launch_finalize_global(ctx->tables, ema_norms, r, stream)
                                          : launch_finalize_adagc(ctx->tables, ema_norms, r, stream);
@@ -433,7 +439,7 @@ extern "C" int adagc_step_graph(adagc_ctx* ctx, void* const* params, const void*
     hipEvent_t* ev = prof ? &ctx->prof_events[(size_t)ctx->prof_steps * 4] : nullptr;
     ctx->device_scalars_used = true;
     if (prof && hipEventRecord(ev[0], stream) != hipSuccess) return ADAGC_ERR_HIP;
-    if (launch_sumsq_partials(ctx->tables, bf16g, ctx->nontemporal, ctx->grid_norm, stream) != hipSuccess) return ADAGC_ERR_HIP;
+    if (launch_sumsq_partials(ctx->tables, bf16g, ctx->grid_norm, stream) != hipSuccess) return ADAGC_ERR_HIP;
     if (prof && hipEventRecord(ev[1], stream) != hipSuccess) return ADAGC_ERR_HIP;
     if (launch_rules_from_device(ctx->tables, ema_norms, step_params, ctx->cfg.optimizer, stream) != hipSuccess)
         return ADAGC_ERR_HIP;
@@ -602,7 +608,7 @@ extern "C" int adagc_muon_step(adagc_ctx* ctx, void* const* params, const void* 
 
     // gradient norms and clip coefficients: the kernels of adagc_step
     if (prof && hipEventRecord(ev[0], stream) != hipSuccess) return ADAGC_ERR_HIP;
-    if (launch_sumsq_partials(t, bf16g, ctx->nontemporal, ctx->grid_norm, stream) != hipSuccess) return ADAGC_ERR_HIP;
+    if (launch_sumsq_partials(t, bf16g, ctx->grid_norm, stream) != hipSuccess) return ADAGC_ERR_HIP;
     if (prof && hipEventRecord(ev[1], stream) != hipSuccess) return ADAGC_ERR_HIP;
     const hipError_t e = global_rule ? launch_finalize_global(t, ema_norms, r, stream) : launch_finalize_adagc(t, ema_norms, r, stream);
     if (e != hipSuccess) return ADAGC_ERR_HIP;
@@ -719,16 +725,15 @@ extern "C" int adagc_get_segment_table(adagc_ctx* ctx, int64_t* chunk_begin, uin
     if (!guard.ok) return ADAGC_ERR_HIP;
     if (chunk_begin) std::memcpy(chunk_begin, ctx->chunk_begin.data(), ((size_t)ctx->n_tensors + 1) * sizeof(int64_t));
     if (chunk_tensor || chunk_index) {
-        std::vector<ChunkRef> refs;
+        std::vector<WorkRef> work;
         try {
-            refs.resize((size_t)ctx->n_chunks);
+            work.resize((size_t)ctx->n_chunks);
         } catch (const std::bad_alloc&) { return ADAGC_ERR_OOM; }
-        if (hipMemcpy(refs.data(), ctx->tables.chunks, refs.size() * sizeof(ChunkRef), hipMemcpyDeviceToHost) !=
-            hipSuccess)
+        if (hipMemcpy(work.data(), ctx->tables.work, work.size() * sizeof(WorkRef), hipMemcpyDeviceToHost) != hipSuccess)
             return ADAGC_ERR_HIP;
-        for (size_t k = 0; k < refs.size(); ++k) {
-            if (chunk_tensor) chunk_tensor[k] = refs[k].tensor;
-            if (chunk_index) chunk_index[k] = refs[k].index;
+        for (const WorkRef& w : work) {                    // back from visiting order to list order
+            if (chunk_tensor) chunk_tensor[w.slot] = w.tensor;
+            if (chunk_index) chunk_index[w.slot] = w.index;
         }
     }
     return ADAGC_OK;

@@ -21,14 +21,10 @@
 // tree, waves through LDS in wave order, chunks by a second kernel in slot order.
 // No floating-point atomics anywhere.
 
-#include "adagc_internal.h"
+#include "adagc_device.h"
 
 namespace adagc {
 namespace {
-
-// Native clang vectors (the nontemporal builtins do not take HIP's struct vector types).
-typedef float    f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 // ---------------------------------------------------------------------------------------------
 // wave64 reduction in double: rotate-and-add inside each row of 16 lanes with DPP, then read the
@@ -65,88 +61,12 @@ __device__ __forceinline__ double wave_sum_f64(double x)
     return ((r0 + r1) + r2) + r3;
 }
 
-// ---------------------------------------------------------------------------------------------
-// loads / stores
-
-template <bool NT, typename T>
-__device__ __forceinline__ T ld(const T* p)
-{
-    if constexpr (NT) return __builtin_nontemporal_load(p);
-    else return *p;
-}
-
-template <bool NT, typename T>
-__device__ __forceinline__ void st(T* p, T v)
-{
-    if constexpr (NT) __builtin_nontemporal_store(v, p);
-    else *p = v;
-}
-
-__device__ __forceinline__ float bf16_bits_to_float(uint32_t b) { return __uint_as_float(b << 16); }
-
-// Four consecutive gradient elements, widened to fp32.  `vec` counts groups of four from `base`.
-template <bool BF16, bool NT>
-__device__ __forceinline__ f32x4 load_grad4(const void* base, int vec)
-{
-    if constexpr (BF16) {
-        u32x2 r = ld<NT>(reinterpret_cast<const u32x2*>(base) + vec);
-        f32x4 o;
-        o.x = __uint_as_float(r.x << 16);
-        o.y = __uint_as_float(r.x & 0xFFFF0000u);
-        o.z = __uint_as_float(r.y << 16);
-        o.w = __uint_as_float(r.y & 0xFFFF0000u);
-        return o;
-    } else {
-        return ld<NT>(reinterpret_cast<const f32x4*>(base) + vec);
-    }
-}
-
-template <bool BF16>
-__device__ __forceinline__ float load_grad1(const void* base, int j)
-{
-    if constexpr (BF16) return bf16_bits_to_float(reinterpret_cast<const uint16_t*>(base)[j]);
-    else return reinterpret_cast<const float*>(base)[j];
-}
-
-template <bool BF16>
-__device__ __forceinline__ const void* grad_chunk_ptr(const void* grad, int64_t first)
-{
-    if constexpr (BF16) return reinterpret_cast<const uint16_t*>(grad) + first;
-    else return reinterpret_cast<const float*>(grad) + first;
-}
-
-// fp32 -> bf16, round to nearest even (add half an ulp of the kept part, plus the parity bit).
-__device__ __forceinline__ uint32_t float_to_bf16_bits(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    uint32_t rounded = (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-    uint32_t quiet_nan = (u >> 16) | 0x40u;
-    return ((u & 0x7FFFFFFFu) > 0x7F800000u) ? quiet_nan : rounded;
-}
-
 __device__ __forceinline__ u32x2 pack_bf16x4(f32x4 v)
 {
     u32x2 o;
     o.x = float_to_bf16_bits(v.x) | (float_to_bf16_bits(v.y) << 16);
     o.y = float_to_bf16_bits(v.z) | (float_to_bf16_bits(v.w) << 16);
     return o;
-}
-
-struct ChunkView {
-    uint32_t tensor;
-    int64_t  first;   // first element of the chunk inside its tensor
-    int      len;     // 1..kChunkElems
-};
-
-__device__ __forceinline__ ChunkView chunk_view(const DeviceTables& t, uint32_t c)
-{
-    ChunkRef ck = t.chunks[c];
-    ChunkView v;
-    v.tensor = ck.tensor;
-    v.first = (int64_t)ck.index * kChunkElems;
-    int64_t rest = t.targs[ck.tensor].numel - v.first;
-    v.len = rest < (int64_t)kChunkElems ? (int)rest : kChunkElems;
-    return v;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -162,37 +82,50 @@ __device__ __forceinline__ void acc4(double (&acc)[4], f32x4 g)
     acc[3] = fma(w, w, acc[3]);
 }
 
-template <bool BF16, bool NTL>
+// The loads are ordinary ones: streaming loads leave nothing in the 256 MB memory-side cache, and the update kernel reads the
+// same gradients next.  GPT-2-small shapes (498 MB of gradients): 657 us per step with streaming loads, 622 without; 266 MB of
+// bf16 gradients 680, 635; lists of many GB do not care (this kernel alone then reads 7.2 TB/s either way).
+template <bool BF16>
 __global__ __launch_bounds__(kBlock) void sumsq_partials_kernel(DeviceTables t)
 {
     __shared__ double wave_sums[kWavesPerBlock];
     const int tid = threadIdx.x;
 
     for (uint32_t k = blockIdx.x; k < t.n_chunks; k += gridDim.x) {
-        const uint32_t c = t.schedule ? t.schedule[k] : k;     // no visiting order given: list order
-        const ChunkView cv = chunk_view(t, c);
-        const TensorArgs& ta = t.targs[cv.tensor];
-        const void* g = grad_chunk_ptr<BF16>(ta.grad, cv.first);
+        const WorkRef w = load_work(t.work, k);
+        const TensorArgs ta = load_tensor(t.targs, w.tensor);
+        const int len = (int)w.len;
+        const gcbytes g = grad_at<BF16>(ta.grad, first_element(w));
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
 
         if (ta.vec_ok) {
-            if (cv.len == kChunkElems) {
+            if (len == kChunkElems) {
                 f32x4 r[kVecPerLane];
 #pragma unroll
-                for (int u = 0; u < kVecPerLane; ++u) r[u] = load_grad4<BF16, NTL>(g, u * kBlock + tid);
+                for (int u = 0; u < kVecPerLane; ++u) r[u] = load_grad4<BF16, false>(g, u * kBlock + tid);
 #pragma unroll
                 for (int u = 0; u < kVecPerLane; ++u) acc4(acc, r[u]);
             } else {
-                const int nvec = cv.len >> 2;
-                for (int v = tid; v < nvec; v += kBlock) acc4(acc, load_grad4<BF16, NTL>(g, v));
+                // four loads at a time; a vector past the end counts as zeros, which add nothing to a sum of squares
+                constexpr int kFlight = kVecPerLane < 4 ? kVecPerLane : 4;
+                const int nvec = len >> 2;
                 const int j = (nvec << 2) + tid;
-                if (j < cv.len) {
-                    double x = (double)load_grad1<BF16>(g, j);
-                    acc[0] = fma(x, x, acc[0]);
+                const float last = j < len ? load_grad1<BF16>(g, j) : 0.f;
+                for (int v0 = 0; v0 < nvec; v0 += kFlight * kBlock) {
+                    f32x4 r[kFlight];
+#pragma unroll
+                    for (int u = 0; u < kFlight; ++u) {
+                        const int v = v0 + u * kBlock + tid;
+                        r[u] = v < nvec ? load_grad4<BF16, false>(g, v) : f32x4{0.f, 0.f, 0.f, 0.f};
+                    }
+#pragma unroll
+                    for (int u = 0; u < kFlight; ++u) acc4(acc, r[u]);
                 }
+                const double x = (double)last;
+                acc[0] = fma(x, x, acc[0]);
             }
         } else {
-            for (int j = tid; j < cv.len; j += kBlock) {
+            for (int j = tid; j < len; j += kBlock) {
                 double x = (double)load_grad1<BF16>(g, j);
                 acc[0] = fma(x, x, acc[0]);
             }
@@ -204,8 +137,8 @@ __global__ __launch_bounds__(kBlock) void sumsq_partials_kernel(DeviceTables t)
         if (tid == 0) {
             double b = wave_sums[0];
 #pragma unroll
-            for (int w = 1; w < kWavesPerBlock; ++w) b += wave_sums[w];
-            t.partials[c] = b;
+            for (int v = 1; v < kWavesPerBlock; ++v) b += wave_sums[v];
+            t.partials[w.slot] = b;
         }
         __syncthreads();
     }
@@ -543,9 +476,56 @@ __device__ __forceinline__ void tele_vec(double (&acc)[3], f32x4 p_old, f32x4 p_
 // Workgroups are dealt to the XCDs in turn (workgroup b to XCD b mod 8), so items are numbered such that
 // eight consecutive workgroups work on eight consecutive positions of the visiting order (one from each of
 // its parts) and the items of one chunk all go to the same XCD:
-//   item T  ->  position 8*(T / (8*I)) + T % 8,  item (T / 8) % I of that chunk      (I = items_per_chunk).
+//   item T  ->  position 8*(T / (8*I)) + T % 8,  item (T / 8) % I of that chunk      (I = items_per_chunk, a power of two).
+// Chunks of one item come after the others, one item each: in a list of many small tensors three of a chunk's four items
+// would be empty, and an empty workgroup costs its dispatch and its chain of loads all the same.
+
+struct WorkItem {
+    WorkRef chunk;
+    int     part;     // which item of the chunk
+};
+
+__device__ __forceinline__ uint64_t work_items(const DeviceTables& t, uint32_t log2_items)
+{
+    return ((((uint64_t)t.n_long + 7u) & ~(uint64_t)7u) << log2_items) + (t.n_chunks - t.n_long);
+}
+
+// False: this number is only there to fill a group of eight.
+__device__ __forceinline__ bool work_item(const DeviceTables& t, uint64_t item, uint32_t log2_items, WorkItem& w)
+{
+    const uint64_t in_long = (((uint64_t)t.n_long + 7u) & ~(uint64_t)7u) << log2_items;
+    uint32_t k;
+    if (item < in_long) {
+        k = (uint32_t)(item >> (3 + log2_items)) * 8u + ((uint32_t)item & 7u);
+        w.part = (int)(((uint32_t)item >> 3) & ((1u << log2_items) - 1u));
+        if (k >= t.n_long) return false;
+    } else {
+        k = t.n_long + (uint32_t)(item - in_long);
+        w.part = 0;
+    }
+    w.chunk = load_work(t.work, k);
+    return true;
+}
+
+// All loads of this wave are there before anything else is done.  With seven arrays and a copy to write, stores that start
+// while the item's last loads are still on their way cost more in read/write turnaround than they gain: 133 M parameters with
+// bf16 gradients and copies 646 us per step without, 631 with; 1.9 B with fp32 gradients 10.78, 10.72 ms.  Without the copy
+// (1500 ragged tensors 2.27, 2.34 ms; 5000 small ones 106, 112 us) and for Lion (6.65, 6.71 ms) it is the other way round.
+__device__ __forceinline__ void wait_for_loads()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (0xF << 8));          // vmcnt(0)
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// Waves per SIMD that the update kernel may have in flight.  One wave holds 16 loads of 1 KiB, so two are enough to cover
+// the latency, and more only open more DRAM rows at once: AdamW on GPT-2-small shapes 657 us per step with 2, 667 with 3, 670
+// with 4 (Llama-3-8B shapes 10.75, 10.90, 10.87 ms for 4 layers).  Lion has fewer arrays in flight: 6.56, 6.55, 6.60 ms.
+template <int OPT>
+constexpr int kUpdateWaves = OPT == ADAGC_OPT_ADAMW ? 2 : 3;
+
 template <int OPT, bool BF16G, bool COPY, int U, bool NT, bool TELE>
-__global__ __launch_bounds__(kBlock) void update_kernel(DeviceTables t, UpdateArgs a, uint32_t items_per_chunk,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kUpdateWaves<OPT>, kUpdateWaves<OPT>))) void update_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items,
                                                         const StepScalars* device_scalars)
 {
     static_assert(kVecPerLane % U == 0, "a chunk is a whole number of tiles");
@@ -561,53 +541,65 @@ __global__ __launch_bounds__(kBlock) void update_kernel(DeviceTables t, UpdateAr
     const int tid = threadIdx.x;
     __shared__ double tele_sums[3][kWavesPerBlock];
 
-    const uint32_t group = 8u * items_per_chunk;
-    const int tiles_per_item = kTiles / (int)items_per_chunk;
-    const uint64_t n_items = (((uint64_t)t.n_chunks + 7u) & ~(uint64_t)7u) * items_per_chunk;
+    const int tiles_per_item = kTiles >> log2_items;
+    const uint64_t n_items = work_items(t, log2_items);
     for (uint64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
-        const uint32_t r = (uint32_t)(item % group);
-        const uint32_t k = (uint32_t)(item / group) * 8u + (r & 7u);
-        const int isub = (int)(r >> 3);
-        if (k >= t.n_chunks) continue;
-        const uint32_t c = t.schedule ? t.schedule[k] : k;     // no visiting order given: list order
-        const ChunkView cv = chunk_view(t, c);
-        const TensorArgs& ta = t.targs[cv.tensor];
-        const double h = t.coef64[cv.tensor];     // the tensor's coefficient as computed, in double
-        const double uc = a.update_clip ? t.ucoef64[cv.tensor] : 1.0;   // update clipping: scales the direction
-        const void* g = grad_chunk_ptr<BF16G>(ta.grad, cv.first);
-        float* p = reinterpret_cast<float*>(ta.param) + cv.first;
-        float* m = reinterpret_cast<float*>(ta.exp_avg) + cv.first;
-        float* v = kHasV ? reinterpret_cast<float*>(ta.exp_avg_sq) + cv.first : nullptr;
-        uint16_t* pc = COPY ? reinterpret_cast<uint16_t*>(ta.param_copy) + cv.first : nullptr;
+        WorkItem w;
+        if (!work_item(t, item, log2_items, w)) continue;
+        const uint32_t tensor = w.chunk.tensor;
+        const int len = (int)w.chunk.len;
+        const int64_t first = first_element(w.chunk);
+        const TensorArgs ta = load_tensor(t.targs, tensor);
+        const double h = uniform_load(t.coef64 + tensor);     // the tensor's coefficient as computed, in double
+        const double uc = a.update_clip ? uniform_load(t.ucoef64 + tensor) : 1.0;   // update clipping: scales the direction
+        const gcbytes g = grad_at<BF16G>(ta.grad, first);
+        const gfloat p = (gfloat)ta.param + first;
+        const gfloat m = (gfloat)ta.exp_avg + first;
+        const gfloat v = kHasV ? (gfloat)ta.exp_avg_sq + first : nullptr;
+        const gu16 pc = COPY ? (gu16)ta.param_copy + first : nullptr;
         double tele[3] = {0.0, 0.0, 0.0};
 
 #pragma unroll 1
         for (int tt = 0; tt < tiles_per_item; ++tt) {
-            const int sub = isub * tiles_per_item + tt;
+            const int sub = w.part * tiles_per_item + tt;
             const int e0 = sub * kTileElems;                                   // the tile's elements inside the chunk:
-            const int e1 = cv.len < e0 + kTileElems ? cv.len : e0 + kTileElems; // [e0, e1), empty past a ragged end
+            const int e1 = len < e0 + kTileElems ? len : e0 + kTileElems; // [e0, e1), empty past a ragged end
             if (e0 >= e1) break;
             if (ta.vec_ok) {
-                f32x4* p4 = reinterpret_cast<f32x4*>(p);
-                f32x4* m4 = reinterpret_cast<f32x4*>(m);
-                f32x4* v4 = reinterpret_cast<f32x4*>(v);
-                u32x2* c4 = reinterpret_cast<u32x2*>(pc);
+                const auto p4 = (ADAGC_GLOBAL f32x4_any*)p;
+                const auto m4 = (ADAGC_GLOBAL f32x4_any*)m;
+                const auto v4 = (ADAGC_GLOBAL f32x4_any*)v;
+                const auto c4 = (ADAGC_GLOBAL u32x2_any*)pc;
                 const int v0 = sub * kTileVecs;
 
-                if (e1 - e0 == kTileElems) {
+                // Whole tiles and ragged ends alike: all loads before the first store (in a loop over the vectors of a
+                // ragged end they would wait for the stores of the round before).  Lanes past the last whole vector load
+                // that one again and store nothing; up to three single elements come with the tile that ends the chunk.
+                const int nvec = len >> 2;
+                const int j = (nvec << 2) + tid;
+                const bool single = e1 == len && j < len;
+                ElemState s = {0.f, 0.f, 0.f};
+                float g1 = 0.f;
+                if (single) {
+                    s = {p[j], m[j], kHasV ? v[j] : 0.f};
+                    g1 = load_grad1<BF16G>(g, j);
+                }
+                if (v0 < nvec) {
                     f32x4 gg[U], pp[U], mm[U], vv[U];
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
-                        const int idx = v0 + u * kBlock + tid;
+                        const int want = v0 + u * kBlock + tid, idx = want < nvec ? want : nvec - 1;
                         gg[u] = load_grad4<BF16G, NTL>(g, idx);
                         pp[u] = ld<NTL>(p4 + idx);
                         mm[u] = ld<NTL>(m4 + idx);
                         if constexpr (kHasV) vv[u] = ld<NTL>(v4 + idx);
                         else vv[u] = f32x4{0.f, 0.f, 0.f, 0.f};
                     }
+                    if constexpr (kHasV && COPY) wait_for_loads();
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
                         const int idx = v0 + u * kBlock + tid;
+                        if (idx >= nvec) break;
                         const f32x4 p_old = pp[u];
                         apply_vec<OPT>(a, h, uc, gg[u], pp[u], mm[u], vv[u]);
                         if constexpr (TELE) tele_vec<kHasV>(tele, p_old, pp[u], mm[u], vv[u]);
@@ -616,34 +608,15 @@ __global__ __launch_bounds__(kBlock) void update_kernel(DeviceTables t, UpdateAr
                         if constexpr (kHasV) st<NTS>(v4 + idx, vv[u]);
                         if constexpr (COPY) st<NTS>(c4 + idx, pack_bf16x4(pp[u]));
                     }
-                } else {
-                    // the last tile of a ragged chunk: its whole vectors, then up to three single elements
-                    const int nvec = cv.len >> 2;
-                    for (int idx = v0 + tid; idx < nvec; idx += kBlock) {
-                        f32x4 gg = load_grad4<BF16G, NTL>(g, idx);
-                        f32x4 pp = ld<NTL>(p4 + idx);
-                        f32x4 mm = ld<NTL>(m4 + idx);
-                        f32x4 vv = f32x4{0.f, 0.f, 0.f, 0.f};
-                        if constexpr (kHasV) vv = ld<NTL>(v4 + idx);
-                        const f32x4 p_old = pp;
-                        apply_vec<OPT>(a, h, uc, gg, pp, mm, vv);
-                        if constexpr (TELE) tele_vec<kHasV>(tele, p_old, pp, mm, vv);
-                        st<NTS>(p4 + idx, pp);
-                        st<NTS>(m4 + idx, mm);
-                        if constexpr (kHasV) st<NTS>(v4 + idx, vv);
-                        if constexpr (COPY) st<NTS>(c4 + idx, pack_bf16x4(pp));
-                    }
-                    const int j = (nvec << 2) + tid;
-                    if (j < cv.len) {
-                        ElemState s = {p[j], m[j], kHasV ? v[j] : 0.f};
-                        const float p_old = s.p;
-                        apply_elem<OPT>(a, h, uc, load_grad1<BF16G>(g, j), s);
-                        if constexpr (TELE) tele_elem<kHasV>(tele, p_old, s.p, s.m, s.v);
-                        p[j] = s.p;
-                        m[j] = s.m;
-                        if constexpr (kHasV) v[j] = s.v;
-                        if constexpr (COPY) pc[j] = (uint16_t)float_to_bf16_bits(s.p);
-                    }
+                }
+                if (single) {
+                    const float p_old = s.p;
+                    apply_elem<OPT>(a, h, uc, g1, s);
+                    if constexpr (TELE) tele_elem<kHasV>(tele, p_old, s.p, s.m, s.v);
+                    p[j] = s.p;
+                    m[j] = s.m;
+                    if constexpr (kHasV) v[j] = s.v;
+                    if constexpr (COPY) pc[j] = (uint16_t)float_to_bf16_bits(s.p);
                 }
             } else {
                 for (int j = e0 + tid; j < e1; j += kBlock) {
@@ -660,18 +633,18 @@ __global__ __launch_bounds__(kBlock) void update_kernel(DeviceTables t, UpdateAr
         }
 
         if constexpr (TELE) {
-            // every item of every chunk writes its slots, an empty item writes zeros
+            // every item writes its slots; those that a chunk of one item has no item for stay zero from the start
 #pragma unroll
             for (int q = 0; q < 3; ++q) {
-                const double w = wave_sum_f64(tele[q]);
-                if ((tid & 63) == 0) tele_sums[q][tid >> 6] = w;
+                const double part = wave_sum_f64(tele[q]);
+                if ((tid & 63) == 0) tele_sums[q][tid >> 6] = part;
             }
             __syncthreads();
             if (tid < 3) {
                 double b = tele_sums[tid][0];
 #pragma unroll
-                for (int w = 1; w < kWavesPerBlock; ++w) b += tele_sums[tid][w];
-                t.tele_partials[((size_t)tid * t.n_chunks + c) * items_per_chunk + isub] = b;
+                for (int k = 1; k < kWavesPerBlock; ++k) b += tele_sums[tid][k];
+                t.tele_partials[(((size_t)tid * t.n_chunks + w.chunk.slot) << log2_items) + w.part] = b;
             }
             __syncthreads();
         }
@@ -723,45 +696,39 @@ __device__ __forceinline__ void stat_acc(double (&acc)[2], float theta, double d
 }
 
 template <int OPT, bool BF16G, bool LINF, bool NT>
-__global__ __launch_bounds__(kBlock) void direction_stats_kernel(DeviceTables t, UpdateArgs a, uint32_t items_per_chunk)
+__global__ __launch_bounds__(kBlock) void direction_stats_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items)
 {
-    constexpr int U = 4;
+    constexpr int U = default_unroll(OPT);
     constexpr bool kHasV = (OPT == ADAGC_OPT_ADAMW);
-    constexpr int kTiles = kVecPerLane / U;
     constexpr int kTileVecs = U * kBlock;
     constexpr int kTileElems = kTileVecs * 4;
     const int tid = threadIdx.x;
     __shared__ double wave_part[2][kWavesPerBlock];
 
-    const uint32_t group = 8u * items_per_chunk;
-    const int tiles_per_item = kTiles / (int)items_per_chunk;
-    const uint64_t n_items = (((uint64_t)t.n_chunks + 7u) & ~(uint64_t)7u) * items_per_chunk;
+    const int item_elems = kChunkElems >> log2_items;      // may be less than a tile: the caller chooses
+    const uint64_t n_items = work_items(t, log2_items);
     for (uint64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
-        const uint32_t r = (uint32_t)(item % group);
-        const uint32_t k = (uint32_t)(item / group) * 8u + (r & 7u);
-        const int isub = (int)(r >> 3);
-        if (k >= t.n_chunks) continue;
-        const uint32_t c = t.schedule ? t.schedule[k] : k;
-        const ChunkView cv = chunk_view(t, c);
-        const TensorArgs& ta = t.targs[cv.tensor];
-        const void* g = grad_chunk_ptr<BF16G>(ta.grad, cv.first);
-        const float* p = reinterpret_cast<const float*>(ta.param) + cv.first;
-        const float* m = reinterpret_cast<const float*>(ta.exp_avg) + cv.first;
-        const float* v = kHasV ? reinterpret_cast<const float*>(ta.exp_avg_sq) + cv.first : nullptr;
+        WorkItem w;
+        if (!work_item(t, item, log2_items, w)) continue;
+        const int len = (int)w.chunk.len;
+        const int64_t first = first_element(w.chunk);
+        const TensorArgs ta = load_tensor(t.targs, w.chunk.tensor);
+        const gcbytes g = grad_at<BF16G>(ta.grad, first);
+        const gcfloat p = (gcfloat)ta.param + first;
+        const gcfloat m = (gcfloat)ta.exp_avg + first;
+        const gcfloat v = kHasV ? (gcfloat)ta.exp_avg_sq + first : nullptr;
         double acc[2] = {0.0, 0.0};
 
+        const int item_begin = w.part * item_elems;
+        const int item_end = len < item_begin + item_elems ? len : item_begin + item_elems;
 #pragma unroll 1
-        for (int tt = 0; tt < tiles_per_item; ++tt) {
-            const int sub = isub * tiles_per_item + tt;
-            const int e0 = sub * kTileElems;
-            const int e1 = cv.len < e0 + kTileElems ? cv.len : e0 + kTileElems;
-            if (e0 >= e1) break;
+        for (int e0 = item_begin; e0 < item_end; e0 += kTileElems) {
+            const int e1 = item_end < e0 + kTileElems ? item_end : e0 + kTileElems;
             if (ta.vec_ok) {
-                const f32x4* p4 = reinterpret_cast<const f32x4*>(p);
-                const f32x4* m4 = reinterpret_cast<const f32x4*>(m);
-                const f32x4* v4 = reinterpret_cast<const f32x4*>(v);
-                const int v0 = sub * kTileVecs;
-                const int vend = (e1 - e0 == kTileElems) ? v0 + kTileVecs : (cv.len >> 2);
+                const auto p4 = (const ADAGC_GLOBAL f32x4_any*)p;
+                const auto m4 = (const ADAGC_GLOBAL f32x4_any*)m;
+                const auto v4 = (const ADAGC_GLOBAL f32x4_any*)v;
+                const int v0 = e0 >> 2, vend = e1 >> 2;
                 if (e1 - e0 == kTileElems) {
                     f32x4 gg[U], pp[U], mm[U], vv[U];
 #pragma unroll
@@ -792,8 +759,8 @@ __global__ __launch_bounds__(kBlock) void direction_stats_kernel(DeviceTables t,
                         stat_acc<LINF>(acc, pp.z, direction_elem<OPT>(a, gg.z, mm.z, vv.z));
                         stat_acc<LINF>(acc, pp.w, direction_elem<OPT>(a, gg.w, mm.w, vv.w));
                     }
-                    const int j = ((cv.len >> 2) << 2) + tid;      // up to three single elements at the ragged end
-                    if (j < cv.len)
+                    const int j = (vend << 2) + tid;            // up to three single elements at the ragged end
+                    if (j < e1)
                         stat_acc<LINF>(acc, p[j], direction_elem<OPT>(a, load_grad1<BF16G>(g, j), m[j], kHasV ? v[j] : 0.f));
                 }
             } else {
@@ -802,18 +769,18 @@ __global__ __launch_bounds__(kBlock) void direction_stats_kernel(DeviceTables t,
             }
         }
 
-        // every item of every chunk writes its two slots, an empty item writes zeros
+        // every item writes its two slots; those that a chunk of one item has no item for stay zero from the start
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            const double w = LINF ? wave_max_f64(acc[q]) : wave_sum_f64(acc[q]);
-            if ((tid & 63) == 0) wave_part[q][tid >> 6] = w;
+            const double part = LINF ? wave_max_f64(acc[q]) : wave_sum_f64(acc[q]);
+            if ((tid & 63) == 0) wave_part[q][tid >> 6] = part;
         }
         __syncthreads();
         if (tid < 2) {
             double b = wave_part[tid][0];
 #pragma unroll
-            for (int w = 1; w < kWavesPerBlock; ++w) b = LINF ? fmax(b, wave_part[tid][w]) : b + wave_part[tid][w];
-            t.ustat_partials[((size_t)tid * t.n_chunks + c) * items_per_chunk + isub] = b;
+            for (int v = 1; v < kWavesPerBlock; ++v) b = LINF ? fmax(b, wave_part[tid][v]) : b + wave_part[tid][v];
+            t.ustat_partials[(((size_t)tid * t.n_chunks + w.chunk.slot) << log2_items) + w.part] = b;
         }
         __syncthreads();
     }
@@ -883,7 +850,6 @@ __global__ __launch_bounds__(kBlock) void finalize_telemetry_kernel(DeviceTables
 }
 
 using UpdateFn = void (*)(DeviceTables, UpdateArgs, uint32_t, const StepScalars*);
-using SumsqFn = void (*)(DeviceTables);
 
 template <int OPT, bool BF16G, bool COPY, int U>
 UpdateFn select_update_flags(int nt, int tele)
@@ -915,17 +881,12 @@ UpdateFn select_update(int optimizer, int grad_bf16, int with_copy, int unroll, 
     }
 }
 
-SumsqFn select_sumsq(int grad_bf16, int nt)
-{
-    if (nt) return grad_bf16 ? sumsq_partials_kernel<true, true> : sumsq_partials_kernel<false, true>;
-    return grad_bf16 ? sumsq_partials_kernel<true, false> : sumsq_partials_kernel<false, false>;
-}
-
 }  // namespace
 
-hipError_t launch_sumsq_partials(const DeviceTables& t, int grad_bf16, int nt, int grid, hipStream_t stream)
+hipError_t launch_sumsq_partials(const DeviceTables& t, int grad_bf16, int grid, hipStream_t stream)
 {
-    select_sumsq(grad_bf16, nt)<<<dim3(grid), dim3(kBlock), 0, stream>>>(t);
+    if (grad_bf16) sumsq_partials_kernel<true><<<dim3(grid), dim3(kBlock), 0, stream>>>(t);
+    else sumsq_partials_kernel<false><<<dim3(grid), dim3(kBlock), 0, stream>>>(t);
     return hipGetLastError();
 }
 
@@ -956,6 +917,8 @@ hipError_t launch_finalize_global(const DeviceTables& t, float* ema, const RuleA
 
 using StatsFn = void (*)(DeviceTables, UpdateArgs, uint32_t);
 
+static uint32_t log2_of(int power_of_two) { return (uint32_t)__builtin_ctz((unsigned)power_of_two); }
+
 template <int OPT, bool BF16G>
 static StatsFn select_stats_flags(bool linf, int nt)
 {
@@ -970,7 +933,7 @@ hipError_t launch_update_clip_rule(const DeviceTables& t, const UpdateArgs& u, c
     StatsFn fn;
     if (optimizer == ADAGC_OPT_LION) fn = grad_bf16 ? select_stats_flags<ADAGC_OPT_LION, true>(linf, nt) : select_stats_flags<ADAGC_OPT_LION, false>(linf, nt);
     else fn = grad_bf16 ? select_stats_flags<ADAGC_OPT_ADAMW, true>(linf, nt) : select_stats_flags<ADAGC_OPT_ADAMW, false>(linf, nt);
-    fn<<<dim3(grid), dim3(kBlock), 0, stream>>>(t, u, (uint32_t)items_per_chunk);
+    fn<<<dim3(grid), dim3(kBlock), 0, stream>>>(t, u, log2_of(items_per_chunk));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     finalize_update_clip_kernel<<<dim3(t.n_tensors), dim3(kBlock), 0, stream>>>(t, r, (uint32_t)items_per_chunk);
@@ -999,7 +962,7 @@ hipError_t launch_update(const DeviceTables& t, const UpdateArgs& a, int optimiz
                          hipStream_t stream, bool device_scalars)
 {
     select_update(optimizer, grad_bf16, with_copy, unroll, nt, tele)<<<dim3(grid), dim3(kBlock), 0, stream>>>(
-        t, a, (uint32_t)items_per_chunk, device_scalars ? t.scalars : nullptr);
+        t, a, log2_of(items_per_chunk), device_scalars ? t.scalars : nullptr);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !tele) return e;
     finalize_telemetry_kernel<<<dim3(t.n_tensors), dim3(kBlock), 0, stream>>>(t, (uint32_t)items_per_chunk);

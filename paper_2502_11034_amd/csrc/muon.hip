@@ -17,27 +17,11 @@
 // (kernels.hip); the Newton-Schulz products run in muon_gemm.hip.  Arithmetic is double with one rounding per
 // stored value, as in the other update kernels; reductions are in fixed order.
 
+#include "adagc_device.h"
 #include "muon_internal.h"
 
 namespace adagc {
 namespace {
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ uint32_t f32_to_bf16_bits(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    uint32_t rounded = (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-    return ((u & 0x7FFFFFFFu) > 0x7F800000u) ? ((u >> 16) | 0x40u) : rounded;
-}
-
-template <bool BF16>
-__device__ __forceinline__ float grad_at(const void* g, int64_t j)
-{
-    if constexpr (BF16) return __uint_as_float((uint32_t)reinterpret_cast<const uint16_t*>(g)[j] << 16);
-    else return reinterpret_cast<const float*>(g)[j];
-}
 
 // M' and U of one element.  The momentum is stored as fp32; U uses the stored value.
 __device__ __forceinline__ double momentum_elem(double h, double mu, int nesterov, float g, float m_prev, float* m_new)
@@ -64,39 +48,25 @@ __global__ __launch_bounds__(kBlock) void muon_momentum_kernel(DeviceTables t, d
     __shared__ double wave_sums[kWavesPerBlock];
     const int tid = threadIdx.x;
     for (uint32_t k = blockIdx.x; k < t.n_chunks; k += gridDim.x) {
-        const uint32_t c = t.schedule ? t.schedule[k] : k;     // the visiting order of the norm kernel (XCD-aware)
-        const ChunkRef ck = t.chunks[c];
-        const TensorArgs& ta = t.targs[ck.tensor];
-        const int64_t first = (int64_t)ck.index * kChunkElems;
-        const int64_t rest = ta.numel - first;
-        const int len = rest < (int64_t)kChunkElems ? (int)rest : kChunkElems;
-        const double h = t.coef64[ck.tensor];
-        float* m = reinterpret_cast<float*>(ta.exp_avg) + first;
+        const WorkRef ck = load_work(t.work, k);                // the visiting order of the norm kernel (XCD-aware)
+        const TensorArgs ta = load_tensor(t.targs, ck.tensor);
+        const int len = (int)ck.len;
+        const double h = uniform_load(t.coef64 + ck.tensor);
+        const gcbytes g0 = grad_at<BF16>(ta.grad, first_element(ck));
+        const gfloat m = (gfloat)ta.exp_avg + first_element(ck);
         double acc = 0.0;
         int done = 0;
         if (ta.vec_ok) {
             const int groups = len / 4;
-            f32x4* m4 = reinterpret_cast<f32x4*>(m);
-            auto load_g = [&](int j, float (&g)[4]) {
-                if constexpr (BF16) {
-                    const u32x2 w = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(reinterpret_cast<const uint16_t*>(ta.grad) + first) + j);
-                    g[0] = __uint_as_float(w.x << 16);
-                    g[1] = __uint_as_float(w.x & 0xFFFF0000u);
-                    g[2] = __uint_as_float(w.y << 16);
-                    g[3] = __uint_as_float(w.y & 0xFFFF0000u);
-                } else {
-                    const f32x4 w = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(ta.grad) + first) + j);
-                    g[0] = w.x; g[1] = w.y; g[2] = w.z; g[3] = w.w;
-                }
-            };
-            auto update4 = [&](int j, const float (&g)[4], const f32x4 mp) {
+            const auto m4 = (ADAGC_GLOBAL f32x4_any*)m;
+            auto update4 = [&](int j, const f32x4 g, const f32x4 mp) {
                 f32x4 mn;
                 float e;
-                double u = momentum_elem(h, mu, nesterov, g[0], mp.x, &e); mn.x = e; acc = fma(u, u, acc);
-                u = momentum_elem(h, mu, nesterov, g[1], mp.y, &e); mn.y = e; acc = fma(u, u, acc);
-                u = momentum_elem(h, mu, nesterov, g[2], mp.z, &e); mn.z = e; acc = fma(u, u, acc);
-                u = momentum_elem(h, mu, nesterov, g[3], mp.w, &e); mn.w = e; acc = fma(u, u, acc);
-                __builtin_nontemporal_store(mn, m4 + j);
+                double u = momentum_elem(h, mu, nesterov, g.x, mp.x, &e); mn.x = e; acc = fma(u, u, acc);
+                u = momentum_elem(h, mu, nesterov, g.y, mp.y, &e); mn.y = e; acc = fma(u, u, acc);
+                u = momentum_elem(h, mu, nesterov, g.z, mp.z, &e); mn.z = e; acc = fma(u, u, acc);
+                u = momentum_elem(h, mu, nesterov, g.w, mp.w, &e); mn.w = e; acc = fma(u, u, acc);
+                st<true>(m4 + j, mn);
             };
             if (len == kChunkElems) {
                 // a full chunk is 16 vectors per lane: 8 of each array in flight at a time
@@ -104,28 +74,23 @@ __global__ __launch_bounds__(kBlock) void muon_momentum_kernel(DeviceTables t, d
                 static_assert(kPerLane % kFlight == 0, "chunk size and block size");
 #pragma unroll
                 for (int base = 0; base < kPerLane; base += kFlight) {
-                    float g[kFlight][4];
-                    f32x4 mp[kFlight];
+                    f32x4 g[kFlight], mp[kFlight];
 #pragma unroll
                     for (int v = 0; v < kFlight; ++v) {
-                        load_g((base + v) * kBlock + tid, g[v]);
-                        mp[v] = __builtin_nontemporal_load(m4 + (base + v) * kBlock + tid);
+                        g[v] = load_grad4<BF16, true>(g0, (base + v) * kBlock + tid);
+                        mp[v] = ld<true>(m4 + (base + v) * kBlock + tid);
                     }
 #pragma unroll
                     for (int v = 0; v < kFlight; ++v) update4((base + v) * kBlock + tid, g[v], mp[v]);
                 }
             } else {
-                for (int j = tid; j < groups; j += kBlock) {
-                    float g[4];
-                    load_g(j, g);
-                    update4(j, g, __builtin_nontemporal_load(m4 + j));
-                }
+                for (int j = tid; j < groups; j += kBlock) update4(j, load_grad4<BF16, true>(g0, j), ld<true>(m4 + j));
             }
             done = groups * 4;
         }
         for (int j = done + tid; j < len; j += kBlock) {
             float m_new;
-            const double u = momentum_elem(h, mu, nesterov, grad_at<BF16>(ta.grad, first + j), m[j], &m_new);
+            const double u = momentum_elem(h, mu, nesterov, load_grad1<BF16>(g0, j), m[j], &m_new);
             m[j] = m_new;
             acc = fma(u, u, acc);
         }
@@ -136,24 +101,26 @@ __global__ __launch_bounds__(kBlock) void muon_momentum_kernel(DeviceTables t, d
             double b = wave_sums[0];
 #pragma unroll
             for (int w = 1; w < kWavesPerBlock; ++w) b += wave_sums[w];
-            t.partials[c] = b;
+            t.partials[ck.slot] = b;
         }
         __syncthreads();
     }
 }
 
-// What a workgroup needs to know about matrix z of its batch: the caller's arrays, and where the matrix lies in the
-// workspace.  The iteration runs on the wide orientation: X is mp x np, Y = X^T; a tall matrix is its own Y.
+// What a workgroup needs to know about matrix z of its batch.  The iteration runs on the wide orientation: X is mp x np,
+// Y = X^T; a tall matrix is its own Y.
 struct MatrixView {
     uint32_t tensor;
     int64_t  rows, cols;
+    double   scale;
     bool     tall;
 };
 
 __device__ __forceinline__ MatrixView matrix_view(const MuonMatrix* members, uint32_t z)
 {
-    const MuonMatrix mm = members[z];
-    return {mm.tensor, mm.rows, mm.cols, mm.rows > mm.cols};
+    const MuonMatrix* mm = members + z;
+    const int64_t rows = uniform_load(&mm->rows), cols = uniform_load(&mm->cols);
+    return {uniform_load(&mm->tensor), rows, cols, uniform_load(&mm->scale), rows > cols};
 }
 
 __device__ __forceinline__ bool is_aligned(const void* p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
@@ -162,10 +129,10 @@ __device__ __forceinline__ bool is_aligned(const void* p, uintptr_t a) { return 
 // its extent padded to multiples of 128; every element of the padded extent is written: zeros outside the matrix.
 // same[r][c] (leading dimension ld_same) receives the tile as is, trans[c][r] (ld_trans) its transpose, through LDS so
 // that both are written along their rows.
-// VEC (cols a multiple of 4, g and m 16-byte aligned; bf16 g 8-byte): a lane handles 4 consecutive elements of a
+// VEC (cols a multiple of 4, g and m aligned to their elements): a lane handles 4 consecutive elements of a
 // row on the way in and 4 consecutive elements of a transposed row on the way out: 16-byte loads, 8-byte stores.
 template <bool BF16, bool VEC>
-__device__ __forceinline__ void normalise_tile(uint16_t* tile, const void* g, const float* m, int64_t rows, int64_t cols, int64_t r0,
+__device__ __forceinline__ void normalise_tile(uint16_t* tile, gcbytes g, gcfloat m, int64_t rows, int64_t cols, int64_t r0,
                                                int64_t c0, double h, double denom, double mu, int nesterov, uint16_t* same,
                                                int64_t ld_same, uint16_t* trans, int64_t ld_trans)
 {
@@ -173,12 +140,11 @@ __device__ __forceinline__ void normalise_tile(uint16_t* tile, const void* g, co
     auto x0_bits = [&](float gv, float mv) {
         const double gh = h * (double)gv;
         const double u = nesterov ? gh + mu * (double)mv : (double)mv;         // m already holds this step's momentum
-        return f32_to_bf16_bits((float)(u / denom));
+        return float_to_bf16_bits((float)(u / denom));
     };
     if constexpr (VEC) {
         const int q = (threadIdx.x & 15) * 4, p = threadIdx.x >> 4;            // 16 lanes per row, 16 rows per pass
-        float gv[4][4];
-        f32x4 mv[4];
+        f32x4 gv[4], mv[4];
         bool in[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {                                          // all loads first
@@ -186,25 +152,16 @@ __device__ __forceinline__ void normalise_tile(uint16_t* tile, const void* g, co
             in[k] = r < rows && c < cols;
             if (!in[k]) continue;
             const int64_t j = r * cols + c;
-            if constexpr (BF16) {
-                const u32x2 w = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(reinterpret_cast<const uint16_t*>(g) + j));
-                gv[k][0] = __uint_as_float(w.x << 16);
-                gv[k][1] = __uint_as_float(w.x & 0xFFFF0000u);
-                gv[k][2] = __uint_as_float(w.y << 16);
-                gv[k][3] = __uint_as_float(w.y & 0xFFFF0000u);
-            } else {
-                const f32x4 w = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(g) + j));
-                gv[k][0] = w.x; gv[k][1] = w.y; gv[k][2] = w.z; gv[k][3] = w.w;
-            }
-            mv[k] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(m + j));
+            gv[k] = load_grad4<BF16, true>(g + j * (BF16 ? 2 : 4), 0);
+            mv[k] = ld<true>((const ADAGC_GLOBAL f32x4_any*)(m + j));
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int tr = p + 16 * k;
             u32x2 bits = {0u, 0u};
             if (in[k]) {
-                bits.x = x0_bits(gv[k][0], mv[k].x) | (x0_bits(gv[k][1], mv[k].y) << 16);
-                bits.y = x0_bits(gv[k][2], mv[k].z) | (x0_bits(gv[k][3], mv[k].w) << 16);
+                bits.x = x0_bits(gv[k].x, mv[k].x) | (x0_bits(gv[k].y, mv[k].y) << 16);
+                bits.y = x0_bits(gv[k].z, mv[k].z) | (x0_bits(gv[k].w, mv[k].w) << 16);
             }
             *reinterpret_cast<u32x2*>(&tile[tr * kTileLd + q]) = bits;
             *reinterpret_cast<u32x2*>(same + (r0 + tr) * ld_same + c0 + q) = bits;
@@ -226,7 +183,7 @@ __device__ __forceinline__ void normalise_tile(uint16_t* tile, const void* g, co
             uint16_t bits = 0;
             if (r < rows && c < cols) {
                 const int64_t j = r * cols + c;
-                bits = (uint16_t)x0_bits(grad_at<BF16>(g, j), m[j]);
+                bits = (uint16_t)x0_bits(load_grad1<BF16>(g + j * (BF16 ? 2 : 4), 0), m[j]);
             }
             tile[(ty + 4 * k) * kTileLd + tx] = bits;
             same[r * ld_same + c] = bits;
@@ -247,42 +204,43 @@ __global__ __launch_bounds__(256) void muon_normalise_kernel(DeviceTables t, con
 {
     __shared__ __attribute__((aligned(8))) uint16_t tile[64 * 68];
     const MatrixView mv = matrix_view(members, blockIdx.y);
-    const TensorArgs& ta = t.targs[mv.tensor];
+    const TensorArgs ta = load_tensor(t.targs, mv.tensor);
     const uint32_t tile_cols = (uint32_t)((mv.tall ? mp : np) / 64);
     const int64_t r0 = (int64_t)(blockIdx.x / tile_cols) * 64, c0 = (int64_t)(blockIdx.x % tile_cols) * 64;
     const int64_t at = (int64_t)blockIdx.y * mp * np;
     uint16_t *same = (mv.tall ? y : x) + at, *trans = (mv.tall ? x : y) + at;
     const int64_t ld_same = mv.tall ? mp : np, ld_trans = mv.tall ? np : mp;
-    const double h = t.coef64[mv.tensor];
-    const double denom = sqrt(t.sumsq[mv.tensor]) + 1e-7;
-    const float* m = static_cast<const float*>(ta.exp_avg);
+    const double h = uniform_load(t.coef64 + mv.tensor);
+    const double denom = sqrt(uniform_load(t.sumsq + mv.tensor)) + 1e-7;
+    const gcbytes g = (gcbytes)ta.grad;
+    const gcfloat m = (gcfloat)ta.exp_avg;
     // the workspace is padded to 128 elements a row, so only the caller's arrays decide
-    if (mv.cols % 4 == 0 && is_aligned(ta.grad, BF16 ? 8 : 16) && is_aligned(m, 16))
-        normalise_tile<BF16, true>(tile, ta.grad, m, mv.rows, mv.cols, r0, c0, h, denom, mu, nesterov, same, ld_same, trans, ld_trans);
+    if (mv.cols % 4 == 0 && is_aligned(ta.grad, BF16 ? 2 : 4) && is_aligned(ta.exp_avg, 4))
+        normalise_tile<BF16, true>(tile, g, m, mv.rows, mv.cols, r0, c0, h, denom, mu, nesterov, same, ld_same, trans, ld_trans);
     else
-        normalise_tile<BF16, false>(tile, ta.grad, m, mv.rows, mv.cols, r0, c0, h, denom, mu, nesterov, same, ld_same, trans, ld_trans);
+        normalise_tile<BF16, false>(tile, g, m, mv.rows, mv.cols, r0, c0, h, denom, mu, nesterov, same, ld_same, trans, ld_trans);
 }
 
 // theta <- theta - lr (wd theta + scale O); workgroup (b, z): elements b * 4096 ... of matrix z of the batch, which O
 // (bf16, rows of ld_o elements) holds row by row.
 // 4096 elements per workgroup whatever the row length: with a workgroup per row, a row of 768 kept 192 of 256 lanes busy
 // with one access each.
-// VEC: cols is a multiple of 4 and theta (and the copy) are 16-byte (8-byte) aligned: 4 elements per lane and access.
+// Where cols is a multiple of 4 and theta (and the copy) are aligned to their elements: 4 elements per lane and access.
 constexpr int kApplyElems = 4096;
 template <bool COPY>
 __global__ __launch_bounds__(256) void muon_apply_kernel(DeviceTables t, const MuonMatrix* members, int mp, int np, const uint16_t* x,
                                                           const uint16_t* y, double lr, double wd)
 {
     const MatrixView mv = matrix_view(members, blockIdx.y);
-    const TensorArgs& ta = t.targs[mv.tensor];
+    const TensorArgs ta = load_tensor(t.targs, mv.tensor);
     const int64_t numel = mv.rows * mv.cols, first = (int64_t)blockIdx.x * kApplyElems;
     if (first >= numel) return;
     const int len = numel - first < kApplyElems ? (int)(numel - first) : kApplyElems;
-    const double scale = members[blockIdx.y].scale;
+    const double scale = mv.scale;
     const int64_t ld_o = mv.tall ? mp : np;
     const uint16_t* o = (mv.tall ? y : x) + (int64_t)blockIdx.y * mp * np;
-    float* theta = static_cast<float*>(ta.param) + first;
-    uint16_t* copy = COPY ? static_cast<uint16_t*>(ta.param_copy) + first : nullptr;
+    const gfloat theta = (gfloat)ta.param + first;
+    const gu16 copy = COPY ? (gu16)ta.param_copy + first : nullptr;
     const uint32_t cols = (uint32_t)mv.cols;
     const int64_t row0 = first / mv.cols;                           // the same in all lanes
     const uint32_t col0 = (uint32_t)(first - row0 * mv.cols);
@@ -293,7 +251,7 @@ __global__ __launch_bounds__(256) void muon_apply_kernel(DeviceTables t, const M
         return (float)(th - lr * (wd * th + scale * ov));
     };
     const int tid = threadIdx.x;
-    if (cols % 4 == 0 && is_aligned(ta.param, 16) && (!COPY || is_aligned(ta.param_copy, 8))) {
+    if (cols % 4 == 0 && is_aligned(ta.param, 4) && (!COPY || is_aligned(ta.param_copy, 2))) {
         constexpr int kPer = kApplyElems / 4 / 256;
         f32x4 th[kPer];
         u32x2 ow[kPer];
@@ -302,7 +260,7 @@ __global__ __launch_bounds__(256) void muon_apply_kernel(DeviceTables t, const M
             const uint32_t e = (uint32_t)(u * 256 + tid) * 4u;
             if ((int)e >= len) continue;                            // len is a multiple of 4 here, as cols is
             const uint32_t q = col0 + e, r = q / cols, c = q - r * cols;
-            th[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(theta + e));
+            th[u] = ld<true>((const ADAGC_GLOBAL f32x4_any*)(theta + e));
             ow[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(o + (int64_t)r * ld_o + c));
         }
 #pragma unroll
@@ -314,12 +272,12 @@ __global__ __launch_bounds__(256) void muon_apply_kernel(DeviceTables t, const M
             out.y = one(th[u].y, ow[u].x >> 16);
             out.z = one(th[u].z, ow[u].y & 0xFFFFu);
             out.w = one(th[u].w, ow[u].y >> 16);
-            __builtin_nontemporal_store(out, reinterpret_cast<f32x4*>(theta + e));
+            st<true>((ADAGC_GLOBAL f32x4_any*)(theta + e), out);
             if constexpr (COPY) {
                 u32x2 cw;
-                cw.x = f32_to_bf16_bits(out.x) | (f32_to_bf16_bits(out.y) << 16);
-                cw.y = f32_to_bf16_bits(out.z) | (f32_to_bf16_bits(out.w) << 16);
-                __builtin_nontemporal_store(cw, reinterpret_cast<u32x2*>(copy + e));
+                cw.x = float_to_bf16_bits(out.x) | (float_to_bf16_bits(out.y) << 16);
+                cw.y = float_to_bf16_bits(out.z) | (float_to_bf16_bits(out.w) << 16);
+                st<true>((ADAGC_GLOBAL u32x2_any*)(copy + e), cw);
             }
         }
     } else {
@@ -327,7 +285,7 @@ __global__ __launch_bounds__(256) void muon_apply_kernel(DeviceTables t, const M
             const uint32_t q = col0 + (uint32_t)e, r = q / cols, c = q - r * cols;
             const float out = one(theta[e], o[(int64_t)r * ld_o + c]);
             theta[e] = out;
-            if constexpr (COPY) copy[e] = (uint16_t)f32_to_bf16_bits(out);
+            if constexpr (COPY) copy[e] = (uint16_t)float_to_bf16_bits(out);
         }
     }
 }

@@ -5,7 +5,7 @@
 // records reach the GPU as kernel arguments, so there is no copy, no memset and no event either.
 //
 // The norm, rule and update kernels are the ones adagc_step launches (kernels.hip), given pointers
-// into that array; the chunks are visited in list order.
+// into that array; the chunks are visited in list order, those of one work item last.
 
 #include <mutex>
 
@@ -20,8 +20,8 @@ constexpr size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 constexpr size_t kMaxT = ADAGC_STATIC_MAX_TENSORS;
 constexpr size_t kMaxC = ADAGC_STATIC_MAX_CHUNKS;
 constexpr size_t kOffTargs = 0;
-constexpr size_t kOffChunks = kOffTargs + align256(kMaxT * sizeof(TensorArgs));
-constexpr size_t kOffPartials = kOffChunks + align256(kMaxC * sizeof(ChunkRef));
+constexpr size_t kOffWork = kOffTargs + align256(kMaxT * sizeof(TensorArgs));
+constexpr size_t kOffPartials = kOffWork + align256(kMaxC * sizeof(WorkRef));
 constexpr size_t kOffSumsq = kOffPartials + align256(kMaxC * sizeof(double));
 constexpr size_t kOffCoef64 = kOffSumsq + align256(kMaxT * sizeof(double));
 constexpr size_t kOffGlobal = kOffCoef64 + align256(kMaxT * sizeof(double));
@@ -58,20 +58,28 @@ hipError_t scratch_address(int device, unsigned char** out)
 constexpr int kBatch = 56;
 struct TensorBatch {
     TensorArgs t[kBatch];
+    uint32_t   long_at[kBatch];    // where the tensor's long chunks go in the work table, and its short one if it has one
+    uint32_t   short_at[kBatch];
     uint32_t   first;    // list index of t[0]
     uint32_t   count;
 };
-static_assert(sizeof(TensorBatch) + 2 * sizeof(void*) <= 4096, "a batch fits the kernel-argument block");
+static_assert(sizeof(TensorBatch) + 3 * sizeof(void*) <= 4096, "a batch fits the kernel-argument block");
 
-// Workgroup b stores the record of tensor first+b and writes that tensor's rows of the chunk table.
-__global__ __launch_bounds__(kBlock) void store_tensor_batch_kernel(TensorBatch batch, TensorArgs* targs, ChunkRef* chunks)
+// Workgroup b stores the record of tensor first+b and writes that tensor's rows of the work table.
+__global__ __launch_bounds__(kBlock) void store_tensor_batch_kernel(TensorBatch batch, TensorArgs* targs, WorkRef* work, int items_per_chunk)
 {
     const uint32_t b = blockIdx.x;
     if (b >= batch.count) return;
     const TensorArgs a = batch.t[b];
     const uint32_t i = batch.first + b;
     if (threadIdx.x == 0) targs[i] = a;
-    for (uint32_t k = threadIdx.x; k < a.chunk_count; k += kBlock) chunks[a.chunk_begin + k] = ChunkRef{i, k};
+    const uint32_t last = a.chunk_count - 1;
+    const int64_t last_len = a.numel - (int64_t)last * kChunkElems;
+    const bool last_is_long = is_long_chunk(last_len, items_per_chunk);
+    for (uint32_t k = threadIdx.x; k < a.chunk_count; k += kBlock) {
+        const uint32_t at = k < last || last_is_long ? batch.long_at[b] + k : batch.short_at[b];
+        work[at] = WorkRef{i, a.chunk_begin + k, k, k < last ? (uint32_t)kChunkElems : (uint32_t)last_len};
+    }
 }
 
 inline bool aligned(const void* p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
@@ -105,13 +113,20 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
     if (n_tensors > (int64_t)kMaxT) return ADAGC_ERR_TOO_LARGE;
 
     // Everything is validated before anything is enqueued: one pass over the list.
-    uint64_t n_chunks = 0;
+    const int unroll = default_unroll(cfg->optimizer), items_per_chunk = default_items(unroll);
+    uint64_t n_chunks = 0, n_long = 0;
+    // long chunks of tensor i: all but a last one of one work item
+    auto long_chunks = [&](int64_t i) {
+        const int64_t whole = descs[i].numel / kChunkElems, rest = descs[i].numel % kChunkElems;
+        return whole + (rest > 0 && is_long_chunk(rest, items_per_chunk) ? 1 : 0);
+    };
     for (int64_t i = 0; i < n_tensors; ++i) {
         if (descs[i].numel <= 0 || descs[i].flags != 0 || descs[i].reserved != 0) return ADAGC_ERR_INVALID_ARG;
         if (!params[i] || !grads[i] || !exp_avg[i] || (adamw && !exp_avg_sq[i]) || (copy && !params_bf16[i]))
             return ADAGC_ERR_INVALID_ARG;
         n_chunks += (uint64_t)((descs[i].numel + kChunkElems - 1) / kChunkElems);
         if (n_chunks > (uint64_t)kMaxC) return ADAGC_ERR_TOO_LARGE;
+        n_long += (uint64_t)long_chunks(i);
     }
 
     int device = -1;
@@ -123,9 +138,8 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
 
     DeviceTables t{};
     TensorArgs* d_targs = reinterpret_cast<TensorArgs*>(base + kOffTargs);
-    ChunkRef* d_chunks = reinterpret_cast<ChunkRef*>(base + kOffChunks);
-    t.chunks = d_chunks;
-    t.schedule = nullptr;                         // list order
+    WorkRef* d_work = reinterpret_cast<WorkRef*>(base + kOffWork);
+    t.work = d_work;
     t.targs = d_targs;
     t.partials = reinterpret_cast<double*>(base + kOffPartials);
     t.sumsq = reinterpret_cast<double*>(base + kOffSumsq);
@@ -138,11 +152,12 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
     t.tele_norm = nullptr;
     t.scalars = nullptr;
     t.n_chunks = (uint32_t)n_chunks;
+    t.n_long = (uint32_t)n_long;
     t.n_tensors = (uint32_t)n_tensors;
 
     // Tensor records and chunk table, a batch of tensors per launch.
-    const uintptr_t grad_align = bf16g ? 8 : 16;
-    uint32_t chunk_begin = 0;
+    const uintptr_t grad_align = bf16g ? 2 : 4;
+    uint32_t chunk_begin = 0, long_at = 0, short_at = (uint32_t)n_long;
     TensorBatch batch;
     for (int64_t first = 0; first < n_tensors; first += kBatch) {
         const int64_t count = (n_tensors - first) < kBatch ? (n_tensors - first) : kBatch;
@@ -157,16 +172,24 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
             a.numel = descs[i].numel;
             a.chunk_begin = chunk_begin;
             a.chunk_count = (uint32_t)((descs[i].numel + kChunkElems - 1) / kChunkElems);
-            a.vec_ok = (aligned(a.param, 16) && aligned(a.exp_avg, 16) && aligned(a.grad, grad_align) &&
-                        (!adamw || aligned(a.exp_avg_sq, 16)) && (!copy || aligned(a.param_copy, 8)))
+            a.vec_ok = (aligned(a.param, 4) && aligned(a.exp_avg, 4) && aligned(a.grad, grad_align) &&
+                        (!adamw || aligned(a.exp_avg_sq, 4)) && (!copy || aligned(a.param_copy, 2)))
                            ? 1u : 0u;
             a.pad = 0;
             chunk_begin += a.chunk_count;
+            const uint32_t n = (uint32_t)long_chunks(i);
+            batch.long_at[b] = long_at;
+            batch.short_at[b] = short_at;
+            long_at += n;
+            short_at += a.chunk_count - n;
         }
-        for (int64_t b = count; b < kBatch; ++b) batch.t[b] = TensorArgs{};
+        for (int64_t b = count; b < kBatch; ++b) {
+            batch.t[b] = TensorArgs{};
+            batch.long_at[b] = batch.short_at[b] = 0;
+        }
         batch.first = (uint32_t)first;
         batch.count = (uint32_t)count;
-        store_tensor_batch_kernel<<<dim3((uint32_t)count), dim3(kBlock), 0, stream>>>(batch, d_targs, d_chunks);
+        store_tensor_batch_kernel<<<dim3((uint32_t)count), dim3(kBlock), 0, stream>>>(batch, d_targs, d_work, items_per_chunk);
         if (hipGetLastError() != hipSuccess) return ADAGC_ERR_HIP;
     }
 
@@ -174,17 +197,16 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
     UpdateArgs u;
     host_step_scalars(*hp, step, r, u);
     const bool global_rule = r.warmup || hp->clip_mode != ADAGC_MODE_ADAGC;
-    const int items_per_chunk = kChunkElems >= 4096 ? kChunkElems / 4096 : 1;
-    const int64_t items = (((int64_t)n_chunks + 7) / 8 * 8) * items_per_chunk;
+    const int64_t items = count_work_items((int64_t)n_chunks, (int64_t)n_long, items_per_chunk);
     const int64_t max_grid = (int64_t)(0xFFFFFFFFu / (uint32_t)kBlock);
     const int grid_norm = (int)((int64_t)n_chunks > max_grid ? max_grid : (int64_t)n_chunks);
     const int grid_update = (int)(items > max_grid ? max_grid : items);
 
-    if (launch_sumsq_partials(t, bf16g, 1, grid_norm, stream) != hipSuccess) return ADAGC_ERR_HIP;
+    if (launch_sumsq_partials(t, bf16g, grid_norm, stream) != hipSuccess) return ADAGC_ERR_HIP;
     const hipError_t e = global_rule ? launch_finalize_global(t, ema_norms, r, stream)
                                      : launch_finalize_adagc(t, ema_norms, r, stream);
     if (e != hipSuccess) return ADAGC_ERR_HIP;
-    if (launch_update(t, u, cfg->optimizer, bf16g, copy, 4, items_per_chunk, 1, 0, grid_update, stream) != hipSuccess)
+    if (launch_update(t, u, cfg->optimizer, bf16g, copy, unroll, items_per_chunk, 1, 0, grid_update, stream) != hipSuccess)
         return ADAGC_ERR_HIP;
     return ADAGC_OK;
 }

@@ -1,0 +1,109 @@
+"""The step on tensors of every size around the kernels' tiles and work items, laid end to end without gaps (every alignment to an
+element, as in flat parameter buffers), must be bit for bit the step on the same tensors in allocations of their own: the kernels
+take both through the same vectors, and neither the address nor the place in the visiting order enters a result.  The step on
+separate allocations is held against the oracle elsewhere."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2502_11034_amd import binding as B
+from paper_2502_11034_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+# one below, at and above: a vector, a round of a workgroup, the work items (2048, 4096), a chunk (16384) and its last item
+SIZES = [1, 2, 3, 4, 5, 7, 255, 1023, 1024, 1025, 2047, 2048, 2049, 4095, 4096, 4097, 4101, 8191, 8193, 12287, 12289, 16383, 16384, 16385,
+         16387, 18431, 18433, 20480, 20481, 32767, 49157, 6, 70001]
+
+
+def _run(numels, flat, optimizer, grad_dtype, mode, entry, steps, seed=5):
+    """State after `steps` steps: flat tensors p, m, v, copies, gamma, and the reported norms."""
+    rng = np.random.default_rng(seed)
+    starts = [0]
+    for n in numels:
+        starts.append(starts[-1] + n)
+    total = starts[-1]
+    host = {"p": rng.standard_normal(total) * 0.02, "g": rng.standard_normal(total) * 0.01, "m": rng.standard_normal(total) * 0.002,
+            "v": rng.random(total) * 1e-4 + 1e-6}
+    types = {"p": torch.float32, "g": torch.bfloat16 if grad_dtype == B.ADAGC_GRAD_BF16 else torch.float32, "m": torch.float32,
+             "v": torch.float32, "c": torch.bfloat16}
+    host["c"] = np.zeros(total)
+    lists = {}
+    for k, values in host.items():
+        whole = torch.from_numpy(values).to(types[k]).to(DEV)
+        views = [whole[a:b] for a, b in zip(starts, starts[1:])]
+        lists[k] = views if flat else [x.clone() for x in views]
+    lion = optimizer == B.ADAGC_OPT_LION
+    gamma = torch.tensor([0.009 * n ** 0.5 for n in numels], dtype=torch.float32, device=DEV)
+    hp = B.make_hyper(lr=1e-3, t_start=0, clip_mode=mode, lambda_rel=1e-3 if mode == B.ADAGC_MODE_AGC else 1.04)
+    v = None if lion else lists["v"]
+    extra = []
+    if entry == "static":
+        for t in range(7, 7 + steps):
+            B.adagc_step_static(numels, lists["p"], lists["g"], lists["m"], v, gamma, hp, t, optimizer=optimizer, grad_dtype=grad_dtype,
+                                params_bf16=lists["c"])
+    else:
+        ctx = B.AdaGC(numels, optimizer, grad_dtype, True, telemetry=True, update_clipping=mode == B.ADAGC_MODE_AGC)
+        ctx.set_param_copies(lists["c"])
+        for t in range(7, 7 + steps):
+            ctx.step(lists["p"], lists["g"], lists["m"], v, gamma, hp, t)
+        extra = [torch.from_numpy(x.copy()) for x in ctx.get_norms() + ctx.get_state_norms()]
+        ctx.close()
+    torch.cuda.synchronize()
+    return [torch.cat(lists[k]) for k in ("p", "m", "v", "c")] + [gamma] + extra
+
+
+@pytest.mark.parametrize("entry", ["step", "static"])
+@pytest.mark.parametrize("grad_dtype", [B.ADAGC_GRAD_F32, B.ADAGC_GRAD_BF16])
+@pytest.mark.parametrize("optimizer", [B.ADAGC_OPT_ADAMW, B.ADAGC_OPT_LION])
+def test_flat_buffers_equal_separate_allocations(optimizer, grad_dtype, entry):
+    a, b = (_run(SIZES, flat, optimizer, grad_dtype, B.ADAGC_MODE_ADAGC, entry, 2) for flat in (True, False))
+    for k, (x, y) in enumerate(zip(a, b)):
+        assert torch.equal(x, y), "array %d" % k
+
+
+@pytest.mark.parametrize("optimizer", [B.ADAGC_OPT_ADAMW, B.ADAGC_OPT_LION])
+def test_flat_buffers_equal_separate_allocations_with_update_clipping(optimizer):
+    a, b = (_run(SIZES, flat, optimizer, B.ADAGC_GRAD_BF16, B.ADAGC_MODE_AGC, "step", 2) for flat in (True, False))
+    for k, (x, y) in enumerate(zip(a, b)):
+        assert torch.equal(x, y), "array %d" % k
+
+
+def test_static_step_equals_step_on_many_small_tensors():
+    """More tensors than one table launch takes, most of them shorter than a work item."""
+    numels = [int(s.numel) for s in W.ragged_stress_list(700, 30000, None, seed=3)]
+    a = _run(numels, True, B.ADAGC_OPT_ADAMW, B.ADAGC_GRAD_F32, B.ADAGC_MODE_ADAGC, "static", 2)
+    b = _run(numels, False, B.ADAGC_OPT_ADAMW, B.ADAGC_GRAD_F32, B.ADAGC_MODE_ADAGC, "step", 2)
+    for k, (x, y) in enumerate(zip(a, b)):
+        assert torch.equal(x, y), "array %d" % k
+
+
+@pytest.mark.parametrize("split,unroll", [(1, 4), (2, 2), (4, 1), (8, 2), (16, 1)])
+@pytest.mark.parametrize("optimizer", [B.ADAGC_OPT_ADAMW, B.ADAGC_OPT_LION])
+def test_update_clipping_with_every_size_of_work_item(optimizer, split, unroll):
+    """The direction's norms are summed over the update's work items, which may be smaller than a round of its loads: the
+    coefficients and the step must be the default's up to the order of summation (maxima: exactly)."""
+    numels = SIZES
+    gen = torch.Generator(device="cpu").manual_seed(9)
+    make = lambda scale: [(torch.randn(n, generator=gen) * scale).to(DEV) for n in numels]
+    p0, g, m0 = make(0.02), make(0.01), make(0.002)
+    v0 = [x.square() + 1e-6 for x in m0]
+    for mode in (B.ADAGC_MODE_AGC, B.ADAGC_MODE_CLIPPY):
+        hp = B.make_hyper(lr=1e-3, t_start=0, clip_mode=mode, lambda_rel=1e-3 if mode == B.ADAGC_MODE_AGC else 1e-2,
+                          lambda_abs=1e-5 if mode == B.ADAGC_MODE_CLIPPY else 1.0)
+        results = []
+        for kw in ({}, dict(update_split=split, unroll=unroll)):
+            p, m, v = ([x.clone() for x in lst] for lst in (p0, m0, v0))
+            gamma = torch.ones(len(numels), device=DEV)
+            ctx = B.AdaGC(numels, optimizer, update_clipping=True, **kw)
+            ctx.step(p, g, m, None if optimizer == B.ADAGC_OPT_LION else v, gamma, hp, 3)
+            norms, coefs, flags = ctx.get_norms()
+            ctx.close()
+            results.append((torch.cat(p), norms, coefs, flags))
+        a, b = results
+        assert a[3].any()
+        np.testing.assert_allclose(a[1], b[1], rtol=2e-7)            # two fp32 roundings of sums that differ by 1e-13
+        np.testing.assert_allclose(a[2], b[2], rtol=2e-7)
+        assert np.array_equal(a[3], b[3])
+        assert ((a[0] - b[0]).abs() <= 2e-7 * a[0].abs() + 1e-12).all()
