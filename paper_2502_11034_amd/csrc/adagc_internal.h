@@ -77,11 +77,10 @@ struct UpdateArgs {
     int    pad;
 };
 
-// Scalars of one step kept in device memory: written by a small kernel from the caller's
-// device-resident adagc_step_params, read by the rule kernels and the update kernel.  This is what
+// Scalars of one step kept in device memory: written by the norm kernel from the caller's
+// device-resident adagc_step_params, read by the update kernel.  This is what
 // lets a step be recorded into a HIP graph once and replayed for other step numbers.
 struct StepScalars {
-    RuleArgs   r;
     UpdateArgs u;
     int32_t    status;   // 0 = valid; otherwise the step leaves all state untouched
     int32_t    pad;
@@ -93,6 +92,7 @@ struct DeviceTables {
     const TensorArgs* targs;
     double*           partials;   // one per chunk
     double*           sumsq;      // one per tensor
+    uint32_t*         arrivals;   // tensors whose sum is stored (model-wide rules); zero before and after every launch
     double*           global;     // [0] = model's sum of squares, [1] = its coefficient, [2] = 1 if clipped
     float*            norm;       // per tensor, pre-clip
     float*            coef;       // per tensor, fp32 (reported to the caller)
@@ -172,9 +172,12 @@ inline void host_step_scalars(const adagc_hyper& hp, int64_t step, RuleArgs& r, 
 }
 
 // Launchers (kernels.hip).  Each only enqueues on `stream`.
-hipError_t launch_sumsq_partials(const DeviceTables& t, int grad_bf16, int grid, hipStream_t stream);
-hipError_t launch_finalize_adagc(const DeviceTables& t, float* ema, const RuleArgs& r, hipStream_t stream);
-hipError_t launch_finalize_global(const DeviceTables& t, float* ema, const RuleArgs& r, hipStream_t stream);
+// Gradient norms, then the clipping rules.  params: null, or the DEVICE parameters of this step, which are then read instead
+// of r (and from which the norm kernel leaves t.scalars for launch_update).
+hipError_t launch_sumsq_partials(const DeviceTables& t, int grad_bf16, int grid, hipStream_t stream,
+                                 const adagc_step_params* params = nullptr, int optimizer = 0);
+hipError_t launch_rules(const DeviceTables& t, float* ema, const RuleArgs& r, hipStream_t stream,
+                        const adagc_step_params* params = nullptr, int optimizer = 0);
 hipError_t launch_update(const DeviceTables& t, const UpdateArgs& u, int optimizer, int grad_bf16,
                          int with_copy, int unroll, int items_per_chunk, int nt, int tele, int grid,
                          hipStream_t stream, bool device_scalars = false);
@@ -184,9 +187,5 @@ hipError_t launch_update_clip_rule(const DeviceTables& t, const UpdateArgs& u, c
                                    int grad_bf16, int items_per_chunk, int nt, int grid, hipStream_t stream);
 // Per-tensor sums of the per-chunk partials into t.sumsq (K2's fixed order); used by the Muon path for ||U||^2.
 hipError_t launch_tensor_sumsq(const DeviceTables& t, hipStream_t stream);
-// Rule stage of adagc_step_graph: scalars from device-resident step parameters, then the per-tensor
-// sums, the model-wide rule (a no-op outside warm-up and the global modes) and the per-tensor rule.
-hipError_t launch_rules_from_device(const DeviceTables& t, float* ema, const adagc_step_params* params,
-                                    int optimizer, hipStream_t stream);
 
 }  // namespace adagc

@@ -210,6 +210,7 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     const size_t o_partials = carve(nc * sizeof(double));
     const size_t o_sumsq = carve(nt * sizeof(double));
     const size_t o_global = carve(4 * sizeof(double));
+    const size_t o_arrivals = carve(sizeof(uint32_t));
     const size_t o_scalars = carve(sizeof(StepScalars));
     const size_t o_coef64 = carve(nt * sizeof(double));
     const size_t o_norm = carve(nt * sizeof(float));
@@ -271,6 +272,7 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     t.partials = reinterpret_cast<double*>(base + o_partials);
     t.sumsq = reinterpret_cast<double*>(base + o_sumsq);
     t.global = reinterpret_cast<double*>(base + o_global);
+    t.arrivals = reinterpret_cast<uint32_t*>(base + o_arrivals);
     t.scalars = reinterpret_cast<StepScalars*>(base + o_scalars);
     t.coef64 = reinterpret_cast<double*>(base + o_coef64);
     t.norm = reinterpret_cast<float*>(base + o_norm);
@@ -385,7 +387,6 @@ extern "C" int adagc_step(adagc_ctx* ctx, void* const* params, const void* const
     RuleArgs r;
     UpdateArgs u;
     host_step_scalars(*hp, step, r, u);
-    const bool global_rule = r.warmup || hp->clip_mode != ADAGC_MODE_ADAGC;
     ctx->device_scalars_used = false;
     const bool prof = ctx->prof_steps < ctx->prof_capacity;
     hipEvent_t* ev = prof ? &ctx->prof_events[(size_t)ctx->prof_steps * 4] : nullptr;
@@ -402,9 +403,7 @@ extern "C" int adagc_step(adagc_ctx* ctx, void* const* params, const void* const
     } else {
         if (launch_sumsq_partials(ctx->tables, bf16g, ctx->grid_norm, stream) != hipSuccess) return ADAGC_ERR_HIP;
         if (prof && hipEventRecord(ev[1], stream) != hipSuccess) return ADAGC_ERR_HIP;
-        const hipError_t e = global_rule ? launch_finalize_global(ctx->tables, ema_norms, r, stream)
-                                         : launch_finalize_adagc(ctx->tables, ema_norms, r, stream);
-        if (e != hipSuccess) return ADAGC_ERR_HIP;
+        if (launch_rules(ctx->tables, ema_norms, r, stream) != hipSuccess) return ADAGC_ERR_HIP;
         if (prof && hipEventRecord(ev[2], stream) != hipSuccess) return ADAGC_ERR_HIP;
     }
     if (launch_update(ctx->tables, u, ctx->cfg.optimizer, bf16g, copy, ctx->unroll, ctx->items_per_chunk,
@@ -439,9 +438,10 @@ extern "C" int adagc_step_graph(adagc_ctx* ctx, void* const* params, const void*
     hipEvent_t* ev = prof ? &ctx->prof_events[(size_t)ctx->prof_steps * 4] : nullptr;
     ctx->device_scalars_used = true;
     if (prof && hipEventRecord(ev[0], stream) != hipSuccess) return ADAGC_ERR_HIP;
-    if (launch_sumsq_partials(ctx->tables, bf16g, ctx->grid_norm, stream) != hipSuccess) return ADAGC_ERR_HIP;
+    if (launch_sumsq_partials(ctx->tables, bf16g, ctx->grid_norm, stream, step_params, ctx->cfg.optimizer) != hipSuccess)
+        return ADAGC_ERR_HIP;
     if (prof && hipEventRecord(ev[1], stream) != hipSuccess) return ADAGC_ERR_HIP;
-    if (launch_rules_from_device(ctx->tables, ema_norms, step_params, ctx->cfg.optimizer, stream) != hipSuccess)
+    if (launch_rules(ctx->tables, ema_norms, RuleArgs{}, stream, step_params, ctx->cfg.optimizer) != hipSuccess)
         return ADAGC_ERR_HIP;
     if (prof && hipEventRecord(ev[2], stream) != hipSuccess) return ADAGC_ERR_HIP;
     if (launch_update(ctx->tables, UpdateArgs{}, ctx->cfg.optimizer, bf16g, copy, ctx->unroll, ctx->items_per_chunk,
@@ -600,7 +600,6 @@ extern "C" int adagc_muon_step(adagc_ctx* ctx, void* const* params, const void* 
     RuleArgs r;
     UpdateArgs u;
     host_step_scalars(h, step, r, u);
-    const bool global_rule = r.warmup || h.clip_mode != ADAGC_MODE_ADAGC;
     ctx->device_scalars_used = false;
     const bool prof = ctx->prof_steps < ctx->prof_capacity;
     hipEvent_t* ev = prof ? &ctx->prof_events[(size_t)ctx->prof_steps * 4] : nullptr;
@@ -610,8 +609,7 @@ extern "C" int adagc_muon_step(adagc_ctx* ctx, void* const* params, const void* 
     if (prof && hipEventRecord(ev[0], stream) != hipSuccess) return ADAGC_ERR_HIP;
     if (launch_sumsq_partials(t, bf16g, ctx->grid_norm, stream) != hipSuccess) return ADAGC_ERR_HIP;
     if (prof && hipEventRecord(ev[1], stream) != hipSuccess) return ADAGC_ERR_HIP;
-    const hipError_t e = global_rule ? launch_finalize_global(t, ema_norms, r, stream) : launch_finalize_adagc(t, ema_norms, r, stream);
-    if (e != hipSuccess) return ADAGC_ERR_HIP;
+    if (launch_rules(t, ema_norms, r, stream) != hipSuccess) return ADAGC_ERR_HIP;
     if (prof && hipEventRecord(ev[2], stream) != hipSuccess) return ADAGC_ERR_HIP;
 
     // momentum with the clipped gradient, and ||U||_F^2 of every tensor

@@ -1,18 +1,18 @@
 // HIP kernels of libadagc for gfx950 (wave64).
 //
 //   sumsq_partials_kernel   per chunk:   sum of g^2 in fp64              (l2 norm of Sec. 4.1, for Eq. 3)
-//   finalize_adagc_kernel   per tensor:  norm, h_i, clip flag, EMA update          (Eq. 3, Alg. 1)
-//   tensor_sumsq_kernel / global_rule_kernel / finalize_global_kernel
-//                           one coefficient for the whole model: warm-up branch of Alg. 1
-//                           (GlobalGC + running minimum), GlobalGC on every step (Eq. 2),
-//                           Global AdaGC (Eq. 3 on the model's norm; "Ablation Study", Sec. 5.6)
+//   rules_kernel            per tensor:  norm, h_i, clip flag, EMA update          (Eq. 3, Alg. 1); where one coefficient
+//                           serves the whole model, by the workgroup that comes last: warm-up branch of Alg. 1
+//                           (GlobalGC + running minimum), GlobalGC on every step (Eq. 2), Global AdaGC (Eq. 3 on the
+//                           model's norm; "Ablation Study", Sec. 5.6), ZClip
+//   global_rule_kernel / finalize_global_kernel
+//                           those model-wide rules on long lists
 //   update_kernel           per quarter chunk: clipped gradient into AdamW / Lion  (Alg. 1)
 //   direction_stats_kernel / finalize_update_clip_kernel
 //                           update clipping (AGC and Clippy rows of Table 2): norms of theta and of the
 //                           optimizer's direction per tensor, and the coefficient that scales the direction
-//   prepare_step_kernel / global_rule_device_kernel / finalize_device_kernel
-//                           the same rules with the step's scalars read from device memory, for a
-//                           launch sequence that is recorded once and replayed for later steps
+//   The norm, rules and update kernels also run with the step's scalars read from device memory, for a launch sequence
+//                           that is recorded once and replayed for later steps
 //
 // Nothing here is a dense contraction, so there is no MFMA: the streaming kernels
 // are bound by HBM and are built around 128-bit coalesced accesses with many
@@ -70,6 +70,60 @@ __device__ __forceinline__ u32x2 pack_bf16x4(f32x4 v)
 }
 
 // ---------------------------------------------------------------------------------------------
+// A step whose scalars come from device memory (adagc_step_graph): the step number and the hyper-parameters are read when
+// the kernels run, so a recorded launch sequence stays valid for other steps.  Which branch of Alg. 1 applies is therefore
+// decided on the device as well.
+
+// The rule's scalars from the caller's step parameters; false if adagc_step would reject those.
+__device__ __forceinline__ bool rule_from_params(const adagc_step_params* params, int optimizer, RuleArgs& r)
+{
+    const adagc_hyper hp = params->hp;
+    const int64_t step = params->step;
+    auto unit = [](float b) { return b >= 0.0f && b < 1.0f; };   // false for NaN
+    auto finite = [](float x) { return fabsf(x) <= 3.402823466e+38f; };
+    bool ok = step >= 1 && finite(hp.lr) && finite(hp.weight_decay) && unit(hp.beta1) && unit(hp.beta2) &&
+              unit(hp.ema_beta) && hp.lambda_rel >= 0.0f && hp.lambda_abs > 0.0f && hp.t_start >= 0 &&
+              hp.clip_mode >= ADAGC_MODE_ADAGC && hp.clip_mode <= ADAGC_MODE_ZCLIP &&
+              (hp.clip_mode != ADAGC_MODE_ZCLIP || hp.z_thres > 0.0f);
+    if (optimizer == ADAGC_OPT_ADAMW) ok = ok && hp.eps >= 0.0f && finite(hp.eps);
+    r.lambda_rel = (double)hp.lambda_rel;
+    r.ema_beta = (double)hp.ema_beta;
+    r.lambda_abs = (double)hp.lambda_abs;
+    r.z_thres = (double)hp.z_thres;
+    r.lr = (double)hp.lr;
+    r.pad = 0;
+    r.first_step = (step == 1) ? 1 : 0;
+    r.warmup = ((step - 1) < (int64_t)hp.t_start) ? 1 : 0;
+    r.mode = hp.clip_mode;
+    return ok;
+}
+
+// One lane: validate the caller's step parameters and leave the update kernel's scalars in device memory.
+__device__ __forceinline__ void prepare_update_scalars(const DeviceTables& t, const adagc_step_params* params, int optimizer)
+{
+    RuleArgs r;
+    const bool ok = rule_from_params(params, optimizer, r);
+    const adagc_hyper hp = params->hp;
+    UpdateArgs u;
+    const double lr = hp.lr, b1 = hp.beta1, b2 = hp.beta2, wd = hp.weight_decay, tt = (double)params->step;
+    u.beta1 = b1;
+    u.one_minus_beta1 = 1.0 - b1;
+    u.beta2 = b2;
+    u.one_minus_beta2 = 1.0 - b2;
+    u.inv_bias2 = 1.0 / (1.0 - pow(b2, tt));
+    u.step_size = lr / (1.0 - pow(b1, tt));
+    u.lr_wd = lr * wd;
+    u.eps = (double)hp.eps;
+    u.lr = lr;
+    u.weight_decay = wd;
+    u.inv_bias1 = 1.0 / (1.0 - pow(b1, tt));
+    u.update_clip = 0;                          // the update-clipping modes are rejected above
+    u.pad = 0;
+    t.scalars->u = u;
+    t.scalars->status = ok ? 0 : 1;
+}
+
+// ---------------------------------------------------------------------------------------------
 // K1: one fp64 partial sum of squares per chunk.  Workgroup b takes positions b, b+grid, b+2*grid, ...
 // of the visiting order (by default the grid has one workgroup per chunk).
 
@@ -85,11 +139,13 @@ __device__ __forceinline__ void acc4(double (&acc)[4], f32x4 g)
 // The loads are ordinary ones: streaming loads leave nothing in the 256 MB memory-side cache, and the update kernel reads the
 // same gradients next.  GPT-2-small shapes (498 MB of gradients): 657 us per step with streaming loads, 622 without; 266 MB of
 // bf16 gradients 680, 635; lists of many GB do not care (this kernel alone then reads 7.2 TB/s either way).
+// params: null, or the device-resident parameters of this step, from which one lane makes the update kernel's scalars.
 template <bool BF16>
-__global__ __launch_bounds__(kBlock) void sumsq_partials_kernel(DeviceTables t)
+__global__ __launch_bounds__(kBlock) void sumsq_partials_kernel(DeviceTables t, const adagc_step_params* params, int optimizer)
 {
     __shared__ double wave_sums[kWavesPerBlock];
     const int tid = threadIdx.x;
+    if (params && blockIdx.x == gridDim.x - 1 && tid == 0) prepare_update_scalars(t, params, optimizer);
 
     for (uint32_t k = blockIdx.x; k < t.n_chunks; k += gridDim.x) {
         const WorkRef w = load_work(t.work, k);
@@ -173,6 +229,31 @@ __device__ __forceinline__ double tensor_slot_sum(const DeviceTables& t, const d
     return total;
 }
 
+// Hand-over between workgroups of one launch.  The L2s of the 8 XCDs are not coherent with each other, so what one
+// workgroup leaves for another is written and read with agent-scope accesses, and the count that says so is a release on
+// the writer's side and an acquire on the last one's.
+template <typename T>
+__device__ __forceinline__ T load_shared(const T* p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <typename T>
+__device__ __forceinline__ void store_shared(T* p, T v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One lane: count this workgroup in; true for the last of `total`, which finds everything the others stored before they
+// counted themselves, and leaves the counter at zero for the next launch.
+__device__ __forceinline__ bool arrive_last(uint32_t* counter, uint32_t total)
+{
+    if (__hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT) != total - 1u) return false;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    store_shared(counter, 0u);
+    return true;
+}
+
 // AdaGC branch of Alg. 1 / Eq. 3 for tensor i with sum of squares s, in double, with separately rounded
 // operations.  One lane.
 __device__ __forceinline__ void adagc_rule(const DeviceTables& t, float* ema, const RuleArgs& r, uint32_t i, double s)
@@ -193,24 +274,7 @@ __device__ __forceinline__ void adagc_rule(const DeviceTables& t, float* ema, co
     ema[i] = (float)gamma_new;
 }
 
-__global__ __launch_bounds__(kBlock) void finalize_adagc_kernel(DeviceTables t, float* ema, RuleArgs r)
-{
-    __shared__ double wave_sums[kWavesPerBlock];
-    const uint32_t i = blockIdx.x;
-    const double s = tensor_slot_sum(t, t.partials, i, wave_sums);
-    if (threadIdx.x == 0) adagc_rule(t, ema, r, i, s);
-}
-
-// Global stage 1: per-tensor sum of squares only.
-__global__ __launch_bounds__(kBlock) void tensor_sumsq_kernel(DeviceTables t)
-{
-    __shared__ double wave_sums[kWavesPerBlock];
-    const uint32_t i = blockIdx.x;
-    const double s = tensor_slot_sum(t, t.partials, i, wave_sums);
-    if (threadIdx.x == 0) t.sumsq[i] = s;
-}
-
-// Global stage 2: the model's norm over all tensors (fixed order) and one coefficient for the
+// Model-wide rules: the model's norm over all tensors (fixed order) and one coefficient for the
 // whole model.  Warm-up steps and the GlobalGC mode use Eq. 2; the Global AdaGC mode applies Eq. 3
 // (and, during warm-up, the running minimum of Alg. 1) to the model's norm with the single gamma
 // kept in ema[0]; the ZClip mode applies Table 2's z-score rule with its mean in ema[0] and its
@@ -219,7 +283,7 @@ __device__ __forceinline__ void global_rule(const DeviceTables& t, float* ema, c
 {
     const int tid = threadIdx.x;
     double acc = 0.0;
-    for (uint32_t i = tid; i < t.n_tensors; i += kBlock) acc += t.sumsq[i];
+    for (uint32_t i = tid; i < t.n_tensors; i += kBlock) acc += load_shared(t.sumsq + i);
     double s = wave_sum_f64(acc);
     if ((tid & 63) == 0) wave_sums[tid >> 6] = s;
     __syncthreads();
@@ -286,19 +350,13 @@ __device__ __forceinline__ void global_rule(const DeviceTables& t, float* ema, c
     t.global[2] = clipped ? 1.0 : 0.0;
 }
 
-__global__ __launch_bounds__(kBlock) void global_rule_kernel(DeviceTables t, float* ema, RuleArgs r)
-{
-    __shared__ double wave_sums[kWavesPerBlock];
-    global_rule(t, ema, r, wave_sums);
-}
-
-// Global stage 3 for tensor i: it takes the model's coefficient.  In the AdaGC mode (warm-up branch of
+// Tensor i under a model-wide rule: it takes the model's coefficient.  In the AdaGC mode (warm-up branch of
 // Alg. 1) gamma_i = min{gamma_i, h*n_i}, or h*n_i on the first step; the global modes keep no per-tensor
 // state.
 __device__ __forceinline__ void take_global_coefficient(const DeviceTables& t, float* ema, const RuleArgs& r, uint32_t i)
 {
     const double h = t.global[1];
-    const double norm = sqrt(t.sumsq[i]);
+    const double norm = sqrt(load_shared(t.sumsq + i));
     t.norm[i] = (float)norm;
     t.coef[i] = (float)h;
     t.coef64[i] = h;
@@ -312,74 +370,72 @@ __device__ __forceinline__ void take_global_coefficient(const DeviceTables& t, f
     }
 }
 
-__global__ __launch_bounds__(kBlock) void finalize_global_kernel(DeviceTables t, float* ema, RuleArgs r)
-{
-    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
-    if (i < t.n_tensors) take_global_coefficient(t, ema, r, i);
-}
+// Does this step use one coefficient for the whole model?
+__device__ __host__ __forceinline__ bool model_wide(const RuleArgs& r) { return r.warmup || r.mode != ADAGC_MODE_ADAGC; }
 
-// ---------------------------------------------------------------------------------------------
-// The same rules with the step's scalars taken from device memory (adagc_step_graph): the step number
-// and the hyper-parameters are read when the kernels run, so a recorded launch sequence stays valid
-// for other steps.  Which branch of Alg. 1 applies is therefore decided on the device as well.
+// K2, one workgroup per tensor.  Per-tensor rule: workgroup i evaluates it.  Model-wide rules on lists of up to kFewTensors
+// tensors: the workgroup that stores the last tensor's sum evaluates the rule and hands the coefficient to every tensor.  As
+// three kernels that took 14 us of launches on 148 tensors (GPT-2-small's warm-up step 763 -> 733 us), and with the scalars
+// in device memory, six kernels instead of three, 44.6 us per step on 4 M parameters (now 39.8).  Counting in costs 14 ns a
+// tensor, on one address: 5000 tensors 187 us per step against 164 with the two kernels after this one, which longer lists
+// therefore keep.
+// (The release finds the L2 clean here, where next to nothing is written.  Counted in the norm kernel, one release per chunk,
+// it cost half as much again as the whole step.)
+constexpr uint32_t kFewTensors = 512;
 
-// One lane: validate the caller's step parameters and derive the scalars of both stages from them.
-__global__ void prepare_step_kernel(DeviceTables t, const adagc_step_params* params, int optimizer)
-{
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    const adagc_hyper hp = params->hp;
-    const int64_t step = params->step;
-    auto unit = [](float b) { return b >= 0.0f && b < 1.0f; };   // false for NaN
-    auto finite = [](float x) { return fabsf(x) <= 3.402823466e+38f; };
-    bool ok = step >= 1 && finite(hp.lr) && finite(hp.weight_decay) && unit(hp.beta1) && unit(hp.beta2) &&
-              unit(hp.ema_beta) && hp.lambda_rel >= 0.0f && hp.lambda_abs > 0.0f && hp.t_start >= 0 &&
-              hp.clip_mode >= ADAGC_MODE_ADAGC && hp.clip_mode <= ADAGC_MODE_ZCLIP &&
-              (hp.clip_mode != ADAGC_MODE_ZCLIP || hp.z_thres > 0.0f);
-    if (optimizer == ADAGC_OPT_ADAMW) ok = ok && hp.eps >= 0.0f && finite(hp.eps);
-    StepScalars sc;
-    const double lr = hp.lr, b1 = hp.beta1, b2 = hp.beta2, wd = hp.weight_decay, tt = (double)step;
-    sc.r.lambda_rel = (double)hp.lambda_rel;
-    sc.r.ema_beta = (double)hp.ema_beta;
-    sc.r.lambda_abs = (double)hp.lambda_abs;
-    sc.r.z_thres = (double)hp.z_thres;
-    sc.r.pad = 0;
-    sc.r.first_step = (step == 1) ? 1 : 0;
-    sc.r.warmup = ((step - 1) < (int64_t)hp.t_start) ? 1 : 0;
-    sc.r.mode = hp.clip_mode;
-    sc.u.beta1 = b1;
-    sc.u.one_minus_beta1 = 1.0 - b1;
-    sc.u.beta2 = b2;
-    sc.u.one_minus_beta2 = 1.0 - b2;
-    sc.u.inv_bias2 = 1.0 / (1.0 - pow(b2, tt));
-    sc.u.step_size = lr / (1.0 - pow(b1, tt));
-    sc.u.lr_wd = lr * wd;
-    sc.u.eps = (double)hp.eps;
-    sc.u.lr = lr;
-    sc.u.weight_decay = wd;
-    sc.u.inv_bias1 = 1.0 / (1.0 - pow(b1, tt));
-    sc.u.update_clip = 0;                       // the update-clipping modes are rejected above
-    sc.u.pad = 0;
-    sc.r.lr = lr;
-    sc.status = ok ? 0 : 1;
-    sc.pad = 0;
-    *t.scalars = sc;
-}
-
-__global__ __launch_bounds__(kBlock) void global_rule_device_kernel(DeviceTables t, float* ema)
+__global__ __launch_bounds__(kBlock) void rules_kernel(DeviceTables t, float* ema, RuleArgs r, const adagc_step_params* params,
+                                                       int optimizer)
 {
     __shared__ double wave_sums[kWavesPerBlock];
-    const RuleArgs r = t.scalars->r;
-    if (t.scalars->status != 0 || !(r.warmup || r.mode != ADAGC_MODE_ADAGC)) return;   // uniform
+    __shared__ int    last;
+    const int tid = threadIdx.x;
+    if (params && !rule_from_params(params, optimizer, r)) return;       // the same in all workgroups: nothing is touched
+    const uint32_t i = blockIdx.x;
+    const double s = tensor_slot_sum(t, t.partials, i, wave_sums);
+    if (!model_wide(r)) {
+        if (tid == 0) adagc_rule(t, ema, r, i, s);
+        return;
+    }
+    if (t.n_tensors > kFewTensors) {
+        if (tid == 0) t.sumsq[i] = s;
+        return;
+    }
+    if (tid == 0) {
+        store_shared(t.sumsq + i, s);
+        last = arrive_last(t.arrivals, t.n_tensors) ? 1 : 0;
+    }
+    __syncthreads();                             // wave_sums is free again as well
+    if (!last) return;
     global_rule(t, ema, r, wave_sums);
+    __syncthreads();
+    for (uint32_t k = tid; k < t.n_tensors; k += kBlock) take_global_coefficient(t, ema, r, k);
 }
 
-__global__ __launch_bounds__(kBlock) void finalize_device_kernel(DeviceTables t, float* ema)
+// Per-tensor sum of squares only.
+__global__ __launch_bounds__(kBlock) void tensor_sumsq_kernel(DeviceTables t)
 {
+    __shared__ double wave_sums[kWavesPerBlock];
+    const uint32_t i = blockIdx.x;
+    const double s = tensor_slot_sum(t, t.partials, i, wave_sums);
+    if (threadIdx.x == 0) t.sumsq[i] = s;
+}
+
+// Model-wide rules on long lists: the rule, then every tensor's share.
+__global__ __launch_bounds__(kBlock) void global_rule_kernel(DeviceTables t, float* ema, RuleArgs r, const adagc_step_params* params,
+                                                             int optimizer)
+{
+    __shared__ double wave_sums[kWavesPerBlock];
+    if (params && !rule_from_params(params, optimizer, r)) return;
+    if (model_wide(r)) global_rule(t, ema, r, wave_sums);                // the same in all lanes
+}
+
+__global__ __launch_bounds__(kBlock) void finalize_global_kernel(DeviceTables t, float* ema, RuleArgs r, const adagc_step_params* params,
+                                                                 int optimizer)
+{
+    if (params && !rule_from_params(params, optimizer, r)) return;
+    if (!model_wide(r)) return;
     const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= t.n_tensors || t.scalars->status != 0) return;
-    const RuleArgs r = t.scalars->r;
-    if (r.warmup || r.mode != ADAGC_MODE_ADAGC) take_global_coefficient(t, ema, r, i);
-    else adagc_rule(t, ema, r, i, t.sumsq[i]);
+    if (i < t.n_tensors) take_global_coefficient(t, ema, r, i);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -836,17 +892,13 @@ __global__ __launch_bounds__(kBlock) void finalize_update_clip_kernel(DeviceTabl
     t.flag[i] = active ? 1 : 0;
 }
 
-// Telemetry finalize: per tensor, the three norms from the item slots (same fixed order as K2).
+// Telemetry: workgroup (i, q) turns tensor i's item slots of quantity q into its norm (same fixed order as K2).
 __global__ __launch_bounds__(kBlock) void finalize_telemetry_kernel(DeviceTables t, uint32_t items_per_chunk)
 {
     __shared__ double wave_sums[kWavesPerBlock];
-    const uint32_t i = blockIdx.x;
-    for (int q = 0; q < 3; ++q) {
-        const double s = tensor_slot_sum(t, t.tele_partials + (size_t)q * t.n_chunks * items_per_chunk, i, wave_sums,
-                                         items_per_chunk);
-        if (threadIdx.x == 0) t.tele_norm[(size_t)q * t.n_tensors + i] = (float)sqrt(s);
-        __syncthreads();
-    }
+    const uint32_t i = blockIdx.x, q = blockIdx.y;
+    const double s = tensor_slot_sum(t, t.tele_partials + (size_t)q * t.n_chunks * items_per_chunk, i, wave_sums, items_per_chunk);
+    if (threadIdx.x == 0) t.tele_norm[(size_t)q * t.n_tensors + i] = (float)sqrt(s);
 }
 
 using UpdateFn = void (*)(DeviceTables, UpdateArgs, uint32_t, const StepScalars*);
@@ -883,35 +935,31 @@ UpdateFn select_update(int optimizer, int grad_bf16, int with_copy, int unroll, 
 
 }  // namespace
 
-hipError_t launch_sumsq_partials(const DeviceTables& t, int grad_bf16, int grid, hipStream_t stream)
+hipError_t launch_sumsq_partials(const DeviceTables& t, int grad_bf16, int grid, hipStream_t stream, const adagc_step_params* params,
+                                 int optimizer)
 {
-    if (grad_bf16) sumsq_partials_kernel<true><<<dim3(grid), dim3(kBlock), 0, stream>>>(t);
-    else sumsq_partials_kernel<false><<<dim3(grid), dim3(kBlock), 0, stream>>>(t);
+    if (grad_bf16) sumsq_partials_kernel<true><<<dim3(grid), dim3(kBlock), 0, stream>>>(t, params, optimizer);
+    else sumsq_partials_kernel<false><<<dim3(grid), dim3(kBlock), 0, stream>>>(t, params, optimizer);
     return hipGetLastError();
 }
 
-hipError_t launch_finalize_adagc(const DeviceTables& t, float* ema, const RuleArgs& r, hipStream_t stream)
+hipError_t launch_rules(const DeviceTables& t, float* ema, const RuleArgs& r, hipStream_t stream, const adagc_step_params* params,
+                        int optimizer)
 {
-    finalize_adagc_kernel<<<dim3(t.n_tensors), dim3(kBlock), 0, stream>>>(t, ema, r);
+    rules_kernel<<<dim3(t.n_tensors), dim3(kBlock), 0, stream>>>(t, ema, r, params, optimizer);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || t.n_tensors <= kFewTensors || (!params && !model_wide(r))) return e;
+    global_rule_kernel<<<dim3(1), dim3(kBlock), 0, stream>>>(t, ema, r, params, optimizer);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const uint32_t blocks = (t.n_tensors + kBlock - 1) / kBlock;
+    finalize_global_kernel<<<dim3(blocks), dim3(kBlock), 0, stream>>>(t, ema, r, params, optimizer);
     return hipGetLastError();
 }
 
 hipError_t launch_tensor_sumsq(const DeviceTables& t, hipStream_t stream)
 {
     tensor_sumsq_kernel<<<dim3(t.n_tensors), dim3(kBlock), 0, stream>>>(t);
-    return hipGetLastError();
-}
-
-hipError_t launch_finalize_global(const DeviceTables& t, float* ema, const RuleArgs& r, hipStream_t stream)
-{
-    tensor_sumsq_kernel<<<dim3(t.n_tensors), dim3(kBlock), 0, stream>>>(t);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    global_rule_kernel<<<dim3(1), dim3(kBlock), 0, stream>>>(t, ema, r);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const uint32_t blocks = (t.n_tensors + kBlock - 1) / kBlock;
-    finalize_global_kernel<<<dim3(blocks), dim3(kBlock), 0, stream>>>(t, ema, r);
     return hipGetLastError();
 }
 
@@ -940,23 +988,6 @@ hipError_t launch_update_clip_rule(const DeviceTables& t, const UpdateArgs& u, c
     return hipGetLastError();
 }
 
-hipError_t launch_rules_from_device(const DeviceTables& t, float* ema, const adagc_step_params* params,
-                                    int optimizer, hipStream_t stream)
-{
-    prepare_step_kernel<<<dim3(1), dim3(64), 0, stream>>>(t, params, optimizer);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    tensor_sumsq_kernel<<<dim3(t.n_tensors), dim3(kBlock), 0, stream>>>(t);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    global_rule_device_kernel<<<dim3(1), dim3(kBlock), 0, stream>>>(t, ema);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const uint32_t blocks = (t.n_tensors + kBlock - 1) / kBlock;
-    finalize_device_kernel<<<dim3(blocks), dim3(kBlock), 0, stream>>>(t, ema);
-    return hipGetLastError();
-}
-
 hipError_t launch_update(const DeviceTables& t, const UpdateArgs& a, int optimizer, int grad_bf16,
                          int with_copy, int unroll, int items_per_chunk, int nt, int tele, int grid,
                          hipStream_t stream, bool device_scalars)
@@ -965,7 +996,7 @@ hipError_t launch_update(const DeviceTables& t, const UpdateArgs& a, int optimiz
         t, a, log2_of(items_per_chunk), device_scalars ? t.scalars : nullptr);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !tele) return e;
-    finalize_telemetry_kernel<<<dim3(t.n_tensors), dim3(kBlock), 0, stream>>>(t, (uint32_t)items_per_chunk);
+    finalize_telemetry_kernel<<<dim3(t.n_tensors, 3), dim3(kBlock), 0, stream>>>(t, (uint32_t)items_per_chunk);
     return hipGetLastError();
 }
 

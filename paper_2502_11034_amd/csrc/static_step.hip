@@ -25,7 +25,8 @@ constexpr size_t kOffPartials = kOffWork + align256(kMaxC * sizeof(WorkRef));
 constexpr size_t kOffSumsq = kOffPartials + align256(kMaxC * sizeof(double));
 constexpr size_t kOffCoef64 = kOffSumsq + align256(kMaxT * sizeof(double));
 constexpr size_t kOffGlobal = kOffCoef64 + align256(kMaxT * sizeof(double));
-constexpr size_t kOffNorm = kOffGlobal + align256(4 * sizeof(double));
+constexpr size_t kOffArrivals = kOffGlobal + align256(4 * sizeof(double));
+constexpr size_t kOffNorm = kOffArrivals + align256(sizeof(uint32_t));
 constexpr size_t kOffCoef = kOffNorm + align256(kMaxT * sizeof(float));
 constexpr size_t kOffFlag = kOffCoef + align256(kMaxT * sizeof(float));
 constexpr size_t kScratchBytes = kOffFlag + align256(kMaxT);
@@ -63,16 +64,21 @@ struct TensorBatch {
     uint32_t   first;    // list index of t[0]
     uint32_t   count;
 };
-static_assert(sizeof(TensorBatch) + 3 * sizeof(void*) <= 4096, "a batch fits the kernel-argument block");
+static_assert(sizeof(TensorBatch) + 4 * sizeof(void*) <= 4096, "a batch fits the kernel-argument block");
 
-// Workgroup b stores the record of tensor first+b and writes that tensor's rows of the work table.
-__global__ __launch_bounds__(kBlock) void store_tensor_batch_kernel(TensorBatch batch, TensorArgs* targs, WorkRef* work, int items_per_chunk)
+// Workgroup b stores the record of tensor first+b and writes that tensor's rows of the work table; the list's first also clears
+// the arrival count of the rules.
+__global__ __launch_bounds__(kBlock) void store_tensor_batch_kernel(TensorBatch batch, TensorArgs* targs, WorkRef* work, uint32_t* arrivals,
+                                                                    int items_per_chunk)
 {
     const uint32_t b = blockIdx.x;
     if (b >= batch.count) return;
     const TensorArgs a = batch.t[b];
     const uint32_t i = batch.first + b;
-    if (threadIdx.x == 0) targs[i] = a;
+    if (threadIdx.x == 0) {
+        targs[i] = a;
+        if (i == 0) *arrivals = 0u;
+    }
     const uint32_t last = a.chunk_count - 1;
     const int64_t last_len = a.numel - (int64_t)last * kChunkElems;
     const bool last_is_long = is_long_chunk(last_len, items_per_chunk);
@@ -145,6 +151,7 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
     t.sumsq = reinterpret_cast<double*>(base + kOffSumsq);
     t.coef64 = reinterpret_cast<double*>(base + kOffCoef64);
     t.global = reinterpret_cast<double*>(base + kOffGlobal);
+    t.arrivals = reinterpret_cast<uint32_t*>(base + kOffArrivals);
     t.norm = out_norms ? out_norms : reinterpret_cast<float*>(base + kOffNorm);
     t.coef = out_coefs ? out_coefs : reinterpret_cast<float*>(base + kOffCoef);
     t.flag = out_clipped ? out_clipped : reinterpret_cast<uint8_t*>(base + kOffFlag);
@@ -189,23 +196,20 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
         }
         batch.first = (uint32_t)first;
         batch.count = (uint32_t)count;
-        store_tensor_batch_kernel<<<dim3((uint32_t)count), dim3(kBlock), 0, stream>>>(batch, d_targs, d_work, items_per_chunk);
+        store_tensor_batch_kernel<<<dim3((uint32_t)count), dim3(kBlock), 0, stream>>>(batch, d_targs, d_work, t.arrivals, items_per_chunk);
         if (hipGetLastError() != hipSuccess) return ADAGC_ERR_HIP;
     }
 
     RuleArgs r;
     UpdateArgs u;
     host_step_scalars(*hp, step, r, u);
-    const bool global_rule = r.warmup || hp->clip_mode != ADAGC_MODE_ADAGC;
     const int64_t items = count_work_items((int64_t)n_chunks, (int64_t)n_long, items_per_chunk);
     const int64_t max_grid = (int64_t)(0xFFFFFFFFu / (uint32_t)kBlock);
     const int grid_norm = (int)((int64_t)n_chunks > max_grid ? max_grid : (int64_t)n_chunks);
     const int grid_update = (int)(items > max_grid ? max_grid : items);
 
     if (launch_sumsq_partials(t, bf16g, grid_norm, stream) != hipSuccess) return ADAGC_ERR_HIP;
-    const hipError_t e = global_rule ? launch_finalize_global(t, ema_norms, r, stream)
-                                     : launch_finalize_adagc(t, ema_norms, r, stream);
-    if (e != hipSuccess) return ADAGC_ERR_HIP;
+    if (launch_rules(t, ema_norms, r, stream) != hipSuccess) return ADAGC_ERR_HIP;
     if (launch_update(t, u, cfg->optimizer, bf16g, copy, unroll, items_per_chunk, 1, 0, grid_update, stream) != hipSuccess)
         return ADAGC_ERR_HIP;
     return ADAGC_OK;

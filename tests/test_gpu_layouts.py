@@ -107,3 +107,45 @@ def test_update_clipping_with_every_size_of_work_item(optimizer, split, unroll):
         np.testing.assert_allclose(a[2], b[2], rtol=2e-7)
         assert np.array_equal(a[3], b[3])
         assert ((a[0] - b[0]).abs() <= 2e-7 * a[0].abs() + 1e-12).all()
+
+
+@pytest.mark.parametrize("entry", ["step", "graph", "static"])
+@pytest.mark.parametrize("n", [1, 2, 511, 512, 513, 1700])
+def test_model_wide_rules_on_short_and_long_lists(n, entry):
+    """Up to 512 tensors the last workgroup of the rules kernel evaluates a model-wide rule, beyond that a kernel of its own:
+    the warm-up branch, the model's coefficient and its running minimum, and GlobalGC, on both sides of that line, several steps
+    in a row (the count has to be zero again after each)."""
+    rng = np.random.default_rng(n)
+    numels = [int(x) for x in rng.integers(1, 40, n)]
+    numels[-1] = 50000
+    g = [torch.from_numpy(rng.standard_normal(k).astype(np.float32)).to(DEV) for k in numels]
+    norms = np.array([float(x.double().norm()) for x in g])
+    model = float(np.sqrt((norms ** 2).sum()))
+    p, m = ([torch.zeros_like(x) for x in g] for _ in range(2))
+    v = [torch.zeros_like(x) for x in g]
+    gamma = torch.full((n,), 1e9, dtype=torch.float32, device=DEV)
+    out_n, out_c = torch.zeros(n, device=DEV), torch.zeros(n, device=DEV)
+    out_f = torch.zeros(n, dtype=torch.uint8, device=DEV)
+    ctx = None if entry == "static" else B.AdaGC(numels)
+    sp = torch.zeros(56, dtype=torch.uint8, device=DEV)
+    least = np.full(n, 1e9)
+    for step, (threshold, mode) in enumerate([(0.5 * model, B.ADAGC_MODE_ADAGC), (0.25 * model, B.ADAGC_MODE_ADAGC),
+                                              (2.0 * model, B.ADAGC_MODE_GLOBALGC), (0.1 * model, B.ADAGC_MODE_GLOBALGC)], start=2):
+        hp = B.make_hyper(t_start=100, lambda_abs=threshold, clip_mode=mode)
+        if entry == "step":
+            ctx.step(p, g, m, v, gamma, hp, step)
+        elif entry == "graph":
+            sp.copy_(torch.frombuffer(bytearray(B.step_params_bytes(hp, step)), dtype=torch.uint8))
+            ctx.step_graph(p, g, m, v, gamma, sp)
+        else:
+            B.adagc_step_static(numels, p, g, m, v, gamma, hp, step, out_norms=out_n, out_coefs=out_c, out_clipped=out_f)
+        got = ctx.get_norms() if ctx else tuple(x.cpu().numpy() for x in (out_n, out_c, out_f))
+        h = min(1.0, float(np.float32(threshold)) / model)
+        np.testing.assert_allclose(got[0], norms, rtol=2e-7)
+        np.testing.assert_allclose(got[1], np.full(n, h), rtol=2e-7)
+        assert (got[2] == (1 if h < 1.0 else 0)).all()
+        if mode == B.ADAGC_MODE_ADAGC:
+            least = np.minimum(least, h * norms)
+        np.testing.assert_allclose(gamma.cpu().numpy(), least, rtol=2e-7)
+    if ctx:
+        ctx.close()
