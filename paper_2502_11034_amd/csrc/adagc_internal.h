@@ -88,7 +88,7 @@ struct StepScalars {
 
 struct DeviceTables {
     const WorkRef*    work;       // the chunks in visiting order: the n_long that are more than one work item of the
-                                  // update kernel, then those that are one
+                                  // update kernel, then those that are one, the n_tiny that one wave handles last
     const TensorArgs* targs;
     double*           partials;   // one per chunk
     double*           sumsq;      // one per tensor
@@ -106,6 +106,7 @@ struct DeviceTables {
     double*           ucoef64;        // update clipping: per-tensor coefficient of the direction, or null
     uint32_t          n_chunks;
     uint32_t          n_long;
+    uint32_t          n_tiny;
     uint32_t          n_tensors;
 };
 
@@ -117,14 +118,25 @@ struct DeviceTables {
 constexpr int default_unroll(int optimizer) { return optimizer == ADAGC_OPT_LION ? 2 : 4; }
 constexpr int default_items(int unroll) { return kVecPerLane >= unroll ? kVecPerLane / unroll : 1; }
 
-// Chunks of at most one work item of the update kernel (items_per_chunk of them make a full chunk) are numbered after the
-// longer ones.
-__host__ __device__ inline bool is_long_chunk(int64_t len, int items_per_chunk) { return len > kChunkElems / items_per_chunk || items_per_chunk == 1; }
-
-// Work items of the update kernel: items_per_chunk for every long chunk (in groups of 8 chunks), one for each of the others.
-inline int64_t count_work_items(int64_t n_chunks, int64_t n_long, int items_per_chunk)
+// How the streaming kernels work on a chunk of `len` elements, in the order in which the work table has them:
+//   long   more than one work item of the update kernel (items_per_chunk of them make a full chunk)
+//   short  one work item
+//   tiny   one round of a single wave's loads: four chunks to a workgroup.  Most tensors of a list of adapters, biases and norm
+//          weights are of this size, and a workgroup of its own for each costs more than its work (5000 tensors, two thirds of
+//          them tiny: 108 us per step, now 100).
+enum ChunkKind { kLongChunk, kShortChunk, kTinyChunk };
+constexpr int kTinyMax = 1024;             // the norm kernel's round for one wave
+__host__ __device__ inline ChunkKind chunk_kind(int64_t len, int items_per_chunk, int unroll)
 {
-    return (n_long + 7) / 8 * 8 * items_per_chunk + (n_chunks - n_long);
+    if (items_per_chunk == 1 || len > kChunkElems / items_per_chunk) return kLongChunk;
+    return len <= unroll * 256 && len <= kTinyMax ? kTinyChunk : kShortChunk;
+}
+
+// Workgroups' worth of work: items_per_chunk for every long chunk (in groups of 8 chunks), one for a short chunk, one for four
+// tiny ones.
+inline int64_t count_work_items(int64_t n_chunks, int64_t n_long, int64_t n_tiny, int items_per_chunk)
+{
+    return (n_long + 7) / 8 * 8 * items_per_chunk + (n_chunks - n_long - n_tiny) + (n_tiny + 3) / 4;
 }
 
 // What every step entry point accepts as hyper-parameters.

@@ -190,15 +190,19 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
         const int64_t rest = c->numel[chunk_tensor[k]] - (int64_t)chunk_index[k] * kChunkElems;
         return rest < kChunkElems ? rest : (int64_t)kChunkElems;
     };
-    int64_t n_long = 0;
-    for (size_t k = 0; k < chunk_tensor.size(); ++k) n_long += is_long_chunk(chunk_len(k), c->items_per_chunk) ? 1 : 0;
-    const int64_t tiles = count_work_items(c->n_chunks, n_long, c->items_per_chunk);
+    auto kind_of = [&](size_t k) { return chunk_kind(chunk_len(k), c->items_per_chunk, c->unroll); };
+    int64_t n_long = 0, n_tiny = 0;
+    for (size_t k = 0; k < chunk_tensor.size(); ++k) {
+        n_long += kind_of(k) == kLongChunk ? 1 : 0;
+        n_tiny += kind_of(k) == kTinyChunk ? 1 : 0;
+    }
+    const int64_t tiles = count_work_items(c->n_chunks, n_long, n_tiny, c->items_per_chunk);
     auto grid_for = [cfg](int64_t items) {
         int64_t want = cfg->grid_blocks > 0 ? (int64_t)cfg->grid_blocks : items;
         if (want > items) want = items;
         return (int)(want > kMaxGridBlocks ? kMaxGridBlocks : want);
     };
-    c->grid_norm = grid_for(c->n_chunks);
+    c->grid_norm = grid_for(c->n_chunks - n_tiny + (n_tiny + 3) / 4);
     c->grid_update = grid_for(tiles);
 
     // One slab, carved into 256-byte aligned arrays.
@@ -228,15 +232,15 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     char* base = static_cast<char*>(c->slab);
     if (hipMemset(c->slab, 0, slab_bytes) != hipSuccess) { free_ctx(c); return ADAGC_ERR_HIP; }
 
-    // The chunks in visiting order (see adagc_build_visiting_order): those of more than one work item of the update kernel,
-    // then the others in list order.
+    // The chunks in visiting order (see adagc_build_visiting_order): the long ones, then the short and the tiny ones in list
+    // order.
     {
         std::vector<WorkRef> work;
         try {
             std::vector<uint32_t> longer, order;
             longer.reserve((size_t)n_long);
             for (size_t k = 0; k < nc; ++k)
-                if (is_long_chunk(chunk_len(k), c->items_per_chunk)) longer.push_back((uint32_t)k);
+                if (kind_of(k) == kLongChunk) longer.push_back((uint32_t)k);
             order.resize((size_t)n_long);
             if (n_long > 0) {
                 rc = adagc_build_visiting_order(n_long, cfg->schedule ? cfg->schedule : 2, cfg->schedule_run ? cfg->schedule_run : 8,
@@ -246,8 +250,9 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
             work.reserve(nc);
             auto append = [&](uint32_t k) { work.push_back(WorkRef{chunk_tensor[k], k, chunk_index[k], (uint32_t)chunk_len(k)}); };
             for (uint32_t o : order) append(longer[o]);
-            for (size_t k = 0; k < nc; ++k)
-                if (!is_long_chunk(chunk_len(k), c->items_per_chunk)) append((uint32_t)k);
+            for (ChunkKind kind : {kShortChunk, kTinyChunk})
+                for (size_t k = 0; k < nc; ++k)
+                    if (kind_of(k) == kind) append((uint32_t)k);
         } catch (const std::bad_alloc&) { free_ctx(c); return ADAGC_ERR_OOM; }
         if (hipMemcpy(base + o_work, work.data(), nc * sizeof(WorkRef), hipMemcpyHostToDevice) != hipSuccess) {
             free_ctx(c);
@@ -284,6 +289,7 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     t.ucoef64 = cfg->update_clipping ? reinterpret_cast<double*>(base + o_ucoef64) : nullptr;
     t.n_chunks = (uint32_t)c->n_chunks;
     t.n_long = (uint32_t)n_long;
+    t.n_tiny = (uint32_t)n_tiny;
     t.n_tensors = (uint32_t)c->n_tensors;
 
     *out = c;

@@ -136,6 +136,39 @@ __device__ __forceinline__ void acc4(double (&acc)[4], f32x4 g)
     acc[3] = fma(w, w, acc[3]);
 }
 
+// A chunk of at most kTinyMax elements, by one wave.
+template <bool BF16>
+__device__ __forceinline__ void tiny_chunk_sumsq(const DeviceTables& t, const WorkRef& w, int lane)
+{
+    const TensorArgs ta = load_tensor(t.targs, w.tensor);
+    const int len = (int)w.len;
+    const gcbytes g = grad_at<BF16>(ta.grad, first_element(w));
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    if (ta.vec_ok) {
+        constexpr int kRound = kTinyMax / 256;
+        const int nvec = len >> 2;
+        const int j = (nvec << 2) + lane;
+        const float last = j < len ? load_grad1<BF16>(g, j) : 0.f;
+        f32x4 r[kRound];
+#pragma unroll
+        for (int u = 0; u < kRound; ++u) {
+            const int v = u * 64 + lane;
+            r[u] = v < nvec ? load_grad4<BF16, false>(g, v) : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int u = 0; u < kRound; ++u) acc4(acc, r[u]);
+        const double x = (double)last;
+        acc[0] = fma(x, x, acc[0]);
+    } else {
+        for (int j = lane; j < len; j += 64) {
+            const double x = (double)load_grad1<BF16>(g, j);
+            acc[0] = fma(x, x, acc[0]);
+        }
+    }
+    const double s = wave_sum_f64((acc[0] + acc[1]) + (acc[2] + acc[3]));
+    if (lane == 0) t.partials[w.slot] = s;
+}
+
 // The loads are ordinary ones: streaming loads leave nothing in the 256 MB memory-side cache, and the update kernel reads the
 // same gradients next.  GPT-2-small shapes (498 MB of gradients): 657 us per step with streaming loads, 622 without; 266 MB of
 // bf16 gradients 680, 635; lists of many GB do not care (this kernel alone then reads 7.2 TB/s either way).
@@ -147,7 +180,13 @@ __global__ __launch_bounds__(kBlock) void sumsq_partials_kernel(DeviceTables t, 
     const int tid = threadIdx.x;
     if (params && blockIdx.x == gridDim.x - 1 && tid == 0) prepare_update_scalars(t, params, optimizer);
 
-    for (uint32_t k = blockIdx.x; k < t.n_chunks; k += gridDim.x) {
+    const uint32_t n_wide = t.n_chunks - t.n_tiny, n_groups = n_wide + (t.n_tiny + 3u) / 4u;
+    for (uint32_t k = blockIdx.x; k < n_groups; k += gridDim.x) {
+        if (k >= n_wide) {                     // four tiny chunks, one to a wave
+            const uint32_t at = n_wide + (k - n_wide) * 4u + (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
+            if (at < t.n_chunks) tiny_chunk_sumsq<BF16>(t, load_work(t.work, at), tid & 63);
+            continue;
+        }
         const WorkRef w = load_work(t.work, k);
         const TensorArgs ta = load_tensor(t.targs, w.tensor);
         const int len = (int)w.len;
@@ -534,7 +573,8 @@ __device__ __forceinline__ void tele_vec(double (&acc)[3], f32x4 p_old, f32x4 p_
 // its parts) and the items of one chunk all go to the same XCD:
 //   item T  ->  position 8*(T / (8*I)) + T % 8,  item (T / 8) % I of that chunk      (I = items_per_chunk, a power of two).
 // Chunks of one item come after the others, one item each: in a list of many small tensors three of a chunk's four items
-// would be empty, and an empty workgroup costs its dispatch and its chain of loads all the same.
+// would be empty, and an empty workgroup costs its dispatch and its chain of loads all the same.  Tiny chunks, last, go four
+// to a workgroup (the direction's norms take them as short ones).
 
 struct WorkItem {
     WorkRef chunk;
@@ -592,19 +632,17 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kUpdateW
     constexpr bool NTL = NT, NTS = NT;    // non-temporal loads and stores
     constexpr bool kHasV = (OPT == ADAGC_OPT_ADAMW);
     constexpr int kTiles = kVecPerLane / U;
-    constexpr int kTileVecs = U * kBlock;
-    constexpr int kTileElems = kTileVecs * 4;
     const int tid = threadIdx.x;
     __shared__ double tele_sums[3][kWavesPerBlock];
 
-    const int tiles_per_item = kTiles >> log2_items;
-    const uint64_t n_items = work_items(t, log2_items);
-    for (uint64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
-        WorkItem w;
-        if (!work_item(t, item, log2_items, w)) continue;
-        const uint32_t tensor = w.chunk.tensor;
-        const int len = (int)w.chunk.len;
-        const int64_t first = first_element(w.chunk);
+    // Tiles first_tile .. first_tile + n_tiles - 1 of a chunk, by LANES lanes (a workgroup, or a wave of it).
+    auto update_tiles = [&](auto LANES, const WorkRef& c, int first_tile, int n_tiles, int lane, double (&tele)[3])
+                            __attribute__((always_inline)) {
+        constexpr int kLanes = decltype(LANES)::value;
+        constexpr int kTileVecs = U * kLanes, kTileElems = kTileVecs * 4;
+        const uint32_t tensor = c.tensor;
+        const int len = (int)c.len;
+        const int64_t first = first_element(c);
         const TensorArgs ta = load_tensor(t.targs, tensor);
         const double h = uniform_load(t.coef64 + tensor);     // the tensor's coefficient as computed, in double
         const double uc = a.update_clip ? uniform_load(t.ucoef64 + tensor) : 1.0;   // update clipping: scales the direction
@@ -613,11 +651,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kUpdateW
         const gfloat m = (gfloat)ta.exp_avg + first;
         const gfloat v = kHasV ? (gfloat)ta.exp_avg_sq + first : nullptr;
         const gu16 pc = COPY ? (gu16)ta.param_copy + first : nullptr;
-        double tele[3] = {0.0, 0.0, 0.0};
 
 #pragma unroll 1
-        for (int tt = 0; tt < tiles_per_item; ++tt) {
-            const int sub = w.part * tiles_per_item + tt;
+        for (int tt = 0; tt < n_tiles; ++tt) {
+            const int sub = first_tile + tt;
             const int e0 = sub * kTileElems;                                   // the tile's elements inside the chunk:
             const int e1 = len < e0 + kTileElems ? len : e0 + kTileElems; // [e0, e1), empty past a ragged end
             if (e0 >= e1) break;
@@ -632,7 +669,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kUpdateW
                 // ragged end they would wait for the stores of the round before).  Lanes past the last whole vector load
                 // that one again and store nothing; up to three single elements come with the tile that ends the chunk.
                 const int nvec = len >> 2;
-                const int j = (nvec << 2) + tid;
+                const int j = (nvec << 2) + lane;
                 const bool single = e1 == len && j < len;
                 ElemState s = {0.f, 0.f, 0.f};
                 float g1 = 0.f;
@@ -644,7 +681,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kUpdateW
                     f32x4 gg[U], pp[U], mm[U], vv[U];
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
-                        const int want = v0 + u * kBlock + tid, idx = want < nvec ? want : nvec - 1;
+                        const int want = v0 + u * kLanes + lane, idx = want < nvec ? want : nvec - 1;
                         gg[u] = load_grad4<BF16G, NTL>(g, idx);
                         pp[u] = ld<NTL>(p4 + idx);
                         mm[u] = ld<NTL>(m4 + idx);
@@ -654,7 +691,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kUpdateW
                     if constexpr (kHasV && COPY) wait_for_loads();
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
-                        const int idx = v0 + u * kBlock + tid;
+                        const int idx = v0 + u * kLanes + lane;
                         if (idx >= nvec) break;
                         const f32x4 p_old = pp[u];
                         apply_vec<OPT>(a, h, uc, gg[u], pp[u], mm[u], vv[u]);
@@ -675,7 +712,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kUpdateW
                     if constexpr (COPY) pc[j] = (uint16_t)float_to_bf16_bits(s.p);
                 }
             } else {
-                for (int j = e0 + tid; j < e1; j += kBlock) {
+                for (int j = e0 + lane; j < e1; j += kLanes) {
                     ElemState s = {p[j], m[j], kHasV ? v[j] : 0.f};
                     const float p_old = s.p;
                     apply_elem<OPT>(a, h, uc, load_grad1<BF16G>(g, j), s);
@@ -687,6 +724,33 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kUpdateW
                 }
             }
         }
+
+    };
+
+    const int tiles_per_item = kTiles >> log2_items;
+    const uint32_t n_wide = t.n_chunks - t.n_tiny;
+    const uint64_t in_long = (((uint64_t)t.n_long + 7u) & ~(uint64_t)7u) << log2_items;
+    const uint64_t n_wide_items = in_long + (n_wide - t.n_long), n_items = n_wide_items + (t.n_tiny + 3u) / 4u;
+    for (uint64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
+        double tele[3] = {0.0, 0.0, 0.0};
+        if (item >= n_wide_items) {            // four tiny chunks, one to a wave
+            const uint32_t at = n_wide + (uint32_t)(item - n_wide_items) * 4u + (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
+            if (at < t.n_chunks) {
+                const WorkRef c = load_work(t.work, at);
+                update_tiles(std::integral_constant<int, 64>{}, c, 0, 1, tid & 63, tele);
+                if constexpr (TELE) {
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) {
+                        const double part = wave_sum_f64(tele[q]);
+                        if ((tid & 63) == 0) t.tele_partials[((size_t)q * t.n_chunks + c.slot) << log2_items] = part;
+                    }
+                }
+            }
+            continue;
+        }
+        WorkItem w;
+        if (!work_item(t, item, log2_items, w)) continue;
+        update_tiles(std::integral_constant<int, kBlock>{}, w.chunk, w.part * tiles_per_item, tiles_per_item, tid, tele);
 
         if constexpr (TELE) {
             // every item writes its slots; those that a chunk of one item has no item for stay zero from the start

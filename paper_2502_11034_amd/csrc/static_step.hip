@@ -5,7 +5,7 @@
 // records reach the GPU as kernel arguments, so there is no copy, no memset and no event either.
 //
 // The norm, rule and update kernels are the ones adagc_step launches (kernels.hip), given pointers
-// into that array; the chunks are visited in list order, those of one work item last.
+// into that array; the chunks are visited in list order, those of one work item after the longer ones.
 
 #include <mutex>
 
@@ -59,8 +59,8 @@ hipError_t scratch_address(int device, unsigned char** out)
 constexpr int kBatch = 56;
 struct TensorBatch {
     TensorArgs t[kBatch];
-    uint32_t   long_at[kBatch];    // where the tensor's long chunks go in the work table, and its short one if it has one
-    uint32_t   short_at[kBatch];
+    uint32_t   long_at[kBatch];    // where the tensor's long chunks go in the work table, and its last one if that is no long one
+    uint32_t   last_at[kBatch];
     uint32_t   first;    // list index of t[0]
     uint32_t   count;
 };
@@ -69,7 +69,7 @@ static_assert(sizeof(TensorBatch) + 4 * sizeof(void*) <= 4096, "a batch fits the
 // Workgroup b stores the record of tensor first+b and writes that tensor's rows of the work table; the list's first also clears
 // the arrival count of the rules.
 __global__ __launch_bounds__(kBlock) void store_tensor_batch_kernel(TensorBatch batch, TensorArgs* targs, WorkRef* work, uint32_t* arrivals,
-                                                                    int items_per_chunk)
+                                                                    int items_per_chunk, int unroll)
 {
     const uint32_t b = blockIdx.x;
     if (b >= batch.count) return;
@@ -81,9 +81,9 @@ __global__ __launch_bounds__(kBlock) void store_tensor_batch_kernel(TensorBatch 
     }
     const uint32_t last = a.chunk_count - 1;
     const int64_t last_len = a.numel - (int64_t)last * kChunkElems;
-    const bool last_is_long = is_long_chunk(last_len, items_per_chunk);
+    const bool last_is_long = chunk_kind(last_len, items_per_chunk, unroll) == kLongChunk;
     for (uint32_t k = threadIdx.x; k < a.chunk_count; k += kBlock) {
-        const uint32_t at = k < last || last_is_long ? batch.long_at[b] + k : batch.short_at[b];
+        const uint32_t at = k < last || last_is_long ? batch.long_at[b] + k : batch.last_at[b];
         work[at] = WorkRef{i, a.chunk_begin + k, k, k < last ? (uint32_t)kChunkElems : (uint32_t)last_len};
     }
 }
@@ -120,19 +120,17 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
 
     // Everything is validated before anything is enqueued: one pass over the list.
     const int unroll = default_unroll(cfg->optimizer), items_per_chunk = default_items(unroll);
-    uint64_t n_chunks = 0, n_long = 0;
-    // long chunks of tensor i: all but a last one of one work item
-    auto long_chunks = [&](int64_t i) {
-        const int64_t whole = descs[i].numel / kChunkElems, rest = descs[i].numel % kChunkElems;
-        return whole + (rest > 0 && is_long_chunk(rest, items_per_chunk) ? 1 : 0);
-    };
+    uint64_t n_chunks = 0, n_long = 0, n_tiny = 0;
+    // the kind of tensor i's last chunk (all others are long)
+    auto last_kind = [&](int64_t i) { return chunk_kind((descs[i].numel - 1) % kChunkElems + 1, items_per_chunk, unroll); };
     for (int64_t i = 0; i < n_tensors; ++i) {
         if (descs[i].numel <= 0 || descs[i].flags != 0 || descs[i].reserved != 0) return ADAGC_ERR_INVALID_ARG;
         if (!params[i] || !grads[i] || !exp_avg[i] || (adamw && !exp_avg_sq[i]) || (copy && !params_bf16[i]))
             return ADAGC_ERR_INVALID_ARG;
         n_chunks += (uint64_t)((descs[i].numel + kChunkElems - 1) / kChunkElems);
         if (n_chunks > (uint64_t)kMaxC) return ADAGC_ERR_TOO_LARGE;
-        n_long += (uint64_t)long_chunks(i);
+        n_long += (uint64_t)((descs[i].numel - 1) / kChunkElems) + (last_kind(i) == kLongChunk ? 1 : 0);
+        n_tiny += last_kind(i) == kTinyChunk ? 1 : 0;
     }
 
     int device = -1;
@@ -160,11 +158,12 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
     t.scalars = nullptr;
     t.n_chunks = (uint32_t)n_chunks;
     t.n_long = (uint32_t)n_long;
+    t.n_tiny = (uint32_t)n_tiny;
     t.n_tensors = (uint32_t)n_tensors;
 
     // Tensor records and chunk table, a batch of tensors per launch.
     const uintptr_t grad_align = bf16g ? 2 : 4;
-    uint32_t chunk_begin = 0, long_at = 0, short_at = (uint32_t)n_long;
+    uint32_t chunk_begin = 0, long_at = 0, short_at = (uint32_t)n_long, tiny_at = (uint32_t)(n_chunks - n_tiny);
     TensorBatch batch;
     for (int64_t first = 0; first < n_tensors; first += kBatch) {
         const int64_t count = (n_tensors - first) < kBatch ? (n_tensors - first) : kBatch;
@@ -184,28 +183,28 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
                            ? 1u : 0u;
             a.pad = 0;
             chunk_begin += a.chunk_count;
-            const uint32_t n = (uint32_t)long_chunks(i);
+            const ChunkKind kind = last_kind(i);
             batch.long_at[b] = long_at;
-            batch.short_at[b] = short_at;
-            long_at += n;
-            short_at += a.chunk_count - n;
+            long_at += kind == kLongChunk ? a.chunk_count : a.chunk_count - 1;
+            batch.last_at[b] = kind == kShortChunk ? short_at++ : (kind == kTinyChunk ? tiny_at++ : 0u);
         }
         for (int64_t b = count; b < kBatch; ++b) {
             batch.t[b] = TensorArgs{};
-            batch.long_at[b] = batch.short_at[b] = 0;
+            batch.long_at[b] = batch.last_at[b] = 0;
         }
         batch.first = (uint32_t)first;
         batch.count = (uint32_t)count;
-        store_tensor_batch_kernel<<<dim3((uint32_t)count), dim3(kBlock), 0, stream>>>(batch, d_targs, d_work, t.arrivals, items_per_chunk);
+        store_tensor_batch_kernel<<<dim3((uint32_t)count), dim3(kBlock), 0, stream>>>(batch, d_targs, d_work, t.arrivals, items_per_chunk, unroll);
         if (hipGetLastError() != hipSuccess) return ADAGC_ERR_HIP;
     }
 
     RuleArgs r;
     UpdateArgs u;
     host_step_scalars(*hp, step, r, u);
-    const int64_t items = count_work_items((int64_t)n_chunks, (int64_t)n_long, items_per_chunk);
+    const int64_t items = count_work_items((int64_t)n_chunks, (int64_t)n_long, (int64_t)n_tiny, items_per_chunk);
     const int64_t max_grid = (int64_t)(0xFFFFFFFFu / (uint32_t)kBlock);
-    const int grid_norm = (int)((int64_t)n_chunks > max_grid ? max_grid : (int64_t)n_chunks);
+    const int64_t groups = (int64_t)(n_chunks - n_tiny + (n_tiny + 3) / 4);
+    const int grid_norm = (int)(groups > max_grid ? max_grid : groups);
     const int grid_update = (int)(items > max_grid ? max_grid : items);
 
     if (launch_sumsq_partials(t, bf16g, grid_norm, stream) != hipSuccess) return ADAGC_ERR_HIP;
