@@ -101,6 +101,7 @@ struct DeviceTables {
     double*           tele_partials;  // telemetry: [3][n_chunks][items per chunk] sums of m^2, v^2, (dtheta)^2 (or null)
     float*            tele_norm;      // telemetry: [3][n_tensors] norms
     StepScalars*      scalars;        // used by adagc_step_graph only
+    float*            ema_before;     // per tensor, small lists: gamma as the step found it
     double*           ustat_partials; // update clipping: [2][n_chunks][items per chunk] partial norms of theta and of
                                       // the direction (sums of squares for AGC, maxima for Clippy), or null
     double*           ucoef64;        // update clipping: per-tensor coefficient of the direction, or null
@@ -138,6 +139,17 @@ inline int64_t count_work_items(int64_t n_chunks, int64_t n_long, int64_t n_tiny
 {
     return (n_long + 7) / 8 * 8 * items_per_chunk + (n_chunks - n_long - n_tiny) + (n_tiny + 3) / 4;
 }
+
+// Small lists evaluate the per-tensor rule (Eq. 3) inside the update kernel, every wave for its own chunk, from the tensor's
+// partial sums and a copy of gamma that the norm kernel makes: one launch less, for one more load per wave.  That pays while
+// the update kernel is only a few rounds of workgroups, and needs tensors whose slots one wave can sum in the rules kernel's
+// order (see rule_in_update).
+constexpr int64_t kFusedMaxItems = 1024;
+constexpr int64_t kFusedMaxChunks = 64;        // of one tensor
+struct FusedRule {
+    float*   ema;        // null: the rules kernel has run, coefficients are in coef64
+    RuleArgs r;
+};
 
 // What every step entry point accepts as hyper-parameters.
 inline bool hyper_ok(const adagc_hyper& h, int optimizer)
@@ -187,12 +199,12 @@ inline void host_step_scalars(const adagc_hyper& hp, int64_t step, RuleArgs& r, 
 // Gradient norms, then the clipping rules.  params: null, or the DEVICE parameters of this step, which are then read instead
 // of r (and from which the norm kernel leaves t.scalars for launch_update).
 hipError_t launch_sumsq_partials(const DeviceTables& t, int grad_bf16, int grid, hipStream_t stream,
-                                 const adagc_step_params* params = nullptr, int optimizer = 0);
+                                 const adagc_step_params* params = nullptr, int optimizer = 0, const float* ema_to_keep = nullptr);
 hipError_t launch_rules(const DeviceTables& t, float* ema, const RuleArgs& r, hipStream_t stream,
                         const adagc_step_params* params = nullptr, int optimizer = 0);
 hipError_t launch_update(const DeviceTables& t, const UpdateArgs& u, int optimizer, int grad_bf16,
                          int with_copy, int unroll, int items_per_chunk, int nt, int tele, int grid,
-                         hipStream_t stream, bool device_scalars = false);
+                         hipStream_t stream, bool device_scalars = false, const FusedRule& rule = FusedRule{});
 // Update-clipping modes (AGC, Clippy): norms of theta and of the direction per work item, then one workgroup
 // per tensor turns them into the tensor's update coefficient.
 hipError_t launch_update_clip_rule(const DeviceTables& t, const UpdateArgs& u, const RuleArgs& r, int optimizer,

@@ -21,6 +21,7 @@ struct adagc_ctx {
     int          unroll = 0;
     int          nontemporal = 0;
     int          items_per_chunk = 1;   // work items of the update kernel per chunk
+    bool         small_list = false;    // the per-tensor rule goes into the update kernel (FusedRule)
 
     std::vector<int64_t>    numel;
     std::vector<int64_t>    chunk_begin;      // n_tensors + 1
@@ -202,6 +203,12 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
         if (want > items) want = items;
         return (int)(want > kMaxGridBlocks ? kMaxGridBlocks : want);
     };
+    int64_t most_chunks = 0;
+    for (int64_t i = 0; i < n_tensors; ++i) {
+        const int64_t n = c->chunk_begin[(size_t)i + 1] - c->chunk_begin[(size_t)i];
+        if (n > most_chunks) most_chunks = n;
+    }
+    c->small_list = tiles <= kFusedMaxItems && most_chunks <= kFusedMaxChunks;
     c->grid_norm = grid_for(c->n_chunks - n_tiny + (n_tiny + 3) / 4);
     c->grid_update = grid_for(tiles);
 
@@ -215,6 +222,7 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     const size_t o_sumsq = carve(nt * sizeof(double));
     const size_t o_global = carve(4 * sizeof(double));
     const size_t o_arrivals = carve(sizeof(uint32_t));
+    const size_t o_ema_before = carve(nt * sizeof(float));
     const size_t o_scalars = carve(sizeof(StepScalars));
     const size_t o_coef64 = carve(nt * sizeof(double));
     const size_t o_norm = carve(nt * sizeof(float));
@@ -278,6 +286,7 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     t.sumsq = reinterpret_cast<double*>(base + o_sumsq);
     t.global = reinterpret_cast<double*>(base + o_global);
     t.arrivals = reinterpret_cast<uint32_t*>(base + o_arrivals);
+    t.ema_before = reinterpret_cast<float*>(base + o_ema_before);
     t.scalars = reinterpret_cast<StepScalars*>(base + o_scalars);
     t.coef64 = reinterpret_cast<double*>(base + o_coef64);
     t.norm = reinterpret_cast<float*>(base + o_norm);
@@ -393,6 +402,7 @@ extern "C" int adagc_step(adagc_ctx* ctx, void* const* params, const void* const
     RuleArgs r;
     UpdateArgs u;
     host_step_scalars(*hp, step, r, u);
+    FusedRule  rule{};
     ctx->device_scalars_used = false;
     const bool prof = ctx->prof_steps < ctx->prof_capacity;
     hipEvent_t* ev = prof ? &ctx->prof_events[(size_t)ctx->prof_steps * 4] : nullptr;
@@ -407,13 +417,14 @@ extern "C" int adagc_step(adagc_ctx* ctx, void* const* params, const void* const
         if (prof && (hipEventRecord(ev[1], stream) != hipSuccess || hipEventRecord(ev[2], stream) != hipSuccess))
             return ADAGC_ERR_HIP;
     } else {
-        if (launch_sumsq_partials(ctx->tables, bf16g, ctx->grid_norm, stream) != hipSuccess) return ADAGC_ERR_HIP;
+        if (ctx->small_list && !r.warmup && r.mode == ADAGC_MODE_ADAGC) rule = FusedRule{ema_norms, r};
+        if (launch_sumsq_partials(ctx->tables, bf16g, ctx->grid_norm, stream, nullptr, 0, rule.ema) != hipSuccess) return ADAGC_ERR_HIP;
         if (prof && hipEventRecord(ev[1], stream) != hipSuccess) return ADAGC_ERR_HIP;
-        if (launch_rules(ctx->tables, ema_norms, r, stream) != hipSuccess) return ADAGC_ERR_HIP;
+        if (!rule.ema && launch_rules(ctx->tables, ema_norms, r, stream) != hipSuccess) return ADAGC_ERR_HIP;
         if (prof && hipEventRecord(ev[2], stream) != hipSuccess) return ADAGC_ERR_HIP;
     }
     if (launch_update(ctx->tables, u, ctx->cfg.optimizer, bf16g, copy, ctx->unroll, ctx->items_per_chunk,
-                      ctx->nontemporal, ctx->cfg.telemetry, ctx->grid_update, stream) != hipSuccess)
+                      ctx->nontemporal, ctx->cfg.telemetry, ctx->grid_update, stream, false, rule) != hipSuccess)
         return ADAGC_ERR_HIP;
     if (prof) {
         if (hipEventRecord(ev[3], stream) != hipSuccess) return ADAGC_ERR_HIP;

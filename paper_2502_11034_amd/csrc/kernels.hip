@@ -173,8 +173,10 @@ __device__ __forceinline__ void tiny_chunk_sumsq(const DeviceTables& t, const Wo
 // same gradients next.  GPT-2-small shapes (498 MB of gradients): 657 us per step with streaming loads, 622 without; 266 MB of
 // bf16 gradients 680, 635; lists of many GB do not care (this kernel alone then reads 7.2 TB/s either way).
 // params: null, or the device-resident parameters of this step, from which one lane makes the update kernel's scalars.
+// ema_to_keep: null, or the gammas that the update kernel will need as they are now (see FusedRule).
 template <bool BF16>
-__global__ __launch_bounds__(kBlock) void sumsq_partials_kernel(DeviceTables t, const adagc_step_params* params, int optimizer)
+__global__ __launch_bounds__(kBlock) void sumsq_partials_kernel(DeviceTables t, const adagc_step_params* params, int optimizer,
+                                                                const float* ema_to_keep)
 {
     __shared__ double wave_sums[kWavesPerBlock];
     const int tid = threadIdx.x;
@@ -184,10 +186,15 @@ __global__ __launch_bounds__(kBlock) void sumsq_partials_kernel(DeviceTables t, 
     for (uint32_t k = blockIdx.x; k < n_groups; k += gridDim.x) {
         if (k >= n_wide) {                     // four tiny chunks, one to a wave
             const uint32_t at = n_wide + (k - n_wide) * 4u + (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
-            if (at < t.n_chunks) tiny_chunk_sumsq<BF16>(t, load_work(t.work, at), tid & 63);
+            if (at < t.n_chunks) {
+                const WorkRef w = load_work(t.work, at);
+                if (ema_to_keep && w.index == 0 && (tid & 63) == 0) t.ema_before[w.tensor] = ema_to_keep[w.tensor];
+                tiny_chunk_sumsq<BF16>(t, w, tid & 63);
+            }
             continue;
         }
         const WorkRef w = load_work(t.work, k);
+        if (ema_to_keep && w.index == 0 && tid == 0) t.ema_before[w.tensor] = ema_to_keep[w.tensor];
         const TensorArgs ta = load_tensor(t.targs, w.tensor);
         const int len = (int)w.len;
         const gcbytes g = grad_at<BF16>(ta.grad, first_element(w));
@@ -293,24 +300,34 @@ __device__ __forceinline__ bool arrive_last(uint32_t* counter, uint32_t total)
     return true;
 }
 
-// AdaGC branch of Alg. 1 / Eq. 3 for tensor i with sum of squares s, in double, with separately rounded
-// operations.  One lane.
-__device__ __forceinline__ void adagc_rule(const DeviceTables& t, float* ema, const RuleArgs& r, uint32_t i, double s)
+// AdaGC branch of Alg. 1 / Eq. 3 for a tensor with sum of squares s and threshold state gamma_prev, in double, with
+// separately rounded operations.
+struct TensorRule {
+    double norm, h, gamma_new;
+    bool   active;
+};
+
+__device__ __forceinline__ TensorRule adagc_rule(const RuleArgs& r, double s, double gamma_prev)
 {
-    const double norm = sqrt(s);
-    const double gamma_prev = (double)ema[i];
+    TensorRule o;
+    o.norm = sqrt(s);
     const double threshold = __dmul_rn(r.lambda_rel, gamma_prev);
-    const bool active = norm > threshold;                 // strict; false if either side is NaN
-    const double h = active ? __ddiv_rn(threshold, norm) : 1.0;
-    const double clipped_norm = active ? threshold : norm;
-    const double gamma_new = __dadd_rn(__dmul_rn(r.ema_beta, gamma_prev),
-                                       __dmul_rn(__dsub_rn(1.0, r.ema_beta), clipped_norm));
+    o.active = o.norm > threshold;                        // strict; false if either side is NaN
+    o.h = o.active ? __ddiv_rn(threshold, o.norm) : 1.0;
+    const double clipped_norm = o.active ? threshold : o.norm;
+    o.gamma_new = __dadd_rn(__dmul_rn(r.ema_beta, gamma_prev), __dmul_rn(__dsub_rn(1.0, r.ema_beta), clipped_norm));
+    return o;
+}
+
+// One lane: tensor i's results.
+__device__ __forceinline__ void store_rule(const DeviceTables& t, float* ema, uint32_t i, double s, const TensorRule& o)
+{
     t.sumsq[i] = s;
-    t.norm[i] = (float)norm;
-    t.coef[i] = (float)h;
-    t.coef64[i] = h;
-    t.flag[i] = active ? 1 : 0;
-    ema[i] = (float)gamma_new;
+    t.norm[i] = (float)o.norm;
+    t.coef[i] = (float)o.h;
+    t.coef64[i] = o.h;
+    t.flag[i] = o.active ? 1 : 0;
+    ema[i] = (float)o.gamma_new;
 }
 
 // Model-wide rules: the model's norm over all tensors (fixed order) and one coefficient for the
@@ -432,7 +449,7 @@ __global__ __launch_bounds__(kBlock) void rules_kernel(DeviceTables t, float* em
     const uint32_t i = blockIdx.x;
     const double s = tensor_slot_sum(t, t.partials, i, wave_sums);
     if (!model_wide(r)) {
-        if (tid == 0) adagc_rule(t, ema, r, i, s);
+        if (tid == 0) store_rule(t, ema, i, s, adagc_rule(r, s, (double)ema[i]));
         return;
     }
     if (t.n_tensors > kFewTensors) {
@@ -603,6 +620,22 @@ __device__ __forceinline__ bool work_item(const DeviceTables& t, uint64_t item, 
     return true;
 }
 
+// The per-tensor rule inside the update kernel (FusedRule); all 64 lanes.  A tensor has at most 64 partial sums: one to a
+// lane, the other lanes' and waves' shares of the rules kernel's order are zeros there too, so the sum is the same bit for bit.
+// The lane with the tensor's first element stores the results (`stores`).
+// 27 tensors of 0.5 M parameters: 14.7 us per step with the rules in a kernel of their own, 11.4 so; 100 tensors of 3.6 M
+// parameters (1000 work items) 29, 25.8.
+__device__ __forceinline__ double rule_in_update(const DeviceTables& t, const FusedRule& rule, uint32_t tensor, const TensorArgs& ta,
+                                                 bool stores)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    const double mine = lane < ta.chunk_count ? t.partials[ta.chunk_begin + lane] : 0.0;
+    const double s = wave_sum_f64(mine);
+    const TensorRule o = adagc_rule(rule.r, s, (double)uniform_load(t.ema_before + tensor));
+    if (stores) store_rule(t, rule.ema, tensor, s, o);
+    return o.h;
+}
+
 // All loads of this wave are there before anything else is done.  With seven arrays and a copy to write, stores that start
 // while the item's last loads are still on their way cost more in read/write turnaround than they gain: 133 M parameters with
 // bf16 gradients and copies 646 us per step without, 631 with; 1.9 B with fp32 gradients 10.78, 10.72 ms.  Without the copy
@@ -622,7 +655,7 @@ constexpr int kUpdateWaves = OPT == ADAGC_OPT_ADAMW ? 2 : 3;
 
 template <int OPT, bool BF16G, bool COPY, int U, bool NT, bool TELE>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kUpdateWaves<OPT>, kUpdateWaves<OPT>))) void update_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items,
-                                                        const StepScalars* device_scalars)
+                                                        const StepScalars* device_scalars, FusedRule rule)
 {
     static_assert(kVecPerLane % U == 0, "a chunk is a whole number of tiles");
     if (device_scalars) {                      // adagc_step_graph: this step's scalars live in device memory
@@ -644,7 +677,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kUpdateW
         const int len = (int)c.len;
         const int64_t first = first_element(c);
         const TensorArgs ta = load_tensor(t.targs, tensor);
-        const double h = uniform_load(t.coef64 + tensor);     // the tensor's coefficient as computed, in double
+        // the tensor's coefficient as computed, in double
+        const double h = rule.ema ? rule_in_update(t, rule, tensor, ta, c.index == 0 && first_tile == 0 && lane == 0)
+                                  : uniform_load(t.coef64 + tensor);
         const double uc = a.update_clip ? uniform_load(t.ucoef64 + tensor) : 1.0;   // update clipping: scales the direction
         const gcbytes g = grad_at<BF16G>(ta.grad, first);
         const gfloat p = (gfloat)ta.param + first;
@@ -965,7 +1000,7 @@ __global__ __launch_bounds__(kBlock) void finalize_telemetry_kernel(DeviceTables
     if (threadIdx.x == 0) t.tele_norm[(size_t)q * t.n_tensors + i] = (float)sqrt(s);
 }
 
-using UpdateFn = void (*)(DeviceTables, UpdateArgs, uint32_t, const StepScalars*);
+using UpdateFn = void (*)(DeviceTables, UpdateArgs, uint32_t, const StepScalars*, FusedRule);
 
 template <int OPT, bool BF16G, bool COPY, int U>
 UpdateFn select_update_flags(int nt, int tele)
@@ -1000,10 +1035,10 @@ UpdateFn select_update(int optimizer, int grad_bf16, int with_copy, int unroll, 
 }  // namespace
 
 hipError_t launch_sumsq_partials(const DeviceTables& t, int grad_bf16, int grid, hipStream_t stream, const adagc_step_params* params,
-                                 int optimizer)
+                                 int optimizer, const float* ema_to_keep)
 {
-    if (grad_bf16) sumsq_partials_kernel<true><<<dim3(grid), dim3(kBlock), 0, stream>>>(t, params, optimizer);
-    else sumsq_partials_kernel<false><<<dim3(grid), dim3(kBlock), 0, stream>>>(t, params, optimizer);
+    if (grad_bf16) sumsq_partials_kernel<true><<<dim3(grid), dim3(kBlock), 0, stream>>>(t, params, optimizer, ema_to_keep);
+    else sumsq_partials_kernel<false><<<dim3(grid), dim3(kBlock), 0, stream>>>(t, params, optimizer, ema_to_keep);
     return hipGetLastError();
 }
 
@@ -1054,10 +1089,10 @@ hipError_t launch_update_clip_rule(const DeviceTables& t, const UpdateArgs& u, c
 
 hipError_t launch_update(const DeviceTables& t, const UpdateArgs& a, int optimizer, int grad_bf16,
                          int with_copy, int unroll, int items_per_chunk, int nt, int tele, int grid,
-                         hipStream_t stream, bool device_scalars)
+                         hipStream_t stream, bool device_scalars, const FusedRule& rule)
 {
     select_update(optimizer, grad_bf16, with_copy, unroll, nt, tele)<<<dim3(grid), dim3(kBlock), 0, stream>>>(
-        t, a, log2_of(items_per_chunk), device_scalars ? t.scalars : nullptr);
+        t, a, log2_of(items_per_chunk), device_scalars ? t.scalars : nullptr, rule);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !tele) return e;
     finalize_telemetry_kernel<<<dim3(t.n_tensors, 3), dim3(kBlock), 0, stream>>>(t, (uint32_t)items_per_chunk);

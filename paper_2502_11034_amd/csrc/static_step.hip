@@ -26,7 +26,8 @@ constexpr size_t kOffSumsq = kOffPartials + align256(kMaxC * sizeof(double));
 constexpr size_t kOffCoef64 = kOffSumsq + align256(kMaxT * sizeof(double));
 constexpr size_t kOffGlobal = kOffCoef64 + align256(kMaxT * sizeof(double));
 constexpr size_t kOffArrivals = kOffGlobal + align256(4 * sizeof(double));
-constexpr size_t kOffNorm = kOffArrivals + align256(sizeof(uint32_t));
+constexpr size_t kOffEmaBefore = kOffArrivals + align256(sizeof(uint32_t));
+constexpr size_t kOffNorm = kOffEmaBefore + align256(kMaxT * sizeof(float));
 constexpr size_t kOffCoef = kOffNorm + align256(kMaxT * sizeof(float));
 constexpr size_t kOffFlag = kOffCoef + align256(kMaxT * sizeof(float));
 constexpr size_t kScratchBytes = kOffFlag + align256(kMaxT);
@@ -121,6 +122,7 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
     // Everything is validated before anything is enqueued: one pass over the list.
     const int unroll = default_unroll(cfg->optimizer), items_per_chunk = default_items(unroll);
     uint64_t n_chunks = 0, n_long = 0, n_tiny = 0;
+    bool small_tensors = true;
     // the kind of tensor i's last chunk (all others are long)
     auto last_kind = [&](int64_t i) { return chunk_kind((descs[i].numel - 1) % kChunkElems + 1, items_per_chunk, unroll); };
     for (int64_t i = 0; i < n_tensors; ++i) {
@@ -129,6 +131,7 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
             return ADAGC_ERR_INVALID_ARG;
         n_chunks += (uint64_t)((descs[i].numel + kChunkElems - 1) / kChunkElems);
         if (n_chunks > (uint64_t)kMaxC) return ADAGC_ERR_TOO_LARGE;
+        if (descs[i].numel > kFusedMaxChunks * kChunkElems) small_tensors = false;
         n_long += (uint64_t)((descs[i].numel - 1) / kChunkElems) + (last_kind(i) == kLongChunk ? 1 : 0);
         n_tiny += last_kind(i) == kTinyChunk ? 1 : 0;
     }
@@ -150,6 +153,7 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
     t.coef64 = reinterpret_cast<double*>(base + kOffCoef64);
     t.global = reinterpret_cast<double*>(base + kOffGlobal);
     t.arrivals = reinterpret_cast<uint32_t*>(base + kOffArrivals);
+    t.ema_before = reinterpret_cast<float*>(base + kOffEmaBefore);
     t.norm = out_norms ? out_norms : reinterpret_cast<float*>(base + kOffNorm);
     t.coef = out_coefs ? out_coefs : reinterpret_cast<float*>(base + kOffCoef);
     t.flag = out_clipped ? out_clipped : reinterpret_cast<uint8_t*>(base + kOffFlag);
@@ -207,9 +211,11 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
     const int grid_norm = (int)(groups > max_grid ? max_grid : groups);
     const int grid_update = (int)(items > max_grid ? max_grid : items);
 
-    if (launch_sumsq_partials(t, bf16g, grid_norm, stream) != hipSuccess) return ADAGC_ERR_HIP;
-    if (launch_rules(t, ema_norms, r, stream) != hipSuccess) return ADAGC_ERR_HIP;
-    if (launch_update(t, u, cfg->optimizer, bf16g, copy, unroll, items_per_chunk, 1, 0, grid_update, stream) != hipSuccess)
+    FusedRule rule{};
+    if (small_tensors && items <= kFusedMaxItems && !r.warmup && r.mode == ADAGC_MODE_ADAGC) rule = FusedRule{ema_norms, r};
+    if (launch_sumsq_partials(t, bf16g, grid_norm, stream, nullptr, 0, rule.ema) != hipSuccess) return ADAGC_ERR_HIP;
+    if (!rule.ema && launch_rules(t, ema_norms, r, stream) != hipSuccess) return ADAGC_ERR_HIP;
+    if (launch_update(t, u, cfg->optimizer, bf16g, copy, unroll, items_per_chunk, 1, 0, grid_update, stream, false, rule) != hipSuccess)
         return ADAGC_ERR_HIP;
     return ADAGC_OK;
 }

@@ -149,3 +149,37 @@ def test_model_wide_rules_on_short_and_long_lists(n, entry):
         np.testing.assert_allclose(gamma.cpu().numpy(), least, rtol=2e-7)
     if ctx:
         ctx.close()
+
+
+@pytest.mark.parametrize("numels", [[64 * 16384, 5], [64 * 16384 + 1, 5], [63 * 16384 + 1, 16385], [1024 * 4096], [1024 * 4096 + 1],
+                                    [4096] * 1024, [4096] * 1025, [1], [1000] * 300 + [17000]], ids=len)
+@pytest.mark.parametrize("optimizer", [B.ADAGC_OPT_ADAMW, B.ADAGC_OPT_LION])
+def test_rule_in_the_update_equals_the_rules_kernel(optimizer, numels):
+    """Small lists evaluate the per-tensor rule in the update kernel, adagc_step_graph always in the rules kernel: the same norms,
+    coefficients, flags and gammas bit for bit on both sides of both limits (64 chunks of a tensor, 1024 work items), and the
+    same step up to the last bit of the bias corrections (the device's pow against the host's), several steps in a row."""
+    gen = torch.Generator(device="cpu").manual_seed(len(numels))
+    g = [(torch.randn(n, generator=gen) * 0.01).to(DEV) for n in numels]
+    lion = optimizer == B.ADAGC_OPT_LION
+    sp = torch.zeros(56, dtype=torch.uint8, device=DEV)
+    results = []
+    for graph in (False, True):
+        p, m, v = ([torch.full_like(x, c) for x in g] for c in (0.02, 0.001, 1e-4))
+        gamma = torch.tensor([(0.005 if i % 2 else 0.02) * n ** 0.5 for i, n in enumerate(numels)], dtype=torch.float32, device=DEV)
+        ctx = B.AdaGC(numels, optimizer)
+        seen = []
+        for step in (5, 6, 7):
+            hp = B.make_hyper(lr=1e-3, t_start=0)
+            if graph:
+                sp.copy_(torch.frombuffer(bytearray(B.step_params_bytes(hp, step)), dtype=torch.uint8))
+                ctx.step_graph(p, g, m, None if lion else v, gamma, sp)
+            else:
+                ctx.step(p, g, m, None if lion else v, gamma, hp, step)
+            seen += list(ctx.get_norms()) + [gamma.cpu().numpy()]
+        ctx.close()
+        results.append((seen, torch.cat(p), torch.cat(m), torch.cat(v)))
+    (a, *sa), (b, *sb) = results
+    for x, y in zip(a, b):
+        assert np.array_equal(x, y)
+    for x, y in zip(sa, sb):
+        assert ((x - y).abs() <= 2e-7 * y.abs()).all()
