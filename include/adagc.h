@@ -332,7 +332,8 @@ int adagc_get_segment_table(adagc_ctx* ctx, int64_t* chunk_begin, uint32_t* chun
  * following adagc_step records four events (before the norm kernel, after it,
  * after the per-tensor finalize, after the fused update).  adagc_profile_end
  * waits for the last recorded step, writes three durations per step in
- * milliseconds (norm, finalize, update) to ms (HOST float[3*max_steps]), the
+ * milliseconds (norm, finalize, update; finalize is next to nothing on small lists, whose rule is part
+ * of the update kernel) to ms (HOST float[3*max_steps]), the
  * number of recorded steps to n_steps, and releases the events.
  */
 int adagc_profile_begin(adagc_ctx* ctx, int32_t max_steps);
