@@ -108,8 +108,8 @@ typedef struct {
                                      norm kernel; a chunk or a part of one in the update kernel) */
     int32_t unroll;               /* 128-bit vectors per lane per array kept in flight by the update kernel:
                                      1, 2 or 4 (default: AdamW 4, Lion 2) */
-    int32_t nontemporal;          /* streaming (non-temporal) loads and stores of the update kernel: 1 = on (default),
-                                     2 = off */
+    int32_t nontemporal;          /* streaming (non-temporal) loads and stores of the update kernel, and of the norm kernel
+                                     on lists with more than 8 GiB of gradients: 1 = on (default), 2 = off */
     int32_t schedule;             /* visiting order of the chunks, see adagc_build_visiting_order: number of
                                      contiguous parts the list is cut into (default 2; 1 = list order) */
     int32_t update_split;         /* work items of the update kernel per chunk: 1 = whole chunks, or 2, 4, ...

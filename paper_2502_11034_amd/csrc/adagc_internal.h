@@ -140,6 +140,10 @@ inline int64_t count_work_items(int64_t n_chunks, int64_t n_long, int64_t n_tiny
     return (n_long + 7) / 8 * 8 * items_per_chunk + (n_chunks - n_long - n_tiny) + (n_tiny + 3) / 4;
 }
 
+// Whether the norm kernel reads the gradients past the memory-side cache: lists of more than 8 GiB of them, 32 times what
+// it holds (figures at the kernel; at 4 and 8 GB the two are within what runs differ by).
+inline bool stream_gradients(int64_t total_elems, bool grad_bf16) { return total_elems > ((int64_t)1 << 33) / (grad_bf16 ? 2 : 4); }
+
 // Small lists evaluate the per-tensor rule (Eq. 3) inside the update kernel, every wave for its own chunk, from the tensor's
 // partial sums and a copy of gamma that the norm kernel makes: one launch less, for one more load per wave.  That pays while
 // the update kernel is only a few rounds of workgroups, and needs tensors whose slots one wave can sum in the rules kernel's
@@ -198,7 +202,7 @@ inline void host_step_scalars(const adagc_hyper& hp, int64_t step, RuleArgs& r, 
 // Launchers (kernels.hip).  Each only enqueues on `stream`.
 // Gradient norms, then the clipping rules.  params: null, or the DEVICE parameters of this step, which are then read instead
 // of r (and from which the norm kernel leaves t.scalars for launch_update).
-hipError_t launch_sumsq_partials(const DeviceTables& t, int grad_bf16, int grid, hipStream_t stream,
+hipError_t launch_sumsq_partials(const DeviceTables& t, int grad_bf16, bool streaming, int grid, hipStream_t stream,
                                  const adagc_step_params* params = nullptr, int optimizer = 0, const float* ema_to_keep = nullptr);
 hipError_t launch_rules(const DeviceTables& t, float* ema, const RuleArgs& r, hipStream_t stream,
                         const adagc_step_params* params = nullptr, int optimizer = 0);

@@ -21,6 +21,7 @@ struct adagc_ctx {
     int          unroll = 0;
     int          nontemporal = 0;
     int          items_per_chunk = 1;   // work items of the update kernel per chunk
+    bool         stream_grads = false;  // the norm kernel reads past the memory-side cache
     bool         small_list = false;    // the per-tensor rule goes into the update kernel (FusedRule)
 
     std::vector<int64_t>    numel;
@@ -207,11 +208,13 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
         if (want > items) want = items;
         return (int)(want > kMaxGridBlocks ? kMaxGridBlocks : want);
     };
-    int64_t most_chunks = 0;
+    int64_t most_chunks = 0, total_elems = 0;
     for (int64_t i = 0; i < n_tensors; ++i) {
         const int64_t n = c->chunk_begin[(size_t)i + 1] - c->chunk_begin[(size_t)i];
         if (n > most_chunks) most_chunks = n;
+        total_elems += descs[i].numel;
     }
+    c->stream_grads = c->nontemporal && stream_gradients(total_elems, cfg->grad_dtype == ADAGC_GRAD_BF16);
     c->small_list = tiles <= kFusedMaxItems && most_chunks <= kFusedMaxChunks;
     c->grid_norm = grid_for(c->n_chunks - n_tiny + (n_tiny + 3) / 4);
     c->grid_update = grid_for(tiles);
@@ -429,7 +432,7 @@ extern "C" int adagc_step(adagc_ctx* ctx, void* const* params, const void* const
             return ADAGC_ERR_HIP;
     } else {
         if (ctx->small_list && !r.warmup && r.mode == ADAGC_MODE_ADAGC) rule = FusedRule{ema_norms, r};
-        if (launch_sumsq_partials(ctx->tables, bf16g, ctx->grid_norm, stream, nullptr, 0, rule.ema) != hipSuccess) return ADAGC_ERR_HIP;
+        if (launch_sumsq_partials(ctx->tables, bf16g, ctx->stream_grads, ctx->grid_norm, stream, nullptr, 0, rule.ema) != hipSuccess) return ADAGC_ERR_HIP;
         if (prof && hipEventRecord(ev[1], stream) != hipSuccess) return ADAGC_ERR_HIP;
         if (!rule.ema && launch_rules(ctx->tables, ema_norms, r, stream) != hipSuccess) return ADAGC_ERR_HIP;
         if (prof && hipEventRecord(ev[2], stream) != hipSuccess) return ADAGC_ERR_HIP;
@@ -466,7 +469,7 @@ extern "C" int adagc_step_graph(adagc_ctx* ctx, void* const* params, const void*
     hipEvent_t* ev = prof ? &ctx->prof_events[(size_t)ctx->prof_steps * 4] : nullptr;
     ctx->device_scalars_used = true;
     if (prof && hipEventRecord(ev[0], stream) != hipSuccess) return ADAGC_ERR_HIP;
-    if (launch_sumsq_partials(ctx->tables, bf16g, ctx->grid_norm, stream, step_params, ctx->cfg.optimizer) != hipSuccess)
+    if (launch_sumsq_partials(ctx->tables, bf16g, ctx->stream_grads, ctx->grid_norm, stream, step_params, ctx->cfg.optimizer) != hipSuccess)
         return ADAGC_ERR_HIP;
     if (prof && hipEventRecord(ev[1], stream) != hipSuccess) return ADAGC_ERR_HIP;
     if (launch_rules(ctx->tables, ema_norms, RuleArgs{}, stream, step_params, ctx->cfg.optimizer) != hipSuccess)
@@ -635,7 +638,7 @@ extern "C" int adagc_muon_step(adagc_ctx* ctx, void* const* params, const void* 
 
     // gradient norms and clip coefficients: the kernels of adagc_step
     if (prof && hipEventRecord(ev[0], stream) != hipSuccess) return ADAGC_ERR_HIP;
-    if (launch_sumsq_partials(t, bf16g, ctx->grid_norm, stream) != hipSuccess) return ADAGC_ERR_HIP;
+    if (launch_sumsq_partials(t, bf16g, ctx->stream_grads, ctx->grid_norm, stream) != hipSuccess) return ADAGC_ERR_HIP;
     if (prof && hipEventRecord(ev[1], stream) != hipSuccess) return ADAGC_ERR_HIP;
     if (launch_rules(t, ema_norms, r, stream) != hipSuccess) return ADAGC_ERR_HIP;
     if (prof && hipEventRecord(ev[2], stream) != hipSuccess) return ADAGC_ERR_HIP;

@@ -169,12 +169,13 @@ __device__ __forceinline__ void tiny_chunk_sumsq(const DeviceTables& t, const Wo
     if (lane == 0) t.partials[w.slot] = s;
 }
 
-// The loads are ordinary ones: streaming loads leave nothing in the 256 MB memory-side cache, and the update kernel reads the
-// same gradients next.  GPT-2-small shapes (498 MB of gradients): 657 us per step with streaming loads, 622 without; 266 MB of
-// bf16 gradients 680, 635; lists of many GB do not care (this kernel alone then reads 7.2 TB/s either way).
+// NTL: streaming loads, for lists whose gradients are many times the 256 MB of the memory-side cache (stream_gradients).  On
+// smaller ones they would leave nothing in it for the update kernel, which reads the same gradients next: GPT-2-small shapes
+// (498 MB of gradients) 657 us per step with streaming loads, 622 without; 266 MB of bf16 gradients 680, 635; 1.6 GB 2.33, 2.26
+// ms.  On 32 GB ordinary loads only cost this kernel time: 4.45 ms streaming, 5.0 ordinary.
 // params: null, or the device-resident parameters of this step, from which one lane makes the update kernel's scalars.
 // ema_to_keep: null, or the gammas that the update kernel will need as they are now (see FusedRule).
-template <bool BF16>
+template <bool BF16, bool NTL>
 __global__ __launch_bounds__(kBlock) void sumsq_partials_kernel(DeviceTables t, const adagc_step_params* params, int optimizer,
                                                                 const float* ema_to_keep)
 {
@@ -204,7 +205,7 @@ __global__ __launch_bounds__(kBlock) void sumsq_partials_kernel(DeviceTables t, 
             if (len == kChunkElems) {
                 f32x4 r[kVecPerLane];
 #pragma unroll
-                for (int u = 0; u < kVecPerLane; ++u) r[u] = load_grad4<BF16, false>(g, u * kBlock + tid);
+                for (int u = 0; u < kVecPerLane; ++u) r[u] = load_grad4<BF16, NTL>(g, u * kBlock + tid);
 #pragma unroll
                 for (int u = 0; u < kVecPerLane; ++u) acc4(acc, r[u]);
             } else {
@@ -218,7 +219,7 @@ __global__ __launch_bounds__(kBlock) void sumsq_partials_kernel(DeviceTables t, 
 #pragma unroll
                     for (int u = 0; u < kFlight; ++u) {
                         const int v = v0 + u * kBlock + tid;
-                        r[u] = v < nvec ? load_grad4<BF16, false>(g, v) : f32x4{0.f, 0.f, 0.f, 0.f};
+                        r[u] = v < nvec ? load_grad4<BF16, NTL>(g, v) : f32x4{0.f, 0.f, 0.f, 0.f};
                     }
 #pragma unroll
                     for (int u = 0; u < kFlight; ++u) acc4(acc, r[u]);
@@ -1034,11 +1035,14 @@ UpdateFn select_update(int optimizer, int grad_bf16, int with_copy, int unroll, 
 
 }  // namespace
 
-hipError_t launch_sumsq_partials(const DeviceTables& t, int grad_bf16, int grid, hipStream_t stream, const adagc_step_params* params,
-                                 int optimizer, const float* ema_to_keep)
+using NormFn = void (*)(DeviceTables, const adagc_step_params*, int, const float*);
+
+hipError_t launch_sumsq_partials(const DeviceTables& t, int grad_bf16, bool streaming, int grid, hipStream_t stream,
+                                 const adagc_step_params* params, int optimizer, const float* ema_to_keep)
 {
-    if (grad_bf16) sumsq_partials_kernel<true><<<dim3(grid), dim3(kBlock), 0, stream>>>(t, params, optimizer, ema_to_keep);
-    else sumsq_partials_kernel<false><<<dim3(grid), dim3(kBlock), 0, stream>>>(t, params, optimizer, ema_to_keep);
+    const NormFn fn = grad_bf16 ? (streaming ? sumsq_partials_kernel<true, true> : sumsq_partials_kernel<true, false>)
+                                : (streaming ? sumsq_partials_kernel<false, true> : sumsq_partials_kernel<false, false>);
+    fn<<<dim3(grid), dim3(kBlock), 0, stream>>>(t, params, optimizer, ema_to_keep);
     return hipGetLastError();
 }
 

@@ -123,6 +123,7 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
     const int unroll = default_unroll(cfg->optimizer), items_per_chunk = default_items(unroll);
     uint64_t n_chunks = 0, n_long = 0, n_tiny = 0;
     bool small_tensors = true;
+    int64_t total_elems = 0;
     // the kind of tensor i's last chunk (all others are long)
     auto last_kind = [&](int64_t i) { return chunk_kind((descs[i].numel - 1) % kChunkElems + 1, items_per_chunk, unroll); };
     for (int64_t i = 0; i < n_tensors; ++i) {
@@ -132,6 +133,7 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
         n_chunks += (uint64_t)((descs[i].numel + kChunkElems - 1) / kChunkElems);
         if (n_chunks > (uint64_t)kMaxC) return ADAGC_ERR_TOO_LARGE;
         if (descs[i].numel > kFusedMaxChunks * kChunkElems) small_tensors = false;
+        total_elems += descs[i].numel;
         n_long += (uint64_t)((descs[i].numel - 1) / kChunkElems) + (last_kind(i) == kLongChunk ? 1 : 0);
         n_tiny += last_kind(i) == kTinyChunk ? 1 : 0;
     }
@@ -213,7 +215,7 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
 
     FusedRule rule{};
     if (small_tensors && items <= kFusedMaxItems && !r.warmup && r.mode == ADAGC_MODE_ADAGC) rule = FusedRule{ema_norms, r};
-    if (launch_sumsq_partials(t, bf16g, grid_norm, stream, nullptr, 0, rule.ema) != hipSuccess) return ADAGC_ERR_HIP;
+    if (launch_sumsq_partials(t, bf16g, stream_gradients(total_elems, bf16g), grid_norm, stream, nullptr, 0, rule.ema) != hipSuccess) return ADAGC_ERR_HIP;
     if (!rule.ema && launch_rules(t, ema_norms, r, stream) != hipSuccess) return ADAGC_ERR_HIP;
     if (launch_update(t, u, cfg->optimizer, bf16g, copy, unroll, items_per_chunk, 1, 0, grid_update, stream, false, rule) != hipSuccess)
         return ADAGC_ERR_HIP;
