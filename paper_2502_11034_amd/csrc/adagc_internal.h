@@ -92,7 +92,7 @@ struct DeviceTables {
     const TensorArgs* targs;
     double*           partials;   // one per chunk
     double*           sumsq;      // one per tensor
-    uint32_t*         arrivals;   // tensors whose sum is stored (model-wide rules); zero before and after every launch
+    uint32_t*         arrivals;   // tensors whose sum is stored (model-wide rules); cleared by the norm kernel
     double*           global;     // [0] = model's sum of squares, [1] = its coefficient, [2] = 1 if clipped
     float*            norm;       // per tensor, pre-clip
     float*            coef;       // per tensor, fp32 (reported to the caller)

@@ -175,13 +175,17 @@ __device__ __forceinline__ void tiny_chunk_sumsq(const DeviceTables& t, const Wo
 // ms.  On 32 GB ordinary loads only cost this kernel time: 4.45 ms streaming, 5.0 ordinary.
 // params: null, or the device-resident parameters of this step, from which one lane makes the update kernel's scalars.
 // ema_to_keep: null, or the gammas that the update kernel will need as they are now (see FusedRule).
+// One lane also clears the arrival count of the rules kernel.
 template <bool BF16, bool NTL>
 __global__ __launch_bounds__(kBlock) void sumsq_partials_kernel(DeviceTables t, const adagc_step_params* params, int optimizer,
                                                                 const float* ema_to_keep)
 {
     __shared__ double wave_sums[kWavesPerBlock];
     const int tid = threadIdx.x;
-    if (params && blockIdx.x == gridDim.x - 1 && tid == 0) prepare_update_scalars(t, params, optimizer);
+    if (blockIdx.x == gridDim.x - 1 && tid == 0) {
+        *t.arrivals = 0u;                      // the rules kernel comes next on the stream
+        if (params) prepare_update_scalars(t, params, optimizer);
+    }
 
     const uint32_t n_wide = t.n_chunks - t.n_tiny, n_groups = n_wide + (t.n_tiny + 3u) / 4u;
     for (uint32_t k = blockIdx.x; k < n_groups; k += gridDim.x) {
@@ -292,12 +296,12 @@ __device__ __forceinline__ void store_shared(T* p, T v)
 }
 
 // One lane: count this workgroup in; true for the last of `total`, which finds everything the others stored before they
-// counted themselves, and leaves the counter at zero for the next launch.
+// counted themselves.  The counter starts a step at zero because the norm kernel clears it: steps that overlapped by mistake
+// leave it at any value, and that must not reach a later one.
 __device__ __forceinline__ bool arrive_last(uint32_t* counter, uint32_t total)
 {
     if (__hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT) != total - 1u) return false;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    store_shared(counter, 0u);
     return true;
 }
 

@@ -65,21 +65,17 @@ struct TensorBatch {
     uint32_t   first;    // list index of t[0]
     uint32_t   count;
 };
-static_assert(sizeof(TensorBatch) + 4 * sizeof(void*) <= 4096, "a batch fits the kernel-argument block");
+static_assert(sizeof(TensorBatch) + 3 * sizeof(void*) <= 4096, "a batch fits the kernel-argument block");
 
-// Workgroup b stores the record of tensor first+b and writes that tensor's rows of the work table; the list's first also clears
-// the arrival count of the rules.
-__global__ __launch_bounds__(kBlock) void store_tensor_batch_kernel(TensorBatch batch, TensorArgs* targs, WorkRef* work, uint32_t* arrivals,
+// Workgroup b stores the record of tensor first+b and writes that tensor's rows of the work table.
+__global__ __launch_bounds__(kBlock) void store_tensor_batch_kernel(TensorBatch batch, TensorArgs* targs, WorkRef* work,
                                                                     int items_per_chunk, int unroll)
 {
     const uint32_t b = blockIdx.x;
     if (b >= batch.count) return;
     const TensorArgs a = batch.t[b];
     const uint32_t i = batch.first + b;
-    if (threadIdx.x == 0) {
-        targs[i] = a;
-        if (i == 0) *arrivals = 0u;
-    }
+    if (threadIdx.x == 0) targs[i] = a;
     const uint32_t last = a.chunk_count - 1;
     const int64_t last_len = a.numel - (int64_t)last * kChunkElems;
     const bool last_is_long = chunk_kind(last_len, items_per_chunk, unroll) == kLongChunk;
@@ -200,7 +196,7 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
         }
         batch.first = (uint32_t)first;
         batch.count = (uint32_t)count;
-        store_tensor_batch_kernel<<<dim3((uint32_t)count), dim3(kBlock), 0, stream>>>(batch, d_targs, d_work, t.arrivals, items_per_chunk, unroll);
+        store_tensor_batch_kernel<<<dim3((uint32_t)count), dim3(kBlock), 0, stream>>>(batch, d_targs, d_work, items_per_chunk, unroll);
         if (hipGetLastError() != hipSuccess) return ADAGC_ERR_HIP;
     }
 

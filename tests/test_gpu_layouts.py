@@ -151,6 +151,41 @@ def test_model_wide_rules_on_short_and_long_lists(n, entry):
         ctx.close()
 
 
+def test_steps_that_overlap_leave_nothing_behind():
+    """Steps of one context share its scratch and have to be ordered by the caller.  Where that is missed the overlapping steps'
+    own results mean nothing, but the next properly ordered step must be right again: the count by which the rules kernel finds
+    its last workgroup starts every step at zero, whatever value it was left at."""
+    n = 512
+    rng = np.random.default_rng(4)
+    numels = [int(x) for x in rng.integers(1, 3000, n)]
+    state = lambda: [[torch.zeros(k, device=DEV) for k in numels] for _ in range(3)]
+    g = [torch.from_numpy(rng.standard_normal(k).astype(np.float32)).to(DEV) for k in numels]
+    norms = np.array([float(x.double().norm()) for x in g])
+    model = float(np.sqrt((norms ** 2).sum()))
+    gamma = torch.ones(n, device=DEV)
+    ctx = B.AdaGC(numels)
+    p, m, v = state()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    lists = [B.ptr_array(x) for x in (p, g, m, v)]
+    hp = B.make_hyper(t_start=0, lambda_abs=0.5 * model, clip_mode=B.ADAGC_MODE_GLOBALGC)
+    ctx.step(*lists, gamma, hp, 2)               # the pointer table is uploaded once, before the steps that overlap
+    torch.cuda.synchronize()
+    for _ in range(50):
+        for s in streams:
+            ctx.step(*lists, gamma, hp, 2, stream=s.cuda_stream)
+    torch.cuda.synchronize()
+    for k, part in enumerate((0.25, 2.0, 0.125)):
+        p, m, v = state()
+        hp = B.make_hyper(t_start=0, lambda_abs=part * model, clip_mode=B.ADAGC_MODE_GLOBALGC)
+        ctx.step(p, g, m, v, gamma, hp, 3 + k)
+        got = ctx.get_norms()
+        h = min(1.0, float(np.float32(part * model)) / model)
+        np.testing.assert_allclose(got[0], norms, rtol=2e-7)
+        np.testing.assert_allclose(got[1], np.full(n, h), rtol=2e-7)
+        assert (got[2] == (1 if h < 1.0 else 0)).all()
+    ctx.close()
+
+
 @pytest.mark.parametrize("numels", [[64 * 16384, 5], [64 * 16384 + 1, 5], [63 * 16384 + 1, 16385], [1024 * 4096], [1024 * 4096 + 1],
                                     [4096] * 1024, [4096] * 1025, [1], [1000] * 300 + [17000]], ids=len)
 @pytest.mark.parametrize("optimizer", [B.ADAGC_OPT_ADAMW, B.ADAGC_OPT_LION])
