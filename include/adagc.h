@@ -113,7 +113,8 @@ typedef struct {
     int32_t schedule;             /* visiting order of the chunks, see adagc_build_visiting_order: number of
                                      contiguous parts the list is cut into (default 2; 1 = list order) */
     int32_t update_split;         /* work items of the update kernel per chunk: 1 = whole chunks, or 2, 4, ...
-                                     up to chunk_elems / (unroll*1024).  Default (0): 4096-element items
+                                     up to chunk_elems / (unroll*1024), chunk_elems / 4096 where unroll
+                                     is 0.  Default (0): 4096-element items
                                      for AdamW, 2048 for Lion
                                      (small items shorten the tail of the launch and give short lists more
                                      workgroups; whole chunks cost the fewest dispatches) */

@@ -136,7 +136,10 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
         return ADAGC_ERR_INVALID_ARG;
     if (cfg->unroll != 0 && cfg->unroll != 1 && cfg->unroll != 2 && cfg->unroll != 4) return ADAGC_ERR_INVALID_ARG;
     {
-        const int tiles = kVecPerLane / (cfg->unroll ? cfg->unroll : default_unroll(cfg->optimizer));       // unroll*1024-element tiles per chunk
+        // unroll*1024-element tiles per chunk, 4096-element ones where the caller leaves unroll to the library (whose own choice
+        // depends on the optimizer and may change; it divides 4, so every such split is whole tiles)
+        const int tiles = kVecPerLane / (cfg->unroll ? cfg->unroll : 4);
+        static_assert(4 % default_unroll(ADAGC_OPT_ADAMW) == 0 && 4 % default_unroll(ADAGC_OPT_LION) == 0, "see above");
         const int sp = cfg->update_split;
         if (sp < 0 || sp > tiles || (sp & (sp - 1)) != 0) return ADAGC_ERR_INVALID_ARG;
     }

@@ -67,6 +67,10 @@ def test_create_validates_before_touching_the_device():
     assert _create([4], update_split=3)[0] == B.ADAGC_ERR_INVALID_ARG
     assert _create([4], update_split=8)[0] == B.ADAGC_ERR_INVALID_ARG      # more than 16384 / (4*1024)
     assert _create([4], update_split=16, unroll=2)[0] == B.ADAGC_ERR_INVALID_ARG
+    assert _create([4], optimizer=B.ADAGC_OPT_LION, update_split=8)[0] == B.ADAGC_ERR_INVALID_ARG      # the same limit for Lion
+    rc, ctx = _create([4], optimizer=B.ADAGC_OPT_LION, update_split=8, unroll=2)
+    assert rc != B.ADAGC_ERR_INVALID_ARG
+    L.adagc_destroy(ctx)
     assert _create([4], schedule_run=-1)[0] == B.ADAGC_ERR_INVALID_ARG
     cfg = B.adagc_config()
     assert L.adagc_create(None, None, 1, ctypes.byref(cfg)) == B.ADAGC_ERR_INVALID_ARG
