@@ -36,6 +36,8 @@ def build(force=True, verbose=False, extra_flags=(), out=None):
            # packed-fp32 code generation is switched off on purpose (known-bad forms on this part)
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
            "-Wall", "-Wextra", "-Wno-unused-parameter",
+           # an access that claims more alignment than its address has: tensors may start anywhere
+           "-Werror=align-mismatch",
            "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, "-x", "hip"]
     cmd += list(extra_flags)
     cmd += [os.path.join(CSRC, s) for s in SOURCES]

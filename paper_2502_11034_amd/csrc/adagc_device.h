@@ -24,11 +24,15 @@ typedef uint64_t u64x8 __attribute__((ext_vector_type(8)));
 typedef float    f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
 
-typedef ADAGC_GLOBAL float*          gfloat;
-typedef const ADAGC_GLOBAL float*    gcfloat;
-typedef ADAGC_GLOBAL uint16_t*       gu16;
-typedef const ADAGC_GLOBAL uint16_t* gcu16;
-typedef const ADAGC_GLOBAL char*     gcbytes;
+// Single elements, at any address at all: what the element-by-element path reads and writes.
+typedef float    f32_any __attribute__((aligned(1)));
+typedef uint16_t u16_any __attribute__((aligned(1)));
+
+typedef ADAGC_GLOBAL f32_any*       gfloat;
+typedef const ADAGC_GLOBAL f32_any* gcfloat;
+typedef ADAGC_GLOBAL u16_any*       gu16;
+typedef const ADAGC_GLOBAL u16_any* gcu16;
+typedef const ADAGC_GLOBAL char*    gcbytes;
 
 // Something that is the same for the whole workgroup and does not change while the kernel runs, through the scalar unit.
 // Loads of this kind that do not depend on each other are on their way together.
@@ -68,15 +72,31 @@ static_assert(offsetof(TensorArgs, grad) == 8 && offsetof(TensorArgs, exp_avg) =
                   offsetof(TensorArgs, chunk_count) == 52 && offsetof(TensorArgs, vec_ok) == 56,
               "load_tensor takes the record apart by hand");
 
-template <bool NT, typename T>
-__device__ __forceinline__ T ld(const ADAGC_GLOBAL T* p)
+// Not templates of the vector's type: a deduced type is the vector without its typedef's alignment, and the access would claim
+// the full one.
+template <bool NT>
+__device__ __forceinline__ f32x4 ld(const ADAGC_GLOBAL f32x4_any* p)
 {
     if constexpr (NT) return __builtin_nontemporal_load(p);
     else return *p;
 }
 
-template <bool NT, typename T>
-__device__ __forceinline__ void st(ADAGC_GLOBAL T* p, std::common_type_t<T> v)
+template <bool NT>
+__device__ __forceinline__ u32x2 ld(const ADAGC_GLOBAL u32x2_any* p)
+{
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+
+template <bool NT>
+__device__ __forceinline__ void st(ADAGC_GLOBAL f32x4_any* p, f32x4 v)
+{
+    if constexpr (NT) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+
+template <bool NT>
+__device__ __forceinline__ void st(ADAGC_GLOBAL u32x2_any* p, u32x2 v)
 {
     if constexpr (NT) __builtin_nontemporal_store(v, p);
     else *p = v;
