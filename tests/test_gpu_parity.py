@@ -194,8 +194,8 @@ def test_infinite_lambda_rel_is_plain_adamw():
         np.testing.assert_allclose(to_numpy(p), to_numpy(q), rtol=2e-5, atol=2e-7)
 
 
-def test_unaligned_pointers_take_the_scalar_path():
-    """Views that start 1 element into a buffer are 4-byte aligned only."""
+def test_pointers_aligned_to_their_elements_only():
+    """Views that start 1 element into a buffer are 4-byte aligned only (2-byte: the copies), which vector accesses take."""
     rng = np.random.default_rng(2)
     numels = [5, 1000, 16384 + 7, 40000]
     hp = B.make_hyper(t_start=0)
