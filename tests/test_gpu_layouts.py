@@ -114,7 +114,7 @@ def test_update_clipping_with_every_size_of_work_item(optimizer, split, unroll):
 def test_model_wide_rules_on_short_and_long_lists(n, entry):
     """Up to 512 tensors the last workgroup of the rules kernel evaluates a model-wide rule, beyond that a kernel of its own:
     the warm-up branch, the model's coefficient and its running minimum, and GlobalGC, on both sides of that line, several steps
-    in a row (the count has to be zero again after each)."""
+    in a row (the count starts each at zero)."""
     rng = np.random.default_rng(n)
     numels = [int(x) for x in rng.integers(1, 40, n)]
     numels[-1] = 50000
@@ -186,35 +186,52 @@ def test_steps_that_overlap_leave_nothing_behind():
     ctx.close()
 
 
-@pytest.mark.parametrize("numels", [[64 * 16384, 5], [64 * 16384 + 1, 5], [63 * 16384 + 1, 16385], [1024 * 4096], [1024 * 4096 + 1],
-                                    [4096] * 1024, [4096] * 1025, [1], [1000] * 300 + [17000]], ids=len)
+# The rule's two limits, 64 chunks of a tensor and 1024 work items (4096 elements each with AdamW, 2048 with Lion): at them and one
+# beyond, in whole chunks and in short ones.
+FUSED = {"64_chunks": [64 * 16384, 5], "65_chunks": [64 * 16384 + 1, 5], "ragged_64th": [63 * 16384 + 1, 16385],
+         "1024_long_adamw": [64 * 16384] * 4, "1025_long_adamw": [64 * 16384] * 4 + [1],
+         "1024_long_lion": [64 * 16384] * 2, "1025_long_lion": [64 * 16384] * 2 + [1],
+         "1024_short_adamw": [4096] * 1024, "1025_short_adamw": [4096] * 1025,
+         "1024_short_lion": [2048] * 1024, "1025_short_lion": [2048] * 1025, "one": [1], "tiny_and_long": [1000] * 300 + [17000]}
+
+
+@pytest.mark.parametrize("numels", FUSED.values(), ids=FUSED.keys())
 @pytest.mark.parametrize("optimizer", [B.ADAGC_OPT_ADAMW, B.ADAGC_OPT_LION])
 def test_rule_in_the_update_equals_the_rules_kernel(optimizer, numels):
-    """Small lists evaluate the per-tensor rule in the update kernel, adagc_step_graph always in the rules kernel: the same norms,
-    coefficients, flags and gammas bit for bit on both sides of both limits (64 chunks of a tensor, 1024 work items), and the
-    same step up to the last bit of the bias corrections (the device's pow against the host's), several steps in a row."""
+    """Small lists evaluate the per-tensor rule in the update kernel (adagc_step and adagc_step_static, each by its own look at the
+    list), adagc_step_graph always in the rules kernel: the same norms, coefficients, flags and gammas bit for bit on both sides
+    of both limits, and the same step up to the last bit of the bias corrections (the device's pow against the host's), several
+    steps in a row."""
     gen = torch.Generator(device="cpu").manual_seed(len(numels))
     g = [(torch.randn(n, generator=gen) * 0.01).to(DEV) for n in numels]
     lion = optimizer == B.ADAGC_OPT_LION
     sp = torch.zeros(56, dtype=torch.uint8, device=DEV)
     results = []
-    for graph in (False, True):
+    for entry in ("graph", "step", "static"):
         p, m, v = ([torch.full_like(x, c) for x in g] for c in (0.02, 0.001, 1e-4))
+        state = (p, g, m, None if lion else v)
         gamma = torch.tensor([(0.005 if i % 2 else 0.02) * n ** 0.5 for i, n in enumerate(numels)], dtype=torch.float32, device=DEV)
-        ctx = B.AdaGC(numels, optimizer)
+        outs = [torch.zeros(len(numels), dtype=t, device=DEV) for t in (torch.float32, torch.float32, torch.uint8)]
+        ctx = None if entry == "static" else B.AdaGC(numels, optimizer)
         seen = []
         for step in (5, 6, 7):
             hp = B.make_hyper(lr=1e-3, t_start=0)
-            if graph:
+            if entry == "graph":
                 sp.copy_(torch.frombuffer(bytearray(B.step_params_bytes(hp, step)), dtype=torch.uint8))
-                ctx.step_graph(p, g, m, None if lion else v, gamma, sp)
+                ctx.step_graph(*state, gamma, sp)
+            elif entry == "step":
+                ctx.step(*state, gamma, hp, step)
             else:
-                ctx.step(p, g, m, None if lion else v, gamma, hp, step)
-            seen += list(ctx.get_norms()) + [gamma.cpu().numpy()]
-        ctx.close()
+                B.adagc_step_static(numels, *state, gamma, hp, step, optimizer=optimizer, out_norms=outs[0], out_coefs=outs[1],
+                                    out_clipped=outs[2])
+            seen += list(ctx.get_norms()) if ctx else [x.cpu().numpy() for x in outs]
+            seen.append(gamma.cpu().numpy())
+        if ctx:
+            ctx.close()
         results.append((seen, torch.cat(p), torch.cat(m), torch.cat(v)))
-    (a, *sa), (b, *sb) = results
-    for x, y in zip(a, b):
-        assert np.array_equal(x, y)
-    for x, y in zip(sa, sb):
-        assert ((x - y).abs() <= 2e-7 * y.abs()).all()
+    a, *sa = results[0]
+    for b, *sb in results[1:]:
+        for x, y in zip(a, b):
+            assert np.array_equal(x, y)
+        for x, y in zip(sa, sb):
+            assert ((x - y).abs() <= 2e-7 * y.abs()).all()
