@@ -43,6 +43,7 @@ struct adagc_ctx {
     size_t       results_at = 0;              // their place in the slab: norm, coef, flag, and with telemetry the three norms
     size_t       coef_at = 0, flag_at = 0, tele_at = 0;      // relative to the first
     size_t       results_bytes = 0;
+    int32_t*     readback_status = nullptr;   // pinned, after the results: the status word of a step with device scalars
     hipEvent_t   upload_done[kStagingSlots] = {nullptr, nullptr, nullptr, nullptr};
     bool         upload_pending[kStagingSlots] = {false, false, false, false};
     uint64_t     uploads = 0;                 // tables uploaded so far; slot = uploads % kStagingSlots
@@ -284,11 +285,13 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
         }
     }
     const size_t staging_bytes = adagc_ctx::kStagingSlots * nt * sizeof(TensorArgs);
-    if (hipHostMalloc(reinterpret_cast<void**>(&c->staging), staging_bytes + c->results_bytes, hipHostMallocDefault) != hipSuccess) {
+    const size_t status_at = staging_bytes + align_up(c->results_bytes, 64);
+    if (hipHostMalloc(reinterpret_cast<void**>(&c->staging), status_at + sizeof(int32_t), hipHostMallocDefault) != hipSuccess) {
         free_ctx(c);
         return ADAGC_ERR_HIP;
     }
     c->readback = reinterpret_cast<char*>(c->staging) + staging_bytes;
+    c->readback_status = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(c->staging) + status_at);
     for (hipEvent_t& ev : c->upload_done)
         if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
             free_ctx(c);
@@ -703,18 +706,18 @@ namespace {
 
 // The result arrays from byte `from` up to byte `to` (relative to the first) into the read-back area, in one copy to pinned
 // memory: a copy to pageable memory waits for the GPU by itself, so that three of them waited three times (GPT-2-small step with
-// both read-backs 729 us; now 673.  27 tensors 113, 46).  After adagc_step_graph also the status word the
-// device wrote for that step.
+// both read-backs 729 us; now 673.  27 tensors 113, 46).  After adagc_step_graph also the status word that the device wrote for
+// that step, to pinned memory as well.
 int read_back(adagc_ctx* ctx, size_t from, size_t to, hipStream_t stream)
 {
     const char* src = static_cast<const char*>(ctx->slab) + ctx->results_at;
-    int32_t status = 0;
     if (hipMemcpyAsync(ctx->readback + from, src + from, to - from, hipMemcpyDeviceToHost, stream) != hipSuccess) return ADAGC_ERR_HIP;
-    if (ctx->device_scalars_used &&
-        hipMemcpyAsync(&status, &ctx->tables.scalars->status, sizeof(status), hipMemcpyDeviceToHost, stream) != hipSuccess)
+    const bool status = ctx->device_scalars_used;
+    if (status && hipMemcpyAsync(ctx->readback_status, &ctx->tables.scalars->status, sizeof(int32_t), hipMemcpyDeviceToHost,
+                                 stream) != hipSuccess)
         return ADAGC_ERR_HIP;
     if (hipStreamSynchronize(stream) != hipSuccess) return ADAGC_ERR_HIP;
-    return status == 0 ? ADAGC_OK : ADAGC_ERR_INVALID_ARG;
+    return !status || *ctx->readback_status == 0 ? ADAGC_OK : ADAGC_ERR_INVALID_ARG;
 }
 
 }  // namespace
