@@ -435,14 +435,16 @@ __device__ __forceinline__ void take_global_coefficient(const DeviceTables& t, f
 __device__ __host__ __forceinline__ bool model_wide(const RuleArgs& r) { return r.warmup || r.mode != ADAGC_MODE_ADAGC; }
 
 // K2, one workgroup per tensor.  Per-tensor rule: workgroup i evaluates it.  Model-wide rules on lists of up to kFewTensors
-// tensors: the workgroup that stores the last tensor's sum evaluates the rule and hands the coefficient to every tensor.  As
-// three kernels that took 14 us of launches on 148 tensors (GPT-2-small's warm-up step 763 -> 733 us), and with the scalars
-// in device memory, six kernels instead of three, 44.6 us per step on 4 M parameters (now 39.8).  Counting in costs 14 ns a
-// tensor, on one address: 5000 tensors 187 us per step against 164 with the two kernels after this one, which longer lists
-// therefore keep.
-// (The release finds the L2 clean here, where next to nothing is written.  Counted in the norm kernel, one release per chunk,
-// it cost half as much again as the whole step.)
-constexpr uint32_t kFewTensors = 512;
+// tensors: the workgroup that stores the last tensor's sum evaluates the rule and hands the coefficient to every tensor, which
+// saves two launches and costs the counting, 14 ns a tensor on one address (the release finds the L2 clean here, where next to
+// nothing is written; counted in the norm kernel, one release per chunk, it cost half as much again as the whole step).
+// us per step with GlobalGC, counted / in two more kernels, tensors of 1000 elements and of 65 536:
+//   step         64 tensors 11.9 / 15.2 and 30.2 / 32.7   192: 14.8 / 15.5 and 74.5 / 75.0   256: 15.9 / 15.1 and 93.2 / 91.2
+//                512: 20.3 / 15.7 and 173.8 / 169.1
+//   graph replay 64 tensors 13.3 / 14.5 and 31.1 / 32.4   192: 15.8 / 14.8 and 75.2 / 76.3   256: 17.4 / 15.0 and 94.2 / 92.7
+//                512: 21.3 / 16.1 and 174.6 / 170.7
+// (Where a slow host's launches are what a step waits for, counting is ahead up to 300 tensors.)
+constexpr uint32_t kFewTensors = 192;
 
 __global__ __launch_bounds__(kBlock) void rules_kernel(DeviceTables t, float* ema, RuleArgs r, const adagc_step_params* params,
                                                        int optimizer)

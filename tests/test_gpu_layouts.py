@@ -110,9 +110,9 @@ def test_update_clipping_with_every_size_of_work_item(optimizer, split, unroll):
 
 
 @pytest.mark.parametrize("entry", ["step", "graph", "static"])
-@pytest.mark.parametrize("n", [1, 2, 511, 512, 513, 1700])
+@pytest.mark.parametrize("n", [1, 2, 191, 192, 193, 511, 512, 513, 1700])
 def test_model_wide_rules_on_short_and_long_lists(n, entry):
-    """Up to 512 tensors the last workgroup of the rules kernel evaluates a model-wide rule, beyond that a kernel of its own:
+    """Up to 192 tensors the last workgroup of the rules kernel evaluates a model-wide rule, beyond that a kernel of its own:
     the warm-up branch, the model's coefficient and its running minimum, and GlobalGC, on both sides of that line, several steps
     in a row (the count starts each at zero)."""
     rng = np.random.default_rng(n)
@@ -155,7 +155,7 @@ def test_steps_that_overlap_leave_nothing_behind():
     """Steps of one context share its scratch and have to be ordered by the caller.  Where that is missed the overlapping steps'
     own results mean nothing, but the next properly ordered step must be right again: the count by which the rules kernel finds
     its last workgroup starts every step at zero, whatever value it was left at."""
-    n = 512
+    n = 192
     rng = np.random.default_rng(4)
     numels = [int(x) for x in rng.integers(1, 3000, n)]
     state = lambda: [[torch.zeros(k, device=DEV) for k in numels] for _ in range(3)]
