@@ -141,13 +141,16 @@ inline int64_t count_work_items(int64_t n_chunks, int64_t n_long, int64_t n_tiny
 }
 
 // Whether the norm kernel reads the gradients past the memory-side cache: lists of more than 8 GiB of them, 32 times what
-// it holds (figures at the kernel; at 4 and 8 GB the two are within what runs differ by).
+// it holds.  Ordinary loads pay up to about what it holds, from 0.5 to 8 GB the two are within 1 %, at 32 GB streaming ones do
+// (figures at the kernel).
 inline bool stream_gradients(int64_t total_elems, bool grad_bf16) { return total_elems > ((int64_t)1 << 33) / (grad_bf16 ? 2 : 4); }
 
 // Small lists evaluate the per-tensor rule (Eq. 3) inside the update kernel, every wave for its own chunk, from the tensor's
 // partial sums and a copy of gamma that the norm kernel makes: one launch less, for one more load per wave.  That pays while
 // the update kernel is only a few rounds of workgroups, and needs tensors whose slots one wave can sum in the rules kernel's
-// order (see rule_in_update).
+// order (see rule_in_update).  us per step, in the rules kernel / in the update: 64 work items 11.9 / 9.8, 512: 18.0 / 15.4,
+// 1024: 28.4 / 25.9, 2048: 47.2 / 45.4, 4096: 88.9 / 87.3, 8192: 164.0 / 163.9.  So the line lies well inside the range that
+// gains, where the launch is still a tenth of the step.
 constexpr int64_t kFusedMaxItems = 1024;
 constexpr int64_t kFusedMaxChunks = 64;        // of one tensor
 struct FusedRule {

@@ -193,9 +193,8 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     c->nontemporal = cfg->nontemporal == 2 ? 0 : 1;
     //  - work items of the update kernel: see default_unroll.
     // Both streaming kernels walk their work items b, b+grid, ..., so any grid size is valid.
-    c->items_per_chunk = cfg->update_split ? cfg->update_split
-                                            : default_items(c->unroll > default_unroll(cfg->optimizer) ? c->unroll
-                                                                                                       : default_unroll(cfg->optimizer));
+    const int least_unroll = default_unroll(cfg->optimizer);
+    c->items_per_chunk = cfg->update_split ? cfg->update_split : default_items(c->unroll > least_unroll ? c->unroll : least_unroll);
     auto chunk_len = [&](size_t k) {
         const int64_t rest = c->numel[chunk_tensor[k]] - (int64_t)chunk_index[k] * kChunkElems;
         return rest < kChunkElems ? rest : (int64_t)kChunkElems;
@@ -438,7 +437,8 @@ extern "C" int adagc_step(adagc_ctx* ctx, void* const* params, const void* const
             return ADAGC_ERR_HIP;
     } else {
         if (ctx->small_list && !r.warmup && r.mode == ADAGC_MODE_ADAGC) rule = FusedRule{ema_norms, r};
-        if (launch_sumsq_partials(ctx->tables, bf16g, ctx->stream_grads, ctx->grid_norm, stream, nullptr, 0, rule.ema) != hipSuccess) return ADAGC_ERR_HIP;
+        if (launch_sumsq_partials(ctx->tables, bf16g, ctx->stream_grads, ctx->grid_norm, stream, nullptr, 0, rule.ema) != hipSuccess)
+            return ADAGC_ERR_HIP;
         if (prof && hipEventRecord(ev[1], stream) != hipSuccess) return ADAGC_ERR_HIP;
         if (!rule.ema && launch_rules(ctx->tables, ema_norms, r, stream) != hipSuccess) return ADAGC_ERR_HIP;
         if (prof && hipEventRecord(ev[2], stream) != hipSuccess) return ADAGC_ERR_HIP;
@@ -475,7 +475,8 @@ extern "C" int adagc_step_graph(adagc_ctx* ctx, void* const* params, const void*
     hipEvent_t* ev = prof ? &ctx->prof_events[(size_t)ctx->prof_steps * 4] : nullptr;
     ctx->device_scalars_used = true;
     if (prof && hipEventRecord(ev[0], stream) != hipSuccess) return ADAGC_ERR_HIP;
-    if (launch_sumsq_partials(ctx->tables, bf16g, ctx->stream_grads, ctx->grid_norm, stream, step_params, ctx->cfg.optimizer) != hipSuccess)
+    if (launch_sumsq_partials(ctx->tables, bf16g, ctx->stream_grads, ctx->grid_norm, stream, step_params,
+                              ctx->cfg.optimizer) != hipSuccess)
         return ADAGC_ERR_HIP;
     if (prof && hipEventRecord(ev[1], stream) != hipSuccess) return ADAGC_ERR_HIP;
     if (launch_rules(ctx->tables, ema_norms, RuleArgs{}, stream, step_params, ctx->cfg.optimizer) != hipSuccess)

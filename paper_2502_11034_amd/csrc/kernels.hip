@@ -7,7 +7,8 @@
 //                           model's norm; "Ablation Study", Sec. 5.6), ZClip
 //   global_rule_kernel / finalize_global_kernel
 //                           those model-wide rules on long lists
-//   update_kernel           per quarter chunk: clipped gradient into AdamW / Lion  (Alg. 1)
+//   update_kernel           per work item (a quarter of a chunk, an eighth for Lion; chunks of up to 1024, Lion 512, elements
+//                           go four to a workgroup): clipped gradient into AdamW / Lion  (Alg. 1)
 //   direction_stats_kernel / finalize_update_clip_kernel
 //                           update clipping (AGC and Clippy rows of Table 2): norms of theta and of the
 //                           optimizer's direction per tensor, and the coefficient that scales the direction
@@ -170,9 +171,12 @@ __device__ __forceinline__ void tiny_chunk_sumsq(const DeviceTables& t, const Wo
 }
 
 // NTL: streaming loads, for lists whose gradients are many times the 256 MB of the memory-side cache (stream_gradients).  On
-// smaller ones they would leave nothing in it for the update kernel, which reads the same gradients next: GPT-2-small shapes
-// (498 MB of gradients) 657 us per step with streaming loads, 622 without; 266 MB of bf16 gradients 680, 635; 1.6 GB 2.33, 2.26
-// ms.  On 32 GB ordinary loads only cost this kernel time: 4.45 ms streaming, 5.0 ordinary.
+// lists that fit it they would leave nothing there for the update kernel, which reads the same gradients next.  us per step,
+// ordinary / streaming loads, with gradients that another kernel writes anew before every step, as a backward pass does:
+// 17 MB 31.5 / 33.0, 67 MB 93.6 / 99.4, 268 MB 351 / 374, 266 MB of bf16 647 / 673; then nothing either way beyond 1 %: 498 MB
+// 671 / 665, 1.6 GB 2131 / 2123, 3.9 GB of bf16 9.83 / 9.93 ms, 7.7 GB 10.99 / 10.99.  (Where the same gradients are stepped
+// again and again, what the cache still holds serves the next step's norms too, and more seems gained than a training step
+// has: 498 MB 625 / 655.)  On 32 GB ordinary loads cost this kernel time: 4.49 ms streaming, 4.98 ordinary.
 // params: null, or the device-resident parameters of this step, from which one lane makes the update kernel's scalars.
 // ema_to_keep: null, or the gammas that the update kernel will need as they are now (see FusedRule).
 // One lane also clears the arrival count of the rules kernel.
@@ -644,9 +648,11 @@ __device__ __forceinline__ double rule_in_update(const DeviceTables& t, const Fu
 }
 
 // All loads of this wave are there before anything else is done.  With seven arrays and a copy to write, stores that start
-// while the item's last loads are still on their way cost more in read/write turnaround than they gain: 133 M parameters with
-// bf16 gradients and copies 646 us per step without, 631 with; 1.9 B with fp32 gradients 10.78, 10.72 ms.  Without the copy
-// (1500 ragged tensors 2.27, 2.34 ms; 5000 small ones 106, 112 us) and for Lion (6.65, 6.71 ms) it is the other way round.
+// while the item's last loads are still on their way cost a little more in read/write turnaround than they gain.  AdamW with the
+// copy, without / with the wait: GPT-2-small shapes 686 / 679 us per step, 133 M parameters with bf16 gradients 639 / 635 (664 /
+// 660 and 890 / 876 through other entry points), 1.9 B 10.89 / 10.76 ms; 1500 ragged tensors 1.96 both; 5000 small ones lose
+// by it, 109 / 113 us.  Without the copy the two are within 1 % on large lists and small ones lose (103 / 106 us); Lion 6.65 /
+// 6.71 ms.
 __device__ __forceinline__ void wait_for_loads()
 {
     __builtin_amdgcn_sched_barrier(0);
@@ -656,13 +662,15 @@ __device__ __forceinline__ void wait_for_loads()
 
 // Waves per SIMD that the update kernel may have in flight.  One wave holds 16 loads of 1 KiB, so two are enough to cover
 // the latency, and more only open more DRAM rows at once: AdamW on GPT-2-small shapes 657 us per step with 2, 667 with 3, 670
-// with 4 (Llama-3-8B shapes 10.75, 10.90, 10.87 ms for 4 layers).  Lion has fewer arrays in flight: 6.56, 6.55, 6.60 ms.
+// with 4 (Llama-3-8B shapes 10.75, 10.90, 10.87 ms for 4 layers).  Lion has fewer arrays in flight and wants 3: GPT-2-small
+// shapes 476 us with 2, 448 with 3, 448 with 4; 1500 ragged tensors 1518, 1450, 1495; Llama-3-8B shapes with bf16 gradients and
+// copies 7.10, 6.65, 6.97 ms (5000 small tensors 88, 77, 72 us).
 template <int OPT>
 constexpr int kUpdateWaves = OPT == ADAGC_OPT_ADAMW ? 2 : 3;
 
 template <int OPT, bool BF16G, bool COPY, int U, bool NT, bool TELE>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kUpdateWaves<OPT>, kUpdateWaves<OPT>))) void update_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items,
-                                                        const StepScalars* device_scalars, FusedRule rule)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kUpdateWaves<OPT>, kUpdateWaves<OPT>)))
+void update_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items, const StepScalars* device_scalars, FusedRule rule)
 {
     static_assert(kVecPerLane % U == 0, "a chunk is a whole number of tiles");
     if (device_scalars) {                      // adagc_step_graph: this step's scalars live in device memory
@@ -1087,9 +1095,9 @@ hipError_t launch_update_clip_rule(const DeviceTables& t, const UpdateArgs& u, c
                                    int grad_bf16, int items_per_chunk, int nt, int grid, hipStream_t stream)
 {
     const bool linf = r.mode == ADAGC_MODE_CLIPPY;
-    StatsFn fn;
-    if (optimizer == ADAGC_OPT_LION) fn = grad_bf16 ? select_stats_flags<ADAGC_OPT_LION, true>(linf, nt) : select_stats_flags<ADAGC_OPT_LION, false>(linf, nt);
-    else fn = grad_bf16 ? select_stats_flags<ADAGC_OPT_ADAMW, true>(linf, nt) : select_stats_flags<ADAGC_OPT_ADAMW, false>(linf, nt);
+    const bool lion = optimizer == ADAGC_OPT_LION;
+    const StatsFn fn = grad_bf16 ? (lion ? select_stats_flags<ADAGC_OPT_LION, true> : select_stats_flags<ADAGC_OPT_ADAMW, true>)(linf, nt)
+                                 : (lion ? select_stats_flags<ADAGC_OPT_LION, false> : select_stats_flags<ADAGC_OPT_ADAMW, false>)(linf, nt);
     fn<<<dim3(grid), dim3(kBlock), 0, stream>>>(t, u, log2_of(items_per_chunk));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -22,7 +22,10 @@
 // v_mfma_f32_16x16x32_bf16, fp32 accumulation); where the launch has enough of them to fill the compute units,
 // 256 x 256 tiles with 8 waves in a 4 x 2 grid (each 64 x 128).  One launch can cover a batch of equal-shaped
 // products.  Operand tiles, 64 deep, are loaded from global memory straight into LDS (global_load_lds_dwordx4, no
-// staging registers), swizzled against bank conflicts, into a ring of five: see the main loop.  Workgroups are dealt
+// staging registers), swizzled against bank conflicts, into a ring of five: see the main loop.  (The 256-tile kernels spill
+// four registers, three in the symmetric form: stored before and after the main loop, reloaded in the epilogue, nothing inside
+// the loop.  Their accesses count among the vector-memory operations that the explicit waits count, which makes a wait
+// stricter, never weaker.)  Workgroups are dealt
 // to the 8 XCDs in turn, so block ids are remapped to give each XCD (one L2 each) a contiguous band of output tiles.
 
 #include <utility>

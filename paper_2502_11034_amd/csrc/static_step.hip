@@ -196,7 +196,8 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
         }
         batch.first = (uint32_t)first;
         batch.count = (uint32_t)count;
-        store_tensor_batch_kernel<<<dim3((uint32_t)count), dim3(kBlock), 0, stream>>>(batch, d_targs, d_work, items_per_chunk, unroll);
+        store_tensor_batch_kernel<<<dim3((uint32_t)count), dim3(kBlock), 0, stream>>>(batch, d_targs, d_work, items_per_chunk,
+                                                                                      unroll);
         if (hipGetLastError() != hipSuccess) return ADAGC_ERR_HIP;
     }
 
@@ -211,7 +212,8 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
 
     FusedRule rule{};
     if (small_tensors && items <= kFusedMaxItems && !r.warmup && r.mode == ADAGC_MODE_ADAGC) rule = FusedRule{ema_norms, r};
-    if (launch_sumsq_partials(t, bf16g, stream_gradients(total_elems, bf16g), grid_norm, stream, nullptr, 0, rule.ema) != hipSuccess) return ADAGC_ERR_HIP;
+    if (launch_sumsq_partials(t, bf16g, stream_gradients(total_elems, bf16g), grid_norm, stream, nullptr, 0, rule.ema) != hipSuccess)
+        return ADAGC_ERR_HIP;
     if (!rule.ema && launch_rules(t, ema_norms, r, stream) != hipSuccess) return ADAGC_ERR_HIP;
     if (launch_update(t, u, cfg->optimizer, bf16g, copy, unroll, items_per_chunk, 1, 0, grid_update, stream, false, rule) != hipSuccess)
         return ADAGC_ERR_HIP;
