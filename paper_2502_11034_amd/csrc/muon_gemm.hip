@@ -10,7 +10,7 @@
 //   B  = b A + c A A          P = Q = A (A is symmetric)      (alpha c, beta b, D = A)
 //   X' = a X + B X            P = B, Q = Y = X^T              (alpha 1, beta a, D = X)
 // The result is written row-major (C), transposed (Ct, N x M), or both; D is read through its transpose
-// Dt (N x M).  The epilogue goes through LDS, so that all of these are 16-byte accesses along rows (store_result).
+// Dt (N x M).
 //
 // A = X X^T and A A are symmetric: for those only the tiles on and below the diagonal are computed and each is
 // written twice, to its place and to its mirror image, which saves about a quarter of a step's multiplications.
@@ -18,16 +18,15 @@
 // M and N are multiples of the 128 x 128 block tile and K of 128 (two 64-deep tiles): the caller (muon.hip) keeps every matrix
 // in zero-padded workspace buffers, and zero rows and columns stay zero through the iteration.
 //
-// Tiling: 128 x 128 block tile with 4 waves in a 2 x 2 grid (each wave 64 x 64 = 4 x 4 accumulators of
-// v_mfma_f32_16x16x32_bf16, fp32 accumulation); where the launch has enough of them to fill the compute units,
-// 256 x 256 tiles with 8 waves in a 4 x 2 grid (each 64 x 128).  One launch can cover a batch of equal-shaped
-// products.  Operand tiles, 64 deep, are loaded from global memory straight into LDS (global_load_lds_dwordx4, no
-// staging registers), swizzled against bank conflicts, into a ring of five: see the main loop.  (The 256-tile kernels spill
-// four registers, three in the symmetric form: stored before and after the main loop, reloaded in the epilogue, nothing inside
-// the loop.  Their accesses count among the vector-memory operations that the explicit waits count, which makes a wait
-// stricter, never weaker.)  Workgroups are dealt
-// to the 8 XCDs in turn, so block ids are remapped to give each XCD (one L2 each) a contiguous band of output tiles.
+// Tiling: 128 x 128 block tile with 4 waves, or, where the launch has enough of them to fill the compute units,
+// 256 x 256 with 8; every wave has 4 quadrants of the block tile's rows and columns, in accumulators of
+// v_mfma_f32_16x16x32_bf16.  One launch can cover a batch of equal-shaped products.  Operand tiles, 64 deep, are loaded
+// from global memory straight into LDS (global_load_lds_dwordx4, no staging registers), swizzled against bank conflicts, by
+// halves into a ring of five places (see "Main loop").  A compute unit's workgroups stay and take tile after tile: the next
+// tile's first loads are on their way while this one's results are stored (see "Epilogue").  The 256-tile kernels are at the
+// register limit of 256 and spill 20 to 28 of them around the loop, none inside it.
 
+#include <algorithm>
 #include <utility>
 
 #include "muon_internal.h"
@@ -40,67 +39,93 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
 
-// Distance in elements from one matrix of a batch to the next, per array (0 for a single product).
-struct GemmBatch {
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+#define ADAGC_LDS __attribute__((address_space(3)))
+#define ADAGC_CONST __attribute__((address_space(4)))
+
+// A batch of products of one shape; matrix z of every array at its base + z times its stride (elements).
+struct GemmWork {
+    const uint16_t *p, *q, *dt;
+    uint16_t *c, *ct;
     int64_t stride_p, stride_q, stride_dt, stride_c, stride_ct;
+    int32_t ldp, ldq, lddt, ldc, ldct;
+    int32_t k;
+    int32_t tiles_m, tiles_n;       // block tiles of one matrix
+    int32_t tiles;                  // the ones of them that are computed (SYM: on and below the diagonal)
+    int32_t all;                    // ... of the whole batch
+    float   alpha, beta;
 };
 
-#ifndef ADAGC_GEMM_GROUP_M
-#define ADAGC_GEMM_GROUP_M 8
-#endif
-#ifndef ADAGC_GEMM_BIG_THREADS
-#define ADAGC_GEMM_BIG_THREADS 512      // lanes of a 256 x 256 workgroup: 8 waves; 4 waves (256) measured no better overall
-#endif
 constexpr int kBK = 64;
-constexpr int kVecPerRow = kBK / 8;                    // 16-byte vectors per tile row
 
-__device__ __forceinline__ uint32_t f32_to_bf16_rne(float f)
+// Two floats to bf16, round to nearest even, NaNs quieted: one instruction, with the bits of float_to_bf16_bits for every float.
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 {
-    uint32_t u = __float_as_uint(f);
-    uint32_t rounded = (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-    return ((u & 0x7FFFFFFFu) > 0x7F800000u) ? ((u >> 16) | 0x40u) : rounded;
+    const f32x2 v = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
-// Which output tile a workgroup computes, and the batch's matrix it belongs to.
+// An output tile: its place in matrix z of the batch.  z < 0: none.
 struct TilePlace {
-    int tile_m, tile_n, z;
+    int z, tile_m, tile_n;
 };
 
-// XCD-aware tile order: block b runs on XCD b mod 8; XCD x gets the x-th contiguous eighth of the tiles of the whole
-// batch (with 8 or more matrices in the batch an XCD then stays on its own matrices).  Within a matrix: SYM walks the
-// lower triangle row by row; otherwise the tiles are walked in panels of kGroupM tile rows, down the rows of a panel
-// first: the workgroups that run at the same time on an XCD then form a patch a few tiles high and wide and share
-// both operands in its L2.
-template <int BT, bool SYM>
-__device__ __forceinline__ TilePlace place_tile(int b, int all_tiles, int M, int N)
+// Tile b of a matrix, in an order in which tiles that follow one another form a patch a few tiles high and wide, so that the
+// workgroups that run at the same time on an XCD share both operands in its L2.  SYM: the lower triangle in panels of kPanel
+// tile columns, down the rows of a panel; otherwise panels of kPanelRows tile rows, along the columns.
+template <bool SYM>
+__device__ __forceinline__ void tile_of_matrix(int b, int tiles_m, int tiles_n, int* tile_m, int* tile_n)
 {
-    const int tiles_n = N / BT;
-    const int n_tiles = SYM ? tiles_n * (tiles_n + 1) / 2 : (M / BT) * tiles_n;     // per matrix
-    if (all_tiles % 8 == 0) b = (b % 8) * (all_tiles / 8) + b / 8;
-    TilePlace t;
-    t.z = b / n_tiles;
-    b -= t.z * n_tiles;
     if constexpr (SYM) {
-        // b-th tile of the lower triangle: row r starts at r (r + 1) / 2
-        int r = (int)((sqrtf(8.0f * (float)b + 1.0f) - 1.0f) * 0.5f);
-        while (r * (r + 1) / 2 > b) --r;
-        while ((r + 1) * (r + 2) / 2 <= b) ++r;
-        t.tile_m = r;
-        t.tile_n = b - r * (r + 1) / 2;
+        constexpr int kPanel = 4;
+        for (int c0 = 0;; c0 += kPanel) {
+            const int rows = tiles_m - c0, cols = rows < kPanel ? rows : kPanel;
+            const int n = cols * rows - cols * (cols - 1) / 2;
+            if (b < n) {
+                int r = 0;                                 // the panel's first rows have 1, 2, ... cols - 1 tiles
+                while (r < cols - 1 && b > r) b -= ++r;
+                const int full = r == cols - 1 ? b / cols : 0;
+                *tile_m = c0 + r + full;
+                *tile_n = c0 + b - full * cols;
+                return;
+            }
+            b -= n;
+        }
     } else {
-        constexpr int kGroupM = ADAGC_GEMM_GROUP_M;
-        const int tiles_m = M / BT;
-        const int per_group = kGroupM * tiles_n;
-        const int group = b / per_group;
-        const int first_m = group * kGroupM;
-        const int rows_here = (tiles_m - first_m) < kGroupM ? (tiles_m - first_m) : kGroupM;
-        const int in_group = b - group * per_group;
-        t.tile_m = first_m + in_group % rows_here;
-        t.tile_n = in_group / rows_here;
+        constexpr int kPanelRows = 8;
+        const int per_panel = kPanelRows * tiles_n;
+        const int first_m = b / per_panel * kPanelRows;
+        const int rows = tiles_m - first_m < kPanelRows ? tiles_m - first_m : kPanelRows;
+        const int i = b - first_m * tiles_n;
+        *tile_m = first_m + i % rows;
+        *tile_n = i / rows;
     }
+}
+
+// The tile of this workgroup in a round.  A round is as many consecutive tiles of the batch as there are workgroups, dealt to
+// the 8 XCDs (workgroup b runs on XCD b mod 8, one L2 each) in contiguous eighths: the whole chip is on one or two matrices at a
+// time, and what the XCDs' patches have in common comes out of the memory-side cache.  With a contiguous eighth of the whole
+// batch per XCD, 8 matrices at a time, 12 products X X^T of 4096 x 14336 took 2321 us, now 2223.
+template <bool SYM>
+__device__ __forceinline__ TilePlace tile_of_workgroup(const ADAGC_CONST GemmWork& w, int round)
+{
+    const int xcd = (int)blockIdx.x % 8, slot = (int)blockIdx.x / 8, wgs = (int)gridDim.x;      // a multiple of 8
+    const int64_t first = (int64_t)round * wgs, left = w.all - first;
+    const int now = (int)(left < wgs ? left : wgs);
+    const int lo = now * xcd / 8, hi = now * (xcd + 1) / 8;
+    if (slot >= hi - lo) return {-1, 0, 0};
+    const int i = (int)first + lo + slot;
+    TilePlace t;
+    t.z = __builtin_amdgcn_readfirstlane(i / w.tiles);
+    tile_of_matrix<SYM>(i - t.z * w.tiles, w.tiles_m, w.tiles_n, &t.tile_m, &t.tile_n);
+    t.tile_m = __builtin_amdgcn_readfirstlane(t.tile_m);
+    t.tile_n = __builtin_amdgcn_readfirstlane(t.tile_n);
     return t;
 }
 
@@ -148,282 +173,325 @@ __device__ __forceinline__ void load_to_lds_16(const void* base, uint32_t off, c
                  : "memory");
 }
 
-// Epilogue of a workgroup: bf16(alpha acc + beta D) to Ct and C, staged through LDS so that every global access is a
-// 16-byte vector per lane along a row of the array it touches.  (In the accumulator layout a lane holds 4 consecutive
-// rows of one column and 16 lanes hold 16 columns: stored directly, that is 8 bytes per lane for Ct and D, each in a
-// different cache line, and 2 bytes per lane for C.)
+// Main loop.  What bounds it: on ordinary data the power the chip may draw (its clock falls to 1.65 - 1.75 GHz under this
+// loop; 4096 x 4096 x 16384 takes 376 us on normal random operands and 294 on zeros, a library kernel 345 - 391 and 247 - 265
+// on the cards tried), otherwise the time an operand load takes.
 //
-// The staging tile T holds the BT x BT result transposed, T[c][r] = result(r, c), as Ct and Dt do: row c of T is BT
-// contiguous elements of global row tile_n BT + c of Ct.  Within a row the 16-byte chunks are permuted: chunk g sits
-// at position g ^ f(c), f(c) = (c ^ (c / chunks)) mod chunks, which spreads over the LDS banks both the accumulator-
-// layout accesses (16 lanes = 16 consecutive c, one r) and the reads of the C pass (8 consecutive c at a time).
-//   1. Dt's tile is loaded into T (global_load_lds, the permutation applied on the global side);
-//   2. every lane reads the D values of its accumulator elements from T, and writes the rounded results back to the
-//      same places;
-//   3. T is written out row by row to Ct, and, gathered by columns, row by row to C.
-// Accumulator register r of lane l is element (row (l/16)*4 + r, column l%16) of its 16 x 16 block.
-// On entry no wave reads LDS any more (all are past the main loop's last barrier).
-template <int BT, int kMI, int kNI, bool SYM, int kWaves>
-__device__ __forceinline__ void store_result(uint16_t* T, const f32x4 (&acc)[kMI][kNI], int lane, int wave, int wave_row, int wave_col,
-                                             int tile_m, int tile_n, float alpha, float beta, const uint16_t* __restrict__ Dt,
-                                             int lddt, uint16_t* __restrict__ C, int ldc, uint16_t* __restrict__ Ct, int ldct)
-{
-    constexpr int kChunks = BT / 8;                         // 16-byte chunks per row of T
-    constexpr int kChunkBits = BT == 256 ? 5 : 4;
-    static_assert((1 << kChunkBits) == kChunks, "BT is 128 or 256");
-    constexpr int kRowsPerInst = 64 / kChunks;              // rows of T one wave-wide 16-byte access covers: 2 or 4
-    constexpr int kInsts = BT / kRowsPerInst / kWaves;      // such accesses per wave for the whole tile
-    auto f = [](int c) { return (c ^ (c >> kChunkBits)) & (kChunks - 1); };
-    const size_t row0_g = (size_t)tile_m * BT, col0_g = (size_t)tile_n * BT;
-
-    // lane i of a row-wise access: row c = first + i / kChunks of T, position i % kChunks, i.e. chunk (i % kChunks) ^ f(c)
-    const int rw_row = lane / kChunks;
-    const int rw_pos = lane % kChunks;
-    if (Dt) {
-#pragma unroll
-        for (int u = 0; u < kInsts; ++u) {
-            const int first = (u * kWaves + wave) * kRowsPerInst;
-            const int c = first + rw_row;
-            const int g = rw_pos ^ f(c);
-            load_to_lds_16(Dt + (col0_g + first) * lddt + row0_g, (uint32_t)(rw_row * lddt + g * 8) * 2u, T + first * BT);
-        }
-        ADAGC_WAIT_VMEM(0);
-        __syncthreads();
-    }
-    const int col_in = lane & 15;
-    const int row_in = (lane >> 4) * 4;
-#pragma unroll
-    for (int i = 0; i < kMI; ++i)
-#pragma unroll
-        for (int j = 0; j < kNI; ++j) {
-            const int c = wave_col + j * 16 + col_in;
-            const int fc = f(c);
-            const int r = wave_row + i * 16 + row_in;
-            u32x2v* slot = reinterpret_cast<u32x2v*>(T + c * BT + (((r >> 3) ^ fc) << 3) + (r & 7));
-            float v[4] = {alpha * acc[i][j][0], alpha * acc[i][j][1], alpha * acc[i][j][2], alpha * acc[i][j][3]};
-            if (Dt) {
-                const u32x2v d = *slot;
-                v[0] = fmaf(beta, bf16_lo(d.x), v[0]);
-                v[1] = fmaf(beta, bf16_hi(d.x), v[1]);
-                v[2] = fmaf(beta, bf16_lo(d.y), v[2]);
-                v[3] = fmaf(beta, bf16_hi(d.y), v[3]);
-            }
-            u32x2v o;
-            o.x = f32_to_bf16_rne(v[0]) | (f32_to_bf16_rne(v[1]) << 16);
-            o.y = f32_to_bf16_rne(v[2]) | (f32_to_bf16_rne(v[3]) << 16);
-            *slot = o;
-        }
-    __syncthreads();
-    if (Ct) {
-#pragma unroll
-        for (int u = 0; u < kInsts; ++u) {
-            const int c = (u * kWaves + wave) * kRowsPerInst + rw_row;
-            const int g = rw_pos ^ f(c);
-            const u32x4 v = *reinterpret_cast<const u32x4*>(T + c * BT + rw_pos * 8);
-            *reinterpret_cast<u32x4*>(Ct + (col0_g + c) * ldct + row0_g + g * 8) = v;
-        }
-    }
-    if (SYM ? (tile_m != tile_n) : (C != nullptr)) {        // SYM: the mirror image, C is the same array as Ct
-        // one access: 8 rows r of the result, 8 chunks (64 columns) of each; lane i takes row i / 8, chunk i % 8
-        constexpr int kColGroups = BT / 64;
-        constexpr int kCInsts = (BT / 8) * kColGroups / kWaves;
-        const int cr = lane >> 3, cc = lane & 7;
-#pragma unroll 4
-        for (int u = 0; u < kCInsts; ++u) {
-            const int n = u * kWaves + wave;
-            const int r = (n / kColGroups) * 8 + cr;
-            const int c0 = (n % kColGroups) * 64 + cc * 8;
-            uint32_t w[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int ca = c0 + 2 * e, cb = ca + 1;
-                const uint32_t lo = T[ca * BT + (((r >> 3) ^ f(ca)) << 3) + (r & 7)];
-                const uint32_t hi = T[cb * BT + (((r >> 3) ^ f(cb)) << 3) + (r & 7)];
-                w[e] = lo | (hi << 16);
-            }
-            u32x4 v;
-            v.x = w[0];
-            v.y = w[1];
-            v.z = w[2];
-            v.w = w[3];
-            *reinterpret_cast<u32x4*>(C + (row0_g + r) * ldc + col0_g + c0) = v;
-        }
-    }
-}
-
-// BT x BT block tile (128 or 256), operand tiles loaded from global memory straight into LDS.
-// One global_load_lds_dwordx4 of a wave writes 1024 contiguous LDS bytes, lane i the i-th 16: that is 8 rows of a
-// 64-deep tile stored without padding.  Bank conflicts of the fragment reads (16 lanes = 16 consecutive rows per
-// clock over 64 banks) are avoided by a swizzle instead: the 16-byte vector v of tile row r sits at position
-// v ^ ((r / 2) mod 8) of its LDS row, which the loading lane applies on the global side.
-template <int BT, bool SYM, int kGemmThreads>
-__global__ __launch_bounds__(kGemmThreads) void gemm_nt_bf16_kernel(
-    const uint16_t* __restrict__ P, int ldp, const uint16_t* __restrict__ Q, int ldq, int M, int N, int K,
-    float alpha, float beta, const uint16_t* __restrict__ Dt, int lddt, uint16_t* __restrict__ C, int ldc,
-    uint16_t* __restrict__ Ct, int ldct, GemmBatch bt)
+// The block tile's rows and columns are cut in halves: P0, P1 of P and Q0, Q1 of Q, and a wave's accumulators in the four
+// quadrants P0 Q0, P0 Q1, P1 Q1, P1 Q0, in this order.  Group g of the loads is half g mod 2 of both operands of the 64-deep
+// tile g / 2, and LDS is a ring of five places of a group each (32 KB with 256-tiles, 160 KB in all).  In half step h
+//   h even:  P0 Q0, then P0 Q1 are multiplied while Q1 and P1 are read from group h + 1,
+//   h odd:   P1 Q1, then P1 Q0, while P0 and Q0 of the next 64-deep tile are read from group h + 1,
+// and group h + 5 is loaded into the place of group h, whose last reader is behind the barrier.  Every load so has three and
+// a half half steps to arrive.  (With P and Q tiles whole in the ring, half of the loads had less than two half steps: on zeros
+// 339 us against 295, on random operands 395 against 387, 12 products X X^T of 4096 x 14336 2520 against 2425 us.)
+// One access is issued after every few multiplications: a load into LDS occupies the issue for about 16 clocks per wave.
+// Q0 is read where Q1 was, so the two swap their registers from tile to tile.
+//
+// 16 x 16 x 32 multiplications instead of 32 x 32 x 16: half the accumulator traffic per multiplication, and so a
+// higher clock (1313 -> 1343 TFLOP/s when it was introduced), and successive multiplications share an operand all the way
+// through.  The results are the same bit for bit: every sum runs over k in order.
+//
+// Epilogue.  Accumulator register r of lane l is element (row (l / 16) * 4 + r, column l % 16) of its 16 x 16 block: 8 bytes along
+// a row of Ct.  Exchanging half of the lanes' values between two neighbouring blocks (v_permlane16_swap) makes 16 bytes of
+// it, stored, and D loaded, without a detour through LDS; C, whose rows run the other way, is transposed through a 4 KB staging
+// area per wave in the fifth place of the ring (ds_read_b64_tr_b16).  The other four are receiving the next tile's first groups
+// meanwhile, and the stores complete during its first half steps.  (One workgroup per tile and all of LDS as the staging tile:
+// 4866 us for 12 products of 4096 x 14336 x 4096 with D, C and Ct, now 4706; X X^T as above 2373, now 2296.  Loading D
+// already in the last half step changed nothing.)
+template <int BT, bool SYM, bool HAS_D, int kGemmThreads>
+__global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const GemmWork)
 {
     constexpr int kWaves = kGemmThreads / 64;
-    constexpr int kWM = kGemmThreads / 128;                // waves in a kWM x 2 grid
-    constexpr int kTM = BT / kWM, kTN = BT / 2;            // wave tile
-    constexpr int kMI = kTM / 16, kNI = kTN / 16;          // 16 x 16 accumulators per wave
-    constexpr int kRowsPerLoad = 64 / kVecPerRow;          // tile rows one wave-wide load covers: 8
-    constexpr int kLoads = BT / kRowsPerLoad / kWaves;     // loads per wave per operand tile
+    constexpr int kWM = 2, kWN = kWaves / kWM;             // waves in a kWM x kWN grid
+    constexpr int kTM = BT / kWM, kTN = BT / kWN;          // wave tile
+    constexpr int kHM = kTM / 32, kHN = kTN / 32;          // 16 x 16 accumulators per quadrant
+    constexpr int kUnitElems = BT / 2 * kBK;               // half of an operand tile
+    constexpr int kPlaceElems = 2 * kUnitElems;            // Q's half, then P's
+    constexpr int kGL = 2 * kUnitElems / 512 / kWaves;     // loads per wave and group
+    constexpr int kStores = BT * BT / 512 / kWaves;        // stores per wave of one output array
     static_assert(kWaves % 2 == 0, "the swizzle of a load is taken from the wave's parity");
-    // a ring of five operand tiles; the epilogue reuses it as one BT x BT staging tile (or half of it)
-    constexpr int kTileElems = BT * kBK;
-    __shared__ __attribute__((aligned(16))) uint16_t lds[5 * kTileElems];
-    static_assert(5 * kTileElems >= BT * BT, "the staging tile of the epilogue must fit");
+    __shared__ __attribute__((aligned(16))) uint16_t lds[5 * kPlaceElems];
 
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // the same in all lanes: kept in a scalar register
-    const int wm = wave >> 1, wn = wave & 1;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // the same in all lanes: kept in a scalar register
+    const int wm = wave / kWN, wn = wave % kWN;
+    const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>(&lds[0]);
+    // The arguments, read anew where a tile begins and ends: kept through the main loop they would not fit the scalar registers.
+    auto arguments = []() __attribute__((always_inline)) -> const ADAGC_CONST GemmWork& {
+        const ADAGC_CONST GemmWork* a = (const ADAGC_CONST GemmWork*)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(a));
+        return *a;
+    };
+    auto place = [&](int p) { return lds + p * kPlaceElems; };
+    auto at_place = [&](int p) { return lds0 + (uint32_t)(p * kPlaceElems * 2); };
+    auto next_place = [](int p) { return p == 4 ? 0 : p + 1; };
 
-    const TilePlace tp = place_tile<BT, SYM>((int)blockIdx.x, (int)gridDim.x, M, N);
-    const int tile_m = tp.tile_m, tile_n = tp.tile_n;
-    P += (size_t)tp.z * bt.stride_p;
-    Q += (size_t)tp.z * bt.stride_q;
-    if (Dt) Dt += (size_t)tp.z * bt.stride_dt;
-    if (C) C += (size_t)tp.z * bt.stride_c;
-    if (Ct) Ct += (size_t)tp.z * bt.stride_ct;
-    const uint16_t* Pt = P + (size_t)tile_m * BT * ldp;
-    const uint16_t* Qt = Q + (size_t)tile_n * BT * ldq;
-
-    f32x4 acc[kMI][kNI];
-#pragma unroll
-    for (int i = 0; i < kMI; ++i)
-#pragma unroll
-        for (int j = 0; j < kNI; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
-
-    // Load u of this wave covers tile rows first .. first + 7, first = (u kWaves + wave) 8; lane i writes LDS row
-    // first + i / 8, position i mod 8, so it fetches vector (i mod 8) ^ ((row / 2) mod 8) of that row, and
-    // (row / 2) mod 8 = (4 (wave mod 2) + i / 16) mod 8 because kWaves is even.
+    // Loads.  One global_load_lds_dwordx4 of a wave writes 1024 contiguous LDS bytes, lane i the i-th 16: that is 8 rows of a
+    // 64-deep half tile stored without padding.  Bank conflicts of the fragment reads (16 lanes = 16 consecutive rows per
+    // clock over 64 banks) are avoided by a swizzle instead: the 16-byte vector v of row r sits at position v ^ ((r / 2) mod 8)
+    // of its LDS row, which the loading lane applies on the global side.  The rows of a load start at a multiple of 8, and
+    // (r / 2) mod 8 = (4 (wave mod 2) + lane / 16) mod 8 because kWaves is even.
     // The address is split into a part common to the wave (scalar registers) and one 32-bit offset per lane.
-    const int load_row = lane >> 3;
-    const int load_vec = (lane & 7) ^ ((((wave & 1) << 2) + (lane >> 4)) & 7);
-    const uint32_t lane_off_p = (uint32_t)(load_row * ldp + load_vec * 8) * 2u;      // bytes
-    const uint32_t lane_off_q = (uint32_t)(load_row * ldq + load_vec * 8) * 2u;
-    auto load_p = [&](int u, int kt, uint16_t* dst) {
-        const int first = (u * kWaves + wave) * kRowsPerLoad;
-        load_to_lds_16(Pt + (size_t)first * ldp + kt * kBK, lane_off_p, dst + first * kBK);
+    struct Source {
+        const uint16_t *p, *q;
+        int ldp, ldq;
+        uint32_t off_p, off_q;
     };
-    auto load_q = [&](int u, int kt, uint16_t* dst) {
-        const int first = (u * kWaves + wave) * kRowsPerLoad;
-        load_to_lds_16(Qt + (size_t)first * ldq + kt * kBK, lane_off_q, dst + first * kBK);
+    auto source = [&](const TilePlace& t) {
+        const ADAGC_CONST GemmWork& w = arguments();
+        int l = lane;
+        asm volatile("" : "+v"(l));                        // the offsets are made here, not kept through the main loop
+        const int row = l >> 3, vec = (l & 7) ^ ((((wave & 1) << 2) + (l >> 4)) & 7);
+        Source s;
+        s.ldp = w.ldp;
+        s.ldq = w.ldq;
+        s.p = w.p + (size_t)t.z * w.stride_p + (size_t)t.tile_m * BT * w.ldp;
+        s.q = w.q + (size_t)t.z * w.stride_q + (size_t)t.tile_n * BT * w.ldq;
+        s.off_p = (uint32_t)(row * w.ldp + vec * 8) * 2u;
+        s.off_q = (uint32_t)(row * w.ldq + vec * 8) * 2u;
+        return s;
     };
-    // Fragment addressing: lane l holds row l mod 16 of its 16-row block and the 16-byte vector 4 kk + l / 16 of that
-    // row; a block's first row is a multiple of 16, so (row / 2) mod 8 = (l / 2) mod 8.
-    const int frag_row = lane & 15;
-    const int frag_hi = lane >> 4;
-    const int frag_x = (lane >> 1) & 7;
-    // fragment n of slice kk, in the order p0 q0 p1 q1 ..., then what is left of the longer operand
-    auto read_frag = [&](const uint16_t* bp, const uint16_t* bq, int kk, int n, bf16x8 (&fa)[kMI], bf16x8 (&fb)[kNI]) {
-        const int pos = ((kk * 4 + frag_hi) ^ frag_x) * 8;
-        const int both = 2 * (kMI < kNI ? kMI : kNI);
-        const bool is_p = n < both ? (n & 1) == 0 : kMI > kNI;
-        const int k = n < both ? n >> 1 : n - both / 2;
-        if (is_p) fa[k] = *reinterpret_cast<const bf16x8*>(bp + (wm * kTM + k * 16 + frag_row) * kBK + pos);
-        else fb[k] = *reinterpret_cast<const bf16x8*>(bq + (wn * kTN + k * 16 + frag_row) * kBK + pos);
+    auto load = [&](const Source& s, int n, int g, uint16_t* dst) {
+        const int first = ((n >> 1) * kWaves + wave) * 8, k0 = (g >> 1) * kBK;
+        const size_t row = (size_t)((g & 1) * (BT / 2) + first);
+        if (n & 1) load_to_lds_16(s.q + row * s.ldq + k0, s.off_q, dst + first * kBK);
+        else load_to_lds_16(s.p + row * s.ldp + k0, s.off_p, dst + kUnitElems + first * kBK);
     };
 
-    // Main loop.  What bounds it: the matrix cores and, on ordinary data, the power the chip may draw (its clock falls
-    // to 1.65 - 1.75 GHz under this loop); the memory latency and the issue of loads have to stay out of the way.
-    //
-    // A 64-deep tile is two 32-deep slices.  While one slice is multiplied, the fragments of the next are read from LDS
-    // into a second register set and loads of later tiles are issued, one access after every few multiplications: a
-    // global load into LDS occupies the issue for about 16 clocks per wave, and with all of them in a row at the head of a
-    // tile nothing was multiplied meanwhile (16384-deep products of 4096 x 4096: 1174 TFLOP/s; spread out 1247).
-    //
-    // LDS holds five operand tiles (160 KB with 256-tiles): the current P and Q, the next P and Q, and the P after that.
-    // While tile k is multiplied, Q of tile k+1 is loaded into the place that P of tile k-1 left and P of tile k+2 into
-    // that of Q of tile k-1: half of the loads have two tiles' time to arrive, and the other half are issued first.  With
-    // two buffers of a P and a Q each, all had less than one tile's (1247 -> 1313 TFLOP/s).
-    //
-    // 16 x 16 x 32 multiplications instead of 32 x 32 x 16: half the accumulator traffic per multiplication, and so a
-    // higher clock (1313 -> 1343 TFLOP/s), and successive multiplications share an operand all the way through
-    // (rows are walked up and down in turn: 1373 -> 1381 on another card).  The results are the same bit for bit.
-    bf16x8 fa0[kMI], fb0[kNI], fa1[kMI], fb1[kNI];
-    const int k_tiles = K / kBK;          // at least 2: K is a multiple of 128
-    constexpr int kL = 2 * kLoads;
-    constexpr std::integral_constant<int, 0> none{};
-    // Multiply the slice in set f, while slice kk of the tile in (bp, bq) is read into set n and loads 0 .. NL-1 of tile
-    // k's are issued (the first kLoads: Q of tile k+1 into lq, the others: P of tile k+2 into lp).
-    auto phase = [&](auto READ, const bf16x8 (&fa)[kMI], const bf16x8 (&fb)[kNI], const uint16_t* bp, const uint16_t* bq, int kk,
-                     bf16x8 (&na)[kMI], bf16x8 (&nb)[kNI], auto NL, int k, uint16_t* lp, uint16_t* lq) {
-        constexpr int kM = kMI * kNI, kR = kMI + kNI, nl = decltype(NL)::value;
-        static_for<kM>([&](auto T) __attribute__((always_inline)) {
+    // Fragments.  Lane l holds row l mod 16 of its 16-row block and the 16-byte vector 4 kk + l / 16 of that row; a block's first
+    // row is a multiple of 16, so (row / 2) mod 8 = (l / 2) mod 8, and slice kk = 1 is 64 bytes from slice 0 by exclusive or.
+    // The addresses in the place that is read are made once per half step (opaque, so that what is left of them is immediate).
+    const uint32_t frag = (uint32_t)((lane & 15) * kBK * 2 + (((lane >> 4) ^ ((lane >> 1) & 7)) * 16));
+    const uint32_t frag_q = frag + (uint32_t)(wn * (kTN / 2) * kBK * 2);
+    const uint32_t frag_p = frag + (uint32_t)((kUnitElems + wm * (kTM / 2) * kBK) * 2);
+    auto addresses = [](uint32_t offset, uint32_t at, uint32_t (&a)[2]) {
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            a[kk] = (offset ^ (uint32_t)(kk * 64)) + at;
+            asm("" : "+v"(a[kk]));
+        }
+    };
+    auto read = [](const uint32_t (&a)[2], int block, int kk) {
+        return *reinterpret_cast<const ADAGC_LDS bf16x8*>(a[kk] + (uint32_t)(block * 16 * kBK * 2));
+    };
+
+    f32x4 acc[2 * kHM][2 * kHN];
+    bf16x8 p0[kHM][2], p1[kHM][2], qa[kHN][2], qb[kHN][2];
+    constexpr int S = 2 * kHM * kHN;                       // multiplications per quadrant and 64-deep tile
+    constexpr std::integral_constant<int, 0> no{};
+    constexpr std::integral_constant<int, 1> yes{};
+    // A half step: PART 0 multiplies P0 Q0 (qx), P0 Q1 (qy), PART 1 P1 Q1 (qy), P1 Q0 (qx).  READ: what the next one needs is
+    // read from the place at rd.  side(t) is called after multiplication t.
+    auto half = [&](auto PART, auto READ, bf16x8 (&qx)[kHN][2], bf16x8 (&qy)[kHN][2], uint32_t rd, auto&& side) __attribute__((always_inline)) {
+        constexpr int part = decltype(PART)::value;
+        uint32_t pa[2], qd[2];
+        if constexpr (decltype(READ)::value) {
+            addresses(frag_p, rd, pa);
+            addresses(frag_q, rd, qd);
+        }
+        static_for<2 * S>([&](auto T) __attribute__((always_inline)) {
             constexpr int t = decltype(T)::value;
-            constexpr int j = t / kMI, i = j % 2 ? kMI - 1 - t % kMI : t % kMI;
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+            constexpr int u = t % S, kk = u / (kHM * kHN), v = u % (kHM * kHN);
+            constexpr int j = v / kHM, i = (j + kk) % 2 ? kHM - 1 - v % kHM : v % kHM;      // rows up and down in turn
+            constexpr bool use_y = part ^ (t / S);
+            constexpr int ai = part * kHM + i, aj = (use_y ? kHN : 0) + j;
+            acc[ai][aj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(part ? p1[i][kk] : p0[i][kk], use_y ? qy[j][kk] : qx[j][kk], acc[ai][aj], 0, 0, 0);
             ADAGC_SCHED_FENCE();
             if constexpr (decltype(READ)::value) {
-                static_for<kR>([&](auto N) __attribute__((always_inline)) {
-                    constexpr int n = decltype(N)::value;
-                    if constexpr (n * kM / kR == t) read_frag(bp, bq, kk, n, na, nb);
+                constexpr int NQ = 2 * kHN, NP = 2 * kHM;
+                static_for<NQ + NP>([&](auto R) __attribute__((always_inline)) {
+                    constexpr int n = decltype(R)::value;
+                    if constexpr (part == 0) {             // all of it may be overwritten from the start: in one row, Q1 first
+                        if constexpr (n * (3 * S / 2) / (NQ + NP) == t) {
+                            if constexpr (n < NQ) qy[n % kHN][n / kHN] = read(qd, n % kHN, n / kHN);
+                            else p1[(n - NQ) % kHM][(n - NQ) / kHM] = read(pa, (n - NQ) % kHM, (n - NQ) / kHM);
+                        }
+                    } else if constexpr (n < NP) {         // P0 during the first quadrant, Q0 when the second no longer needs qy
+                        if constexpr (n * S / NP == t) p0[n % kHM][n / kHM] = read(pa, n % kHM, n / kHM);
+                    } else {
+                        if constexpr (S + (n - NP) * (S / 2) / NQ == t)
+                            qy[(n - NP) % kHN][(n - NP) / kHN] = read(qd, (n - NP) % kHN, (n - NP) / kHN);
+                    }
                 });
             }
-            static_for<nl>([&](auto N) __attribute__((always_inline)) {
-                constexpr int n = decltype(N)::value;
-                if constexpr (n * kM / nl == t) {
-                    if constexpr (n < kLoads) load_q(n, k + 1, lq);
-                    else load_p(n - kLoads, k + 2, lp);
-                }
-            });
+            side(T);
             ADAGC_SCHED_FENCE();
         });
     };
-    constexpr std::integral_constant<int, 1> yes{};
-    // Tile k, in places sp and sq of the ring; on entry slice 1 of tile k-1 is in set 1, on exit slice 1 of tile k is and
-    // all of tile k has been read by this wave.  fp, fq: the places that tile k-1 left.
-    auto tile = [&](auto NL, int k, int sp, int sq, int fp, int fq) {
-        const uint16_t *bp = lds + sp * kTileElems, *bq = lds + sq * kTileElems;
-        phase(yes, fa1, fb1, bp, bq, 0, fa0, fb0, NL, k, lds + fp * kTileElems, lds + fq * kTileElems);
-        phase(yes, fa0, fb0, bp, bq, 1, fa1, fb1, none, k, nullptr, nullptr);
-    };
-    auto two_on = [](int place) { return place >= 3 ? place - 3 : place + 2; };
+    auto nothing = [](auto) __attribute__((always_inline)) {};
+
+    TilePlace tp = tile_of_workgroup<SYM>(arguments(), 0);
+    if (tp.z < 0) return;
+    Source src = source(tp);
+    const int groups = 2 * (arguments().k / kBK);                    // a multiple of 4, at least 4
 #pragma unroll
-    for (int n = 0; n < 5; ++n) {
-        if (n == 4 && k_tiles <= 2) break;
+    for (int n = 0; n < 4 * kGL; ++n) load(src, n % kGL, n / kGL, place(n / kGL));
+    ADAGC_WAIT_VMEM(2 * kGL);                              // groups 0 and 1
+    for (int round = 0;; ++round) {
 #pragma unroll
-        for (int u = 0; u < kLoads; ++u) {
-            if (n % 2 == 0) load_p(u, n / 2, lds + n * kTileElems);
-            else load_q(u, n / 2, lds + n * kTileElems);
+        for (int i = 0; i < 2 * kHM; ++i)
+#pragma unroll
+            for (int j = 0; j < 2 * kHN; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
+        // Waits count the wave's accesses that may be outstanding.  Between groups 3 and 4 of a tile that is not the first lie the
+        // last one's stores, kStores or more (more only makes a wait stricter).
+        if (round) ADAGC_WAIT_VMEM(2 * kGL + kStores);
+        barrier_keeping_loads();
+        {
+            uint32_t pa[2], qd[2];
+            addresses(frag_p, lds0, pa);
+            addresses(frag_q, lds0, qd);
+            static_for<2 * kHN>([&](auto N) { constexpr int n = decltype(N)::value; qa[n % kHN][n / kHN] = read(qd, n % kHN, n / kHN); });
+            static_for<2 * kHM>([&](auto N) { constexpr int n = decltype(N)::value; p0[n % kHM][n / kHM] = read(pa, n % kHM, n / kHM); });
         }
-    }
-    if (k_tiles > 2) ADAGC_WAIT_VMEM(3 * kLoads);          // P and Q of tile 0 are there
-    else ADAGC_WAIT_VMEM(2 * kLoads);
-    barrier_keeping_loads();
-    static_for<kMI + kNI>([&](auto N) { read_frag(lds, lds + kTileElems, 0, decltype(N)::value, fa0, fb0); });
-    ADAGC_SCHED_FENCE();
-    phase(yes, fa0, fb0, lds, lds + kTileElems, 1, fa1, fb1, none, 0, nullptr, nullptr);
-    if (k_tiles > 2) ADAGC_WAIT_VMEM(kLoads);              // ... and of tile 1
-    else ADAGC_WAIT_VMEM(0);
-    barrier_keeping_loads();
-    int sp = 2, sq = 3, fp = 1, fq = 0, k = 1;
-    for (; k + 2 < k_tiles; ++k) {
-        tile(std::integral_constant<int, kL>{}, k, sp, sq, fp, fq);
-        ADAGC_WAIT_VMEM(kLoads);                           // all but P of tile k+2
+        ADAGC_SCHED_FENCE();
+        if (groups > 4) {
+#pragma unroll
+            for (int n = 0; n < kGL; ++n) load(src, n, 4, place(4));
+        }
         barrier_keeping_loads();
-        fq = sp;
-        fp = sq;
-        sp = two_on(sp);
-        sq = two_on(sq);
+        const TilePlace tp_next = tile_of_workgroup<SYM>(arguments(), round + 1);
+        int rp = 0, h = 0;                                 // the place of group h
+        // The two half steps of a 64-deep tile.  LA, LB: whether there is a group h + 5, h + 6 to load; WA, WB: how many accesses
+        // may be outstanding when the group that the next half step reads has to be there.
+        auto tile = [&](auto LA, auto LB, auto WA, auto WB, bf16x8 (&x)[kHN][2], bf16x8 (&y)[kHN][2]) __attribute__((always_inline)) {
+            const int pl1 = next_place(rp), pl2 = next_place(pl1);
+            auto loads = [&](int g, uint16_t* dst) {
+                return [&, g, dst](auto T) __attribute__((always_inline)) {
+                    static_for<kGL>([&](auto N) __attribute__((always_inline)) {
+                        constexpr int n = decltype(N)::value;
+                        if constexpr (n * 2 * S / kGL + 1 == decltype(T)::value) load(src, n, g, dst);
+                    });
+                };
+            };
+            if constexpr (decltype(LA)::value) half(no, yes, x, y, at_place(pl1), loads(h + 5, place(rp)));
+            else half(no, yes, x, y, at_place(pl1), nothing);
+            ADAGC_WAIT_VMEM(decltype(WA)::value);
+            barrier_keeping_loads();
+            if constexpr (decltype(LB)::value) half(yes, yes, x, y, at_place(pl2), loads(h + 6, place(pl1)));
+            else half(yes, yes, x, y, at_place(pl2), nothing);
+            ADAGC_WAIT_VMEM(decltype(WB)::value);
+            barrier_keeping_loads();
+            rp = pl2;
+            h += 2;
+        };
+        constexpr std::integral_constant<int, kGL> w1{};
+        constexpr std::integral_constant<int, 2 * kGL> w2{};
+        constexpr std::integral_constant<int, 3 * kGL> w3{};
+        while (h + 12 <= groups) {
+            tile(yes, yes, w3, w3, qa, qb);
+            tile(yes, yes, w3, w3, qb, qa);
+        }
+        if (groups > 4) {
+            tile(yes, yes, w3, w3, qa, qb);
+            tile(yes, no, w3, w2, qb, qa);                 // loads the last group
+        }
+        tile(no, no, w1, no, qa, qb);
+        half(no, yes, qb, qa, at_place(next_place(rp)), nothing);
+        barrier_keeping_loads();                           // all operands are in registers: the ring is free
+        const bool more = tp_next.z >= 0;
+        if (more) src = source(tp_next);
+        half(yes, no, qb, qa, 0u, [&](auto T) __attribute__((always_inline)) {
+            static_for<4 * kGL>([&](auto N) __attribute__((always_inline)) {
+                constexpr int n = decltype(N)::value;
+                if constexpr (n * 2 * S / (4 * kGL) == decltype(T)::value) {
+                    if (more) load(src, n % kGL, n / kGL, place(n / kGL));
+                }
+            });
+        });
+
+        // epilogue
+        const ADAGC_CONST GemmWork& w = arguments();
+        const float alpha = w.alpha, beta = w.beta;
+        const size_t v0 = (size_t)tp.tile_m * BT + wm * (kTM / 2), w0 = (size_t)tp.tile_n * BT + wn * (kTN / 2);
+        const uint16_t* Dt = HAS_D ? w.dt + (size_t)tp.z * w.stride_dt + w0 * w.lddt + v0 : nullptr;
+        uint16_t* Ct = w.ct ? w.ct + (size_t)tp.z * w.stride_ct + w0 * w.ldct + v0 : nullptr;
+        uint16_t* C = (SYM ? tp.tile_m != tp.tile_n : w.c != nullptr) ? w.c + (size_t)tp.z * w.stride_c + v0 * w.ldc + w0 : nullptr;
+        int le = lane;
+        asm volatile("" : "+v"(le));                       // the addresses below are made here, not kept through the main loop
+        const int er = le & 15, eg = le >> 4;
+        // after the exchange, lane l has 8 elements of row l mod 16: of the first block (even l / 16) or the second, from 0 or from 8
+        const uint32_t lane_v = (uint32_t)((eg & 1) * 16 + (eg >> 1) * 8);
+        const uint32_t off_dt = ((uint32_t)er * (uint32_t)w.lddt + lane_v) * 2u, off_ct = ((uint32_t)er * (uint32_t)w.ldct + lane_v) * 2u;
+        const uint32_t off_c = ((uint32_t)er * (uint32_t)w.ldc + (uint32_t)eg * 8u) * 2u;
+        constexpr int kQuadRow = kTM / 2;                  // a quadrant: kTN / 2 rows of Ct, kQuadRow elements of each
+        const uint32_t stage = at_place(4) + (uint32_t)(wave * kQuadRow * (kTN / 2) * 2);
+        // 16-byte vector c of row r of the staging area is at position c ^ stage_swizzle(r): 8 rows that one half of the lanes reads
+        // 32 bytes of, 0 .. 3 and 8 .. 11 of 16, lie in different banks
+        auto stage_swizzle = [](int r) {
+            return kQuadRow == 64 ? (((r >> 1) & 1) * 2 | ((r >> 3) & 1) * 4 | ((r >> 2) & 1)) : (((r >> 3) & 1) * 2 | ((r >> 2) & 1));
+        };
+        constexpr int kPer = kHM / 2 * kHN;                // 16-byte vectors per lane and quadrant
+        auto swap16 = [](uint32_t& x, uint32_t& y) {
+            const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+            x = r[0];
+            y = r[1];
+        };
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                u32x4 dv[kPer];
+                if constexpr (HAS_D) {
+#pragma unroll
+                    for (int n = 0; n < kPer; ++n) {
+                        const int i = (n % (kHM / 2)) * 2, j = n / (kHM / 2);
+                        dv[n] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(Dt + (size_t)(b * (BT / 2) + j * 16) * w.lddt + a * (BT / 2) + i * 16) + off_dt);
+                    }
+                }
+#pragma unroll
+                for (int n = 0; n < kPer; ++n) {
+                    const int i = (n % (kHM / 2)) * 2, j = n / (kHM / 2);
+                    const f32x4 s0 = acc[a * kHM + i][b * kHN + j], s1 = acc[a * kHM + i + 1][b * kHN + j];
+                    float x[4] = {alpha * s0[0], alpha * s0[1], alpha * s0[2], alpha * s0[3]};
+                    float y[4] = {alpha * s1[0], alpha * s1[1], alpha * s1[2], alpha * s1[3]};
+                    if constexpr (HAS_D) {
+                        uint32_t d0 = dv[n].x, d1 = dv[n].y, e0 = dv[n].z, e1 = dv[n].w;
+                        swap16(d0, e0);
+                        swap16(d1, e1);
+                        x[0] = fmaf(beta, bf16_lo(d0), x[0]);
+                        x[1] = fmaf(beta, bf16_hi(d0), x[1]);
+                        x[2] = fmaf(beta, bf16_lo(d1), x[2]);
+                        x[3] = fmaf(beta, bf16_hi(d1), x[3]);
+                        y[0] = fmaf(beta, bf16_lo(e0), y[0]);
+                        y[1] = fmaf(beta, bf16_hi(e0), y[1]);
+                        y[2] = fmaf(beta, bf16_lo(e1), y[2]);
+                        y[3] = fmaf(beta, bf16_hi(e1), y[3]);
+                    }
+                    uint32_t x0 = pack_bf16(x[0], x[1]), x1 = pack_bf16(x[2], x[3]), y0 = pack_bf16(y[0], y[1]), y1 = pack_bf16(y[2], y[3]);
+                    swap16(x0, y0);
+                    swap16(x1, y1);
+                    const u32x4 o = {x0, x1, y0, y1};
+                    if (Ct)
+                        *reinterpret_cast<u32x4*>(reinterpret_cast<char*>(Ct + (size_t)(b * (BT / 2) + j * 16) * w.ldct + a * (BT / 2) + i * 16) + off_ct) = o;
+                    if (C) {
+                        const int r = j * 16 + er, c = (i + (eg & 1)) * 2 + (eg >> 1);
+                        *reinterpret_cast<ADAGC_LDS u32x4*>(stage + (uint32_t)(r * kQuadRow * 2 + ((c ^ stage_swizzle(r)) * 16))) = o;
+                    }
+                }
+                if (C) {
+                    asm volatile("" ::: "memory");
+#pragma unroll
+                    for (int vb = 0; vb < kQuadRow / 16; ++vb) {
+                        // 16 lanes read 4 rows x 16 elements and get a column each: 4 consecutive elements of a row of C
+                        u32x2v t[2];
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) {
+                            const int r = 8 * eg + 4 * e + (er >> 2), c = vb * 2 + ((er & 3) >> 1);
+                            const uint32_t at = stage + (uint32_t)(r * kQuadRow * 2 + ((c ^ stage_swizzle(r)) * 16) + (er & 1) * 8);
+                            t[e] = __builtin_bit_cast(u32x2v, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<ADAGC_LDS s16x4*>(at)));
+                        }
+                        const u32x4 o = {t[0].x, t[0].y, t[1].x, t[1].y};
+                        *reinterpret_cast<u32x4*>(reinterpret_cast<char*>(C + (size_t)(a * (BT / 2) + vb * 16) * w.ldc + b * (BT / 2)) + off_c) = o;
+                    }
+                    asm volatile("" ::: "memory");
+                }
+            }
+        if (!more) return;
+        tp = tp_next;
     }
-    if (k_tiles > 2) {
-        tile(std::integral_constant<int, kLoads>{}, k, sp, sq, fp, fq);
-        ADAGC_WAIT_VMEM(0);
-        barrier_keeping_loads();
-        sp = two_on(sp);
-        sq = two_on(sq);
-        ++k;
-    }
-    tile(none, k, sp, sq, 0, 0);
-    __syncthreads();                                       // the ring is free for the epilogue
-    phase(none, fa1, fb1, nullptr, nullptr, 0, fa0, fb0, none, 0, nullptr, nullptr);
-    store_result<BT, kMI, kNI, SYM, kWaves>(lds, acc, lane, wave, wm * kTM, wn * kTN, tile_m, tile_n, alpha, beta, Dt, lddt, C, ldc, Ct,
-                                            ldct);
 }
 
 
@@ -450,8 +518,6 @@ hipError_t launch_gemm_nt_bf16(const void* P, int ldp, const void* Q, int ldq, i
     if (misaligned(P) || misaligned(Q) || misaligned(Dt) || misaligned(C) || misaligned(Ct)) return hipErrorInvalidValue;
     if (symmetric && (M != N || P != Q || stride_p != stride_q || !Ct || (C && (C != Ct || stride_c != stride_ct))))
         return hipErrorInvalidValue;
-    const uint16_t *p = static_cast<const uint16_t*>(P), *q = static_cast<const uint16_t*>(Q), *dt = static_cast<const uint16_t*>(Dt);
-    uint16_t *c = static_cast<uint16_t*>(C), *ct = static_cast<uint16_t*>(Ct);
     // Tile choice.  A compute unit holds one 256 x 256 workgroup or two 128 x 128 ones, and multiplies about a quarter
     // faster on the large tile (fewer LDS reads per matrix-core instruction); a launch costs whole rounds of workgroups.
     // Compare the two in units of "one 128-tile on a shared compute unit": a round of large tiles is 4 / 1.25 of them.
@@ -461,21 +527,45 @@ hipError_t launch_gemm_nt_bf16(const void* P, int ldp, const void* Q, int ldq, i
     const double cost128 = 2.0 * (double)((n128 + 511) / 512);
     const double cost256 = 3.2 * (double)((n256 + 255) / 256);
     const bool big = (M % 256 == 0) && (N % 256 == 0) && cost256 < cost128;
-    const int64_t blocks = big ? n256 : n128;
-    if (blocks > INT32_MAX) return hipErrorInvalidValue;
-    const GemmBatch bt{stride_p, stride_q, stride_dt, symmetric ? stride_ct : stride_c, stride_ct};
-    if (symmetric) {
-        c = ct;
-        ldc = ldct;
-        if (big)
-            gemm_nt_bf16_kernel<256, true, ADAGC_GEMM_BIG_THREADS><<<dim3((uint32_t)blocks), dim3(ADAGC_GEMM_BIG_THREADS), 0, stream>>>(p, ldp, q, ldq, M, N, K, alpha, beta, dt, lddt, c, ldc, ct, ldct, bt);
-        else
-            gemm_nt_bf16_kernel<128, true, 256><<<dim3((uint32_t)blocks), dim3(256), 0, stream>>>(p, ldp, q, ldq, M, N, K, alpha, beta, dt, lddt, c, ldc, ct, ldct, bt);
-    } else if (big) {
-        gemm_nt_bf16_kernel<256, false, ADAGC_GEMM_BIG_THREADS><<<dim3((uint32_t)blocks), dim3(ADAGC_GEMM_BIG_THREADS), 0, stream>>>(p, ldp, q, ldq, M, N, K, alpha, beta, dt, lddt, c, ldc, ct, ldct, bt);
-    } else {
-        gemm_nt_bf16_kernel<128, false, 256><<<dim3((uint32_t)blocks), dim3(256), 0, stream>>>(p, ldp, q, ldq, M, N, K, alpha, beta, dt, lddt, c, ldc, ct, ldct, bt);
-    }
+    const int64_t all = big ? n256 : n128;
+    if (all > INT32_MAX) return hipErrorInvalidValue;
+    const int bt = big ? 256 : 128;
+    GemmWork w;
+    w.p = static_cast<const uint16_t*>(P);
+    w.q = static_cast<const uint16_t*>(Q);
+    w.dt = static_cast<const uint16_t*>(Dt);
+    w.ct = static_cast<uint16_t*>(Ct);
+    w.c = symmetric ? w.ct : static_cast<uint16_t*>(C);
+    w.stride_p = stride_p;
+    w.stride_q = stride_q;
+    w.stride_dt = stride_dt;
+    w.stride_c = symmetric ? stride_ct : stride_c;
+    w.stride_ct = stride_ct;
+    w.ldp = ldp;
+    w.ldq = ldq;
+    w.lddt = lddt;
+    w.ldc = symmetric ? ldct : ldc;
+    w.ldct = ldct;
+    w.k = K;
+    w.tiles_m = M / bt;
+    w.tiles_n = N / bt;
+    w.tiles = (int32_t)(big ? t256 : t128);
+    w.all = (int32_t)all;
+    w.alpha = alpha;
+    w.beta = beta;
+    // as many workgroups as the chip holds at a time, if there are tiles for them: 32 (64) on each of 8 XCDs
+    const dim3 grid(8u * (uint32_t)std::min<int64_t>((all + 7) / 8, big ? 32 : 64));
+    auto launch = [&](auto SYM, auto HAS_D) {
+        constexpr bool sym = decltype(SYM)::value, has_d = decltype(HAS_D)::value;
+        if (big) gemm_nt_bf16_kernel<256, sym, has_d, 512><<<grid, dim3(512), 0, stream>>>(w);
+        else gemm_nt_bf16_kernel<128, sym, has_d, 256><<<grid, dim3(256), 0, stream>>>(w);
+    };
+    const std::true_type yes{};
+    const std::false_type no{};
+    if (symmetric && Dt) launch(yes, yes);
+    else if (symmetric) launch(yes, no);
+    else if (Dt) launch(no, yes);
+    else launch(no, no);
     return hipGetLastError();
 }
 

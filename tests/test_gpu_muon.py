@@ -785,3 +785,30 @@ def test_muon_attach_takes_smaller_batches_when_memory_is_short():
     ctx.muon_attach([shape] * count)
     assert ctx.muon_workspace_bytes() == 32 * per_matrix
     ctx.close()
+
+
+@pytest.mark.parametrize("batch,M,N,K,symmetric", [
+    (40, 640, 640, 256, True),           # 128-tiles: 600 of them for 512 workgroups, 5 a side (a panel of 4 columns and one of 1)
+    (15, 1280, 1536, 384, False),        # 256-tiles: 450 for 256 workgroups
+    (7, 2304, 2304, 640, True),          # 256-tiles: 315 (9 a side)
+    (300, 128, 128, 128, True)])         # a tile per matrix
+def test_matrix_core_product_when_workgroups_take_several_tiles(batch, M, N, K, symmetric):
+    """A workgroup takes one tile of every round, its next tile's operands on their way while it stores the last one's results.
+    Small integers: every sum is exact in fp32 (|sum| <= 4 K + 8), so the result is the exact one rounded once."""
+    gen = torch.Generator(device=DEV).manual_seed(K + M)
+    P = torch.randint(-2, 3, (batch, M, K), generator=gen, device=DEV).to(torch.float32)
+    Q = P if symmetric else torch.randint(-2, 3, (batch, N, K), generator=gen, device=DEV).to(torch.float32)
+    D = torch.randint(-4, 5, (batch, M, N), generator=gen, device=DEV).to(torch.float32)
+    if symmetric:
+        D = torch.tril(D) + torch.tril(D, -1).transpose(1, 2)
+    ref = torch.stack([(P[z].double() @ Q[z].double().t() + 2.0 * D[z].double()) for z in range(batch)]).to(torch.bfloat16)
+    dP = P.to(torch.bfloat16)
+    dQ = dP if symmetric else Q.to(torch.bfloat16)
+    dDt = D.transpose(1, 2).contiguous().to(torch.bfloat16)
+    for with_c, with_ct in ((False, True),) if symmetric else ((True, True), (True, False), (False, True)):
+        C = torch.zeros((batch, M, N), dtype=torch.bfloat16, device=DEV) if with_c else None
+        Ct = torch.zeros((batch, N, M), dtype=torch.bfloat16, device=DEV) if with_ct else None
+        B.adagc_muon_gemm_nt_batched(dP, dQ, 1.0, 2.0, dDt, C, Ct, symmetric=symmetric)
+        torch.cuda.synchronize()
+        assert C is None or torch.equal(C, ref)
+        assert Ct is None or torch.equal(Ct, ref.transpose(1, 2))
