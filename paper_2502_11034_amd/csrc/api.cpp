@@ -1,9 +1,11 @@
 // Host side of libadagc: context, argument validation, per-step scalar preparation and
 // kernel sequencing.  See include/adagc.h for the contract of every entry point.
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
+#include <utility>
 #include <vector>
 
 #include "adagc_internal.h"
@@ -55,7 +57,7 @@ struct adagc_ctx {
         int mp = 0, np = 0;                  // padded extent of the wide orientation
         std::vector<int64_t> members;        // tensor indices
         int64_t first = 0;                   // place of its first record in muon_matrices
-        int64_t largest = 0;                 // elements of its largest matrix
+        int64_t apply_blocks = 0;            // the most workgroups that the update of one of them needs
     };
     std::vector<adagc_matrix_shape> shapes;
     std::vector<MuonBatch> muon_batches;
@@ -581,11 +583,11 @@ extern "C" int adagc_muon_attach(adagc_ctx* ctx, const adagc_matrix_shape* shape
         std::vector<MuonMatrix> records;
         for (adagc_ctx::MuonBatch& bt : batches) {
             bt.first = (int64_t)records.size();
-            bt.largest = 0;
+            bt.apply_blocks = 0;
             for (int64_t i : bt.members) {
                 const int64_t r = shapes[i].rows, c = shapes[i].cols;
                 records.push_back(MuonMatrix{(uint32_t)i, 0u, r, c, std::sqrt(r > c ? (double)r / (double)c : 1.0)});
-                if (r * c > bt.largest) bt.largest = r * c;
+                bt.apply_blocks = std::max(bt.apply_blocks, muon_apply_blocks(r, c));
             }
         }
         const size_t bytes = records.size() * sizeof(MuonMatrix);
@@ -655,45 +657,21 @@ extern "C" int adagc_muon_step(adagc_ctx* ctx, void* const* params, const void* 
     if (launch_muon_momentum(t, mu, mh->nesterov, bf16g, ctx->grid_norm, stream) != hipSuccess) return ADAGC_ERR_HIP;
     if (launch_tensor_sumsq(t, stream) != hipSuccess) return ADAGC_ERR_HIP;
 
-    // Newton-Schulz and the update, batch by batch.  Matrix z of a batch has slot z of each workspace array:
-    // X is mp x np (leading dimension np), Y = X^T is np x mp (leading dimension mp), A and B are mp x mp.
-    const float ns_a = 3.4445f, ns_b = -4.7750f, ns_c = 2.0315f;
+    // Newton-Schulz and the update, batch by batch.
     for (const adagc_ctx::MuonBatch& bt : ctx->muon_batches) {
-        const int mp = bt.mp, np = bt.np;
         const int count = (int)bt.members.size();
-        const int64_t mn = (int64_t)mp * np, mm = (int64_t)mp * mp;
+        const int64_t mn = (int64_t)bt.mp * bt.np, mm = (int64_t)bt.mp * bt.mp;
         uint16_t* base = static_cast<uint16_t*>(ctx->muon_ws);
-        uint16_t *x = base, *x2 = base + count * mn, *y = base + 2 * count * mn, *y2 = base + 3 * count * mn;
-        uint16_t *wa = base + 4 * count * mn, *wb = wa + count * mm;
-        if (launch_muon_normalise(t, ctx->muon_matrices + bt.first, count, mp, np, mu, mh->nesterov, bf16g, x, y, stream) != hipSuccess)
-            return ADAGC_ERR_HIP;
-        bool any_tall = false, any_wide = false;
-        for (int64_t i : bt.members) {
-            if (ctx->shapes[(size_t)i].rows > ctx->shapes[(size_t)i].cols) any_tall = true;
-            else any_wide = true;
-        }
+        MuonGroup g{bt.mp, bt.np, count, base, base + count * mn, base + 2 * count * mn, base + 2 * count * mn + count * mm};
+        const MuonMatrix* members = ctx->muon_matrices + bt.first;
+        if (launch_muon_normalise(t, members, count, bt.mp, bt.np, mu, mh->nesterov, bf16g, g.x, stream) != hipSuccess) return ADAGC_ERR_HIP;
         for (int k = 0; k < mh->ns_steps; ++k) {
-            // A = X X^T (symmetric: its transposed store is itself)
-            if (launch_gemm_nt_bf16(x, np, x, np, mp, mp, np, 1.0f, 0.0f, nullptr, 0, nullptr, 0, wa, mp, stream, true, count, mn, mn,
-                                    0, mm, mm) != hipSuccess)
-                return ADAGC_ERR_HIP;
-            // B = b A + c A A
-            if (launch_gemm_nt_bf16(wa, mp, wa, mp, mp, mp, mp, ns_c, ns_b, wa, mp, nullptr, 0, wb, mp, stream, true, count, mm, mm, mm,
-                                    mm, mm) != hipSuccess)
-                return ADAGC_ERR_HIP;
-            // X' = a X + B X, written as X' and as Y' = X'^T; (B X)[i][j] = sum_k B[i][k] Y[j][k].  After the last step
-            // only the orientation the update reads is needed: X' for wide matrices, Y' for tall ones.
-            const bool last = k + 1 == mh->ns_steps;
-            uint16_t* out_x = (last && !any_wide) ? nullptr : x2;
-            uint16_t* out_y = (last && !any_tall) ? nullptr : y2;
-            if (launch_gemm_nt_bf16(wb, mp, y, mp, mp, np, mp, 1.0f, ns_a, y, mp, out_x, np, out_y, mp, stream, false, count, mm, mn, mn,
-                                    mn, mn) != hipSuccess)
-                return ADAGC_ERR_HIP;
-            uint16_t* s = x; x = x2; x2 = s;
-            s = y; y = y2; y2 = s;
+            for (const MuonProduct product : {MuonProduct::gram, MuonProduct::poly, MuonProduct::next})
+                if (launch_muon_product(product, g, stream) != hipSuccess) return ADAGC_ERR_HIP;
+            std::swap(g.x, g.x2);
         }
-        if (launch_muon_apply(t, ctx->muon_matrices + bt.first, count, bt.largest, mp, np, x, y, (double)h.lr, (double)h.weight_decay,
-                              copy, stream) != hipSuccess)
+        if (launch_muon_apply(t, members, count, bt.apply_blocks, bt.mp, bt.np, g.x, (double)h.lr, (double)h.weight_decay, copy, stream) !=
+            hipSuccess)
             return ADAGC_ERR_HIP;
     }
     if (prof) {

@@ -5,7 +5,7 @@
 //   muon_momentum_kernel    per chunk:  M <- mu M + h g;  partial sum of squares of U
 //                                       (U = h g + mu M in the Nesterov form, U = M otherwise)
 //   muon_normalise_kernel   per batch:  X0 = bf16(U / (||U||_F + 1e-7)) of every matrix into the zero-padded workspace,
-//                                       row-major and transposed (the matrix-core products want both, see muon_gemm.hip)
+//                                       tall ones transposed
 //   muon_apply_kernel       per batch:  theta <- theta - lr (wd theta + scale O) of every matrix, optional bf16 copy
 //
 // A batch is one launch of each, over all of its matrices: a matrix of a few hundred rows is read in two microseconds,
@@ -107,8 +107,8 @@ __global__ __launch_bounds__(kBlock) void muon_momentum_kernel(DeviceTables t, d
     }
 }
 
-// What a workgroup needs to know about matrix z of its batch.  The iteration runs on the wide orientation: X is mp x np,
-// Y = X^T; a tall matrix is its own Y.
+// What a workgroup needs to know about matrix z of its batch.  The iteration runs on the wide orientation: X is mp x np, the
+// transpose of a tall matrix.
 struct MatrixView {
     uint32_t tensor;
     int64_t  rows, cols;
@@ -127,14 +127,14 @@ __device__ __forceinline__ bool is_aligned(const void* p, uintptr_t a) { return 
 
 // One 64 x 64 tile of X0.  The source U (rows x cols, recomputed from g and the updated momentum) is walked in tiles of
 // its extent padded to multiples of 128; every element of the padded extent is written: zeros outside the matrix.
-// same[r][c] (leading dimension ld_same) receives the tile as is, trans[c][r] (ld_trans) its transpose, through LDS so
-// that both are written along their rows.
+// x: the matrix's X, rows of ld_x elements: U as it is, or, of a tall matrix, its transpose, through LDS so that it is written
+// along its rows.
 // VEC (cols a multiple of 4, g and m aligned to their elements): a lane handles 4 consecutive elements of a
-// row on the way in and 4 consecutive elements of a transposed row on the way out: 16-byte loads, 8-byte stores.
+// row on the way in and 4 consecutive elements of a row of X on the way out: 16-byte loads, 8-byte stores.
 template <bool BF16, bool VEC>
 __device__ __forceinline__ void normalise_tile(uint16_t* tile, gcbytes g, gcfloat m, int64_t rows, int64_t cols, int64_t r0,
-                                               int64_t c0, double h, double denom, double mu, int nesterov, uint16_t* same,
-                                               int64_t ld_same, uint16_t* trans, int64_t ld_trans)
+                                               int64_t c0, double h, double denom, double mu, int nesterov, bool tall, uint16_t* x,
+                                               int64_t ld_x)
 {
     constexpr int kTileLd = VEC ? 68 : 66;                 // u16 per LDS row (VEC: rows stay 8-byte aligned)
     auto x0_bits = [&](float gv, float mv) {
@@ -163,17 +163,17 @@ __device__ __forceinline__ void normalise_tile(uint16_t* tile, gcbytes g, gcfloa
                 bits.x = x0_bits(gv[k].x, mv[k].x) | (x0_bits(gv[k].y, mv[k].y) << 16);
                 bits.y = x0_bits(gv[k].z, mv[k].z) | (x0_bits(gv[k].w, mv[k].w) << 16);
             }
-            *reinterpret_cast<u32x2*>(&tile[tr * kTileLd + q]) = bits;
-            *reinterpret_cast<u32x2*>(same + (r0 + tr) * ld_same + c0 + q) = bits;
+            *reinterpret_cast<u32x2*>(tall ? &tile[tr * kTileLd + q] : x + (r0 + tr) * ld_x + c0 + q) = bits;
         }
+        if (!tall) return;                                                     // the same for the whole workgroup
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const int tc = p + 16 * k;                                         // column of the tile = row of the transpose
+            const int tc = p + 16 * k;                                         // column of the tile = row of X
             u32x2 bits;
             bits.x = (uint32_t)tile[(q + 0) * kTileLd + tc] | ((uint32_t)tile[(q + 1) * kTileLd + tc] << 16);
             bits.y = (uint32_t)tile[(q + 2) * kTileLd + tc] | ((uint32_t)tile[(q + 3) * kTileLd + tc] << 16);
-            *reinterpret_cast<u32x2*>(trans + (c0 + tc) * ld_trans + r0 + q) = bits;
+            *reinterpret_cast<u32x2*>(x + (c0 + tc) * ld_x + r0 + q) = bits;
         }
     } else {
         const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
@@ -185,73 +185,123 @@ __device__ __forceinline__ void normalise_tile(uint16_t* tile, gcbytes g, gcfloa
                 const int64_t j = r * cols + c;
                 bits = (uint16_t)x0_bits(load_grad1<BF16>(g + j * (BF16 ? 2 : 4), 0), m[j]);
             }
-            tile[(ty + 4 * k) * kTileLd + tx] = bits;
-            same[r * ld_same + c] = bits;
+            if (tall) tile[(ty + 4 * k) * kTileLd + tx] = bits;
+            else x[r * ld_x + c] = bits;
         }
+        if (!tall) return;
         __syncthreads();
 #pragma unroll 4
         for (int k = 0; k < 16; ++k) {
             const int64_t c = c0 + ty + 4 * k, r = r0 + tx;
-            trans[c * ld_trans + r] = tile[tx * kTileLd + ty + 4 * k];
+            x[c * ld_x + r] = tile[tx * kTileLd + ty + 4 * k];
         }
     }
 }
 
-// Workgroup (b, z): tile b of matrix z of the batch.  x, y: the batch's arrays, matrix z at z * mp * np.
+// Workgroup (b, z): tile b of matrix z of the batch.  x: the batch's array, matrix z at z * mp * np.
 template <bool BF16>
 __global__ __launch_bounds__(256) void muon_normalise_kernel(DeviceTables t, const MuonMatrix* members, int mp, int np, double mu,
-                                                              int nesterov, uint16_t* x, uint16_t* y)
+                                                              int nesterov, uint16_t* x)
 {
     __shared__ __attribute__((aligned(8))) uint16_t tile[64 * 68];
     const MatrixView mv = matrix_view(members, blockIdx.y);
     const TensorArgs ta = load_tensor(t.targs, mv.tensor);
     const uint32_t tile_cols = (uint32_t)((mv.tall ? mp : np) / 64);
     const int64_t r0 = (int64_t)(blockIdx.x / tile_cols) * 64, c0 = (int64_t)(blockIdx.x % tile_cols) * 64;
-    const int64_t at = (int64_t)blockIdx.y * mp * np;
-    uint16_t *same = (mv.tall ? y : x) + at, *trans = (mv.tall ? x : y) + at;
-    const int64_t ld_same = mv.tall ? mp : np, ld_trans = mv.tall ? np : mp;
+    x += (int64_t)blockIdx.y * mp * np;
     const double h = uniform_load(t.coef64 + mv.tensor);
     const double denom = sqrt(uniform_load(t.sumsq + mv.tensor)) + 1e-7;
     const gcbytes g = (gcbytes)ta.grad;
     const gcfloat m = (gcfloat)ta.exp_avg;
     // the workspace is padded to 128 elements a row, so only the caller's arrays decide
     if (mv.cols % 4 == 0 && is_aligned(ta.grad, BF16 ? 2 : 4) && is_aligned(ta.exp_avg, 4))
-        normalise_tile<BF16, true>(tile, g, m, mv.rows, mv.cols, r0, c0, h, denom, mu, nesterov, same, ld_same, trans, ld_trans);
+        normalise_tile<BF16, true>(tile, g, m, mv.rows, mv.cols, r0, c0, h, denom, mu, nesterov, mv.tall, x, np);
     else
-        normalise_tile<BF16, false>(tile, g, m, mv.rows, mv.cols, r0, c0, h, denom, mu, nesterov, same, ld_same, trans, ld_trans);
+        normalise_tile<BF16, false>(tile, g, m, mv.rows, mv.cols, r0, c0, h, denom, mu, nesterov, mv.tall, x, np);
 }
 
-// theta <- theta - lr (wd theta + scale O); workgroup (b, z): elements b * 4096 ... of matrix z of the batch, which O
-// (bf16, rows of ld_o elements) holds row by row.
-// 4096 elements per workgroup whatever the row length: with a workgroup per row, a row of 768 kept 192 of 256 lanes busy
-// with one access each.
+// theta <- theta - lr (wd theta + scale O), O being X (bf16, rows of np elements) or, of a tall matrix, its transpose.
+// Workgroup (b, z) of matrix z of the batch: elements b * 4096 ..., whatever the row length (with a workgroup per row, a row of
+// 768 kept 192 of 256 lanes busy with one access each); of a tall matrix tile b of 64 x 64, O through LDS.
 // Where cols is a multiple of 4 and theta (and the copy) are aligned to their elements: 4 elements per lane and access.
 constexpr int kApplyElems = 4096;
 template <bool COPY>
 __global__ __launch_bounds__(256) void muon_apply_kernel(DeviceTables t, const MuonMatrix* members, int mp, int np, const uint16_t* x,
-                                                          const uint16_t* y, double lr, double wd)
+                                                          double lr, double wd)
 {
+    __shared__ __attribute__((aligned(8))) uint16_t tile[64 * 68];
     const MatrixView mv = matrix_view(members, blockIdx.y);
     const TensorArgs ta = load_tensor(t.targs, mv.tensor);
-    const int64_t numel = mv.rows * mv.cols, first = (int64_t)blockIdx.x * kApplyElems;
-    if (first >= numel) return;
-    const int len = numel - first < kApplyElems ? (int)(numel - first) : kApplyElems;
     const double scale = mv.scale;
-    const int64_t ld_o = mv.tall ? mp : np;
-    const uint16_t* o = (mv.tall ? y : x) + (int64_t)blockIdx.y * mp * np;
-    const gfloat theta = (gfloat)ta.param + first;
-    const gu16 copy = COPY ? (gu16)ta.param_copy + first : nullptr;
-    const uint32_t cols = (uint32_t)mv.cols;
-    const int64_t row0 = first / mv.cols;                           // the same in all lanes
-    const uint32_t col0 = (uint32_t)(first - row0 * mv.cols);
-    o += row0 * ld_o;
+    x += (int64_t)blockIdx.y * mp * np;
+    const bool vec = mv.cols % 4 == 0 && is_aligned(ta.param, 4) && (!COPY || is_aligned(ta.param_copy, 2));
     auto one = [&](float th_f, uint32_t o_bits) {
         const double th = (double)th_f;
         const double ov = (double)__uint_as_float(o_bits << 16);
         return (float)(th - lr * (wd * th + scale * ov));
     };
+    auto four = [&](gfloat theta, gu16 copy, f32x4 th, uint32_t o0, uint32_t o1, uint32_t o2, uint32_t o3) {
+        const f32x4 out = {one(th.x, o0), one(th.y, o1), one(th.z, o2), one(th.w, o3)};
+        st<true>((ADAGC_GLOBAL f32x4_any*)theta, out);
+        if constexpr (COPY) {
+            u32x2 cw;
+            cw.x = float_to_bf16_bits(out.x) | (float_to_bf16_bits(out.y) << 16);
+            cw.y = float_to_bf16_bits(out.z) | (float_to_bf16_bits(out.w) << 16);
+            st<true>((ADAGC_GLOBAL u32x2_any*)copy, cw);
+        }
+    };
     const int tid = threadIdx.x;
-    if (cols % 4 == 0 && is_aligned(ta.param, 4) && (!COPY || is_aligned(ta.param_copy, 2))) {
+    if (mv.tall) {
+        const int64_t tile_cols = (mv.cols + 63) / 64;
+        const int64_t r0 = blockIdx.x / tile_cols * 64, c0 = blockIdx.x % tile_cols * 64;
+        if (r0 >= mv.rows) return;
+        const int q = (tid & 15) * 4, p = tid >> 4;                            // 16 lanes per row, 16 rows per pass
+        const gfloat theta = (gfloat)ta.param + r0 * mv.cols + c0;
+        const gu16 copy = COPY ? (gu16)ta.param_copy + r0 * mv.cols + c0 : nullptr;
+        const int rows = (int)(mv.rows - r0 < 64 ? mv.rows - r0 : 64), cols = (int)(mv.cols - c0 < 64 ? mv.cols - c0 : 64);
+        u32x2 ow[4];
+        f32x4 th[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)                                            // column c0 + ... of theta, 4 of its rows
+            ow[k] = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(x + (c0 + p + 16 * k) * np + r0 + q));
+        if (vec) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (p + 16 * k < rows && q < cols) th[k] = ld<true>((const ADAGC_GLOBAL f32x4_any*)(theta + (int64_t)(p + 16 * k) * mv.cols + q));
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) *reinterpret_cast<u32x2*>(&tile[(p + 16 * k) * 68 + q]) = ow[k];
+        __syncthreads();
+        if (vec) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int r = p + 16 * k;
+                const int64_t e = (int64_t)r * mv.cols + q;
+                if (r < rows && q < cols)
+                    four(theta + e, COPY ? copy + e : nullptr, th[k], tile[q * 68 + r], tile[(q + 1) * 68 + r], tile[(q + 2) * 68 + r], tile[(q + 3) * 68 + r]);
+            }
+        } else {
+            const int c = tid & 63;
+            for (int r = tid >> 6; r < rows; r += 4) {
+                if (c >= cols) continue;
+                const int64_t e = (int64_t)r * mv.cols + c;
+                const float out = one(theta[e], tile[c * 68 + r]);
+                theta[e] = out;
+                if constexpr (COPY) copy[e] = (uint16_t)float_to_bf16_bits(out);
+            }
+        }
+        return;
+    }
+    const int64_t numel = mv.rows * mv.cols, first = (int64_t)blockIdx.x * kApplyElems;
+    if (first >= numel) return;
+    const int len = numel - first < kApplyElems ? (int)(numel - first) : kApplyElems;
+    const gfloat theta = (gfloat)ta.param + first;
+    const gu16 copy = COPY ? (gu16)ta.param_copy + first : nullptr;
+    const uint32_t cols = (uint32_t)mv.cols;
+    const int64_t row0 = first / mv.cols;                           // the same in all lanes
+    const uint32_t col0 = (uint32_t)(first - row0 * mv.cols);
+    const uint16_t* o = x + row0 * np;
+    if (vec) {
         constexpr int kPer = kApplyElems / 4 / 256;
         f32x4 th[kPer];
         u32x2 ow[kPer];
@@ -261,29 +311,18 @@ __global__ __launch_bounds__(256) void muon_apply_kernel(DeviceTables t, const M
             if ((int)e >= len) continue;                            // len is a multiple of 4 here, as cols is
             const uint32_t q = col0 + e, r = q / cols, c = q - r * cols;
             th[u] = ld<true>((const ADAGC_GLOBAL f32x4_any*)(theta + e));
-            ow[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(o + (int64_t)r * ld_o + c));
+            ow[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(o + (int64_t)r * np + c));
         }
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
             const uint32_t e = (uint32_t)(u * 256 + tid) * 4u;
             if ((int)e >= len) continue;
-            f32x4 out;
-            out.x = one(th[u].x, ow[u].x & 0xFFFFu);
-            out.y = one(th[u].y, ow[u].x >> 16);
-            out.z = one(th[u].z, ow[u].y & 0xFFFFu);
-            out.w = one(th[u].w, ow[u].y >> 16);
-            st<true>((ADAGC_GLOBAL f32x4_any*)(theta + e), out);
-            if constexpr (COPY) {
-                u32x2 cw;
-                cw.x = float_to_bf16_bits(out.x) | (float_to_bf16_bits(out.y) << 16);
-                cw.y = float_to_bf16_bits(out.z) | (float_to_bf16_bits(out.w) << 16);
-                st<true>((ADAGC_GLOBAL u32x2_any*)(copy + e), cw);
-            }
+            four(theta + e, COPY ? copy + e : nullptr, th[u], ow[u].x & 0xFFFFu, ow[u].x >> 16, ow[u].y & 0xFFFFu, ow[u].y >> 16);
         }
     } else {
         for (int e = tid; e < len; e += 256) {
             const uint32_t q = col0 + (uint32_t)e, r = q / cols, c = q - r * cols;
-            const float out = one(theta[e], o[(int64_t)r * ld_o + c]);
+            const float out = one(theta[e], o[(int64_t)r * np + c]);
             theta[e] = out;
             if constexpr (COPY) copy[e] = (uint16_t)float_to_bf16_bits(out);
         }
@@ -300,20 +339,26 @@ hipError_t launch_muon_momentum(const DeviceTables& t, double mu, int nesterov, 
 }
 
 hipError_t launch_muon_normalise(const DeviceTables& t, const MuonMatrix* members, int count, int mp, int np, double mu, int nesterov,
-                                 int grad_bf16, uint16_t* x, uint16_t* y, hipStream_t stream)
+                                 int grad_bf16, uint16_t* x, hipStream_t stream)
 {
     const dim3 grid((uint32_t)(mp / 64) * (uint32_t)(np / 64), (uint32_t)count);
-    if (grad_bf16) muon_normalise_kernel<true><<<grid, dim3(256), 0, stream>>>(t, members, mp, np, mu, nesterov, x, y);
-    else muon_normalise_kernel<false><<<grid, dim3(256), 0, stream>>>(t, members, mp, np, mu, nesterov, x, y);
+    if (grad_bf16) muon_normalise_kernel<true><<<grid, dim3(256), 0, stream>>>(t, members, mp, np, mu, nesterov, x);
+    else muon_normalise_kernel<false><<<grid, dim3(256), 0, stream>>>(t, members, mp, np, mu, nesterov, x);
     return hipGetLastError();
 }
 
-hipError_t launch_muon_apply(const DeviceTables& t, const MuonMatrix* members, int count, int64_t largest, int mp, int np,
-                             const uint16_t* x, const uint16_t* y, double lr, double wd, int with_copy, hipStream_t stream)
+int64_t muon_apply_blocks(int64_t rows, int64_t cols)
 {
-    const dim3 grid((uint32_t)((largest + kApplyElems - 1) / kApplyElems), (uint32_t)count);
-    if (with_copy) muon_apply_kernel<true><<<grid, dim3(256), 0, stream>>>(t, members, mp, np, x, y, lr, wd);
-    else muon_apply_kernel<false><<<grid, dim3(256), 0, stream>>>(t, members, mp, np, x, y, lr, wd);
+    if (rows > cols) return ((rows + 63) / 64) * ((cols + 63) / 64);
+    return (rows * cols + kApplyElems - 1) / kApplyElems;
+}
+
+hipError_t launch_muon_apply(const DeviceTables& t, const MuonMatrix* members, int count, int64_t blocks, int mp, int np,
+                             const uint16_t* x, double lr, double wd, int with_copy, hipStream_t stream)
+{
+    const dim3 grid((uint32_t)blocks, (uint32_t)count);
+    if (with_copy) muon_apply_kernel<true><<<grid, dim3(256), 0, stream>>>(t, members, mp, np, x, lr, wd);
+    else muon_apply_kernel<false><<<grid, dim3(256), 0, stream>>>(t, members, mp, np, x, lr, wd);
     return hipGetLastError();
 }
 

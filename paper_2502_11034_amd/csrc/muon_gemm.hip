@@ -4,13 +4,13 @@
 //   C[i][j] = bf16( alpha * sum_k P[i][k] * Q[j][k]  +  beta * D[i][j] )            ("NT": both operands K-contiguous)
 //
 // P is M x K, Q is N x K, both row-major bf16 with K contiguous, which is the layout the matrix-core
-// instruction wants for both operands: every lane's fragment is 16 contiguous bytes.  All three products
-// of one Newton-Schulz step have this form when X is kept together with its transpose Y:
+// instruction wants for both operands: every lane's fragment is 16 contiguous bytes.  The result is written row-major (C),
+// transposed (Ct, N x M), or both; D is read through its transpose Dt (N x M).  The three products of a Newton-Schulz step are
 //   A  = X X^T                P = Q = X                       (alpha 1, beta 0)
 //   B  = b A + c A A          P = Q = A (A is symmetric)      (alpha c, beta b, D = A)
-//   X' = a X + B X            P = B, Q = Y = X^T              (alpha 1, beta a, D = X)
-// The result is written row-major (C), transposed (Ct, N x M), or both; D is read through its transpose
-// Dt (N x M).
+//   X' = a X + B X            as X'^T = a X^T + X^T B with P = X^T, given by its transpose X, and Q = B; X' is Ct
+// so that X is kept and written in one orientation only.  (With X and its transpose, written by each step, 12 products of
+// 4096 x 14336 x 4096 took 4973 us and 24 of 768 x 3072 x 768 167 us; with X alone 4532 and 139.)
 //
 // A = X X^T and A A are symmetric: for those only the tiles on and below the diagonal are computed and each is
 // written twice, to its place and to its mirror image, which saves about a quarter of a step's multiplications.
@@ -199,11 +199,22 @@ __device__ __forceinline__ void load_to_lds_16(const void* base, uint32_t off, c
 // meanwhile, and the stores complete during its first half steps.  (One workgroup per tile and all of LDS as the staging tile:
 // 4866 us for 12 products of 4096 x 14336 x 4096 with D, C and Ct, now 4706; X X^T as above 2373, now 2296.  Loading D
 // already in the last half step changed nothing.)
-template <int BT, bool SYM, bool HAS_D, int kGemmThreads>
+//
+// PTR: P is given by its transpose, K rows of M consecutive elements (X itself in B X), and its fragments are read transposed
+// (ds_read_b64_tr_b16, two for the 16 bytes of a lane).  Only Ct then.
+// DSource::operand: D is what a part of P's rows and columns holds (A in b A + c A A, X in a X + B X), and is added to the sums
+// while that part lies in LDS, before the 64 products of its place in k: with D as an array 12 products of 14336 x 4096 x 4096
+// took 4369 us, now 4262, and 24 of 3072 x 768 x 768 114 us, now 97 (the 128 KB per tile came all at once, in every compute
+// unit at the same time).  In a symmetric product an element and its mirror image have the same place in k, the lesser of their
+// rows, so the result does not depend on the size of the tiles.
+enum class DSource { none, array, operand };
+template <int BT, bool SYM, bool PTR, DSource D_SOURCE, int kGemmThreads>
 __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const GemmWork)
 {
     constexpr int kWaves = kGemmThreads / 64;
-    constexpr int kWM = 2, kWN = kWaves / kWM;             // waves in a kWM x kWN grid
+    constexpr bool HAS_D = D_SOURCE == DSource::array;
+    // waves in a kWM x kWN grid; with PTR the reads of P are the more expensive ones, so a wave has fewer of its rows
+    constexpr int kWM = PTR ? kWaves / 2 : 2, kWN = kWaves / kWM;
     constexpr int kTM = BT / kWM, kTN = BT / kWN;          // wave tile
     constexpr int kHM = kTM / 32, kHN = kTN / 32;          // 16 x 16 accumulators per quadrant
     constexpr int kUnitElems = BT / 2 * kBK;               // half of an operand tile
@@ -232,7 +243,12 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
     // clock over 64 banks) are avoided by a swizzle instead: the 16-byte vector v of row r sits at position v ^ ((r / 2) mod 8)
     // of its LDS row, which the loading lane applies on the global side.  The rows of a load start at a multiple of 8, and
     // (r / 2) mod 8 = (4 (wave mod 2) + lane / 16) mod 8 because kWaves is even.
+    // PTR: P's half is 64 rows (k) of BT / 2 elements, 4 (8) rows per load.  A fragment read takes 32 bytes, a block's 16 columns, of
+    // 4 rows each for 16 lanes: of rows 0 .. 3 and 8 .. 11 (and 16 more) at a time.  The 32-byte unit u of row r is at position
+    // u ^ swizzle_p(r), so that these lie in different banks.
     // The address is split into a part common to the wave (scalar registers) and one 32-bit offset per lane.
+    auto swizzle_p = [](int r) { return BT == 256 ? ((r & 3) | ((r >> 3) & 1) << 2) : (((r >> 1) & 1) | ((r >> 3) & 1) << 1); };
+    constexpr int kPtrRows = 1024 / BT;                    // rows per load
     struct Source {
         const uint16_t *p, *q;
         int ldp, ldq;
@@ -246,26 +262,51 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
         Source s;
         s.ldp = w.ldp;
         s.ldq = w.ldq;
-        s.p = w.p + (size_t)t.z * w.stride_p + (size_t)t.tile_m * BT * w.ldp;
+        s.p = w.p + (size_t)t.z * w.stride_p + (PTR ? (size_t)t.tile_m * BT : (size_t)t.tile_m * BT * w.ldp);
         s.q = w.q + (size_t)t.z * w.stride_q + (size_t)t.tile_n * BT * w.ldq;
-        s.off_p = (uint32_t)(row * w.ldp + vec * 8) * 2u;
+        if constexpr (PTR) {
+            constexpr int kRowLanes = BT / 16;
+            const int r = l / kRowLanes;
+            s.off_p = (uint32_t)(r * w.ldp + ((l % kRowLanes) ^ (2 * swizzle_p(wave * kPtrRows + r))) * 8) * 2u;
+        } else {
+            s.off_p = (uint32_t)(row * w.ldp + vec * 8) * 2u;
+        }
         s.off_q = (uint32_t)(row * w.ldq + vec * 8) * 2u;
         return s;
     };
     auto load = [&](const Source& s, int n, int g, uint16_t* dst) {
         const int first = ((n >> 1) * kWaves + wave) * 8, k0 = (g >> 1) * kBK;
         const size_t row = (size_t)((g & 1) * (BT / 2) + first);
-        if (n & 1) load_to_lds_16(s.q + row * s.ldq + k0, s.off_q, dst + first * kBK);
-        else load_to_lds_16(s.p + row * s.ldp + k0, s.off_p, dst + kUnitElems + first * kBK);
+        if (n & 1) {
+            load_to_lds_16(s.q + row * s.ldq + k0, s.off_q, dst + first * kBK);
+        } else if constexpr (PTR) {
+            // kWaves kPtrRows is a multiple of 16: the swizzle does not depend on n
+            const int r = ((n >> 1) * kWaves + wave) * kPtrRows;
+            load_to_lds_16(s.p + (size_t)(k0 + r) * s.ldp + (g & 1) * (BT / 2), s.off_p, dst + kUnitElems + r * (BT / 2));
+        } else {
+            load_to_lds_16(s.p + row * s.ldp + k0, s.off_p, dst + kUnitElems + first * kBK);
+        }
     };
 
     // Fragments.  Lane l holds row l mod 16 of its 16-row block and the 16-byte vector 4 kk + l / 16 of that row; a block's first
     // row is a multiple of 16, so (row / 2) mod 8 = (l / 2) mod 8, and slice kk = 1 is 64 bytes from slice 0 by exclusive or.
+    // PTR: lane l gets column l mod 16 of a block in slice kk, 8 rows from 8 (l / 16) on, and supplies the address of 4 columns in
+    // one of them; block i is 32 i bytes away by exclusive or, slices and rows by addition.
     // The addresses in the place that is read are made once per half step (opaque, so that what is left of them is immediate).
     const uint32_t frag = (uint32_t)((lane & 15) * kBK * 2 + (((lane >> 4) ^ ((lane >> 1) & 7)) * 16));
     const uint32_t frag_q = frag + (uint32_t)(wn * (kTN / 2) * kBK * 2);
-    const uint32_t frag_p = frag + (uint32_t)((kUnitElems + wm * (kTM / 2) * kBK) * 2);
-    auto addresses = [](uint32_t offset, uint32_t at, uint32_t (&a)[2]) {
+    const int ptr_row = 8 * (lane >> 4) + ((lane >> 2) & 3);
+    const uint32_t frag_p = PTR ? (uint32_t)(kUnitElems * 2 + ptr_row * BT + ((wm * kHM) ^ swizzle_p(ptr_row)) * 32 + (lane & 3) * 8)
+                                : frag + (uint32_t)((kUnitElems + wm * (kTM / 2) * kBK) * 2);
+    constexpr int kPA = PTR ? kHM : 2;
+    auto addresses_p = [](uint32_t offset, uint32_t at, uint32_t (&a)[kPA]) {
+#pragma unroll
+        for (int i = 0; i < kPA; ++i) {
+            a[i] = (offset ^ (uint32_t)(i * (PTR ? 32 : 64))) + at;
+            asm("" : "+v"(a[i]));
+        }
+    };
+    auto addresses_q = [](uint32_t offset, uint32_t at, uint32_t (&a)[2]) {
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
             a[kk] = (offset ^ (uint32_t)(kk * 64)) + at;
@@ -274,6 +315,16 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
     };
     auto read = [](const uint32_t (&a)[2], int block, int kk) {
         return *reinterpret_cast<const ADAGC_LDS bf16x8*>(a[kk] + (uint32_t)(block * 16 * kBK * 2));
+    };
+    auto read_p = [&](const uint32_t (&a)[kPA], int block, int kk) {
+        if constexpr (PTR) {
+            const uint32_t at = a[block] + (uint32_t)(kk * 32 * BT);
+            const s16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<ADAGC_LDS s16x4*>(at));
+            const s16x4 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<ADAGC_LDS s16x4*>(at + 4u * BT));
+            return __builtin_bit_cast(bf16x8, __builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7));
+        } else {
+            return read(a, block, kk);
+        }
     };
 
     f32x4 acc[2 * kHM][2 * kHN];
@@ -285,10 +336,10 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
     // read from the place at rd.  side(t) is called after multiplication t.
     auto half = [&](auto PART, auto READ, bf16x8 (&qx)[kHN][2], bf16x8 (&qy)[kHN][2], uint32_t rd, auto&& side) __attribute__((always_inline)) {
         constexpr int part = decltype(PART)::value;
-        uint32_t pa[2], qd[2];
+        uint32_t pa[kPA], qd[2];
         if constexpr (decltype(READ)::value) {
-            addresses(frag_p, rd, pa);
-            addresses(frag_q, rd, qd);
+            addresses_p(frag_p, rd, pa);
+            addresses_q(frag_q, rd, qd);
         }
         static_for<2 * S>([&](auto T) __attribute__((always_inline)) {
             constexpr int t = decltype(T)::value;
@@ -305,10 +356,10 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
                     if constexpr (part == 0) {             // all of it may be overwritten from the start: in one row, Q1 first
                         if constexpr (n * (3 * S / 2) / (NQ + NP) == t) {
                             if constexpr (n < NQ) qy[n % kHN][n / kHN] = read(qd, n % kHN, n / kHN);
-                            else p1[(n - NQ) % kHM][(n - NQ) / kHM] = read(pa, (n - NQ) % kHM, (n - NQ) / kHM);
+                            else p1[(n - NQ) % kHM][(n - NQ) / kHM] = read_p(pa, (n - NQ) % kHM, (n - NQ) / kHM);
                         }
                     } else if constexpr (n < NP) {         // P0 during the first quadrant, Q0 when the second no longer needs qy
-                        if constexpr (n * S / NP == t) p0[n % kHM][n / kHM] = read(pa, n % kHM, n / kHM);
+                        if constexpr (n * S / NP == t) p0[n % kHM][n / kHM] = read_p(pa, n % kHM, n / kHM);
                     } else {
                         if constexpr (S + (n - NP) * (S / 2) / NQ == t)
                             qy[(n - NP) % kHN][(n - NP) / kHN] = read(qd, (n - NP) % kHN, (n - NP) / kHN);
@@ -320,6 +371,46 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
         });
     };
     auto nothing = [](auto) __attribute__((always_inline)) {};
+
+    // DSource::operand: quadrant (A, B) of the sums += beta / alpha D, from the place at rd: from P, D[v][w] being P's row v and
+    // column (PTR: column v and row) k = w, or FROM_Q from Q's row w and column k = v.  The accumulator layout wants 4 consecutive v.
+    const float ratio = D_SOURCE == DSource::operand ? arguments().beta / arguments().alpha : 0.f;
+    auto add_d = [&](auto A, auto B, auto FROM_Q, uint32_t rd) __attribute__((always_inline)) {
+        constexpr int a = decltype(A)::value, b = decltype(B)::value;
+        int l = lane;
+        asm volatile("" : "+v"(l));
+        const int er = l & 15, eg = l >> 4;
+        u32x2v d[kHN][kHM];
+#pragma unroll
+        for (int j = 0; j < kHN; ++j)
+#pragma unroll
+            for (int i = 0; i < kHM; ++i) {
+                // the block's rows and columns, in their halves of the tile; as indices k, modulo the 64 of an operand tile
+                const int v = wm * (kTM / 2) + i * 16, u = wn * (kTN / 2) + j * 16;
+                if constexpr (decltype(FROM_Q)::value) {
+                    const int row = u + er, vec = ((v & (kBK - 1)) >> 3) + (eg >> 1);
+                    d[j][i] = *reinterpret_cast<const ADAGC_LDS u32x2v*>(rd + (uint32_t)(row * kBK * 2 + (vec ^ ((row >> 1) & 7)) * 16 + (eg & 1) * 8));
+                } else if constexpr (PTR) {
+                    const int row = (u & (kBK - 1)) + er;
+                    d[j][i] = *reinterpret_cast<const ADAGC_LDS u32x2v*>(rd + (uint32_t)(kUnitElems * 2 + row * BT + ((v / 16) ^ swizzle_p(row)) * 32 + eg * 8));
+                } else {
+                    const int row = v + eg * 4 + (er >> 2), vec = ((u & (kBK - 1)) >> 3) + ((er & 3) >> 1);
+                    const uint32_t at = rd + (uint32_t)(kUnitElems * 2 + row * kBK * 2 + (vec ^ ((row >> 1) & 7)) * 16 + (er & 1) * 8);
+                    d[j][i] = __builtin_bit_cast(u32x2v, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<ADAGC_LDS s16x4*>(at)));
+                }
+            }
+#pragma unroll
+        for (int j = 0; j < kHN; ++j)
+#pragma unroll
+            for (int i = 0; i < kHM; ++i) {
+                f32x4& s = acc[a * kHM + i][b * kHN + j];
+                s[0] = fmaf(ratio, bf16_lo(d[j][i].x), s[0]);
+                s[1] = fmaf(ratio, bf16_hi(d[j][i].x), s[1]);
+                s[2] = fmaf(ratio, bf16_lo(d[j][i].y), s[2]);
+                s[3] = fmaf(ratio, bf16_hi(d[j][i].y), s[3]);
+            }
+        ADAGC_SCHED_FENCE();
+    };
 
     TilePlace tp = tile_of_workgroup<SYM>(arguments(), 0);
     if (tp.z < 0) return;
@@ -340,13 +431,43 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
         if (round) ADAGC_WAIT_VMEM(2 * kGL + kStores);
         barrier_keeping_loads();
         {
-            uint32_t pa[2], qd[2];
-            addresses(frag_p, lds0, pa);
-            addresses(frag_q, lds0, qd);
+            uint32_t pa[kPA], qd[2];
+            addresses_p(frag_p, lds0, pa);
+            addresses_q(frag_q, lds0, qd);
             static_for<2 * kHN>([&](auto N) { constexpr int n = decltype(N)::value; qa[n % kHN][n / kHN] = read(qd, n % kHN, n / kHN); });
-            static_for<2 * kHM>([&](auto N) { constexpr int n = decltype(N)::value; p0[n % kHM][n / kHM] = read(pa, n % kHM, n / kHM); });
+            static_for<2 * kHM>([&](auto N) { constexpr int n = decltype(N)::value; p0[n % kHM][n / kHM] = read_p(pa, n % kHM, n / kHM); });
         }
         ADAGC_SCHED_FENCE();
+        // DSource::operand: the half step at whose start D is added to each quadrant, from P or from Q (-2: never): its half of
+        // P (Q) in 64-deep tile t is group 2 t + half, which half step 2 t + half - 1 reads.  None of the quadrant's products of tile
+        // t has been made then.
+        int d_p[2][2], d_q[2][2];
+        if constexpr (D_SOURCE == DSource::operand) {
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    const int tv = (tp.tile_m * BT + a * (BT / 2) + wm * (kTM / 2)) / kBK, tw = (tp.tile_n * BT + b * (BT / 2) + wn * (kTN / 2)) / kBK;
+                    const bool from_p = !SYM || tv >= tw;
+                    d_p[a][b] = from_p ? 2 * tw + a - 1 : -2;
+                    d_q[a][b] = from_p ? -2 : 2 * tv + b - 1;
+                }
+        }
+        auto add_ds = [&](auto PART, int h, uint32_t rd) __attribute__((always_inline)) {
+            if constexpr (D_SOURCE == DSource::operand) {
+                if constexpr (decltype(PART)::value == 0) {
+                    if (h == d_p[1][0]) add_d(yes, no, no, rd);
+                    if (h == d_p[1][1]) add_d(yes, yes, no, rd);
+                    if (SYM && h == d_q[0][1]) add_d(no, yes, std::integral_constant<int, SYM>{}, rd);
+                    if (SYM && h == d_q[1][1]) add_d(yes, yes, std::integral_constant<int, SYM>{}, rd);
+                } else {
+                    if (h == d_p[0][0]) add_d(no, no, no, rd);
+                    if (h == d_p[0][1]) add_d(no, yes, no, rd);
+                    if (SYM && h == d_q[0][0]) add_d(no, no, std::integral_constant<int, SYM>{}, rd);
+                }
+            }
+        };
+        add_ds(yes, -1, lds0);
         if (groups > 4) {
 #pragma unroll
             for (int n = 0; n < kGL; ++n) load(src, n, 4, place(4));
@@ -366,10 +487,12 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
                     });
                 };
             };
+            add_ds(no, h, at_place(pl1));
             if constexpr (decltype(LA)::value) half(no, yes, x, y, at_place(pl1), loads(h + 5, place(rp)));
             else half(no, yes, x, y, at_place(pl1), nothing);
             ADAGC_WAIT_VMEM(decltype(WA)::value);
             barrier_keeping_loads();
+            add_ds(yes, h + 1, at_place(pl2));
             if constexpr (decltype(LB)::value) half(yes, yes, x, y, at_place(pl2), loads(h + 6, place(pl1)));
             else half(yes, yes, x, y, at_place(pl2), nothing);
             ADAGC_WAIT_VMEM(decltype(WB)::value);
@@ -389,6 +512,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
             tile(yes, no, w3, w2, qb, qa);                 // loads the last group
         }
         tile(no, no, w1, no, qa, qb);
+        add_ds(no, h, at_place(next_place(rp)));
         half(no, yes, qb, qa, at_place(next_place(rp)), nothing);
         barrier_keeping_loads();                           // all operands are in registers: the ring is free
         const bool more = tp_next.z >= 0;
@@ -408,7 +532,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
         const size_t v0 = (size_t)tp.tile_m * BT + wm * (kTM / 2), w0 = (size_t)tp.tile_n * BT + wn * (kTN / 2);
         const uint16_t* Dt = HAS_D ? w.dt + (size_t)tp.z * w.stride_dt + w0 * w.lddt + v0 : nullptr;
         uint16_t* Ct = w.ct ? w.ct + (size_t)tp.z * w.stride_ct + w0 * w.ldct + v0 : nullptr;
-        uint16_t* C = (SYM ? tp.tile_m != tp.tile_n : w.c != nullptr) ? w.c + (size_t)tp.z * w.stride_c + v0 * w.ldc + w0 : nullptr;
+        uint16_t* C = !PTR && (SYM ? tp.tile_m != tp.tile_n : w.c != nullptr) ? w.c + (size_t)tp.z * w.stride_c + v0 * w.ldc + w0 : nullptr;
         int le = lane;
         asm volatile("" : "+v"(le));                       // the addresses below are made here, not kept through the main loop
         const int er = le & 15, eg = le >> 4;
@@ -495,6 +619,35 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
 }
 
 
+// The block tile of a launch, and how many there are of one matrix and in all.
+struct Tiles {
+    int     side;
+    int64_t one, all;
+};
+
+// A compute unit holds one 256 x 256 workgroup or two 128 x 128 ones, and multiplies about a quarter faster on the large tile
+// (fewer LDS reads per matrix-core instruction); a launch costs whole rounds of workgroups.  Compare the two in units of "one
+// 128-tile on a shared compute unit": a round of large tiles is 4 / 1.25 of them.
+Tiles choose_tiles(int M, int N, bool symmetric, int64_t batch)
+{
+    auto tiles = [&](int64_t side) { return symmetric ? M / side * (M / side + 1) / 2 : (M / side) * (N / side); };
+    const int64_t n128 = tiles(128) * batch, n256 = tiles(256) * batch;
+    const double cost128 = 2.0 * (double)((n128 + 511) / 512);
+    const double cost256 = 3.2 * (double)((n256 + 255) / 256);
+    if (M % 256 == 0 && N % 256 == 0 && cost256 < cost128) return {256, tiles(256), n256};
+    return {128, tiles(128), n128};
+}
+
+// As many workgroups as the chip holds at a time, if there are tiles for them: 32 (128-tiles: 64) on each of 8 XCDs.
+template <bool SYM, bool PTR, DSource D>
+void launch_kernel(std::integral_constant<bool, SYM>, std::integral_constant<bool, PTR>, std::integral_constant<DSource, D>, const Tiles& t,
+                   const GemmWork& w, hipStream_t stream)
+{
+    const dim3 grid(8u * (uint32_t)std::min<int64_t>((t.all + 7) / 8, t.side == 256 ? 32 : 64));
+    if (t.side == 256) gemm_nt_bf16_kernel<256, SYM, PTR, D, 512><<<grid, dim3(512), 0, stream>>>(w);
+    else gemm_nt_bf16_kernel<128, SYM, PTR, D, 256><<<grid, dim3(256), 0, stream>>>(w);
+}
+
 }  // namespace
 
 // M, N, K must be multiples of 128 and every leading dimension a multiple of 8 elements (16-byte rows).
@@ -518,18 +671,8 @@ hipError_t launch_gemm_nt_bf16(const void* P, int ldp, const void* Q, int ldq, i
     if (misaligned(P) || misaligned(Q) || misaligned(Dt) || misaligned(C) || misaligned(Ct)) return hipErrorInvalidValue;
     if (symmetric && (M != N || P != Q || stride_p != stride_q || !Ct || (C && (C != Ct || stride_c != stride_ct))))
         return hipErrorInvalidValue;
-    // Tile choice.  A compute unit holds one 256 x 256 workgroup or two 128 x 128 ones, and multiplies about a quarter
-    // faster on the large tile (fewer LDS reads per matrix-core instruction); a launch costs whole rounds of workgroups.
-    // Compare the two in units of "one 128-tile on a shared compute unit": a round of large tiles is 4 / 1.25 of them.
-    const int64_t t128 = symmetric ? (int64_t)(M / 128) * (M / 128 + 1) / 2 : (int64_t)(M / 128) * (N / 128);
-    const int64_t t256 = symmetric ? (int64_t)(M / 256) * (M / 256 + 1) / 2 : (int64_t)(M / 256) * (N / 256);
-    const int64_t n128 = t128 * batch, n256 = t256 * batch;
-    const double cost128 = 2.0 * (double)((n128 + 511) / 512);
-    const double cost256 = 3.2 * (double)((n256 + 255) / 256);
-    const bool big = (M % 256 == 0) && (N % 256 == 0) && cost256 < cost128;
-    const int64_t all = big ? n256 : n128;
-    if (all > INT32_MAX) return hipErrorInvalidValue;
-    const int bt = big ? 256 : 128;
+    const Tiles t = choose_tiles(M, N, symmetric, batch);
+    if (t.all > INT32_MAX) return hipErrorInvalidValue;
     GemmWork w;
     w.p = static_cast<const uint16_t*>(P);
     w.q = static_cast<const uint16_t*>(Q);
@@ -547,25 +690,67 @@ hipError_t launch_gemm_nt_bf16(const void* P, int ldp, const void* Q, int ldq, i
     w.ldc = symmetric ? ldct : ldc;
     w.ldct = ldct;
     w.k = K;
-    w.tiles_m = M / bt;
-    w.tiles_n = N / bt;
-    w.tiles = (int32_t)(big ? t256 : t128);
-    w.all = (int32_t)all;
+    w.tiles_m = M / t.side;
+    w.tiles_n = N / t.side;
+    w.tiles = (int32_t)t.one;
+    w.all = (int32_t)t.all;
     w.alpha = alpha;
     w.beta = beta;
-    // as many workgroups as the chip holds at a time, if there are tiles for them: 32 (64) on each of 8 XCDs
-    const dim3 grid(8u * (uint32_t)std::min<int64_t>((all + 7) / 8, big ? 32 : 64));
-    auto launch = [&](auto SYM, auto HAS_D) {
-        constexpr bool sym = decltype(SYM)::value, has_d = decltype(HAS_D)::value;
-        if (big) gemm_nt_bf16_kernel<256, sym, has_d, 512><<<grid, dim3(512), 0, stream>>>(w);
-        else gemm_nt_bf16_kernel<128, sym, has_d, 256><<<grid, dim3(256), 0, stream>>>(w);
-    };
     const std::true_type yes{};
     const std::false_type no{};
-    if (symmetric && Dt) launch(yes, yes);
-    else if (symmetric) launch(yes, no);
-    else if (Dt) launch(no, yes);
-    else launch(no, no);
+    const std::integral_constant<DSource, DSource::array> array{};
+    const std::integral_constant<DSource, DSource::none> none{};
+    if (symmetric && Dt) launch_kernel(yes, no, array, t, w, stream);
+    else if (symmetric) launch_kernel(yes, no, none, t, w, stream);
+    else if (Dt) launch_kernel(no, no, array, t, w, stream);
+    else launch_kernel(no, no, none, t, w, stream);
+    return hipGetLastError();
+}
+
+hipError_t launch_muon_product(MuonProduct product, const MuonGroup& g, hipStream_t stream)
+{
+    constexpr float kA = 3.4445f, kB = -4.7750f, kC = 2.0315f;
+    const int64_t mn = (int64_t)g.mp * g.np, mm = (int64_t)g.mp * g.mp;
+    const bool next = product == MuonProduct::next;
+    const Tiles t = choose_tiles(next ? g.np : g.mp, g.mp, !next, g.count);
+    if (t.all > INT32_MAX) return hipErrorInvalidValue;
+    GemmWork w{};
+    w.tiles_m = (next ? g.np : g.mp) / t.side;
+    w.tiles_n = g.mp / t.side;
+    w.tiles = (int32_t)t.one;
+    w.all = (int32_t)t.all;
+    const std::true_type yes{};
+    const std::false_type no{};
+    const std::integral_constant<DSource, DSource::operand> operand{};
+    if (product == MuonProduct::gram) {
+        w.p = w.q = g.x;
+        w.c = w.ct = g.a;
+        w.stride_p = w.stride_q = mn;
+        w.stride_c = w.stride_ct = mm;
+        w.ldp = w.ldq = w.k = g.np;
+        w.ldc = w.ldct = g.mp;
+        w.alpha = 1.0f;
+        launch_kernel(yes, no, std::integral_constant<DSource, DSource::none>{}, t, w, stream);
+    } else if (product == MuonProduct::poly) {
+        w.p = w.q = g.a;
+        w.c = w.ct = g.b;
+        w.stride_p = w.stride_q = w.stride_c = w.stride_ct = mm;
+        w.ldp = w.ldq = w.ldc = w.ldct = w.k = g.mp;
+        w.alpha = kC;
+        w.beta = kB;
+        launch_kernel(yes, no, operand, t, w, stream);
+    } else {
+        w.p = g.x;
+        w.q = g.b;
+        w.ct = g.x2;
+        w.stride_p = w.stride_ct = mn;
+        w.stride_q = mm;
+        w.ldp = w.ldct = g.np;
+        w.ldq = w.k = g.mp;
+        w.alpha = 1.0f;
+        w.beta = kA;
+        launch_kernel(no, yes, operand, t, w, stream);
+    }
     return hipGetLastError();
 }
 

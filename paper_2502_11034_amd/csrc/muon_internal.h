@@ -14,6 +14,17 @@ hipError_t launch_gemm_nt_bf16(const void* P, int ldp, const void* Q, int ldq, i
                                float beta, const void* Dt, int lddt, void* C, int ldc, void* Ct, int ldct,
                                hipStream_t stream, bool symmetric = false, int batch = 1, int64_t stride_p = 0,
                                int64_t stride_q = 0, int64_t stride_dt = 0, int64_t stride_c = 0, int64_t stride_ct = 0);
+
+// A batch of matrices of one padded shape in the workspace, matrix z of every array at z times its size: X and the next X
+// (mp x np), A and B (mp x mp), bf16.
+struct MuonGroup {
+    int       mp, np, count;
+    uint16_t *x, *x2, *a, *b;
+};
+// The three products of a Newton-Schulz step: a <- X X^T;  b <- b A + c A A;  x2 <- a X + B X.
+enum class MuonProduct { gram, poly, next };
+hipError_t launch_muon_product(MuonProduct product, const MuonGroup& g, hipStream_t stream);
+
 // One matrix of a batch, in device memory.
 struct MuonMatrix {
     uint32_t tensor;      // its place in the list
@@ -23,13 +34,14 @@ struct MuonMatrix {
 };
 
 // Muon (muon.hip): momentum update with the clipped gradient and the partial sums of squares of U; X0 of a batch's
-// matrices into the padded workspace (members: the batch's records, DEVICE); their parameter update (largest: the most
-// elements of one of them).
+// matrices into the padded workspace (members: the batch's records, DEVICE); their parameter update (blocks: the most
+// workgroups that one of them needs, muon_apply_blocks).
 hipError_t launch_muon_momentum(const DeviceTables& t, double mu, int nesterov, int grad_bf16, int grid, hipStream_t stream);
 hipError_t launch_muon_normalise(const DeviceTables& t, const MuonMatrix* members, int count, int mp, int np, double mu, int nesterov,
-                                 int grad_bf16, uint16_t* x, uint16_t* y, hipStream_t stream);
-hipError_t launch_muon_apply(const DeviceTables& t, const MuonMatrix* members, int count, int64_t largest, int mp, int np,
-                             const uint16_t* x, const uint16_t* y, double lr, double wd, int with_copy, hipStream_t stream);
+                                 int grad_bf16, uint16_t* x, hipStream_t stream);
+int64_t muon_apply_blocks(int64_t rows, int64_t cols);
+hipError_t launch_muon_apply(const DeviceTables& t, const MuonMatrix* members, int count, int64_t blocks, int mp, int np,
+                             const uint16_t* x, double lr, double wd, int with_copy, hipStream_t stream);
 
 }  // namespace adagc
 #endif

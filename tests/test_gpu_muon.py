@@ -812,3 +812,24 @@ def test_matrix_core_product_when_workgroups_take_several_tiles(batch, M, N, K, 
         torch.cuda.synchronize()
         assert C is None or torch.equal(C, ref)
         assert Ct is None or torch.equal(Ct, ref.transpose(1, 2))
+
+
+@pytest.mark.parametrize("ns_steps", [1, 5])
+def test_muon_results_do_not_depend_on_the_size_of_the_tiles(ns_steps):
+    """32 matrices of 768 rows run on 256 x 256 tiles, one of them alone on 128 x 128 tiles.  The polynomial's lower terms are
+    added to the sums at an element's own place in k, whichever tile it lies in, so the bits must be the same: parameters of
+    a wide matrix, of a tall one, and of one whose extents end inside a tile."""
+    shapes = [(768, 2304), (2304, 768), (700, 2250), (2290, 641)] * 8
+    g, m, th = _inputs(21, shapes)
+    gamma = np.array([oracle.l2_norm(x.reshape(-1)) for x in g], np.float32)
+    hp = B.make_hyper(lr=0.02, weight_decay=0.1, t_start=0)
+    mh = B.make_muon_hyper(ns_steps=ns_steps)
+    together = _gpu_muon(shapes, g, m, th, gamma, hp, mh, 4)
+    for i in (0, 1, 2, 3, 30):
+        alone = _gpu_muon([shapes[i]], [g[i]], [m[i]], [th[i]], gamma[i:i + 1], hp, mh, 4)
+        assert np.array_equal(together[0][i].view(np.uint32), alone[0][0].view(np.uint32)), "parameters of tensor %d" % i
+    for i in (0, 1, 2, 3):                        # and the oracle's, as for the end-to-end test
+        th_ref, m_ref = th[i].copy(), m[i].copy()
+        OM.muon_update(th_ref, g[i], m_ref, float(together[4][i]), lr=0.02, weight_decay=0.1, mu=0.95, steps=ns_steps)
+        d = together[0][i].astype(np.float64) - th_ref
+        assert np.sqrt(np.mean(d ** 2)) <= 0.01 * np.sqrt(np.mean((th_ref - th[i].astype(np.float64)) ** 2))
