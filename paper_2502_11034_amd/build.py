@@ -6,8 +6,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libadagc.so")
-SOURCES = ["api.cpp", "segment_table.cpp", "kernels.hip", "static_step.hip", "muon_gemm.hip", "muon.hip"]
-HEADERS = [os.path.join(ROOT, "include", "adagc.h"), os.path.join(CSRC, "adagc_internal.h"), os.path.join(CSRC, "adagc_device.h"), os.path.join(CSRC, "muon_internal.h")]
+SOURCES = ["api.cpp", "segment_table.cpp", "kernels.hip", "static_step.hip", "muon_gemm.hip", "muon.hip", "muon_plan.cpp"]
+HEADERS = [os.path.join(ROOT, "include", "adagc.h"), os.path.join(CSRC, "adagc_internal.h"), os.path.join(CSRC, "adagc_device.h"), os.path.join(CSRC, "muon_internal.h"),
+           os.path.join(CSRC, "muon_plan.h")]
 
 
 def hipcc():

@@ -61,7 +61,14 @@ struct adagc_ctx {
     };
     std::vector<adagc_matrix_shape> shapes;
     std::vector<MuonBatch> muon_batches;
-    MuonMatrix* muon_matrices = nullptr;      // device: the batches' matrices, one batch after another
+    // Batches that are in the workspace at the same time: their products share launches
+    struct MuonRound {
+        std::vector<size_t>     batches;     // places in muon_batches
+        std::vector<MuonGroup>  groups;      // of the batches, in the same order
+        std::vector<MuonLaunch> launches[3]; // by product
+    };
+    std::vector<MuonRound> muon_rounds;
+    MuonMatrix* muon_matrices = nullptr;      // device: the batches' matrices, one batch after another; then the planned launches' arrays
     void*  muon_ws = nullptr;
     size_t muon_ws_bytes = 0;
 
@@ -505,8 +512,10 @@ constexpr int64_t kMuonTile = 128;     // the matrix-core kernel's block tile: w
 constexpr int64_t kMuonMaxBatch = 32;
 constexpr int64_t kMuonWorkspaceBudget = (int64_t)24 << 30;
 inline int64_t pad_to_tile(int64_t x) { return (x + kMuonTile - 1) / kMuonTile * kMuonTile; }
-// bf16 elements of workspace per matrix: X and Y = X^T twice (a step reads one pair and writes the other), A and B
+// bf16 elements of workspace per matrix of the largest batch; what a matrix takes of it: X, the next X, A and B.  Batches share it
+// as far as it goes.
 inline int64_t muon_ws_elems(int64_t mp, int64_t np) { return 4 * mp * np + 2 * mp * mp; }
+inline int64_t muon_matrix_elems(int64_t mp, int64_t np) { return 2 * mp * np + 2 * mp * mp; }
 }  // namespace
 
 extern "C" int adagc_muon_attach(adagc_ctx* ctx, const adagc_matrix_shape* shapes)
@@ -577,9 +586,32 @@ extern "C" int adagc_muon_attach(adagc_ctx* ctx, const adagc_matrix_shape* shape
             return e == hipErrorOutOfMemory ? ADAGC_ERR_OOM : ADAGC_ERR_HIP;
         }
     }
-    // the matrices' records, batch by batch, in device memory
+    // Rounds: every batch, the largest first, joins the first round with room for it.  Then the records of the matrices, batch by
+    // batch, and the planned launches go to device memory.
     int rc = ADAGC_OK;
+    std::vector<adagc_ctx::MuonRound> rounds;
     try {
+        std::vector<size_t> order(batches.size());
+        for (size_t i = 0; i < order.size(); ++i) order[i] = i;
+        auto elems = [&](size_t i) { return (int64_t)batches[i].members.size() * muon_matrix_elems(batches[i].mp, batches[i].np); };
+        std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return elems(a) > elems(b); });
+        std::vector<int64_t> used;
+        for (size_t i : order) {
+            size_t r = 0;
+            while (r < rounds.size() && ((used[r] + elems(i)) * (int64_t)sizeof(uint16_t) > (int64_t)ctx->muon_ws_bytes ||
+                                         rounds[r].batches.size() == (size_t)kMaxGroups))
+                ++r;
+            if (r == rounds.size()) {
+                rounds.emplace_back();
+                used.push_back(0);
+            }
+            const adagc_ctx::MuonBatch& bt = batches[i];
+            const int64_t n = (int64_t)bt.members.size(), mn = (int64_t)bt.mp * bt.np, mm = (int64_t)bt.mp * bt.mp;
+            uint16_t* base = static_cast<uint16_t*>(ctx->muon_ws) + used[r];
+            rounds[r].groups.push_back(MuonGroup{bt.mp, bt.np, (int)n, base, base + n * mn, base + 2 * n * mn, base + 2 * n * mn + n * mm});
+            rounds[r].batches.push_back(i);
+            used[r] += elems(i);
+        }
         std::vector<MuonMatrix> records;
         for (adagc_ctx::MuonBatch& bt : batches) {
             bt.first = (int64_t)records.size();
@@ -590,14 +622,45 @@ extern "C" int adagc_muon_attach(adagc_ctx* ctx, const adagc_matrix_shape* shape
                 bt.apply_blocks = std::max(bt.apply_blocks, muon_apply_blocks(r, c));
             }
         }
-        const size_t bytes = records.size() * sizeof(MuonMatrix);
+        std::vector<GemmItem> items;
+        std::vector<int32_t> first;
+        std::vector<std::pair<size_t, size_t>> places;            // of a launch's items and first, launch by launch
+        for (adagc_ctx::MuonRound& round : rounds) {
+            std::vector<MuonExtent> extents;
+            for (const MuonGroup& g : round.groups) extents.push_back(MuonExtent{g.mp, g.np, g.count});
+            for (int p = 0; p < 3; ++p)
+                for (PlannedLaunch& l : plan_muon_product((MuonProduct)p, extents)) {
+                    places.emplace_back(items.size(), first.size());
+                    items.insert(items.end(), l.items.begin(), l.items.end());
+                    first.insert(first.end(), l.first.begin(), l.first.end());
+                    round.launches[p].push_back(MuonLaunch{l.side, l.workgroups, l.groups, nullptr, nullptr});
+                }
+        }
+        const size_t records_bytes = records.size() * sizeof(MuonMatrix), items_bytes = items.size() * sizeof(GemmItem);
+        const size_t bytes = records_bytes + items_bytes + first.size() * sizeof(int32_t);
+        std::vector<char> image(bytes);
+        std::memcpy(image.data(), records.data(), records_bytes);
+        std::memcpy(image.data() + records_bytes, items.data(), items_bytes);
+        std::memcpy(image.data() + records_bytes + items_bytes, first.data(), first.size() * sizeof(int32_t));
         const hipError_t e = hipMalloc(reinterpret_cast<void**>(&ctx->muon_matrices), bytes);
         if (e != hipSuccess) {
             ctx->muon_matrices = nullptr;
             (void)hipGetLastError();
             rc = e == hipErrorOutOfMemory ? ADAGC_ERR_OOM : ADAGC_ERR_HIP;
-        } else if (hipMemcpy(ctx->muon_matrices, records.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) {
+        } else if (hipMemcpy(ctx->muon_matrices, image.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) {
             rc = ADAGC_ERR_HIP;
+        } else {
+            const char* device = reinterpret_cast<const char*>(ctx->muon_matrices);
+            const GemmItem* device_items = reinterpret_cast<const GemmItem*>(device + records_bytes);
+            const int32_t* device_first = reinterpret_cast<const int32_t*>(device + records_bytes + items_bytes);
+            size_t n = 0;
+            for (adagc_ctx::MuonRound& round : rounds)
+                for (auto& launches : round.launches)
+                    for (MuonLaunch& l : launches) {
+                        l.items = device_items + places[n].first;
+                        l.first = device_first + places[n].second;
+                        ++n;
+                    }
         }
     } catch (const std::bad_alloc&) { rc = ADAGC_ERR_OOM; }
     if (rc != ADAGC_OK) {                 // as if the call had not been made
@@ -609,6 +672,7 @@ extern "C" int adagc_muon_attach(adagc_ctx* ctx, const adagc_matrix_shape* shape
         ctx->shapes.clear();
         return rc;
     }
+    ctx->muon_rounds.swap(rounds);
     ctx->muon_batches.swap(batches);
     return ADAGC_OK;
 }
@@ -657,22 +721,29 @@ extern "C" int adagc_muon_step(adagc_ctx* ctx, void* const* params, const void* 
     if (launch_muon_momentum(t, mu, mh->nesterov, bf16g, ctx->grid_norm, stream) != hipSuccess) return ADAGC_ERR_HIP;
     if (launch_tensor_sumsq(t, stream) != hipSuccess) return ADAGC_ERR_HIP;
 
-    // Newton-Schulz and the update, batch by batch.
-    for (const adagc_ctx::MuonBatch& bt : ctx->muon_batches) {
-        const int count = (int)bt.members.size();
-        const int64_t mn = (int64_t)bt.mp * bt.np, mm = (int64_t)bt.mp * bt.mp;
-        uint16_t* base = static_cast<uint16_t*>(ctx->muon_ws);
-        MuonGroup g{bt.mp, bt.np, count, base, base + count * mn, base + 2 * count * mn, base + 2 * count * mn + count * mm};
-        const MuonMatrix* members = ctx->muon_matrices + bt.first;
-        if (launch_muon_normalise(t, members, count, bt.mp, bt.np, mu, mh->nesterov, bf16g, g.x, stream) != hipSuccess) return ADAGC_ERR_HIP;
-        for (int k = 0; k < mh->ns_steps; ++k) {
-            for (const MuonProduct product : {MuonProduct::gram, MuonProduct::poly, MuonProduct::next})
-                if (launch_muon_product(product, g, stream) != hipSuccess) return ADAGC_ERR_HIP;
-            std::swap(g.x, g.x2);
+    // Newton-Schulz and the update, round by round.
+    for (const adagc_ctx::MuonRound& round : ctx->muon_rounds) {
+        MuonGroup groups[kMaxGroups];
+        const size_t n = round.groups.size();
+        std::copy(round.groups.begin(), round.groups.end(), groups);
+        for (size_t i = 0; i < n; ++i) {
+            const MuonGroup& g = groups[i];
+            if (launch_muon_normalise(t, ctx->muon_matrices + ctx->muon_batches[round.batches[i]].first, g.count, g.mp, g.np, mu, mh->nesterov,
+                                      bf16g, g.x, stream) != hipSuccess)
+                return ADAGC_ERR_HIP;
         }
-        if (launch_muon_apply(t, members, count, bt.apply_blocks, bt.mp, bt.np, g.x, (double)h.lr, (double)h.weight_decay, copy, stream) !=
-            hipSuccess)
-            return ADAGC_ERR_HIP;
+        for (int k = 0; k < mh->ns_steps; ++k) {
+            for (int p = 0; p < 3; ++p)
+                for (const MuonLaunch& l : round.launches[p])
+                    if (launch_muon_product((MuonProduct)p, l, groups, stream) != hipSuccess) return ADAGC_ERR_HIP;
+            for (size_t i = 0; i < n; ++i) std::swap(groups[i].x, groups[i].x2);
+        }
+        for (size_t i = 0; i < n; ++i) {
+            const adagc_ctx::MuonBatch& bt = ctx->muon_batches[round.batches[i]];
+            if (launch_muon_apply(t, ctx->muon_matrices + bt.first, groups[i].count, bt.apply_blocks, bt.mp, bt.np, groups[i].x, (double)h.lr,
+                                  (double)h.weight_decay, copy, stream) != hipSuccess)
+                return ADAGC_ERR_HIP;
+        }
     }
     if (prof) {
         if (hipEventRecord(ev[3], stream) != hipSuccess) return ADAGC_ERR_HIP;

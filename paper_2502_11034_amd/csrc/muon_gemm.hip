@@ -8,9 +8,9 @@
 // transposed (Ct, N x M), or both; D is read through its transpose Dt (N x M).  The three products of a Newton-Schulz step are
 //   A  = X X^T                P = Q = X                       (alpha 1, beta 0)
 //   B  = b A + c A A          P = Q = A (A is symmetric)      (alpha c, beta b, D = A)
-//   X' = a X + B X            as X'^T = a X^T + X^T B with P = X^T, given by its transpose X, and Q = B; X' is Ct
+//   X' = a X + B X            as X'^T = a X^T + X^T B with P = X^T, given by its transpose X, and Q = B; X is Dt, X' is Ct
 // so that X is kept and written in one orientation only.  (With X and its transpose, written by each step, 12 products of
-// 4096 x 14336 x 4096 took 4973 us and 24 of 768 x 3072 x 768 167 us; with X alone 4532 and 139.)
+// 4096 x 14336 x 4096 took 4973 us and 24 of 768 x 3072 x 768 167 us; with X alone 4369 and 114.)
 //
 // A = X X^T and A A are symmetric: for those only the tiles on and below the diagonal are computed and each is
 // written twice, to its place and to its mirror image, which saves about a quarter of a step's multiplications.
@@ -47,7 +47,7 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 #define ADAGC_CONST __attribute__((address_space(4)))
 
 // A batch of products of one shape; matrix z of every array at its base + z times its stride (elements).
-struct GemmWork {
+struct GemmGroup {
     const uint16_t *p, *q, *dt;
     uint16_t *c, *ct;
     int64_t stride_p, stride_q, stride_dt, stride_c, stride_ct;
@@ -56,7 +56,14 @@ struct GemmWork {
     int32_t tiles_m, tiles_n;       // block tiles of one matrix
     int32_t tiles;                  // the ones of them that are computed (SYM: on and below the diagonal)
     int32_t all;                    // ... of the whole batch
-    float   alpha, beta;
+};
+
+// A launch: the tiles of several groups as planned (muon_plan.h), or, without a plan, of one group in their order.
+struct GemmWork {
+    const GemmItem* items;
+    const int32_t*  first;
+    float           alpha, beta;
+    GemmGroup       g[kMaxGroups];
 };
 
 constexpr int kBK = 64;
@@ -71,63 +78,41 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
-// An output tile: its place in matrix z of the batch.  z < 0: none.
+// An output tile: its place in matrix z of a group.  z < 0: none.
 struct TilePlace {
-    int z, tile_m, tile_n;
+    int group, z, tile_m, tile_n;
 };
 
-// Tile b of a matrix, in an order in which tiles that follow one another form a patch a few tiles high and wide, so that the
-// workgroups that run at the same time on an XCD share both operands in its L2.  SYM: the lower triangle in panels of kPanel
-// tile columns, down the rows of a panel; otherwise panels of kPanelRows tile rows, along the columns.
-template <bool SYM>
-__device__ __forceinline__ void tile_of_matrix(int b, int tiles_m, int tiles_n, int* tile_m, int* tile_n)
-{
-    if constexpr (SYM) {
-        constexpr int kPanel = 4;
-        for (int c0 = 0;; c0 += kPanel) {
-            const int rows = tiles_m - c0, cols = rows < kPanel ? rows : kPanel;
-            const int n = cols * rows - cols * (cols - 1) / 2;
-            if (b < n) {
-                int r = 0;                                 // the panel's first rows have 1, 2, ... cols - 1 tiles
-                while (r < cols - 1 && b > r) b -= ++r;
-                const int full = r == cols - 1 ? b / cols : 0;
-                *tile_m = c0 + r + full;
-                *tile_n = c0 + b - full * cols;
-                return;
-            }
-            b -= n;
-        }
-    } else {
-        constexpr int kPanelRows = 8;
-        const int per_panel = kPanelRows * tiles_n;
-        const int first_m = b / per_panel * kPanelRows;
-        const int rows = tiles_m - first_m < kPanelRows ? tiles_m - first_m : kPanelRows;
-        const int i = b - first_m * tiles_n;
-        *tile_m = first_m + i % rows;
-        *tile_n = i / rows;
-    }
-}
-
-// The tile of this workgroup in a round.  A round is as many consecutive tiles of the batch as there are workgroups, dealt to
-// the 8 XCDs (workgroup b runs on XCD b mod 8, one L2 each) in contiguous eighths: the whole chip is on one or two matrices at a
-// time, and what the XCDs' patches have in common comes out of the memory-side cache.  With a contiguous eighth of the whole
-// batch per XCD, 8 matrices at a time, 12 products X X^T of 4096 x 14336 took 2321 us, now 2223.
+// The tile of this workgroup in a round.  Without a plan a round is as many consecutive tiles of the batch as there are
+// workgroups, dealt to the 8 XCDs (workgroup b runs on XCD b mod 8, one L2 each) in contiguous eighths: the whole chip is on one
+// or two matrices at a time, and what the XCDs' patches have in common comes out of the memory-side cache.  With a contiguous
+// eighth of the whole batch per XCD, 8 matrices at a time, 12 products X X^T of 4096 x 14336 took 2321 us, now 2223.
 template <bool SYM>
 __device__ __forceinline__ TilePlace tile_of_workgroup(const ADAGC_CONST GemmWork& w, int round)
 {
-    const int xcd = (int)blockIdx.x % 8, slot = (int)blockIdx.x / 8, wgs = (int)gridDim.x;      // a multiple of 8
-    const int64_t first = (int64_t)round * wgs, left = w.all - first;
+    const int wg = (int)blockIdx.x;
+    if (w.items) {
+        const ADAGC_CONST int32_t* first = (const ADAGC_CONST int32_t*)w.first;
+        const int i = first[wg] + round;
+        if (i >= first[wg + 1]) return {0, -1, 0, 0};
+        const u32x2v item = *(const ADAGC_CONST u32x2v*)(w.items + i);
+        return {(int)(item.x & 0xFFFFu), (int)(item.x >> 16), (int)(item.y & 0xFFFFu), (int)(item.y >> 16)};
+    }
+    const int xcd = wg % 8, slot = wg / 8, wgs = (int)gridDim.x;                                // a multiple of 8
+    const int64_t before = (int64_t)round * wgs, left = w.g[0].all - before;
     const int now = (int)(left < wgs ? left : wgs);
     const int lo = now * xcd / 8, hi = now * (xcd + 1) / 8;
-    if (slot >= hi - lo) return {-1, 0, 0};
-    const int i = (int)first + lo + slot;
+    if (slot >= hi - lo) return {0, -1, 0, 0};
+    const int i = (int)before + lo + slot;
     TilePlace t;
-    t.z = __builtin_amdgcn_readfirstlane(i / w.tiles);
-    tile_of_matrix<SYM>(i - t.z * w.tiles, w.tiles_m, w.tiles_n, &t.tile_m, &t.tile_n);
+    t.group = 0;
+    t.z = __builtin_amdgcn_readfirstlane(i / w.g[0].tiles);
+    tile_of_matrix<SYM>(i - t.z * w.g[0].tiles, w.g[0].tiles_m, w.g[0].tiles_n, &t.tile_m, &t.tile_n);
     t.tile_m = __builtin_amdgcn_readfirstlane(t.tile_m);
     t.tile_n = __builtin_amdgcn_readfirstlane(t.tile_n);
     return t;
 }
+static_assert(sizeof(GemmItem) == 8, "tile_of_workgroup takes the item apart by hand");
 
 // s_waitcnt for "at most n vector-memory operations of this wave still outstanding", nothing else waited for
 #define ADAGC_WAIT_VMEM(n) __builtin_amdgcn_s_waitcnt(((n) & 0xF) | (((n) >> 4) << 14) | (7 << 4) | (0xF << 8))
@@ -202,17 +187,10 @@ __device__ __forceinline__ void load_to_lds_16(const void* base, uint32_t off, c
 //
 // PTR: P is given by its transpose, K rows of M consecutive elements (X itself in B X), and its fragments are read transposed
 // (ds_read_b64_tr_b16, two for the 16 bytes of a lane).  Only Ct then.
-// DSource::operand: D is what a part of P's rows and columns holds (A in b A + c A A, X in a X + B X), and is added to the sums
-// while that part lies in LDS, before the 64 products of its place in k: with D as an array 12 products of 14336 x 4096 x 4096
-// took 4369 us, now 4262, and 24 of 3072 x 768 x 768 114 us, now 97 (the 128 KB per tile came all at once, in every compute
-// unit at the same time).  In a symmetric product an element and its mirror image have the same place in k, the lesser of their
-// rows, so the result does not depend on the size of the tiles.
-enum class DSource { none, array, operand };
-template <int BT, bool SYM, bool PTR, DSource D_SOURCE, int kGemmThreads>
+template <int BT, bool SYM, bool PTR, bool HAS_D, int kGemmThreads>
 __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const GemmWork)
 {
     constexpr int kWaves = kGemmThreads / 64;
-    constexpr bool HAS_D = D_SOURCE == DSource::array;
     // waves in a kWM x kWN grid; with PTR the reads of P are the more expensive ones, so a wave has fewer of its rows
     constexpr int kWM = PTR ? kWaves / 2 : 2, kWN = kWaves / kWM;
     constexpr int kTM = BT / kWM, kTN = BT / kWN;          // wave tile
@@ -251,17 +229,18 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
     constexpr int kPtrRows = 1024 / BT;                    // rows per load
     struct Source {
         const uint16_t *p, *q;
-        int ldp, ldq;
+        int ldp, ldq, groups;                              // groups: of loads, a multiple of 4, at least 4
         uint32_t off_p, off_q;
     };
     auto source = [&](const TilePlace& t) {
-        const ADAGC_CONST GemmWork& w = arguments();
+        const ADAGC_CONST GemmGroup& w = arguments().g[t.group];
         int l = lane;
         asm volatile("" : "+v"(l));                        // the offsets are made here, not kept through the main loop
         const int row = l >> 3, vec = (l & 7) ^ ((((wave & 1) << 2) + (l >> 4)) & 7);
         Source s;
         s.ldp = w.ldp;
         s.ldq = w.ldq;
+        s.groups = 2 * (w.k / kBK);
         s.p = w.p + (size_t)t.z * w.stride_p + (PTR ? (size_t)t.tile_m * BT : (size_t)t.tile_m * BT * w.ldp);
         s.q = w.q + (size_t)t.z * w.stride_q + (size_t)t.tile_n * BT * w.ldq;
         if constexpr (PTR) {
@@ -372,54 +351,14 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
     };
     auto nothing = [](auto) __attribute__((always_inline)) {};
 
-    // DSource::operand: quadrant (A, B) of the sums += beta / alpha D, from the place at rd: from P, D[v][w] being P's row v and
-    // column (PTR: column v and row) k = w, or FROM_Q from Q's row w and column k = v.  The accumulator layout wants 4 consecutive v.
-    const float ratio = D_SOURCE == DSource::operand ? arguments().beta / arguments().alpha : 0.f;
-    auto add_d = [&](auto A, auto B, auto FROM_Q, uint32_t rd) __attribute__((always_inline)) {
-        constexpr int a = decltype(A)::value, b = decltype(B)::value;
-        int l = lane;
-        asm volatile("" : "+v"(l));
-        const int er = l & 15, eg = l >> 4;
-        u32x2v d[kHN][kHM];
-#pragma unroll
-        for (int j = 0; j < kHN; ++j)
-#pragma unroll
-            for (int i = 0; i < kHM; ++i) {
-                // the block's rows and columns, in their halves of the tile; as indices k, modulo the 64 of an operand tile
-                const int v = wm * (kTM / 2) + i * 16, u = wn * (kTN / 2) + j * 16;
-                if constexpr (decltype(FROM_Q)::value) {
-                    const int row = u + er, vec = ((v & (kBK - 1)) >> 3) + (eg >> 1);
-                    d[j][i] = *reinterpret_cast<const ADAGC_LDS u32x2v*>(rd + (uint32_t)(row * kBK * 2 + (vec ^ ((row >> 1) & 7)) * 16 + (eg & 1) * 8));
-                } else if constexpr (PTR) {
-                    const int row = (u & (kBK - 1)) + er;
-                    d[j][i] = *reinterpret_cast<const ADAGC_LDS u32x2v*>(rd + (uint32_t)(kUnitElems * 2 + row * BT + ((v / 16) ^ swizzle_p(row)) * 32 + eg * 8));
-                } else {
-                    const int row = v + eg * 4 + (er >> 2), vec = ((u & (kBK - 1)) >> 3) + ((er & 3) >> 1);
-                    const uint32_t at = rd + (uint32_t)(kUnitElems * 2 + row * kBK * 2 + (vec ^ ((row >> 1) & 7)) * 16 + (er & 1) * 8);
-                    d[j][i] = __builtin_bit_cast(u32x2v, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<ADAGC_LDS s16x4*>(at)));
-                }
-            }
-#pragma unroll
-        for (int j = 0; j < kHN; ++j)
-#pragma unroll
-            for (int i = 0; i < kHM; ++i) {
-                f32x4& s = acc[a * kHM + i][b * kHN + j];
-                s[0] = fmaf(ratio, bf16_lo(d[j][i].x), s[0]);
-                s[1] = fmaf(ratio, bf16_hi(d[j][i].x), s[1]);
-                s[2] = fmaf(ratio, bf16_lo(d[j][i].y), s[2]);
-                s[3] = fmaf(ratio, bf16_hi(d[j][i].y), s[3]);
-            }
-        ADAGC_SCHED_FENCE();
-    };
-
     TilePlace tp = tile_of_workgroup<SYM>(arguments(), 0);
     if (tp.z < 0) return;
     Source src = source(tp);
-    const int groups = 2 * (arguments().k / kBK);                    // a multiple of 4, at least 4
 #pragma unroll
     for (int n = 0; n < 4 * kGL; ++n) load(src, n % kGL, n / kGL, place(n / kGL));
     ADAGC_WAIT_VMEM(2 * kGL);                              // groups 0 and 1
     for (int round = 0;; ++round) {
+        const int groups = src.groups;
 #pragma unroll
         for (int i = 0; i < 2 * kHM; ++i)
 #pragma unroll
@@ -438,36 +377,6 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
             static_for<2 * kHM>([&](auto N) { constexpr int n = decltype(N)::value; p0[n % kHM][n / kHM] = read_p(pa, n % kHM, n / kHM); });
         }
         ADAGC_SCHED_FENCE();
-        // DSource::operand: the half step at whose start D is added to each quadrant, from P or from Q (-2: never): its half of
-        // P (Q) in 64-deep tile t is group 2 t + half, which half step 2 t + half - 1 reads.  None of the quadrant's products of tile
-        // t has been made then.
-        int d_p[2][2], d_q[2][2];
-        if constexpr (D_SOURCE == DSource::operand) {
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b) {
-                    const int tv = (tp.tile_m * BT + a * (BT / 2) + wm * (kTM / 2)) / kBK, tw = (tp.tile_n * BT + b * (BT / 2) + wn * (kTN / 2)) / kBK;
-                    const bool from_p = !SYM || tv >= tw;
-                    d_p[a][b] = from_p ? 2 * tw + a - 1 : -2;
-                    d_q[a][b] = from_p ? -2 : 2 * tv + b - 1;
-                }
-        }
-        auto add_ds = [&](auto PART, int h, uint32_t rd) __attribute__((always_inline)) {
-            if constexpr (D_SOURCE == DSource::operand) {
-                if constexpr (decltype(PART)::value == 0) {
-                    if (h == d_p[1][0]) add_d(yes, no, no, rd);
-                    if (h == d_p[1][1]) add_d(yes, yes, no, rd);
-                    if (SYM && h == d_q[0][1]) add_d(no, yes, std::integral_constant<int, SYM>{}, rd);
-                    if (SYM && h == d_q[1][1]) add_d(yes, yes, std::integral_constant<int, SYM>{}, rd);
-                } else {
-                    if (h == d_p[0][0]) add_d(no, no, no, rd);
-                    if (h == d_p[0][1]) add_d(no, yes, no, rd);
-                    if (SYM && h == d_q[0][0]) add_d(no, no, std::integral_constant<int, SYM>{}, rd);
-                }
-            }
-        };
-        add_ds(yes, -1, lds0);
         if (groups > 4) {
 #pragma unroll
             for (int n = 0; n < kGL; ++n) load(src, n, 4, place(4));
@@ -487,12 +396,10 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
                     });
                 };
             };
-            add_ds(no, h, at_place(pl1));
             if constexpr (decltype(LA)::value) half(no, yes, x, y, at_place(pl1), loads(h + 5, place(rp)));
             else half(no, yes, x, y, at_place(pl1), nothing);
             ADAGC_WAIT_VMEM(decltype(WA)::value);
             barrier_keeping_loads();
-            add_ds(yes, h + 1, at_place(pl2));
             if constexpr (decltype(LB)::value) half(yes, yes, x, y, at_place(pl2), loads(h + 6, place(pl1)));
             else half(yes, yes, x, y, at_place(pl2), nothing);
             ADAGC_WAIT_VMEM(decltype(WB)::value);
@@ -512,7 +419,6 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
             tile(yes, no, w3, w2, qb, qa);                 // loads the last group
         }
         tile(no, no, w1, no, qa, qb);
-        add_ds(no, h, at_place(next_place(rp)));
         half(no, yes, qb, qa, at_place(next_place(rp)), nothing);
         barrier_keeping_loads();                           // all operands are in registers: the ring is free
         const bool more = tp_next.z >= 0;
@@ -527,8 +433,8 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
         });
 
         // epilogue
-        const ADAGC_CONST GemmWork& w = arguments();
-        const float alpha = w.alpha, beta = w.beta;
+        const ADAGC_CONST GemmGroup& w = arguments().g[tp.group];
+        const float alpha = arguments().alpha, beta = arguments().beta;
         const size_t v0 = (size_t)tp.tile_m * BT + wm * (kTM / 2), w0 = (size_t)tp.tile_n * BT + wn * (kTN / 2);
         const uint16_t* Dt = HAS_D ? w.dt + (size_t)tp.z * w.stride_dt + w0 * w.lddt + v0 : nullptr;
         uint16_t* Ct = w.ct ? w.ct + (size_t)tp.z * w.stride_ct + w0 * w.ldct + v0 : nullptr;
@@ -638,14 +544,12 @@ Tiles choose_tiles(int M, int N, bool symmetric, int64_t batch)
     return {128, tiles(128), n128};
 }
 
-// As many workgroups as the chip holds at a time, if there are tiles for them: 32 (128-tiles: 64) on each of 8 XCDs.
-template <bool SYM, bool PTR, DSource D>
-void launch_kernel(std::integral_constant<bool, SYM>, std::integral_constant<bool, PTR>, std::integral_constant<DSource, D>, const Tiles& t,
+template <bool SYM, bool PTR, bool D>
+void launch_kernel(std::integral_constant<bool, SYM>, std::integral_constant<bool, PTR>, std::integral_constant<bool, D>, int side, int grid,
                    const GemmWork& w, hipStream_t stream)
 {
-    const dim3 grid(8u * (uint32_t)std::min<int64_t>((t.all + 7) / 8, t.side == 256 ? 32 : 64));
-    if (t.side == 256) gemm_nt_bf16_kernel<256, SYM, PTR, D, 512><<<grid, dim3(512), 0, stream>>>(w);
-    else gemm_nt_bf16_kernel<128, SYM, PTR, D, 256><<<grid, dim3(256), 0, stream>>>(w);
+    if (side == 256) gemm_nt_bf16_kernel<256, SYM, PTR, D, 512><<<dim3((uint32_t)grid), dim3(512), 0, stream>>>(w);
+    else gemm_nt_bf16_kernel<128, SYM, PTR, D, 256><<<dim3((uint32_t)grid), dim3(256), 0, stream>>>(w);
 }
 
 }  // namespace
@@ -673,7 +577,10 @@ hipError_t launch_gemm_nt_bf16(const void* P, int ldp, const void* Q, int ldq, i
         return hipErrorInvalidValue;
     const Tiles t = choose_tiles(M, N, symmetric, batch);
     if (t.all > INT32_MAX) return hipErrorInvalidValue;
-    GemmWork w;
+    GemmWork work{};
+    work.alpha = alpha;
+    work.beta = beta;
+    GemmGroup& w = work.g[0];
     w.p = static_cast<const uint16_t*>(P);
     w.q = static_cast<const uint16_t*>(Q);
     w.dt = static_cast<const uint16_t*>(Dt);
@@ -694,63 +601,56 @@ hipError_t launch_gemm_nt_bf16(const void* P, int ldp, const void* Q, int ldq, i
     w.tiles_n = N / t.side;
     w.tiles = (int32_t)t.one;
     w.all = (int32_t)t.all;
-    w.alpha = alpha;
-    w.beta = beta;
+    // as many workgroups as the chip holds at a time, if there are tiles for them: 32 (128-tiles: 64) on each of 8 XCDs
+    const int grid = 8 * (int)std::min<int64_t>((t.all + 7) / 8, t.side == 256 ? 32 : 64);
     const std::true_type yes{};
     const std::false_type no{};
-    const std::integral_constant<DSource, DSource::array> array{};
-    const std::integral_constant<DSource, DSource::none> none{};
-    if (symmetric && Dt) launch_kernel(yes, no, array, t, w, stream);
-    else if (symmetric) launch_kernel(yes, no, none, t, w, stream);
-    else if (Dt) launch_kernel(no, no, array, t, w, stream);
-    else launch_kernel(no, no, none, t, w, stream);
+    if (symmetric && Dt) launch_kernel(yes, no, yes, t.side, grid, work, stream);
+    else if (symmetric) launch_kernel(yes, no, no, t.side, grid, work, stream);
+    else if (Dt) launch_kernel(no, no, yes, t.side, grid, work, stream);
+    else launch_kernel(no, no, no, t.side, grid, work, stream);
     return hipGetLastError();
 }
 
-hipError_t launch_muon_product(MuonProduct product, const MuonGroup& g, hipStream_t stream)
+hipError_t launch_muon_product(MuonProduct product, const MuonLaunch& l, const MuonGroup* groups, hipStream_t stream)
 {
     constexpr float kA = 3.4445f, kB = -4.7750f, kC = 2.0315f;
-    const int64_t mn = (int64_t)g.mp * g.np, mm = (int64_t)g.mp * g.mp;
-    const bool next = product == MuonProduct::next;
-    const Tiles t = choose_tiles(next ? g.np : g.mp, g.mp, !next, g.count);
-    if (t.all > INT32_MAX) return hipErrorInvalidValue;
-    GemmWork w{};
-    w.tiles_m = (next ? g.np : g.mp) / t.side;
-    w.tiles_n = g.mp / t.side;
-    w.tiles = (int32_t)t.one;
-    w.all = (int32_t)t.all;
+    GemmWork work{};
+    work.items = l.items;
+    work.first = l.first;
+    for (size_t i = 0; i < l.groups.size(); ++i) {
+        const MuonGroup& g = groups[l.groups[i]];
+        const int64_t mn = (int64_t)g.mp * g.np, mm = (int64_t)g.mp * g.mp;
+        GemmGroup& w = work.g[i];
+        if (product == MuonProduct::gram) {
+            w.p = w.q = g.x;
+            w.c = w.ct = g.a;
+            w.stride_p = w.stride_q = mn;
+            w.stride_c = w.stride_ct = mm;
+            w.ldp = w.ldq = w.k = g.np;
+            w.ldc = w.ldct = g.mp;
+        } else if (product == MuonProduct::poly) {
+            w.p = w.q = w.dt = g.a;
+            w.c = w.ct = g.b;
+            w.stride_p = w.stride_q = w.stride_dt = w.stride_c = w.stride_ct = mm;
+            w.ldp = w.ldq = w.lddt = w.ldc = w.ldct = w.k = g.mp;
+        } else {
+            w.p = w.dt = g.x;
+            w.q = g.b;
+            w.ct = g.x2;
+            w.stride_p = w.stride_dt = w.stride_ct = mn;
+            w.stride_q = mm;
+            w.ldp = w.lddt = w.ldct = g.np;
+            w.ldq = w.k = g.mp;
+        }
+    }
+    work.alpha = product == MuonProduct::poly ? kC : 1.0f;
+    work.beta = product == MuonProduct::poly ? kB : kA;
     const std::true_type yes{};
     const std::false_type no{};
-    const std::integral_constant<DSource, DSource::operand> operand{};
-    if (product == MuonProduct::gram) {
-        w.p = w.q = g.x;
-        w.c = w.ct = g.a;
-        w.stride_p = w.stride_q = mn;
-        w.stride_c = w.stride_ct = mm;
-        w.ldp = w.ldq = w.k = g.np;
-        w.ldc = w.ldct = g.mp;
-        w.alpha = 1.0f;
-        launch_kernel(yes, no, std::integral_constant<DSource, DSource::none>{}, t, w, stream);
-    } else if (product == MuonProduct::poly) {
-        w.p = w.q = g.a;
-        w.c = w.ct = g.b;
-        w.stride_p = w.stride_q = w.stride_c = w.stride_ct = mm;
-        w.ldp = w.ldq = w.ldc = w.ldct = w.k = g.mp;
-        w.alpha = kC;
-        w.beta = kB;
-        launch_kernel(yes, no, operand, t, w, stream);
-    } else {
-        w.p = g.x;
-        w.q = g.b;
-        w.ct = g.x2;
-        w.stride_p = w.stride_ct = mn;
-        w.stride_q = mm;
-        w.ldp = w.ldct = g.np;
-        w.ldq = w.k = g.mp;
-        w.alpha = 1.0f;
-        w.beta = kA;
-        launch_kernel(no, yes, operand, t, w, stream);
-    }
+    if (product == MuonProduct::gram) launch_kernel(yes, no, no, l.side, l.workgroups, work, stream);
+    else if (product == MuonProduct::poly) launch_kernel(yes, no, yes, l.side, l.workgroups, work, stream);
+    else launch_kernel(no, yes, yes, l.side, l.workgroups, work, stream);
     return hipGetLastError();
 }
 

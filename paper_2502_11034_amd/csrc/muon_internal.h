@@ -3,7 +3,10 @@
 #ifndef ADAGC_MUON_INTERNAL_H
 #define ADAGC_MUON_INTERNAL_H
 
+#include <vector>
+
 #include "adagc_internal.h"
+#include "muon_plan.h"
 
 namespace adagc {
 
@@ -21,9 +24,14 @@ struct MuonGroup {
     int       mp, np, count;
     uint16_t *x, *x2, *a, *b;
 };
-// The three products of a Newton-Schulz step: a <- X X^T;  b <- b A + c A A;  x2 <- a X + B X.
-enum class MuonProduct { gram, poly, next };
-hipError_t launch_muon_product(MuonProduct product, const MuonGroup& g, hipStream_t stream);
+// A planned launch (muon_plan.h), its arrays in device memory.
+struct MuonLaunch {
+    int side, workgroups;
+    std::vector<int> groups;
+    const GemmItem*  items;
+    const int32_t*   first;
+};
+hipError_t launch_muon_product(MuonProduct product, const MuonLaunch& l, const MuonGroup* groups, hipStream_t stream);
 
 // One matrix of a batch, in device memory.
 struct MuonMatrix {

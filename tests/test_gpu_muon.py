@@ -816,9 +816,9 @@ def test_matrix_core_product_when_workgroups_take_several_tiles(batch, M, N, K, 
 
 @pytest.mark.parametrize("ns_steps", [1, 5])
 def test_muon_results_do_not_depend_on_the_size_of_the_tiles(ns_steps):
-    """32 matrices of 768 rows run on 256 x 256 tiles, one of them alone on 128 x 128 tiles.  The polynomial's lower terms are
-    added to the sums at an element's own place in k, whichever tile it lies in, so the bits must be the same: parameters of
-    a wide matrix, of a tall one, and of one whose extents end inside a tile."""
+    """32 matrices of 768 rows run on 256 x 256 tiles, one of them alone on 128 x 128 tiles.  Every sum runs over k in order, in
+    whichever tile, so the bits must be the same: parameters of a wide matrix, of a tall one, and of one whose extents end inside a
+    tile."""
     shapes = [(768, 2304), (2304, 768), (700, 2250), (2290, 641)] * 8
     g, m, th = _inputs(21, shapes)
     gamma = np.array([oracle.l2_norm(x.reshape(-1)) for x in g], np.float32)
