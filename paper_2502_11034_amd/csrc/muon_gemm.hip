@@ -23,8 +23,8 @@
 // v_mfma_f32_16x16x32_bf16.  One launch can cover a batch of equal-shaped products.  Operand tiles, 64 deep, are loaded
 // from global memory straight into LDS (global_load_lds_dwordx4, no staging registers), swizzled against bank conflicts, by
 // halves into a ring of five places (see "Main loop").  A compute unit's workgroups stay and take tile after tile: the next
-// tile's first loads are on their way while this one's results are stored (see "Epilogue").  The 256-tile kernels are at the
-// register limit of 256 and spill 20 to 28 of them around the loop, none inside it.
+// tile's first loads are on their way while this one's results are stored (see "Between tiles").  The 256-tile kernels are at the
+// register limit of 256; the one that reads P transposed spills a few around the loop, none inside it.
 
 #include <algorithm>
 #include <utility>
@@ -177,13 +177,16 @@ __device__ __forceinline__ void load_to_lds_16(const void* base, uint32_t off, c
 // higher clock (1313 -> 1343 TFLOP/s when it was introduced), and successive multiplications share an operand all the way
 // through.  The results are the same bit for bit: every sum runs over k in order.
 //
-// Epilogue.  Accumulator register r of lane l is element (row (l / 16) * 4 + r, column l % 16) of its 16 x 16 block: 8 bytes along
-// a row of Ct.  Exchanging half of the lanes' values between two neighbouring blocks (v_permlane16_swap) makes 16 bytes of
-// it, stored, and D loaded, without a detour through LDS; C, whose rows run the other way, is transposed through a 4 KB staging
-// area per wave in the fifth place of the ring (ds_read_b64_tr_b16).  The other four are receiving the next tile's first groups
-// meanwhile, and the stores complete during its first half steps.  (One workgroup per tile and all of LDS as the staging tile:
-// 4866 us for 12 products of 4096 x 14336 x 4096 with D, C and Ct, now 4706; X X^T as above 2373, now 2296.  Loading D
-// already in the last half step changed nothing.)
+// Between tiles.  The last half steps have no operands left to load: the ring takes the four quadrants of D then, or, without D, the
+// next tile's first four groups.  Accumulator register r of lane l is element (row (l / 16) * 4 + r, column l % 16) of its 16 x 16
+// block: 8 bytes along a row of Ct.  Exchanging half of the lanes' values between two neighbouring blocks (v_permlane16_swap) makes
+// 16 bytes of it, stored without a detour through LDS; C, whose rows run the other way, is transposed through the wave's own part
+// of a place of the ring (ds_read_b64_tr_b16).  Where a quadrant of D has been used, the next tile's groups are loaded.  The stores
+// complete during the next tile's first half steps.
+// Measured: one workgroup per tile and all of LDS as the staging tile, 12 products of 4096 x 14336 x 4096 with D, C and Ct 4866 us,
+// with workgroups that stay 4706; X X^T as above 2373, 2296.  D loaded to registers after the sums, with the waits that takes, against
+// the ring: b A + c A A of 48 matrices of 768 rows on 256-tiles 61, 52 us, of 6 of 2048 rows 59, 54, a X + B X of 32 of 1024 rows
+// 235, 225, of Llama-3-8B shapes 5315, 5220.
 //
 // PTR: P is given by its transpose, K rows of M consecutive elements (X itself in B X), and its fragments are read transposed
 // (ds_read_b64_tr_b16, two for the 16 bytes of a lane).  Only Ct then.
@@ -199,6 +202,8 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
     constexpr int kPlaceElems = 2 * kUnitElems;            // Q's half, then P's
     constexpr int kGL = 2 * kUnitElems / 512 / kWaves;     // loads per wave and group
     constexpr int kStores = BT * BT / 512 / kWaves;        // stores per wave of one output array
+    constexpr int kQuadRow = kTM / 2;                      // a quadrant's results: kTN / 2 rows (of Ct) of kQuadRow elements
+    constexpr int kDL = kStores / 4;                       // loads per wave of its part of D, per quadrant
     static_assert(kWaves % 2 == 0, "the swizzle of a load is taken from the wave's parity");
     __shared__ __attribute__((aligned(16))) uint16_t lds[5 * kPlaceElems];
 
@@ -215,6 +220,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
     auto place = [&](int p) { return lds + p * kPlaceElems; };
     auto at_place = [&](int p) { return lds0 + (uint32_t)(p * kPlaceElems * 2); };
     auto next_place = [](int p) { return p == 4 ? 0 : p + 1; };
+    auto previous_place = [](int p) { return p == 0 ? 4 : p - 1; };
 
     // Loads.  One global_load_lds_dwordx4 of a wave writes 1024 contiguous LDS bytes, lane i the i-th 16: that is 8 rows of a
     // 64-deep half tile stored without padding.  Bank conflicts of the fragment reads (16 lanes = 16 consecutive rows per
@@ -265,6 +271,37 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
         } else {
             load_to_lds_16(s.p + row * s.ldp + k0, s.off_p, dst + kUnitElems + first * kBK);
         }
+    };
+
+    // A wave's quadrant in LDS, where D is loaded and results are staged: in the same 1024-byte pieces of a place that the wave loads
+    // operands into, so that nobody else ever touches them.  16-byte vector c of row r is at position c ^ quad_swizzle(r): the 8
+    // rows that one half of the lanes reads 32 bytes of, 0 .. 3 and 8 .. 11 of 16, lie in different banks, and so do 16 rows' vectors c.
+    constexpr int kRowVecs = kQuadRow / 8, kPieceRows = 64 / kRowVecs;
+    auto quad_swizzle = [](int r) {
+        return kQuadRow == 64 ? (((r >> 1) & 1) * 2 | ((r >> 3) & 1) * 4 | ((r >> 2) & 1)) : (((r >> 3) & 1) * 2 | ((r >> 2) & 1));
+    };
+    auto quad_at = [&](uint32_t at, int r, int c) {
+        const int n = r / kPieceRows;
+        return at + (uint32_t)(((n & 1) ? 0 : kUnitElems * 2) + ((n >> 1) * kWaves + wave) * 1024 + (r % kPieceRows) * kQuadRow * 2 + (c ^ quad_swizzle(r)) * 16);
+    };
+    struct SourceD {
+        const uint16_t* p;
+        int ld;
+    };
+    auto source_d = [&](const TilePlace& t) {
+        const ADAGC_CONST GemmGroup& w = arguments().g[t.group];
+        SourceD s;
+        s.ld = w.lddt;
+        s.p = w.dt + (size_t)t.z * w.stride_dt + ((size_t)t.tile_n * BT + wn * (kTN / 2)) * w.lddt + (size_t)t.tile_m * BT + wm * (kTM / 2);
+        return s;
+    };
+    auto load_d = [&](const SourceD& s, int n, int q, uint16_t* dst) {
+        const uint16_t* from = s.p + (size_t)((q & 1) * (BT / 2) + n * kPieceRows) * s.ld + (q >> 1) * (BT / 2);
+        int l = lane;
+        asm volatile("" : "+v"(l));                        // made for each load: there are no registers to keep it in
+        const int r = l / kRowVecs;
+        const uint32_t off = (uint32_t)(r * s.ld + ((l % kRowVecs) ^ quad_swizzle(n * kPieceRows + r)) * 8) * 2u;
+        load_to_lds_16(from, off, dst + ((n & 1) ? 0 : kUnitElems) + ((n >> 1) * kWaves + wave) * 512);
     };
 
     // Fragments.  Lane l holds row l mod 16 of its 16-row block and the 16-byte vector 4 kk + l / 16 of that row; a block's first
@@ -349,14 +386,15 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
             ADAGC_SCHED_FENCE();
         });
     };
-    auto nothing = [](auto) __attribute__((always_inline)) {};
 
     TilePlace tp = tile_of_workgroup<SYM>(arguments(), 0);
     if (tp.z < 0) return;
     Source src = source(tp);
+    SourceD src_d;
 #pragma unroll
     for (int n = 0; n < 4 * kGL; ++n) load(src, n % kGL, n / kGL, place(n / kGL));
     ADAGC_WAIT_VMEM(2 * kGL);                              // groups 0 and 1
+    int rp = 0;                                            // the place of group h
     for (int round = 0;; ++round) {
         const int groups = src.groups;
 #pragma unroll
@@ -365,78 +403,128 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
             for (int j = 0; j < 2 * kHN; ++j)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
-        // Waits count the wave's accesses that may be outstanding.  Between groups 3 and 4 of a tile that is not the first lie the
-        // last one's stores, kStores or more (more only makes a wait stricter).
-        if (round) ADAGC_WAIT_VMEM(2 * kGL + kStores);
+        // Waits count the wave's accesses that may be outstanding.  After group 1 of a tile that is not the first come, without D,
+        // groups 2, 3 and the last tile's stores, kStores or more (more only makes a wait stricter); with D the stores of its last
+        // three quadrants and groups 2, 3, in turn.
+        if (round) ADAGC_WAIT_VMEM(2 * kGL + (HAS_D ? kStores * 3 / 4 : kStores));
         barrier_keeping_loads();
         {
             uint32_t pa[kPA], qd[2];
-            addresses_p(frag_p, lds0, pa);
-            addresses_q(frag_q, lds0, qd);
+            addresses_p(frag_p, at_place(rp), pa);
+            addresses_q(frag_q, at_place(rp), qd);
             static_for<2 * kHN>([&](auto N) { constexpr int n = decltype(N)::value; qa[n % kHN][n / kHN] = read(qd, n % kHN, n / kHN); });
             static_for<2 * kHM>([&](auto N) { constexpr int n = decltype(N)::value; p0[n % kHM][n / kHM] = read_p(pa, n % kHM, n / kHM); });
         }
         ADAGC_SCHED_FENCE();
-        if (groups > 4) {
+        if (groups > 4 && (!HAS_D || round == 0)) {
 #pragma unroll
-            for (int n = 0; n < kGL; ++n) load(src, n, 4, place(4));
+            for (int n = 0; n < kGL; ++n) load(src, n, 4, place(previous_place(rp)));
         }
         barrier_keeping_loads();
         const TilePlace tp_next = tile_of_workgroup<SYM>(arguments(), round + 1);
-        int rp = 0, h = 0;                                 // the place of group h
-        // The two half steps of a 64-deep tile.  LA, LB: whether there is a group h + 5, h + 6 to load; WA, WB: how many accesses
-        // may be outstanding when the group that the next half step reads has to be there.
-        auto tile = [&](auto LA, auto LB, auto WA, auto WB, bf16x8 (&x)[kHN][2], bf16x8 (&y)[kHN][2]) __attribute__((always_inline)) {
-            const int pl1 = next_place(rp), pl2 = next_place(pl1);
-            auto loads = [&](int g, uint16_t* dst) {
-                return [&, g, dst](auto T) __attribute__((always_inline)) {
-                    static_for<kGL>([&](auto N) __attribute__((always_inline)) {
-                        constexpr int n = decltype(N)::value;
-                        if constexpr (n * 2 * S / kGL + 1 == decltype(T)::value) load(src, n, g, dst);
-                    });
-                };
+        const bool more = tp_next.z >= 0;
+        // What follows the last group of the tile's operands in the ring: the four quadrants of D, or the next tile's first groups.
+        auto begin_extras = [&]() {
+            if constexpr (HAS_D) src_d = source_d(tp);
+            else if (more) src = source(tp_next);
+        };
+        auto load_extra = [&](int n, int e, uint16_t* dst) __attribute__((always_inline)) {
+            if constexpr (HAS_D) {
+                if (n < kDL) load_d(src_d, n, e, dst);
+            } else if (more) {
+                load(src, n, e, dst);
+            }
+        };
+        // at most `own` loads of the tile's groups and `extras` of those outstanding
+        auto wait_with_extras = [&](auto OWN, auto EXTRAS) __attribute__((always_inline)) {
+            constexpr int own = decltype(OWN)::value, extras = decltype(EXTRAS)::value;
+            if constexpr (HAS_D) ADAGC_WAIT_VMEM(own + extras * kDL);
+            else if (more) ADAGC_WAIT_VMEM(own + extras * kGL);
+            else ADAGC_WAIT_VMEM(own);
+        };
+        if (groups == 4) {
+            begin_extras();
+#pragma unroll
+            for (int n = 0; n < kGL; ++n) load_extra(n, 0, place(previous_place(rp)));
+        }
+        int h = 0;
+        auto spread = [&](auto&& f) __attribute__((always_inline)) {         // f(0) .. f(kGL - 1) over a half step
+            return [&](auto T) __attribute__((always_inline)) {
+                static_for<kGL>([&](auto N) __attribute__((always_inline)) {
+                    constexpr int n = decltype(N)::value;
+                    if constexpr (n * 2 * S / kGL + 1 == decltype(T)::value) f(n);
+                });
             };
-            if constexpr (decltype(LA)::value) half(no, yes, x, y, at_place(pl1), loads(h + 5, place(rp)));
-            else half(no, yes, x, y, at_place(pl1), nothing);
-            ADAGC_WAIT_VMEM(decltype(WA)::value);
+        };
+        constexpr std::integral_constant<int, kGL> w1{};
+        constexpr std::integral_constant<int, 2 * kGL> w2{};
+        constexpr std::integral_constant<int, 2> two{};
+        constexpr std::integral_constant<int, 3> three{};
+        // The first half step of a 64-deep tile, and both: each reads group h + 1 and loads group h + 5 into the place of group h.
+        auto loads = [&](int g, uint16_t* dst) __attribute__((always_inline)) {
+            return [&, g, dst](auto T) __attribute__((always_inline)) {
+                static_for<kGL>([&](auto N) __attribute__((always_inline)) {
+                    constexpr int n = decltype(N)::value;
+                    if constexpr (n * 2 * S / kGL + 1 == decltype(T)::value) load(src, n, g, dst);
+                });
+            };
+        };
+        auto first_half = [&](bf16x8 (&x)[kHN][2], bf16x8 (&y)[kHN][2]) __attribute__((always_inline)) {
+            const int pl1 = next_place(rp);
+            half(no, yes, x, y, at_place(pl1), loads(h + 5, place(rp)));
+            ADAGC_WAIT_VMEM(3 * kGL);
             barrier_keeping_loads();
-            if constexpr (decltype(LB)::value) half(yes, yes, x, y, at_place(pl2), loads(h + 6, place(pl1)));
-            else half(yes, yes, x, y, at_place(pl2), nothing);
-            ADAGC_WAIT_VMEM(decltype(WB)::value);
+            rp = pl1;
+            ++h;
+        };
+        auto tile = [&](bf16x8 (&x)[kHN][2], bf16x8 (&y)[kHN][2]) __attribute__((always_inline)) {
+            const int pl1 = next_place(rp), pl2 = next_place(pl1);
+            half(no, yes, x, y, at_place(pl1), loads(h + 5, place(rp)));
+            ADAGC_WAIT_VMEM(3 * kGL);
+            barrier_keeping_loads();
+            half(yes, yes, x, y, at_place(pl2), loads(h + 6, place(pl1)));
+            ADAGC_WAIT_VMEM(3 * kGL);
             barrier_keeping_loads();
             rp = pl2;
             h += 2;
         };
-        constexpr std::integral_constant<int, kGL> w1{};
-        constexpr std::integral_constant<int, 2 * kGL> w2{};
-        constexpr std::integral_constant<int, 3 * kGL> w3{};
+        // the same near the end, where group h + 5 is extra number E
+        auto extra = [&](auto PART, auto E, bf16x8 (&x)[kHN][2], bf16x8 (&y)[kHN][2]) __attribute__((always_inline)) {
+            uint16_t* dst = place(rp);
+            half(PART, yes, x, y, at_place(next_place(rp)), spread([&](int n) __attribute__((always_inline)) { load_extra(n, decltype(E)::value, dst); }));
+            if constexpr (decltype(E)::value == 0) wait_with_extras(w2, yes);
+            if constexpr (decltype(E)::value == 1) wait_with_extras(w1, two);
+            if constexpr (decltype(E)::value == 2) wait_with_extras(no, three);
+            barrier_keeping_loads();
+            rp = next_place(rp);
+            ++h;
+        };
         while (h + 12 <= groups) {
-            tile(yes, yes, w3, w3, qa, qb);
-            tile(yes, yes, w3, w3, qb, qa);
+            tile(qa, qb);
+            tile(qb, qa);
         }
         if (groups > 4) {
-            tile(yes, yes, w3, w3, qa, qb);
-            tile(yes, no, w3, w2, qb, qa);                 // loads the last group
+            tile(qa, qb);
+            first_half(qb, qa);                            // loads the last group
+            begin_extras();
+            extra(yes, no, qb, qa);
         }
-        tile(no, no, w1, no, qa, qb);
-        half(no, yes, qb, qa, at_place(next_place(rp)), nothing);
-        barrier_keeping_loads();                           // all operands are in registers: the ring is free
-        const bool more = tp_next.z >= 0;
-        if (more) src = source(tp_next);
-        half(yes, no, qb, qa, 0u, [&](auto T) __attribute__((always_inline)) {
-            static_for<4 * kGL>([&](auto N) __attribute__((always_inline)) {
-                constexpr int n = decltype(N)::value;
-                if constexpr (n * 2 * S / (4 * kGL) == decltype(T)::value) {
-                    if (more) load(src, n % kGL, n / kGL, place(n / kGL));
-                }
-            });
-        });
+        extra(no, yes, qa, qb);
+        extra(yes, two, qa, qb);
+        extra(no, three, qb, qa);
+        // All operands are in registers; rp is the place of the last group, free.  With D the next tile's first group goes there, without,
+        // results are staged there.
+        half(yes, no, qb, qa, 0u, [](auto) __attribute__((always_inline)) {});
+        if (HAS_D && more) {
+            src = source(tp_next);
+#pragma unroll
+            for (int n = 0; n < kGL; ++n) load(src, n, 0, place(rp));
+        }
 
         // epilogue
         const ADAGC_CONST GemmGroup& w = arguments().g[tp.group];
         const float alpha = arguments().alpha, beta = arguments().beta;
         const size_t v0 = (size_t)tp.tile_m * BT + wm * (kTM / 2), w0 = (size_t)tp.tile_n * BT + wn * (kTN / 2);
-        const uint16_t* Dt = HAS_D ? w.dt + (size_t)tp.z * w.stride_dt + w0 * w.lddt + v0 : nullptr;
         uint16_t* Ct = w.ct ? w.ct + (size_t)tp.z * w.stride_ct + w0 * w.ldct + v0 : nullptr;
         uint16_t* C = !PTR && (SYM ? tp.tile_m != tp.tile_n : w.c != nullptr) ? w.c + (size_t)tp.z * w.stride_c + v0 * w.ldc + w0 : nullptr;
         int le = lane;
@@ -444,31 +532,30 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
         const int er = le & 15, eg = le >> 4;
         // after the exchange, lane l has 8 elements of row l mod 16: of the first block (even l / 16) or the second, from 0 or from 8
         const uint32_t lane_v = (uint32_t)((eg & 1) * 16 + (eg >> 1) * 8);
-        const uint32_t off_dt = ((uint32_t)er * (uint32_t)w.lddt + lane_v) * 2u, off_ct = ((uint32_t)er * (uint32_t)w.ldct + lane_v) * 2u;
+        const uint32_t off_ct = ((uint32_t)er * (uint32_t)w.ldct + lane_v) * 2u;
         const uint32_t off_c = ((uint32_t)er * (uint32_t)w.ldc + (uint32_t)eg * 8u) * 2u;
-        constexpr int kQuadRow = kTM / 2;                  // a quadrant: kTN / 2 rows of Ct, kQuadRow elements of each
-        const uint32_t stage = at_place(4) + (uint32_t)(wave * kQuadRow * (kTN / 2) * 2);
-        // 16-byte vector c of row r of the staging area is at position c ^ stage_swizzle(r): 8 rows that one half of the lanes reads
-        // 32 bytes of, 0 .. 3 and 8 .. 11 of 16, lie in different banks
-        auto stage_swizzle = [](int r) {
-            return kQuadRow == 64 ? (((r >> 1) & 1) * 2 | ((r >> 3) & 1) * 4 | ((r >> 2) & 1)) : (((r >> 3) & 1) * 2 | ((r >> 2) & 1));
-        };
         constexpr int kPer = kHM / 2 * kHN;                // 16-byte vectors per lane and quadrant
         auto swap16 = [](uint32_t& x, uint32_t& y) {
             const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
             x = r[0];
             y = r[1];
         };
+        int quad_place = HAS_D ? next_place(rp) : rp;
+        if constexpr (HAS_D) {
+            if (more) ADAGC_WAIT_VMEM(kGL);                // all of D; only this wave reads what it loaded
+            else ADAGC_WAIT_VMEM(0);
+        }
 #pragma unroll
         for (int a = 0; a < 2; ++a)
 #pragma unroll
             for (int b = 0; b < 2; ++b) {
+                const uint32_t quad = at_place(quad_place);
                 u32x4 dv[kPer];
                 if constexpr (HAS_D) {
 #pragma unroll
                     for (int n = 0; n < kPer; ++n) {
                         const int i = (n % (kHM / 2)) * 2, j = n / (kHM / 2);
-                        dv[n] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(Dt + (size_t)(b * (BT / 2) + j * 16) * w.lddt + a * (BT / 2) + i * 16) + off_dt);
+                        dv[n] = *reinterpret_cast<const ADAGC_LDS u32x4*>(quad_at(quad, j * 16 + er, (i + (eg & 1)) * 2 + (eg >> 1)));
                     }
                 }
 #pragma unroll
@@ -497,8 +584,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
                     if (Ct)
                         *reinterpret_cast<u32x4*>(reinterpret_cast<char*>(Ct + (size_t)(b * (BT / 2) + j * 16) * w.ldct + a * (BT / 2) + i * 16) + off_ct) = o;
                     if (C) {
-                        const int r = j * 16 + er, c = (i + (eg & 1)) * 2 + (eg >> 1);
-                        *reinterpret_cast<ADAGC_LDS u32x4*>(stage + (uint32_t)(r * kQuadRow * 2 + ((c ^ stage_swizzle(r)) * 16))) = o;
+                        *reinterpret_cast<ADAGC_LDS u32x4*>(quad_at(quad, j * 16 + er, (i + (eg & 1)) * 2 + (eg >> 1))) = o;
                     }
                 }
                 if (C) {
@@ -510,7 +596,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
 #pragma unroll
                         for (int e = 0; e < 2; ++e) {
                             const int r = 8 * eg + 4 * e + (er >> 2), c = vb * 2 + ((er & 3) >> 1);
-                            const uint32_t at = stage + (uint32_t)(r * kQuadRow * 2 + ((c ^ stage_swizzle(r)) * 16) + (er & 1) * 8);
+                            const uint32_t at = quad_at(quad, r, c) + (uint32_t)((er & 1) * 8);
                             t[e] = __builtin_bit_cast(u32x2v, __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<ADAGC_LDS s16x4*>(at)));
                         }
                         const u32x4 o = {t[0].x, t[0].y, t[1].x, t[1].y};
@@ -518,9 +604,19 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
                     }
                     asm volatile("" ::: "memory");
                 }
+                if constexpr (HAS_D) {
+                    // the quadrant's place takes the next group of the next tile
+                    const int g = 2 * a + b + 1;
+                    if (more && (g < 4 || src.groups > 4)) {
+#pragma unroll
+                        for (int n = 0; n < kGL; ++n) load(src, n, g, place(quad_place));
+                    }
+                    quad_place = next_place(quad_place);
+                }
             }
         if (!more) return;
         tp = tp_next;
+        if (!HAS_D) rp = next_place(rp);                   // where the next tile's first group was loaded
     }
 }
 

@@ -10,15 +10,16 @@ namespace {
 
 constexpr int kXcds = 8, kDepth = 64;      // dies with an L2 each (workgroup b runs on die b mod 8); k per operand tile
 
-// What a tile takes, in microseconds: per operand tile, and for its first loads and its results (those of gram and poly are
-// written twice).  A 256-tile has a compute unit for itself; of 128-tiles a unit holds one, or two that share it.
+// What a tile takes, in microseconds: per operand tile, and for its first loads and its results.  A 256-tile has a compute unit
+// for itself; of 128-tiles a unit holds one, or two that share it.
 struct Cost {
     double step, ends;
 };
 Cost cost_of(MuonProduct product, int side, bool two)
 {
-    if (side == 256) return {1.25, product == MuonProduct::next ? 10.0 : 14.0};
-    return two ? Cost{0.68, 7.5} : Cost{0.30, 5.0};
+    const bool next = product == MuonProduct::next;
+    if (side == 256) return {1.25, next ? 14.0 : 10.0};
+    return two ? Cost{0.68, next ? 9.5 : 7.5} : Cost{0.30, 5.0};
 }
 constexpr double kLaunch = 3.0;
 
@@ -118,15 +119,15 @@ PlannedLaunch plan_launch(MuonProduct product, const std::vector<MuonExtent>& ex
 
 }  // namespace
 
-// The size of the tiles is chosen for the launch, by the estimate.  Measured (estimated), all on 128-tiles against 256-tiles where
-// they fit, in microseconds:
-//   24 of 768 x 3072, 12 of 768 x 2304, 12 of 768 x 768    gram 70 (75) / 77 (77)    poly 34 (34) / 53 (61)    next 181 (176) / 152 (153)
-//   16 of 1024 x 4096, 8 of 1024 x 3072, 8 of 1024 x 1024  gram 105 / 110            poly 47 / 63              next 254 / 193
-//   6 of 2048 x 2560                                       gram 76 / 62              poly 63 / 54              next 125 / 103
-//   1 of 1024 x 4096                                       gram 29 / 76              poly 14 / 31              next 15 / 29
-//   12 of 4096 x 14336, 8 of 4096 x 4096, 8 of 1024 x 4096 gram 3936 / 2568          poly 1446 / 1168          next 7703 / 5058
-// A launch for each group instead of one for all: 141 against 77, 85 against 53 and 185 against 152 on the first list (256-tiles),
-// 2801 against 2568, 1238 against 1168 and 5080 against 5058 on the last.
+// The size of the tiles is chosen for the launch, by the estimate.  Measured, all on 128-tiles against 256-tiles where they fit, in
+// microseconds:
+//   24 of 768 x 3072, 12 of 768 x 2304, 12 of 768 x 768    gram 74 / 77        poly 35 / 52        next 194 / 178
+//   16 of 1024 x 4096, 8 of 1024 x 3072, 8 of 1024 x 1024  gram 110 / 105      poly 48 / 63        next 272 / 225
+//   6 of 2048 x 2560                                       gram 78 / 62        poly 61 / 54        next 129 / 108
+//   1 of 1024 x 4096                                       gram 30 / 75        poly 11 / 28        next 15 / 28
+//   12 of 4096 x 14336, 8 of 4096 x 4096, 8 of 1024 x 4096 gram 3956 / 2638    poly 1459 / 1184    next 8039 / 5220
+// A launch for each group instead of one for all: 141 against 77, 85 against 52 and 185 against 178 on the first list (256-tiles),
+// 2801 against 2638, 1238 against 1184 and 5080 against 5220 on the last.
 std::vector<PlannedLaunch> plan_muon_product(MuonProduct product, const std::vector<MuonExtent>& extents)
 {
     std::vector<int> everything, large, rest;
