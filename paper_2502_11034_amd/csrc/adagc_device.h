@@ -64,12 +64,12 @@ __device__ __forceinline__ TensorArgs load_tensor(const TensorArgs* targs, uint3
     a.chunk_begin = (uint32_t)r[6];
     a.chunk_count = (uint32_t)(r[6] >> 32);
     a.vec_ok = (uint32_t)r[7];
-    a.pad = (uint32_t)(r[7] >> 32);
+    a.line_offset = (uint32_t)(r[7] >> 32);
     return a;
 }
 static_assert(offsetof(TensorArgs, grad) == 8 && offsetof(TensorArgs, exp_avg) == 16 && offsetof(TensorArgs, exp_avg_sq) == 24 &&
                   offsetof(TensorArgs, param_copy) == 32 && offsetof(TensorArgs, numel) == 40 && offsetof(TensorArgs, chunk_begin) == 48 &&
-                  offsetof(TensorArgs, chunk_count) == 52 && offsetof(TensorArgs, vec_ok) == 56,
+                  offsetof(TensorArgs, chunk_count) == 52 && offsetof(TensorArgs, vec_ok) == 56 && offsetof(TensorArgs, line_offset) == 60,
               "load_tensor takes the record apart by hand");
 
 // Not templates of the vector's type: a deduced type is the vector without its typedef's alignment, and the access would claim

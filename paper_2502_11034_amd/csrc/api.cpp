@@ -370,6 +370,7 @@ int prepare_tables(adagc_ctx* ctx, void* const* params, const void* const* grads
 
     // Rebuild the per-tensor records from the caller's pointer arrays.
     const uintptr_t grad_align = bf16g ? 2 : 4;
+    int64_t off_lines = 0, elems = 0;
     for (int64_t i = 0; i < ctx->n_tensors; ++i) {
         TensorArgs& a = ctx->scratch_args[(size_t)i];
         a.param = params[i];
@@ -384,8 +385,11 @@ int prepare_tables(adagc_ctx* ctx, void* const* params, const void* const* grads
         a.vec_ok = (aligned(a.param, 4) && aligned(a.exp_avg, 4) && aligned(a.grad, grad_align) &&
                     (!adamw || aligned(a.exp_avg_sq, 4)) && (!copy || aligned(a.param_copy, 2)))
                        ? 1u : 0u;
-        a.pad = 0;
+        a.line_offset = line_offset_of(a);
+        elems += a.numel;
+        if (a.line_offset) off_lines += a.numel;
     }
+    ctx->tables.off_lines = walk_lines(ctx->cfg.optimizer, bf16g, copy, ctx->n_tensors, elems, off_lines);
 
     const size_t args_bytes = (size_t)ctx->n_tensors * sizeof(TensorArgs);
     if (!ctx->args_uploaded ||

@@ -668,7 +668,7 @@ __device__ __forceinline__ void wait_for_loads()
 template <int OPT>
 constexpr int kUpdateWaves = OPT == ADAGC_OPT_ADAMW ? 2 : 3;
 
-template <int OPT, bool BF16G, bool COPY, int U, bool NT, bool TELE>
+template <int OPT, bool BF16G, bool COPY, int U, bool NT, bool TELE, bool LINES>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kUpdateWaves<OPT>, kUpdateWaves<OPT>)))
 void update_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items, const StepScalars* device_scalars, FusedRule rule)
 {
@@ -709,30 +709,51 @@ void update_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items, const Step
             const int e1 = len < e0 + kTileElems ? len : e0 + kTileElems; // [e0, e1), empty past a ragged end
             if (e0 >= e1) break;
             if (ta.vec_ok) {
-                const auto p4 = (ADAGC_GLOBAL f32x4_any*)p;
-                const auto m4 = (ADAGC_GLOBAL f32x4_any*)m;
-                const auto v4 = (ADAGC_GLOBAL f32x4_any*)v;
-                const auto c4 = (ADAGC_GLOBAL u32x2_any*)pc;
+                // LINES: tiles start on a line.  A wave's access to 16 bytes per lane that does not touches nine lines instead of eight,
+                // two of them in part, and of a line written in part the memory writes what is there anew.  So where the arrays
+                // agree on their place in a line, every tile of the tensor is taken `shift` elements earlier: a chunk's first tile has
+                // the end of the chunk before it, the tensor's last tile what is left, one by one.  Tensors laid end to end (1500 of
+                // up to 4 M elements): 2290 us per step without, 2062 with.  (Not with telemetry: its partial sums
+                // would have the elements in another order than on tensors that lie apart.)  Lists that lie on lines have a kernel
+                // without the shift: 5000 small ones 102 us there, 112 here.
+                const int shift = LINES ? (int)ta.line_offset : 0;
+                const bool starts = LINES && c.index == 0, ends = !LINES || c.index + 1 == ta.chunk_count;
+                const auto p4 = (ADAGC_GLOBAL f32x4_any*)(p - shift);
+                const auto m4 = (ADAGC_GLOBAL f32x4_any*)(m - shift);
+                const auto v4 = (ADAGC_GLOBAL f32x4_any*)(kHasV ? v - shift : nullptr);
+                const auto c4 = (ADAGC_GLOBAL u32x2_any*)(COPY ? pc - shift : nullptr);
+                const gcbytes g4 = g - shift * (BF16G ? 2 : 4);
                 const int v0 = sub * kTileVecs;
 
                 // Whole tiles and ragged ends alike: all loads before the first store (in a loop over the vectors of a
-                // ragged end they would wait for the stores of the round before).  Lanes past the last whole vector load
-                // that one again and store nothing; up to three single elements come with the tile that ends the chunk.
-                const int nvec = len >> 2;
-                const int j = (nvec << 2) + lane;
-                const bool single = e1 == len && j < len;
+                // ragged end they would wait for the stores of the round before).  Lanes outside the whole vectors
+                // vmin .. nvec - 1 load the nearest one and store nothing; up to three single elements come with the tile that
+                // starts the tensor, up to three (and the 31 that no tile has) with the one that ends it.
+                const int vmin = starts ? (shift + 3) >> 2 : 0;
+                const int nvec = ends ? (len + shift) >> 2 : kChunkElems / 4;
+                int j = (nvec << 2) + lane;
+                bool any = v0 < nvec, single = e1 == len && j < len;
+                if constexpr (LINES) {
+                    const int vend = nvec < v0 + kTileVecs ? nvec : v0 + kTileVecs;
+                    any = (v0 > vmin ? v0 : vmin) < vend;
+                    const int before = starts && sub == 0 ? 4 * vmin - shift : 0, n_head = before < len ? before : len;
+                    const int tail = starts && vend <= vmin ? n_head : 4 * vend - shift;
+                    const int n_tail = ends && e1 == len ? len - tail : 0;
+                    j = lane < n_head ? lane : tail + lane - n_head;
+                    single = lane < n_head + n_tail;
+                }
                 ElemState s = {0.f, 0.f, 0.f};
                 float g1 = 0.f;
                 if (single) {
                     s = {p[j], m[j], kHasV ? v[j] : 0.f};
                     g1 = load_grad1<BF16G>(g, j);
                 }
-                if (v0 < nvec) {
+                if (any) {
                     f32x4 gg[U], pp[U], mm[U], vv[U];
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
-                        const int want = v0 + u * kLanes + lane, idx = want < nvec ? want : nvec - 1;
-                        gg[u] = load_grad4<BF16G, NTL>(g, idx);
+                        const int want = v0 + u * kLanes + lane, most = want < nvec ? want : nvec - 1, idx = LINES && most < vmin ? vmin : most;
+                        gg[u] = load_grad4<BF16G, NTL>(g4, idx);
                         pp[u] = ld<NTL>(p4 + idx);
                         mm[u] = ld<NTL>(m4 + idx);
                         if constexpr (kHasV) vv[u] = ld<NTL>(v4 + idx);
@@ -743,6 +764,7 @@ void update_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items, const Step
                     for (int u = 0; u < U; ++u) {
                         const int idx = v0 + u * kLanes + lane;
                         if (idx >= nvec) break;
+                        if (LINES && idx < vmin) continue;
                         const f32x4 p_old = pp[u];
                         apply_vec<OPT>(a, h, uc, gg[u], pp[u], mm[u], vv[u]);
                         if constexpr (TELE) tele_vec<kHasV>(tele, p_old, pp[u], mm[u], vv[u]);
@@ -1017,33 +1039,36 @@ __global__ __launch_bounds__(kBlock) void finalize_telemetry_kernel(DeviceTables
 
 using UpdateFn = void (*)(DeviceTables, UpdateArgs, uint32_t, const StepScalars*, FusedRule);
 
+// lines: only with the launch shape that is not chosen otherwise
 template <int OPT, bool BF16G, bool COPY, int U>
-UpdateFn select_update_flags(int nt, int tele)
+UpdateFn select_update_flags(int nt, int tele, bool lines)
 {
-    if (nt) return tele ? update_kernel<OPT, BF16G, COPY, U, true, true> : update_kernel<OPT, BF16G, COPY, U, true, false>;
-    return tele ? update_kernel<OPT, BF16G, COPY, U, false, true> : update_kernel<OPT, BF16G, COPY, U, false, false>;
+    if constexpr (U == default_unroll(OPT))
+        if (lines && nt && !tele) return update_kernel<OPT, BF16G, COPY, U, true, false, true>;
+    if (nt) return tele ? update_kernel<OPT, BF16G, COPY, U, true, true, false> : update_kernel<OPT, BF16G, COPY, U, true, false, false>;
+    return tele ? update_kernel<OPT, BF16G, COPY, U, false, true, false> : update_kernel<OPT, BF16G, COPY, U, false, false, false>;
 }
 
 template <int OPT, bool BF16G, bool COPY>
-UpdateFn select_update_variant(int unroll, int nt, int tele)
+UpdateFn select_update_variant(int unroll, int nt, int tele, bool lines)
 {
-    if (unroll == 4) return select_update_flags<OPT, BF16G, COPY, 4>(nt, tele);
-    if (unroll == 2) return select_update_flags<OPT, BF16G, COPY, 2>(nt, tele);
-    return select_update_flags<OPT, BF16G, COPY, 1>(nt, tele);
+    if (unroll == 4) return select_update_flags<OPT, BF16G, COPY, 4>(nt, tele, lines);
+    if (unroll == 2) return select_update_flags<OPT, BF16G, COPY, 2>(nt, tele, lines);
+    return select_update_flags<OPT, BF16G, COPY, 1>(nt, tele, lines);
 }
 
-UpdateFn select_update(int optimizer, int grad_bf16, int with_copy, int unroll, int nt, int tele)
+UpdateFn select_update(int optimizer, int grad_bf16, int with_copy, int unroll, int nt, int tele, bool lines)
 {
     const int key = (optimizer == ADAGC_OPT_LION ? 4 : 0) | (grad_bf16 ? 2 : 0) | (with_copy ? 1 : 0);
     switch (key) {
-    case 0: return select_update_variant<ADAGC_OPT_ADAMW, false, false>(unroll, nt, tele);
-    case 1: return select_update_variant<ADAGC_OPT_ADAMW, false, true>(unroll, nt, tele);
-    case 2: return select_update_variant<ADAGC_OPT_ADAMW, true, false>(unroll, nt, tele);
-    case 3: return select_update_variant<ADAGC_OPT_ADAMW, true, true>(unroll, nt, tele);
-    case 4: return select_update_variant<ADAGC_OPT_LION, false, false>(unroll, nt, tele);
-    case 5: return select_update_variant<ADAGC_OPT_LION, false, true>(unroll, nt, tele);
-    case 6: return select_update_variant<ADAGC_OPT_LION, true, false>(unroll, nt, tele);
-    default: return select_update_variant<ADAGC_OPT_LION, true, true>(unroll, nt, tele);
+    case 0: return select_update_variant<ADAGC_OPT_ADAMW, false, false>(unroll, nt, tele, lines);
+    case 1: return select_update_variant<ADAGC_OPT_ADAMW, false, true>(unroll, nt, tele, lines);
+    case 2: return select_update_variant<ADAGC_OPT_ADAMW, true, false>(unroll, nt, tele, lines);
+    case 3: return select_update_variant<ADAGC_OPT_ADAMW, true, true>(unroll, nt, tele, lines);
+    case 4: return select_update_variant<ADAGC_OPT_LION, false, false>(unroll, nt, tele, lines);
+    case 5: return select_update_variant<ADAGC_OPT_LION, false, true>(unroll, nt, tele, lines);
+    case 6: return select_update_variant<ADAGC_OPT_LION, true, false>(unroll, nt, tele, lines);
+    default: return select_update_variant<ADAGC_OPT_LION, true, true>(unroll, nt, tele, lines);
     }
 }
 
@@ -1109,7 +1134,7 @@ hipError_t launch_update(const DeviceTables& t, const UpdateArgs& a, int optimiz
                          int with_copy, int unroll, int items_per_chunk, int nt, int tele, int grid,
                          hipStream_t stream, bool device_scalars, const FusedRule& rule)
 {
-    select_update(optimizer, grad_bf16, with_copy, unroll, nt, tele)<<<dim3(grid), dim3(kBlock), 0, stream>>>(
+    select_update(optimizer, grad_bf16, with_copy, unroll, nt, tele, t.off_lines != 0)<<<dim3(grid), dim3(kBlock), 0, stream>>>(
         t, a, log2_of(items_per_chunk), device_scalars ? t.scalars : nullptr, rule);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !tele) return e;

@@ -165,6 +165,7 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
 
     // Tensor records and chunk table, a batch of tensors per launch.
     const uintptr_t grad_align = bf16g ? 2 : 4;
+    int64_t off_lines = 0;
     uint32_t chunk_begin = 0, long_at = 0, short_at = (uint32_t)n_long, tiny_at = (uint32_t)(n_chunks - n_tiny);
     TensorBatch batch;
     for (int64_t first = 0; first < n_tensors; first += kBatch) {
@@ -183,7 +184,8 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
             a.vec_ok = (aligned(a.param, 4) && aligned(a.exp_avg, 4) && aligned(a.grad, grad_align) &&
                         (!adamw || aligned(a.exp_avg_sq, 4)) && (!copy || aligned(a.param_copy, 2)))
                            ? 1u : 0u;
-            a.pad = 0;
+            a.line_offset = line_offset_of(a);
+            if (a.line_offset) off_lines += a.numel;
             chunk_begin += a.chunk_count;
             const ChunkKind kind = last_kind(i);
             batch.long_at[b] = long_at;
@@ -210,6 +212,7 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
     const int grid_norm = (int)(groups > max_grid ? max_grid : groups);
     const int grid_update = (int)(items > max_grid ? max_grid : items);
 
+    t.off_lines = walk_lines(cfg->optimizer, bf16g, copy, n_tensors, total_elems, off_lines);
     FusedRule rule{};
     if (small_tensors && items <= kFusedMaxItems && !r.warmup && r.mode == ADAGC_MODE_ADAGC) rule = FusedRule{ema_norms, r};
     if (launch_sumsq_partials(t, bf16g, stream_gradients(total_elems, bf16g), grid_norm, stream, nullptr, 0, rule.ema) != hipSuccess)

@@ -235,3 +235,58 @@ def test_rule_in_the_update_equals_the_rules_kernel(optimizer, numels):
             assert np.array_equal(x, y)
         for x, y in zip(sa, sb):
             assert ((x - y).abs() <= 2e-7 * y.abs()).all()
+
+
+# sizes around the ends of vectors, lines, tiles (512, 1024, 2048, 4096 elements) and chunks (16384)
+LINES = [1, 2, 3, 4, 5, 31, 32, 33, 34, 63, 511, 513, 1023, 1024, 1025, 1056, 2047, 2049, 4064, 4095, 4096, 4097, 4128, 8190, 16353, 16383,
+         16384, 16385, 16416, 20480, 32767, 32769, 49153, 400003]            # the last brings the mean above the 16384 that the rule wants
+
+
+@pytest.mark.parametrize("lead", [0, 1, 2, 3, 7, 16, 29, 31, 32])
+@pytest.mark.parametrize("optimizer,grad_dtype,entry", [(B.ADAGC_OPT_ADAMW, B.ADAGC_GRAD_F32, "step"), (B.ADAGC_OPT_ADAMW, B.ADAGC_GRAD_BF16, "static"),
+                                                        (B.ADAGC_OPT_LION, B.ADAGC_GRAD_BF16, "step")])
+def test_tensors_that_start_anywhere_in_a_line(optimizer, grad_dtype, entry, lead):
+    """Where the arrays agree on their place in a 128-byte line, tiles start on lines: every element must be updated once, to the
+    bits it gets in an allocation of its own, and the gaps in front of, between and behind the tensors must stay.  `lead` elements lie
+    in front of the first tensor; once more with the moments elsewhere in a line than the parameters."""
+    rng = np.random.default_rng(lead + 100)
+    total = lead + sum(LINES) + 40
+    lion = optimizer == B.ADAGC_OPT_LION
+    gt = torch.bfloat16 if grad_dtype == B.ADAGC_GRAD_BF16 else torch.float32
+    types = {"p": torch.float32, "g": gt, "m": torch.float32, "v": torch.float32, "c": torch.bfloat16}
+    host = {"p": rng.standard_normal(total) * 0.02, "g": rng.standard_normal(total) * 0.01, "m": rng.standard_normal(total) * 0.002,
+            "v": rng.random(total) * 1e-4 + 1e-6, "c": np.full(total, 7.0)}
+    starts = [lead]
+    for n in LINES:
+        starts.append(starts[-1] + n)
+    gamma = torch.tensor([0.009 * n ** 0.5 for n in LINES], dtype=torch.float32, device=DEV)
+    hp = B.make_hyper(lr=1e-3, t_start=0)
+
+    def run(flat, offset_m=0):
+        whole = {k: torch.from_numpy(np.concatenate([np.zeros(offset_m), x]) if k == "m" else x).to(types[k]).to(DEV) for k, x in host.items()}
+        at = {k: offset_m if k == "m" else 0 for k in host}
+        lists = {k: [whole[k][a + at[k]:b + at[k]] for a, b in zip(starts, starts[1:])] for k in host}
+        if not flat:
+            lists = {k: [x.clone() for x in views] for k, views in lists.items()}
+        v = None if lion else lists["v"]
+        if entry == "static":
+            B.adagc_step_static(LINES, lists["p"], lists["g"], lists["m"], v, gamma.clone(), hp, 7, optimizer=optimizer, grad_dtype=grad_dtype,
+                                params_bf16=lists["c"])
+        else:
+            ctx = B.AdaGC(LINES, optimizer, grad_dtype, True)
+            ctx.set_param_copies(lists["c"])
+            ctx.step(lists["p"], lists["g"], lists["m"], v, gamma.clone(), hp, 7)
+            torch.cuda.synchronize()
+            ctx.close()
+        torch.cuda.synchronize()
+        return lists, whole
+    ref, _ = run(False)
+    for offset_m in (0, 3):
+        got, whole = run(True, offset_m)
+        for k in ("p", "m", "c") + (() if lion else ("v",)):
+            for i, n in enumerate(LINES):
+                assert torch.equal(got[k][i], ref[k][i]), "%s of tensor %d (%d elements)" % (k, i, n)
+        for k in ("p", "c", "v"):
+            ends = torch.cat([whole[k][:lead], whole[k][starts[-1]:]]).cpu()
+            want = torch.from_numpy(np.concatenate([host[k][:lead], host[k][starts[-1]:]])).to(types[k])
+            assert torch.equal(ends, want), "elements outside the tensors (%s)" % k
