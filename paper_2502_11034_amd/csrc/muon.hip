@@ -9,9 +9,10 @@
 //   muon_apply_kernel       per batch:  theta <- theta - lr (wd theta + scale O) of every matrix, optional bf16 copy
 //
 // A batch is one launch of each, over all of its matrices: a matrix of a few hundred rows is read in two microseconds,
-// less than a launch takes.  48 hidden matrices of GPT-2-small (85 M parameters, bf16 gradients, three batches): normalise
-// 48 x 7.7 us -> 3 x 55 us (10 B per parameter, 5.2 TB/s), apply 48 x 6.0 us -> 3 x 59 us (12 B, 5.8 TB/s).  At Llama-3-8B
-// shapes a matrix fills the chip by itself: 2.08 -> 1.94 ms and 1.54 -> 1.46 ms per 872 M parameters.
+// less than a launch takes.  48 hidden matrices of GPT-2-small (85 M parameters, bf16 gradients, three batches): normalise 164 us in
+// all (48 x 7.7 with a launch per matrix; 8 B per parameter, 4.2 TB/s), apply 181 us (48 x 6.0; 12 B, 5.6 TB/s).  872 M parameters at
+// Llama-3-8B shapes, fp32 gradients: normalise 1.65 ms (10 B, 5.3 TB/s; with X and its transpose to write 1.94), apply 1.53 ms (10 B,
+// 5.7 TB/s).
 //
 // The clip coefficient h of every tensor comes from the same norm and rule kernels as for AdamW and Lion
 // (kernels.hip); the Newton-Schulz products run in muon_gemm.hip.  Arithmetic is double with one rounding per
