@@ -27,6 +27,7 @@
 // register limit of 256; the one that reads P transposed spills a few around the loop, none inside it.
 
 #include <algorithm>
+#include <type_traits>
 #include <utility>
 
 #include "muon_internal.h"
@@ -158,6 +159,18 @@ __device__ __forceinline__ void load_to_lds_16(const void* base, uint32_t off, c
                  : "memory");
 }
 
+// The same at base + off_i with offsets that 32 bits do not hold.
+__device__ __forceinline__ void load_to_lds_16(const void* base, uint64_t off, const uint16_t* lds_dst)
+{
+    const uint32_t lds_addr = (uint32_t)reinterpret_cast<uintptr_t>(lds_dst);
+    const uint64_t at = reinterpret_cast<uintptr_t>(base) + off;
+    uint32_t saved_m0;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off\n\ts_mov_b32 m0, %0"
+                 : "=&s"(saved_m0)
+                 : "s"(lds_addr), "v"(at)
+                 : "memory");
+}
+
 // Main loop.  What bounds it: on ordinary data the power the chip may draw (its clock falls to 1.65 - 1.75 GHz under this
 // loop; 4096 x 4096 x 16384 takes 376 us on normal random operands and 294 on zeros, a library kernel 345 - 391 and 247 - 265
 // on the cards tried), otherwise the time an operand load takes.
@@ -190,9 +203,13 @@ __device__ __forceinline__ void load_to_lds_16(const void* base, uint32_t off, c
 //
 // PTR: P is given by its transpose, K rows of M consecutive elements (X itself in B X), and its fragments are read transposed
 // (ds_read_b64_tr_b16, two for the 16 bytes of a lane).  Only Ct then.
-template <int BT, bool SYM, bool PTR, bool HAS_D, int kGemmThreads>
+//
+// WIDE: a lane's offset from the wave's address, up to 15 rows and a few vectors, is kept in 64 bits, for rows of more than
+// kNarrowRow elements (the others have no registers to spare for that).
+template <int BT, bool SYM, bool PTR, bool HAS_D, bool WIDE, int kGemmThreads>
 __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const GemmWork)
 {
+    typedef std::conditional_t<WIDE, uint64_t, uint32_t> Offset;           // bytes
     constexpr int kWaves = kGemmThreads / 64;
     // waves in a kWM x kWN grid; with PTR the reads of P are the more expensive ones, so a wave has fewer of its rows
     constexpr int kWM = PTR ? kWaves / 2 : 2, kWN = kWaves / kWM;
@@ -230,13 +247,13 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
     // PTR: P's half is 64 rows (k) of BT / 2 elements, 4 (8) rows per load.  A fragment read takes 32 bytes, a block's 16 columns, of
     // 4 rows each for 16 lanes: of rows 0 .. 3 and 8 .. 11 (and 16 more) at a time.  The 32-byte unit u of row r is at position
     // u ^ swizzle_p(r), so that these lie in different banks.
-    // The address is split into a part common to the wave (scalar registers) and one 32-bit offset per lane.
+    // The address is split into a part common to the wave (scalar registers) and one offset per lane.
     auto swizzle_p = [](int r) { return BT == 256 ? ((r & 3) | ((r >> 3) & 1) << 2) : (((r >> 1) & 1) | ((r >> 3) & 1) << 1); };
     constexpr int kPtrRows = 1024 / BT;                    // rows per load
     struct Source {
         const uint16_t *p, *q;
         int ldp, ldq, groups;                              // groups: of loads, a multiple of 4, at least 4
-        uint32_t off_p, off_q;
+        Offset off_p, off_q;
     };
     auto source = [&](const TilePlace& t) {
         const ADAGC_CONST GemmGroup& w = arguments().g[t.group];
@@ -252,11 +269,11 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
         if constexpr (PTR) {
             constexpr int kRowLanes = BT / 16;
             const int r = l / kRowLanes;
-            s.off_p = (uint32_t)(r * w.ldp + ((l % kRowLanes) ^ (2 * swizzle_p(wave * kPtrRows + r))) * 8) * 2u;
+            s.off_p = ((Offset)r * (Offset)w.ldp + (Offset)(((l % kRowLanes) ^ (2 * swizzle_p(wave * kPtrRows + r))) * 8)) * 2u;
         } else {
-            s.off_p = (uint32_t)(row * w.ldp + vec * 8) * 2u;
+            s.off_p = ((Offset)row * (Offset)w.ldp + (Offset)(vec * 8)) * 2u;
         }
-        s.off_q = (uint32_t)(row * w.ldq + vec * 8) * 2u;
+        s.off_q = ((Offset)row * (Offset)w.ldq + (Offset)(vec * 8)) * 2u;
         return s;
     };
     auto load = [&](const Source& s, int n, int g, uint16_t* dst) {
@@ -300,7 +317,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
         int l = lane;
         asm volatile("" : "+v"(l));                        // made for each load: there are no registers to keep it in
         const int r = l / kRowVecs;
-        const uint32_t off = (uint32_t)(r * s.ld + ((l % kRowVecs) ^ quad_swizzle(n * kPieceRows + r)) * 8) * 2u;
+        const Offset off = ((Offset)r * (Offset)s.ld + (Offset)(((l % kRowVecs) ^ quad_swizzle(n * kPieceRows + r)) * 8)) * 2u;
         load_to_lds_16(from, off, dst + ((n & 1) ? 0 : kUnitElems) + ((n >> 1) * kWaves + wave) * 512);
     };
 
@@ -532,8 +549,8 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
         const int er = le & 15, eg = le >> 4;
         // after the exchange, lane l has 8 elements of row l mod 16: of the first block (even l / 16) or the second, from 0 or from 8
         const uint32_t lane_v = (uint32_t)((eg & 1) * 16 + (eg >> 1) * 8);
-        const uint32_t off_ct = ((uint32_t)er * (uint32_t)w.ldct + lane_v) * 2u;
-        const uint32_t off_c = ((uint32_t)er * (uint32_t)w.ldc + (uint32_t)eg * 8u) * 2u;
+        const Offset off_ct = ((Offset)er * (Offset)w.ldct + lane_v) * 2u;
+        const Offset off_c = ((Offset)er * (Offset)w.ldc + (Offset)eg * 8u) * 2u;
         constexpr int kPer = kHM / 2 * kHN;                // 16-byte vectors per lane and quadrant
         auto swap16 = [](uint32_t& x, uint32_t& y) {
             const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
@@ -630,22 +647,26 @@ struct Tiles {
 // A compute unit holds one 256 x 256 workgroup or two 128 x 128 ones, and multiplies about a quarter faster on the large tile
 // (fewer LDS reads per matrix-core instruction); a launch costs whole rounds of workgroups.  Compare the two in units of "one
 // 128-tile on a shared compute unit": a round of large tiles is 4 / 1.25 of them.
-Tiles choose_tiles(int M, int N, bool symmetric, int64_t batch)
+Tiles choose_tiles(int M, int N, bool symmetric, int64_t batch, bool wide)
 {
     auto tiles = [&](int64_t side) { return symmetric ? M / side * (M / side + 1) / 2 : (M / side) * (N / side); };
     const int64_t n128 = tiles(128) * batch, n256 = tiles(256) * batch;
     const double cost128 = 2.0 * (double)((n128 + 511) / 512);
     const double cost256 = 3.2 * (double)((n256 + 255) / 256);
-    if (M % 256 == 0 && N % 256 == 0 && cost256 < cost128) return {256, tiles(256), n256};
+    if (!wide && M % 256 == 0 && N % 256 == 0 && cost256 < cost128) return {256, tiles(256), n256};
     return {128, tiles(128), n128};
 }
 
+// Rows of up to this many elements: 15 of them and a few vectors are less than 4 GiB.
+constexpr int kNarrowRow = 1 << 27;
+
 template <bool SYM, bool PTR, bool D>
 void launch_kernel(std::integral_constant<bool, SYM>, std::integral_constant<bool, PTR>, std::integral_constant<bool, D>, int side, int grid,
-                   const GemmWork& w, hipStream_t stream)
+                   const GemmWork& w, hipStream_t stream, bool wide = false)
 {
-    if (side == 256) gemm_nt_bf16_kernel<256, SYM, PTR, D, 512><<<dim3((uint32_t)grid), dim3(512), 0, stream>>>(w);
-    else gemm_nt_bf16_kernel<128, SYM, PTR, D, 256><<<dim3((uint32_t)grid), dim3(256), 0, stream>>>(w);
+    if (side == 256) gemm_nt_bf16_kernel<256, SYM, PTR, D, false, 512><<<dim3((uint32_t)grid), dim3(512), 0, stream>>>(w);
+    else if (!wide) gemm_nt_bf16_kernel<128, SYM, PTR, D, false, 256><<<dim3((uint32_t)grid), dim3(256), 0, stream>>>(w);
+    else if constexpr (!PTR) gemm_nt_bf16_kernel<128, SYM, PTR, D, true, 256><<<dim3((uint32_t)grid), dim3(256), 0, stream>>>(w);
 }
 
 }  // namespace
@@ -671,7 +692,8 @@ hipError_t launch_gemm_nt_bf16(const void* P, int ldp, const void* Q, int ldq, i
     if (misaligned(P) || misaligned(Q) || misaligned(Dt) || misaligned(C) || misaligned(Ct)) return hipErrorInvalidValue;
     if (symmetric && (M != N || P != Q || stride_p != stride_q || !Ct || (C && (C != Ct || stride_c != stride_ct))))
         return hipErrorInvalidValue;
-    const Tiles t = choose_tiles(M, N, symmetric, batch);
+    const bool wide = ldp > kNarrowRow || ldq > kNarrowRow || (Dt && lddt > kNarrowRow) || (C && ldc > kNarrowRow) || (Ct && ldct > kNarrowRow);
+    const Tiles t = choose_tiles(M, N, symmetric, batch, wide);
     if (t.all > INT32_MAX) return hipErrorInvalidValue;
     GemmWork work{};
     work.alpha = alpha;
@@ -701,10 +723,10 @@ hipError_t launch_gemm_nt_bf16(const void* P, int ldp, const void* Q, int ldq, i
     const int grid = 8 * (int)std::min<int64_t>((t.all + 7) / 8, t.side == 256 ? 32 : 64);
     const std::true_type yes{};
     const std::false_type no{};
-    if (symmetric && Dt) launch_kernel(yes, no, yes, t.side, grid, work, stream);
-    else if (symmetric) launch_kernel(yes, no, no, t.side, grid, work, stream);
-    else if (Dt) launch_kernel(no, no, yes, t.side, grid, work, stream);
-    else launch_kernel(no, no, no, t.side, grid, work, stream);
+    if (symmetric && Dt) launch_kernel(yes, no, yes, t.side, grid, work, stream, wide);
+    else if (symmetric) launch_kernel(yes, no, no, t.side, grid, work, stream, wide);
+    else if (Dt) launch_kernel(no, no, yes, t.side, grid, work, stream, wide);
+    else launch_kernel(no, no, no, t.side, grid, work, stream, wide);
     return hipGetLastError();
 }
 

@@ -787,6 +787,50 @@ def test_muon_attach_takes_smaller_batches_when_memory_is_short():
     ctx.close()
 
 
+@pytest.fixture
+def memory_given_back():
+    torch.cuda.empty_cache()
+    yield
+    torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("array", ["P", "Q", "Dt", "C", "Ct", "symmetric"])
+@pytest.mark.parametrize("batch,M,N,ld", [(1, 128, 128, 310000000), (200, 256, 256, 150000000)])
+def test_matrix_core_product_in_rows_longer_than_32_bit_offsets(array, batch, M, N, ld, memory_given_back):
+    """A lane's place in an array is up to 15 rows from the wave's: more than 4 GiB in rows of 2^32 / 30 elements (and 7 rows of an operand
+    in rows of 2^32 / 14).  One array at a time lies in such rows (batch: the matrices side by side in them; 200 of 256 x 256 run on
+    256-tiles in short rows): the result must be that of the same matrices in rows of their own length."""
+    K = 128
+    rows = max(M, N)
+    if rows * ld * 2 > 0.9 * torch.cuda.mem_get_info()[0]:
+        pytest.skip("needs %d GB" % (rows * ld * 2 // 10 ** 9))
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    make = lambda *s: (torch.randn(s, generator=gen, device=DEV) * 0.05).to(torch.bfloat16)
+    P, Q, Dt = make(batch, M, K), make(batch, N, K), make(batch, N, M)
+    if array == "symmetric":
+        Dt = (Dt.float() + Dt.float().transpose(1, 2)).to(torch.bfloat16)
+    buf = torch.empty(rows * ld, dtype=torch.bfloat16, device=DEV)                   # only what the matrices cover is ever touched
+    long = lambda r, c: buf.as_strided((batch, r, c), (c, ld, 1))
+
+    def run(where):
+        ops = {"P": P, "Q": Q, "Dt": Dt, "C": torch.full((batch, M, N), 7.0, dtype=torch.bfloat16, device=DEV),
+               "Ct": torch.full((batch, N, M), 7.0, dtype=torch.bfloat16, device=DEV)}
+        if where in ops:
+            ops[where] = long(*ops[where].shape[1:]).copy_(ops[where])
+        if array == "symmetric":
+            if where:
+                ops["Ct"] = long(N, M).fill_(7.0)
+            B.adagc_muon_gemm_nt_batched(P, P, 2.0315, -4.775, Dt, None, ops["Ct"], symmetric=True)
+        else:
+            B.adagc_muon_gemm_nt_batched(ops["P"], ops["Q"], 2.0315, -4.775, ops["Dt"], ops["C"], ops["Ct"])
+        torch.cuda.synchronize()
+        return ops["C"], ops["Ct"]
+    ref_c, ref_ct = run(None)
+    got_c, got_ct = run(array)
+    assert torch.equal(got_ct, ref_ct)
+    assert torch.equal(got_c, ref_c)
+
+
 @pytest.mark.parametrize("batch,M,N,K,symmetric", [
     (40, 640, 640, 256, True),           # 128-tiles: 600 of them for 512 workgroups, 5 a side (a panel of 4 columns and one of 1)
     (15, 1280, 1536, 384, False),        # 256-tiles: 450 for 256 workgroups
