@@ -8,7 +8,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libadagc.so")
 SOURCES = ["api.cpp", "segment_table.cpp", "kernels.hip", "static_step.hip", "muon_gemm.hip", "muon.hip", "muon_plan.cpp"]
 HEADERS = [os.path.join(ROOT, "include", "adagc.h"), os.path.join(CSRC, "adagc_internal.h"), os.path.join(CSRC, "adagc_device.h"), os.path.join(CSRC, "muon_internal.h"),
-           os.path.join(CSRC, "muon_plan.h")]
+           os.path.join(CSRC, "muon_plan.h"), os.path.join(CSRC, "walk_lines.h")]
 
 
 def hipcc():

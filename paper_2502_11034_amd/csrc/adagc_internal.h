@@ -7,6 +7,7 @@
 #include <cmath>
 
 #include "adagc.h"
+#include "walk_lines.h"
 
 namespace adagc {
 
@@ -120,18 +121,6 @@ struct DeviceTables {
     uint32_t          n_tensors;
     uint32_t          off_lines;  // host: the update kernel walks whole lines (walk_lines)
 };
-
-// Whether a step's update kernel walks whole lines: most of the elements (off_lines of elems) belong to tensors that start off one,
-// and those are long enough for it to pay.  us per step, packed end to end, without / with; mean elements per tensor:
-//   AdamW, f32 gradients          330 000: 356 / 331   91 000: 199 / 187   22 000: 237 / 227   5800: 140 / 142   3200: 108 / 113
-//   AdamW, bf16 and the copy               382 / 329            218 / 191           254 / 226         152 / 142         117 / 113
-//   Lion, bf16 and the copy                243 / 234            142 / 136           168 / 163         103 / 103          81 / 84
-//   Lion, f32 gradients                    238 / 255            136 / 143           164 / 171         102 / 103          79 / 80
-// (Lion without the copy writes two arrays and reads three: the loads' overlap is worth more than the lines.)
-inline uint32_t walk_lines(int optimizer, bool bf16_grads, bool copy, int64_t n_tensors, int64_t elems, int64_t off_lines)
-{
-    return 2 * off_lines > elems && elems >= 16384 * n_tensors && (optimizer == ADAGC_OPT_ADAMW || (bf16_grads && copy));
-}
 
 // Vectors per lane and array that the update kernel keeps in flight, and the work items of a full chunk (one round of those
 // each), unless the caller chooses.  AdamW: 4, items of 4096 elements; in whole chunks a launch has too long a tail (GPT-2-small

@@ -20,6 +20,7 @@ struct adagc_ctx {
     adagc_config cfg{};
     int          grid_norm = 0;     // workgroups of the norm kernel
     int          grid_update = 0;   // workgroups of the update kernel
+    int64_t      n_items = 0;       // its work items, a workgroup for each unless the caller or the device limits them
     int          unroll = 0;
     int          nontemporal = 0;
     int          items_per_chunk = 1;   // work items of the update kernel per chunk
@@ -229,6 +230,7 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     c->stream_grads = c->nontemporal && stream_gradients(total_elems, cfg->grad_dtype == ADAGC_GRAD_BF16);
     c->small_list = tiles <= kFusedMaxItems && most_chunks <= kFusedMaxChunks;
     c->grid_norm = grid_for(c->n_chunks - n_tiny + (n_tiny + 3) / 4);
+    c->n_items = tiles;
     c->grid_update = grid_for(tiles);
 
     // One slab, carved into 256-byte aligned arrays.
@@ -389,7 +391,7 @@ int prepare_tables(adagc_ctx* ctx, void* const* params, const void* const* grads
         elems += a.numel;
         if (a.line_offset) off_lines += a.numel;
     }
-    ctx->tables.off_lines = walk_lines(ctx->cfg.optimizer, bf16g, copy, ctx->n_tensors, elems, off_lines);
+    ctx->tables.off_lines = walk_lines(ctx->cfg.optimizer, bf16g, copy, ctx->n_tensors, elems, off_lines, ctx->grid_update, ctx->n_items);
 
     const size_t args_bytes = (size_t)ctx->n_tensors * sizeof(TensorArgs);
     if (!ctx->args_uploaded ||

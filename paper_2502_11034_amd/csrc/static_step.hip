@@ -212,7 +212,7 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
     const int grid_norm = (int)(groups > max_grid ? max_grid : groups);
     const int grid_update = (int)(items > max_grid ? max_grid : items);
 
-    t.off_lines = walk_lines(cfg->optimizer, bf16g, copy, n_tensors, total_elems, off_lines);
+    t.off_lines = walk_lines(cfg->optimizer, bf16g, copy, n_tensors, total_elems, off_lines, grid_update, items);
     FusedRule rule{};
     if (small_tensors && items <= kFusedMaxItems && !r.warmup && r.mode == ADAGC_MODE_ADAGC) rule = FusedRule{ema_norms, r};
     if (launch_sumsq_partials(t, bf16g, stream_gradients(total_elems, bf16g), grid_norm, stream, nullptr, 0, rule.ema) != hipSuccess)

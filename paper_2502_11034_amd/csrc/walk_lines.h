@@ -1,0 +1,51 @@
+// When the update kernel walks the tensors of a list in whole 128-byte lines (kernels.hip).  Plain C++, without HIP.
+#ifndef ADAGC_WALK_LINES_H
+#define ADAGC_WALK_LINES_H
+
+#include <cstdint>
+
+#include "adagc.h"
+
+namespace adagc {
+
+// The least list (elements) for which whole lines pay, and the least launch (workgroups) where the caller limits it
+// (adagc_config::grid_blocks) below a workgroup for each work item; 0 elements: never.  The kernel that walks lines spends more
+// instructions, and reads and writes up to 37 elements of a tensor one by one: with few workgroups it is bound by those, and in a small
+// list by the chain of accesses of its first and last tiles.  Time per step without / with, equal tensors of 16501 to 1048577
+// elements end to end, by size of the list in 2^20 elements; and lists of 9, 30 and 64 M elements by workgroups:
+//                      1.5         3           4           6          12          160         256         320         640
+//   AdamW, copy        .95 - 1.02  1.01 - 1.07 1.03 - 1.06 1.03 - 1.09 1.07 - 1.11 .97 - 1.07  1.06 - 1.24 1.08 - 1.18 1.07 - 1.20
+//   AdamW, bf16        .95 - 1.00  .99 - 1.06  1.00 - 1.03 1.03 - 1.07 1.04       .90 - .92   .98 - 1.01  1.00 - 1.10 1.06 - 1.11
+//   AdamW, f32         .95 - 1.02  .97 - 1.03  .96 - 1.01  .99 - 1.04 1.02 - 1.04 .83 - .84   .95 - 1.03  1.02 - 1.12 .98 - 1.08
+//   Lion, bf16 + copy  .94 - 1.01  .97 - 1.01  .99 - 1.00  .97 - 1.00 1.01 - 1.02 .82 - .84   .85 - .89   .91 - .99   1.07 - 1.17
+// (Lion at 8: 1.00 - 1.02, with 512 workgroups .93 - 1.04.  Fewer, larger work items, adagc_config::update_split 1 or 2: 1.01 - 1.13 at
+// the size where the line lies and twice that.)
+struct LineLimits {
+    int64_t elems, workgroups;
+};
+inline LineLimits line_limits(int optimizer, bool bf16_grads, bool copy)
+{
+    if (optimizer == ADAGC_OPT_LION && bf16_grads && copy) return {(int64_t)8 << 20, 640};
+    if (optimizer != ADAGC_OPT_ADAMW) return {0, 0};
+    if (copy) return {(int64_t)3 << 20, 256};
+    return {(int64_t)(bf16_grads ? 4 : 6) << 20, 320};
+}
+
+// Whether a step's update kernel walks whole lines: the list and the launch (workgroups for so many work items) are large enough, most
+// of the elements (off_lines of elems) belong to tensors that start off a line, and those are long enough.  us per step, packed end
+// to end, without / with; mean elements per tensor:
+//   AdamW, f32 gradients          330 000: 356 / 331   91 000: 199 / 187   22 000: 237 / 227   5800: 140 / 142   3200: 108 / 113
+//   AdamW, bf16 and the copy               382 / 329            218 / 191           254 / 226         152 / 142         117 / 113
+//   Lion, bf16 and the copy                243 / 234            142 / 136           168 / 163         103 / 103          81 / 84
+//   Lion, f32 gradients                    238 / 255            136 / 143           164 / 171         102 / 103          79 / 80
+// (Lion without the copy writes two arrays and reads three: the loads' overlap is worth more than the lines.)
+inline bool walk_lines(int optimizer, bool bf16_grads, bool copy, int64_t n_tensors, int64_t elems, int64_t off_lines, int64_t workgroups,
+                       int64_t items)
+{
+    const LineLimits least = line_limits(optimizer, bf16_grads, copy);
+    return least.elems && elems >= least.elems && (workgroups >= items || workgroups >= least.workgroups) && 2 * off_lines > elems &&
+           elems >= 16384 * n_tensors;
+}
+
+}  // namespace adagc
+#endif

@@ -237,56 +237,135 @@ def test_rule_in_the_update_equals_the_rules_kernel(optimizer, numels):
             assert ((x - y).abs() <= 2e-7 * y.abs()).all()
 
 
-# sizes around the ends of vectors, lines, tiles (512, 1024, 2048, 4096 elements) and chunks (16384)
+# sizes around the ends of vectors, lines, tiles (512, 1024, 2048, 4096 elements) and chunks (16384); the last brings the list above
+# what walk_lines.h asks for (8 Mi elements for Lion, and the mean of 16384)
 LINES = [1, 2, 3, 4, 5, 31, 32, 33, 34, 63, 511, 513, 1023, 1024, 1025, 1056, 2047, 2049, 4064, 4095, 4096, 4097, 4128, 8190, 16353, 16383,
-         16384, 16385, 16416, 20480, 32767, 32769, 49153, 400003]            # the last brings the mean above the 16384 that the rule wants
+         16384, 16385, 16416, 20480, 32767, 32769, 49153, 8200003]
+LEADS = [0, 1, 2, 3, 7, 15, 29, 31, 32]        # elements in front of the first tensor; with 16 the last one would start on a line
+STEP, STATIC, GRAPH = "step", "static", "graph"
+LINE_RUNS = [(B.ADAGC_OPT_ADAMW, B.ADAGC_GRAD_F32, True, STEP, B.ADAGC_MODE_ADAGC, {}, LEADS),
+             (B.ADAGC_OPT_ADAMW, B.ADAGC_GRAD_F32, False, STEP, B.ADAGC_MODE_ADAGC, {}, LEADS),
+             (B.ADAGC_OPT_ADAMW, B.ADAGC_GRAD_BF16, True, STATIC, B.ADAGC_MODE_ADAGC, {}, LEADS),
+             (B.ADAGC_OPT_LION, B.ADAGC_GRAD_BF16, True, STEP, B.ADAGC_MODE_ADAGC, {}, LEADS),
+             (B.ADAGC_OPT_ADAMW, B.ADAGC_GRAD_BF16, False, STATIC, B.ADAGC_MODE_ADAGC, {}, [1, 31]),
+             (B.ADAGC_OPT_ADAMW, B.ADAGC_GRAD_BF16, False, GRAPH, B.ADAGC_MODE_ADAGC, {}, [1, 31]),
+             (B.ADAGC_OPT_ADAMW, B.ADAGC_GRAD_F32, False, GRAPH, B.ADAGC_MODE_ZCLIP, {}, [0, 29]),
+             (B.ADAGC_OPT_LION, B.ADAGC_GRAD_BF16, True, GRAPH, B.ADAGC_MODE_GLOBALGC, {}, [3, 15]),
+             (B.ADAGC_OPT_LION, B.ADAGC_GRAD_BF16, True, STATIC, B.ADAGC_MODE_GLOBAL_ADAGC, {}, [2, 7]),
+             (B.ADAGC_OPT_ADAMW, B.ADAGC_GRAD_BF16, False, STEP, B.ADAGC_MODE_AGC, {}, [3, 31]),
+             (B.ADAGC_OPT_ADAMW, B.ADAGC_GRAD_F32, True, STEP, B.ADAGC_MODE_CLIPPY, {}, [1, 15]),
+             (B.ADAGC_OPT_LION, B.ADAGC_GRAD_BF16, True, STEP, B.ADAGC_MODE_CLIPPY, {}, [29]),
+             (B.ADAGC_OPT_ADAMW, B.ADAGC_GRAD_F32, False, STEP, B.ADAGC_MODE_ADAGC, {"grid_blocks": 400}, [7]),
+             (B.ADAGC_OPT_LION, B.ADAGC_GRAD_BF16, True, STEP, B.ADAGC_MODE_ADAGC, {"update_split": 1}, [2])]
 
 
-@pytest.mark.parametrize("lead", [0, 1, 2, 3, 7, 16, 29, 31, 32])
-@pytest.mark.parametrize("optimizer,grad_dtype,entry", [(B.ADAGC_OPT_ADAMW, B.ADAGC_GRAD_F32, "step"), (B.ADAGC_OPT_ADAMW, B.ADAGC_GRAD_BF16, "static"),
-                                                        (B.ADAGC_OPT_LION, B.ADAGC_GRAD_BF16, "step")])
-def test_tensors_that_start_anywhere_in_a_line(optimizer, grad_dtype, entry, lead):
-    """Where the arrays agree on their place in a 128-byte line, tiles start on lines: every element must be updated once, to the
-    bits it gets in an allocation of its own, and the gaps in front of, between and behind the tensors must stay.  `lead` elements lie
-    in front of the first tensor; once more with the moments elsewhere in a line than the parameters."""
-    rng = np.random.default_rng(lead + 100)
-    total = lead + sum(LINES) + 40
-    lion = optimizer == B.ADAGC_OPT_LION
-    gt = torch.bfloat16 if grad_dtype == B.ADAGC_GRAD_BF16 else torch.float32
-    types = {"p": torch.float32, "g": gt, "m": torch.float32, "v": torch.float32, "c": torch.bfloat16}
-    host = {"p": rng.standard_normal(total) * 0.02, "g": rng.standard_normal(total) * 0.01, "m": rng.standard_normal(total) * 0.002,
-            "v": rng.random(total) * 1e-4 + 1e-6, "c": np.full(total, 7.0)}
-    starts = [lead]
-    for n in LINES:
-        starts.append(starts[-1] + n)
+class _Lines:
+    """The list LINES in flat buffers, `lead` elements in: values from the seed, on the host."""
+
+    def __init__(self, lead, grad_dtype):
+        gen = torch.Generator().manual_seed(lead + 100)
+        total = lead + sum(LINES) + 40
+        randn = lambda scale: torch.randn(total, generator=gen) * scale
+        self.lead, self.starts = lead, [lead]
+        for n in LINES:
+            self.starts.append(self.starts[-1] + n)
+        self.host = {"p": randn(0.02), "g": randn(0.01).to(torch.bfloat16 if grad_dtype == B.ADAGC_GRAD_BF16 else torch.float32),
+                     "m": randn(0.002), "v": torch.rand(total, generator=gen) * 1e-4 + 1e-6, "c": torch.full((total,), 7.0, dtype=torch.bfloat16)}
+
+    def buffers(self, offset_m=0):
+        """The flat buffers, and the list's views of them; m lies `offset_m` elements further on than the others."""
+        whole = {k: (torch.cat([torch.zeros(offset_m), x]) if k == "m" else x).to(DEV) for k, x in self.host.items()}
+        return whole, {k: [x[a:b] for a, b in zip(self.starts, self.starts[1:])] for k, x in
+                       ((k, x[offset_m:] if k == "m" else x) for k, x in whole.items())}
+
+    def check_gaps(self, whole, offset_m=0):
+        for k, x in whole.items():
+            at = offset_m if k == "m" else 0
+            got = torch.cat([x[at:at + self.lead], x[at + self.starts[-1]:]]).cpu()
+            want = torch.cat([self.host[k][:self.lead], self.host[k][self.starts[-1]:]])
+            assert torch.equal(got, want) and (x[:at] == 0).all(), "elements outside the tensors (%s)" % k
+
+
+def _step_in_lines(lists, optimizer, grad_dtype, copy, entry, mode, kw, warmup=False):
     gamma = torch.tensor([0.009 * n ** 0.5 for n in LINES], dtype=torch.float32, device=DEV)
-    hp = B.make_hyper(lr=1e-3, t_start=0)
-
-    def run(flat, offset_m=0):
-        whole = {k: torch.from_numpy(np.concatenate([np.zeros(offset_m), x]) if k == "m" else x).to(types[k]).to(DEV) for k, x in host.items()}
-        at = {k: offset_m if k == "m" else 0 for k in host}
-        lists = {k: [whole[k][a + at[k]:b + at[k]] for a, b in zip(starts, starts[1:])] for k in host}
-        if not flat:
-            lists = {k: [x.clone() for x in views] for k, views in lists.items()}
-        v = None if lion else lists["v"]
-        if entry == "static":
-            B.adagc_step_static(LINES, lists["p"], lists["g"], lists["m"], v, gamma.clone(), hp, 7, optimizer=optimizer, grad_dtype=grad_dtype,
-                                params_bf16=lists["c"])
-        else:
-            ctx = B.AdaGC(LINES, optimizer, grad_dtype, True)
+    hp = B.make_hyper(lr=1e-3, t_start=100 if warmup else 0, clip_mode=mode, lambda_abs=1e-5 if mode == B.ADAGC_MODE_CLIPPY else float("inf"),
+                      lambda_rel={B.ADAGC_MODE_AGC: 1e-3, B.ADAGC_MODE_CLIPPY: 1e-2}.get(mode, 1.04))
+    v = None if optimizer == B.ADAGC_OPT_LION else lists["v"]
+    if entry == STATIC:
+        B.adagc_step_static(LINES, lists["p"], lists["g"], lists["m"], v, gamma, hp, 7, optimizer=optimizer, grad_dtype=grad_dtype,
+                            params_bf16=lists["c"] if copy else None)
+    else:
+        ctx = B.AdaGC(LINES, optimizer, grad_dtype, copy, update_clipping=mode in (B.ADAGC_MODE_AGC, B.ADAGC_MODE_CLIPPY), **kw)
+        if copy:
             ctx.set_param_copies(lists["c"])
-            ctx.step(lists["p"], lists["g"], lists["m"], v, gamma.clone(), hp, 7)
-            torch.cuda.synchronize()
-            ctx.close()
+        if entry == GRAPH:
+            sp = torch.frombuffer(bytearray(B.step_params_bytes(hp, 7)), dtype=torch.uint8).to(DEV)
+            ctx.step_graph(lists["p"], lists["g"], lists["m"], v, gamma, sp)
+        else:
+            ctx.step(lists["p"], lists["g"], lists["m"], v, gamma, hp, 7)
         torch.cuda.synchronize()
-        return lists, whole
-    ref, _ = run(False)
+        ctx.close()
+    torch.cuda.synchronize()
+    return gamma
+
+
+def _same_state(got, ref, lion):
+    for k in ("p", "m", "c") + (() if lion else ("v",)):
+        for i, n in enumerate(LINES):
+            assert torch.equal(got[k][i], ref[k][i]), "%s of tensor %d (%d elements)" % (k, i, n)
+
+
+@pytest.mark.parametrize("optimizer,grad_dtype,copy,entry,mode,kw,lead", [run[:6] + (lead,) for run in LINE_RUNS for lead in run[6]])
+def test_tensors_that_start_anywhere_in_a_line(optimizer, grad_dtype, copy, entry, mode, kw, lead):
+    """Where the arrays agree on their place in a 128-byte line, tiles start on lines (tests/test_walk_lines.py holds these lists against
+    the rule): every element must be updated once, to the bits it gets in an allocation of its own, and the gaps in front of, between
+    and behind the tensors must stay.  `lead` elements lie in front of the first tensor; once more with the moments elsewhere in a line
+    than the parameters."""
+    data, lion = _Lines(lead, grad_dtype), optimizer == B.ADAGC_OPT_LION
+    ref = {k: [x.clone() for x in views] for k, views in data.buffers()[1].items()}
+    before = [x.clone() for x in ref["p"]]
+    gamma_ref = _step_in_lines(ref, optimizer, grad_dtype, copy, entry, mode, kw)
+    assert all((x != y).any() for x, y in zip(ref["p"], before))
     for offset_m in (0, 3):
-        got, whole = run(True, offset_m)
-        for k in ("p", "m", "c") + (() if lion else ("v",)):
-            for i, n in enumerate(LINES):
-                assert torch.equal(got[k][i], ref[k][i]), "%s of tensor %d (%d elements)" % (k, i, n)
-        for k in ("p", "c", "v"):
-            ends = torch.cat([whole[k][:lead], whole[k][starts[-1]:]]).cpu()
-            want = torch.from_numpy(np.concatenate([host[k][:lead], host[k][starts[-1]:]])).to(types[k])
-            assert torch.equal(ends, want), "elements outside the tensors (%s)" % k
+        whole, got = data.buffers(offset_m)
+        gamma = _step_in_lines(got, optimizer, grad_dtype, copy, entry, mode, kw)
+        _same_state(got, ref, lion)
+        assert torch.equal(gamma, gamma_ref)
+        data.check_gaps(whole, offset_m)
+
+
+@pytest.mark.parametrize("optimizer,grad_dtype,copy", [(B.ADAGC_OPT_ADAMW, B.ADAGC_GRAD_F32, False), (B.ADAGC_OPT_ADAMW, B.ADAGC_GRAD_BF16, True),
+                                                       (B.ADAGC_OPT_LION, B.ADAGC_GRAD_BF16, True)])
+@pytest.mark.parametrize("entry", [STEP, STATIC, GRAPH])
+def test_whole_lines_with_other_tensors_among_them(entry, optimizer, grad_dtype, copy):
+    """A list that is walked in whole lines for the sake of most of its elements: some tensors' moments lie elsewhere in a line, some
+    are in allocations of their own, and some have a momentum that is not even aligned to its elements and go element by element.  Inside
+    the warm-up without a limit, so that the coefficient is 1 whatever the order of the norms' sums."""
+    data, lion = _Lines(5, grad_dtype), optimizer == B.ADAGC_OPT_LION
+    ref = {k: [x.clone() for x in views] for k, views in data.buffers()[1].items()}
+    _step_in_lines(ref, optimizer, grad_dtype, copy, entry, B.ADAGC_MODE_ADAGC, {}, warmup=True)
+    whole, got = data.buffers()
+    shifted, elsewhere = data.buffers(3)
+    packed = {}
+    for i, n in enumerate(LINES[:-1]):
+        if i % 4 == 1:
+            got["m"][i] = elsewhere["m"][i]
+        elif i % 4 == 2:
+            for k in got:
+                got[k][i] = got[k][i].clone()
+        elif i % 4 == 3:
+            packed[i] = torch.full((4 * n + 64,), 0xA5, dtype=torch.uint8, device=DEV)
+            packed[i][33:33 + 4 * n] = got["m"][i].view(torch.uint8)
+    lists = dict(got, m=[packed[i].data_ptr() + 33 if i in packed else x for i, x in enumerate(got["m"])])
+    _step_in_lines(lists, optimizer, grad_dtype, copy, entry, B.ADAGC_MODE_ADAGC, {}, warmup=True)
+    for i, buf in packed.items():
+        n = 4 * LINES[i]
+        assert (buf[:33] == 0xA5).all() and (buf[33 + n:] == 0xA5).all()
+        got["m"][i] = buf[33:33 + n].clone().view(torch.float32)
+    _same_state(got, ref, lion)
+    data.check_gaps(whole)
+    data.check_gaps(shifted, 3)
+    for i in range(len(LINES) - 1):                       # momenta that lie elsewhere: what is at their usual place stays
+        if i % 4 != 0:
+            a, b = data.starts[i], data.starts[i + 1]
+            assert torch.equal(whole["m"][a:b].cpu(), data.host["m"][a:b])
