@@ -17,6 +17,7 @@ struct adagc_ctx {
     int          device = 0;
     int64_t      n_tensors = 0;
     int64_t      n_chunks = 0;
+    int64_t      total_elems = 0;
     adagc_config cfg{};
     int          grid_norm = 0;     // workgroups of the norm kernel
     int          grid_update = 0;   // workgroups of the update kernel
@@ -221,13 +222,13 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
         if (want > items) want = items;
         return (int)(want > kMaxGridBlocks ? kMaxGridBlocks : want);
     };
-    int64_t most_chunks = 0, total_elems = 0;
+    int64_t most_chunks = 0;
     for (int64_t i = 0; i < n_tensors; ++i) {
         const int64_t n = c->chunk_begin[(size_t)i + 1] - c->chunk_begin[(size_t)i];
         if (n > most_chunks) most_chunks = n;
-        total_elems += descs[i].numel;
+        c->total_elems += descs[i].numel;
     }
-    c->stream_grads = c->nontemporal && stream_gradients(total_elems, cfg->grad_dtype == ADAGC_GRAD_BF16);
+    c->stream_grads = c->nontemporal && stream_gradients(c->total_elems, cfg->grad_dtype == ADAGC_GRAD_BF16);
     c->small_list = tiles <= kFusedMaxItems && most_chunks <= kFusedMaxChunks;
     c->grid_norm = grid_for(c->n_chunks - n_tiny + (n_tiny + 3) / 4);
     c->n_items = tiles;
@@ -370,9 +371,9 @@ int prepare_tables(adagc_ctx* ctx, void* const* params, const void* const* grads
     if (adamw && !exp_avg_sq) return ADAGC_ERR_INVALID_ARG;
     if (copy && ctx->param_copies.size() != (size_t)ctx->n_tensors) return ADAGC_ERR_STATE;
 
-    // Rebuild the per-tensor records from the caller's pointer arrays.
+    // Rebuild the per-tensor records from the caller's pointer arrays.  What follows from them alone, line_offset, is zero in the
+    // records that are compared, and worked out for those that are uploaded: most steps find the table as it was.
     const uintptr_t grad_align = bf16g ? 2 : 4;
-    int64_t off_lines = 0, elems = 0;
     for (int64_t i = 0; i < ctx->n_tensors; ++i) {
         TensorArgs& a = ctx->scratch_args[(size_t)i];
         a.param = params[i];
@@ -387,11 +388,8 @@ int prepare_tables(adagc_ctx* ctx, void* const* params, const void* const* grads
         a.vec_ok = (aligned(a.param, 4) && aligned(a.exp_avg, 4) && aligned(a.grad, grad_align) &&
                     (!adamw || aligned(a.exp_avg_sq, 4)) && (!copy || aligned(a.param_copy, 2)))
                        ? 1u : 0u;
-        a.line_offset = line_offset_of(a);
-        elems += a.numel;
-        if (a.line_offset) off_lines += a.numel;
+        a.line_offset = 0;
     }
-    ctx->tables.off_lines = walk_lines(ctx->cfg.optimizer, bf16g, copy, ctx->n_tensors, elems, off_lines, ctx->grid_update, ctx->n_items);
 
     const size_t args_bytes = (size_t)ctx->n_tensors * sizeof(TensorArgs);
     if (!ctx->args_uploaded ||
@@ -403,9 +401,19 @@ int prepare_tables(adagc_ctx* ctx, void* const* params, const void* const* grads
         if (ctx->upload_pending[slot] && hipEventSynchronize(ctx->upload_done[slot]) != hipSuccess) return ADAGC_ERR_HIP;
         TensorArgs* stage = ctx->staging + (size_t)slot * (size_t)ctx->n_tensors;
         std::memcpy(stage, ctx->scratch_args.data(), args_bytes);
+        auto walks = [&](int64_t off_lines) {
+            return walk_lines(ctx->cfg.optimizer, bf16g, copy, ctx->n_tensors, ctx->total_elems, off_lines, ctx->grid_update, ctx->n_items);
+        };
+        int64_t off_lines = 0;
+        if (walks(ctx->total_elems))             // wherever its tensors start
+            for (int64_t i = 0; i < ctx->n_tensors; ++i) {
+                stage[i].line_offset = line_offset_of(ctx->scratch_args[(size_t)i]);
+                if (stage[i].line_offset) off_lines += ctx->numel[(size_t)i];
+            }
         if (hipMemcpyAsync(ctx->d_targs, stage, args_bytes, hipMemcpyHostToDevice, stream) != hipSuccess ||
             hipEventRecord(ctx->upload_done[slot], stream) != hipSuccess)
             return ADAGC_ERR_HIP;
+        ctx->tables.off_lines = walks(off_lines);
         ctx->upload_pending[slot] = true;
         ctx->uploads++;
         ctx->cached_args.swap(ctx->scratch_args);

@@ -163,6 +163,17 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
     t.n_tiny = (uint32_t)n_tiny;
     t.n_tensors = (uint32_t)n_tensors;
 
+    const int64_t items = count_work_items((int64_t)n_chunks, (int64_t)n_long, (int64_t)n_tiny, items_per_chunk);
+    const int64_t max_grid = (int64_t)(0xFFFFFFFFu / (uint32_t)kBlock);
+    const int64_t groups = (int64_t)(n_chunks - n_tiny + (n_tiny + 3) / 4);
+    const int grid_norm = (int)(groups > max_grid ? max_grid : groups);
+    const int grid_update = (int)(items > max_grid ? max_grid : items);
+
+    auto walks = [&](int64_t off_lines) {
+        return walk_lines(cfg->optimizer, bf16g, copy, n_tensors, total_elems, off_lines, grid_update, items);
+    };
+    const bool may_walk = walks(total_elems);        // wherever its tensors start
+
     // Tensor records and chunk table, a batch of tensors per launch.
     const uintptr_t grad_align = bf16g ? 2 : 4;
     int64_t off_lines = 0;
@@ -184,7 +195,7 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
             a.vec_ok = (aligned(a.param, 4) && aligned(a.exp_avg, 4) && aligned(a.grad, grad_align) &&
                         (!adamw || aligned(a.exp_avg_sq, 4)) && (!copy || aligned(a.param_copy, 2)))
                            ? 1u : 0u;
-            a.line_offset = line_offset_of(a);
+            a.line_offset = may_walk ? line_offset_of(a) : 0u;
             if (a.line_offset) off_lines += a.numel;
             chunk_begin += a.chunk_count;
             const ChunkKind kind = last_kind(i);
@@ -206,13 +217,7 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
     RuleArgs r;
     UpdateArgs u;
     host_step_scalars(*hp, step, r, u);
-    const int64_t items = count_work_items((int64_t)n_chunks, (int64_t)n_long, (int64_t)n_tiny, items_per_chunk);
-    const int64_t max_grid = (int64_t)(0xFFFFFFFFu / (uint32_t)kBlock);
-    const int64_t groups = (int64_t)(n_chunks - n_tiny + (n_tiny + 3) / 4);
-    const int grid_norm = (int)(groups > max_grid ? max_grid : groups);
-    const int grid_update = (int)(items > max_grid ? max_grid : items);
-
-    t.off_lines = walk_lines(cfg->optimizer, bf16g, copy, n_tensors, total_elems, off_lines, grid_update, items);
+    t.off_lines = walks(off_lines);
     FusedRule rule{};
     if (small_tensors && items <= kFusedMaxItems && !r.warmup && r.mode == ADAGC_MODE_ADAGC) rule = FusedRule{ema_norms, r};
     if (launch_sumsq_partials(t, bf16g, stream_gradients(total_elems, bf16g), grid_norm, stream, nullptr, 0, rule.ema) != hipSuccess)

@@ -369,3 +369,24 @@ def test_whole_lines_with_other_tensors_among_them(entry, optimizer, grad_dtype,
         if i % 4 != 0:
             a, b = data.starts[i], data.starts[i + 1]
             assert torch.equal(whole["m"][a:b].cpu(), data.host["m"][a:b])
+
+
+def test_a_context_whose_tensors_move_on_and_off_the_lines():
+    """What a step derives from the tensors' places is kept until they move: steps on tensors laid end to end, twice in allocations of
+    their own and end to end again, against a context for each of them."""
+    data = _Lines(7, B.ADAGC_GRAD_F32)
+    hp = B.make_hyper(lr=1e-3, t_start=0)
+    results = []
+    for separate_contexts in (False, True):
+        _, flat = data.buffers()
+        apart = {k: [x.clone() for x in views] for k, views in flat.items()}
+        gamma = torch.tensor([0.009 * n ** 0.5 for n in LINES], dtype=torch.float32, device=DEV)
+        ctxs = [B.AdaGC(LINES) for _ in range(2 if separate_contexts else 1)]
+        for step, (lists, c) in enumerate(((flat, 0), (apart, 1), (apart, 1), (flat, 0)), start=7):
+            ctxs[c % len(ctxs)].step(lists["p"], lists["g"], lists["m"], lists["v"], gamma, hp, step)
+        torch.cuda.synchronize()
+        for c in ctxs:
+            c.close()
+        results.append([torch.cat(x[k]) for x in (flat, apart) for k in "pmv"] + [gamma])
+    for x, y in zip(*results):
+        assert torch.equal(x, y)
