@@ -1039,11 +1039,11 @@ __global__ __launch_bounds__(kBlock) void finalize_telemetry_kernel(DeviceTables
 
 using UpdateFn = void (*)(DeviceTables, UpdateArgs, uint32_t, const StepScalars*, FusedRule);
 
-// lines: only with the launch shape that is not chosen otherwise
+// lines: only with the number of vectors in flight that is not chosen otherwise, and where whole lines ever pay
 template <int OPT, bool BF16G, bool COPY, int U>
 UpdateFn select_update_flags(int nt, int tele, bool lines)
 {
-    if constexpr (U == default_unroll(OPT))
+    if constexpr (U == default_unroll(OPT) && line_limits(OPT, BF16G, COPY).elems > 0)
         if (lines && nt && !tele) return update_kernel<OPT, BF16G, COPY, U, true, false, true>;
     if (nt) return tele ? update_kernel<OPT, BF16G, COPY, U, true, true, false> : update_kernel<OPT, BF16G, COPY, U, true, false, false>;
     return tele ? update_kernel<OPT, BF16G, COPY, U, false, true, false> : update_kernel<OPT, BF16G, COPY, U, false, false, false>;

@@ -23,7 +23,7 @@ namespace adagc {
 struct LineLimits {
     int64_t elems, workgroups;
 };
-inline LineLimits line_limits(int optimizer, bool bf16_grads, bool copy)
+constexpr LineLimits line_limits(int optimizer, bool bf16_grads, bool copy)
 {
     if (optimizer == ADAGC_OPT_LION && bf16_grads && copy) return {(int64_t)8 << 20, 640};
     if (optimizer != ADAGC_OPT_ADAMW) return {0, 0};
