@@ -59,12 +59,15 @@ struct GemmGroup {
     int32_t all;                    // ... of the whole batch
 };
 
-// A launch: the tiles of several groups as planned (muon_plan.h), or, without a plan, of one group in their order.
+// A launch: the tiles of several groups as planned (muon_plan.h), or, without a plan, of one group in their order.  The argument of a
+// launch without a plan is no larger than it has to be: 1 KB of it takes 0.3 us longer to launch (a product of 128 x 128 x 128 7.0 us,
+// with room for one group 6.6).
+template <bool PLANNED>
 struct GemmWork {
     const GemmItem* items;
     const int32_t*  first;
     float           alpha, beta;
-    GemmGroup       g[kMaxGroups];
+    GemmGroup       g[PLANNED ? kMaxGroups : 1];
 };
 
 constexpr int kBK = 64;
@@ -88,8 +91,9 @@ struct TilePlace {
 // workgroups, dealt to the 8 XCDs (workgroup b runs on XCD b mod 8, one L2 each) in contiguous eighths: the whole chip is on one
 // or two matrices at a time, and what the XCDs' patches have in common comes out of the memory-side cache.  With a contiguous
 // eighth of the whole batch per XCD, 8 matrices at a time, 12 products X X^T of 4096 x 14336 took 2321 us, now 2223.
-template <bool SYM>
-__device__ __forceinline__ TilePlace tile_of_workgroup(const ADAGC_CONST GemmWork& w, int round)
+// (Both kinds of launch ask for a plan: with the answer known at compile time two 256-tile kernels spill registers.)
+template <bool SYM, bool PLANNED>
+__device__ __forceinline__ TilePlace tile_of_workgroup(const ADAGC_CONST GemmWork<PLANNED>& w, int round)
 {
     const int wg = (int)blockIdx.x;
     if (w.items) {
@@ -206,8 +210,8 @@ __device__ __forceinline__ void load_to_lds_16(const void* base, uint64_t off, c
 //
 // WIDE: a lane's offset from the wave's address, up to 15 rows and a few vectors, is kept in 64 bits, for rows of more than
 // kNarrowRow elements (the others have no registers to spare for that).
-template <int BT, bool SYM, bool PTR, bool HAS_D, bool WIDE, int kGemmThreads>
-__global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const GemmWork)
+template <int BT, bool PLANNED, bool SYM, bool PTR, bool HAS_D, bool WIDE, int kGemmThreads>
+__global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const GemmWork<PLANNED>)
 {
     typedef std::conditional_t<WIDE, uint64_t, uint32_t> Offset;           // bytes
     constexpr int kWaves = kGemmThreads / 64;
@@ -229,8 +233,8 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
     const int wm = wave / kWN, wn = wave % kWN;
     const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>(&lds[0]);
     // The arguments, read anew where a tile begins and ends: kept through the main loop they would not fit the scalar registers.
-    auto arguments = []() __attribute__((always_inline)) -> const ADAGC_CONST GemmWork& {
-        const ADAGC_CONST GemmWork* a = (const ADAGC_CONST GemmWork*)__builtin_amdgcn_kernarg_segment_ptr();
+    auto arguments = []() __attribute__((always_inline)) -> const ADAGC_CONST GemmWork<PLANNED>& {
+        const ADAGC_CONST GemmWork<PLANNED>* a = (const ADAGC_CONST GemmWork<PLANNED>*)__builtin_amdgcn_kernarg_segment_ptr();
         asm volatile("" : "+s"(a));
         return *a;
     };
@@ -404,7 +408,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
         });
     };
 
-    TilePlace tp = tile_of_workgroup<SYM>(arguments(), 0);
+    TilePlace tp = tile_of_workgroup<SYM, PLANNED>(arguments(), 0);
     if (tp.z < 0) return;
     Source src = source(tp);
     SourceD src_d;
@@ -438,7 +442,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_nt_bf16_kernel(const Gem
             for (int n = 0; n < kGL; ++n) load(src, n, 4, place(previous_place(rp)));
         }
         barrier_keeping_loads();
-        const TilePlace tp_next = tile_of_workgroup<SYM>(arguments(), round + 1);
+        const TilePlace tp_next = tile_of_workgroup<SYM, PLANNED>(arguments(), round + 1);
         const bool more = tp_next.z >= 0;
         // What follows the last group of the tile's operands in the ring: the four quadrants of D, or the next tile's first groups.
         auto begin_extras = [&]() {
@@ -660,13 +664,25 @@ Tiles choose_tiles(int M, int N, bool symmetric, int64_t batch, bool wide)
 // Rows of up to this many elements: 15 of them and a few vectors are less than 4 GiB.
 constexpr int kNarrowRow = 1 << 27;
 
-template <bool SYM, bool PTR, bool D>
-void launch_kernel(std::integral_constant<bool, SYM>, std::integral_constant<bool, PTR>, std::integral_constant<bool, D>, int side, int grid,
-                   const GemmWork& w, hipStream_t stream, bool wide = false)
+template <bool PLANNED, bool SYM, bool PTR, bool D, bool WIDE = false>
+void launch_kernel(int side, int grid, const GemmWork<PLANNED>& w, hipStream_t stream)
 {
-    if (side == 256) gemm_nt_bf16_kernel<256, SYM, PTR, D, false, 512><<<dim3((uint32_t)grid), dim3(512), 0, stream>>>(w);
-    else if (!wide) gemm_nt_bf16_kernel<128, SYM, PTR, D, false, 256><<<dim3((uint32_t)grid), dim3(256), 0, stream>>>(w);
-    else if constexpr (!PTR) gemm_nt_bf16_kernel<128, SYM, PTR, D, true, 256><<<dim3((uint32_t)grid), dim3(256), 0, stream>>>(w);
+    if constexpr (!WIDE) {
+        if (side == 256) {
+            gemm_nt_bf16_kernel<256, PLANNED, SYM, PTR, D, false, 512><<<dim3((uint32_t)grid), dim3(512), 0, stream>>>(w);
+            return;
+        }
+    }
+    gemm_nt_bf16_kernel<128, PLANNED, SYM, PTR, D, WIDE, 256><<<dim3((uint32_t)grid), dim3(256), 0, stream>>>(w);
+}
+
+template <bool WIDE>
+void launch_unplanned(bool symmetric, bool d, int side, int grid, const GemmWork<false>& w, hipStream_t stream)
+{
+    if (symmetric && d) launch_kernel<false, true, false, true, WIDE>(side, grid, w, stream);
+    else if (symmetric) launch_kernel<false, true, false, false, WIDE>(side, grid, w, stream);
+    else if (d) launch_kernel<false, false, false, true, WIDE>(side, grid, w, stream);
+    else launch_kernel<false, false, false, false, WIDE>(side, grid, w, stream);
 }
 
 }  // namespace
@@ -695,7 +711,7 @@ hipError_t launch_gemm_nt_bf16(const void* P, int ldp, const void* Q, int ldq, i
     const bool wide = ldp > kNarrowRow || ldq > kNarrowRow || (Dt && lddt > kNarrowRow) || (C && ldc > kNarrowRow) || (Ct && ldct > kNarrowRow);
     const Tiles t = choose_tiles(M, N, symmetric, batch, wide);
     if (t.all > INT32_MAX) return hipErrorInvalidValue;
-    GemmWork work{};
+    GemmWork<false> work{};
     work.alpha = alpha;
     work.beta = beta;
     GemmGroup& w = work.g[0];
@@ -721,19 +737,15 @@ hipError_t launch_gemm_nt_bf16(const void* P, int ldp, const void* Q, int ldq, i
     w.all = (int32_t)t.all;
     // as many workgroups as the chip holds at a time, if there are tiles for them: 32 (128-tiles: 64) on each of 8 XCDs
     const int grid = 8 * (int)std::min<int64_t>((t.all + 7) / 8, t.side == 256 ? 32 : 64);
-    const std::true_type yes{};
-    const std::false_type no{};
-    if (symmetric && Dt) launch_kernel(yes, no, yes, t.side, grid, work, stream, wide);
-    else if (symmetric) launch_kernel(yes, no, no, t.side, grid, work, stream, wide);
-    else if (Dt) launch_kernel(no, no, yes, t.side, grid, work, stream, wide);
-    else launch_kernel(no, no, no, t.side, grid, work, stream, wide);
+    if (wide) launch_unplanned<true>(symmetric, Dt != nullptr, t.side, grid, work, stream);
+    else launch_unplanned<false>(symmetric, Dt != nullptr, t.side, grid, work, stream);
     return hipGetLastError();
 }
 
 hipError_t launch_muon_product(MuonProduct product, const MuonLaunch& l, const MuonGroup* groups, hipStream_t stream)
 {
     constexpr float kA = 3.4445f, kB = -4.7750f, kC = 2.0315f;
-    GemmWork work{};
+    GemmWork<true> work{};
     work.items = l.items;
     work.first = l.first;
     for (size_t i = 0; i < l.groups.size(); ++i) {
@@ -764,11 +776,9 @@ hipError_t launch_muon_product(MuonProduct product, const MuonLaunch& l, const M
     }
     work.alpha = product == MuonProduct::poly ? kC : 1.0f;
     work.beta = product == MuonProduct::poly ? kB : kA;
-    const std::true_type yes{};
-    const std::false_type no{};
-    if (product == MuonProduct::gram) launch_kernel(yes, no, no, l.side, l.workgroups, work, stream);
-    else if (product == MuonProduct::poly) launch_kernel(yes, no, yes, l.side, l.workgroups, work, stream);
-    else launch_kernel(no, yes, yes, l.side, l.workgroups, work, stream);
+    if (product == MuonProduct::gram) launch_kernel<true, true, false, false>(l.side, l.workgroups, work, stream);
+    else if (product == MuonProduct::poly) launch_kernel<true, true, false, true>(l.side, l.workgroups, work, stream);
+    else launch_kernel<true, false, true, true>(l.side, l.workgroups, work, stream);
     return hipGetLastError();
 }
 
