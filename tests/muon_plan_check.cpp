@@ -48,6 +48,15 @@ static size_t check(MuonProduct product, const std::vector<MuonExtent>& extents)
     return most;
 }
 
+// The sizes of the tiles of a product's launches, largest first, and the most tiles that a workgroup has.
+static std::vector<int> sides(MuonProduct product, const std::vector<MuonExtent>& extents, size_t* most = nullptr)
+{
+    std::vector<int> out;
+    for (const PlannedLaunch& l : plan_muon_product(product, extents)) out.push_back(l.side);
+    if (most) *most = check(product, extents);
+    return out;
+}
+
 int main()
 {
     const MuonProduct products[] = {MuonProduct::gram, MuonProduct::poly, MuonProduct::next};
@@ -66,6 +75,20 @@ int main()
     // 1024 x 4096 have 2800 tiles for 256 workgroups in X X^T
     for (MuonProduct p : products) CHECK(check(p, {{128, 128, 1}}) == 1);
     CHECK(check(MuonProduct::gram, {{4096, 14336, 12}, {4096, 4096, 8}, {1024, 4096, 8}}) <= 20);
+    // the tiles that the lists of tests/test_gpu_muon.py are there for
+    const std::vector<int> small(1, 128), large(1, 256), both{256, 128};
+    size_t most = 0;
+    for (MuonProduct p : products) {
+        CHECK(sides(p, {{768, 2304, 1}}) == small && sides(p, {{768, 2304, 32}}) == large);
+        CHECK(sides(p, {{1280, 2560, 16}}) == large);
+        CHECK(sides(p, {{128, 256, 1}, {128, 128, 1}, {256, 384, 1}, {384, 512, 1}, {512, 640, 1}}) == small);
+        CHECK(sides(p, {{1408, 1536, 1}}) == small && sides(p, {{768, 1024, 1}}) == small && sides(p, {{640, 896, 1}}) == small);
+    }
+    CHECK(sides(MuonProduct::next, {{640, 1408, 20}}, &most) == small && most == 3);
+    CHECK(sides(MuonProduct::next, {{768, 2304, 32}, {640, 1408, 3}}) == both);
+    CHECK(sides(MuonProduct::next, {{256, 4096, 32}}) == large);
+    CHECK(sides(MuonProduct::next, {{512, 4096, 32}}, &most) == large && most == 4);
+    CHECK(sides(MuonProduct::next, {{4096, 14336, 1}}) == small && sides(MuonProduct::next, {{4096, 14336, 2}, {4096, 4096, 1}}) == large);
     std::printf("muon_plan_check: ok\n");
     return 0;
 }

@@ -490,32 +490,88 @@ def _sampled_rows_check(name, P, Q, alpha, beta, D, got, rows):
         assert (np.abs(got[i] - ref) <= 2.0 ** -7 * np.abs(ref) + slack).all(), "%s row %d" % (name, i)
 
 
-def test_newton_schulz_products_at_llama3_8b_ffn_shape():
-    """One step's three products at the size of a 4096 x 14336 weight, on the 256 x 256 tiles the step uses there (the
-    step runs them batched over equal-shaped matrices; a batched product equals the single one bit for bit, which
-    test_batched_matrix_core_product_equals_the_single_ones checks): each checked on sampled rows that the oracle
-    computes one by one from the GPU's own operands, and the symmetric ones for exact symmetry."""
-    m, n = 4096, 14336
-    gen = torch.Generator(device=DEV).manual_seed(9)
-    x = (torch.randn(m, n, device=DEV, generator=gen) * (1.0 / np.sqrt(m * n)) * 3.0).to(torch.bfloat16)      # like a normalised U
-    y = x.t().contiguous()
-    a_, b_, c_ = 3.4445, -4.7750, 2.0315
-    A = torch.empty((m, m), dtype=torch.bfloat16, device=DEV)
-    Bm = torch.empty((m, m), dtype=torch.bfloat16, device=DEV)
-    X2 = torch.empty((m, n), dtype=torch.bfloat16, device=DEV)
-    Y2 = torch.empty((n, m), dtype=torch.bfloat16, device=DEV)
-    B.adagc_muon_gemm_nt(x, x, 1.0, 0.0, None, None, A, symmetric=True)
-    B.adagc_muon_gemm_nt(A, A, c_, b_, A, None, Bm, symmetric=True)
-    B.adagc_muon_gemm_nt(Bm, y, 1.0, a_, y, X2, Y2)
+def _x_after(shapes, g, m, ns_steps):
+    """X of every matrix after so many steps of the iteration, in the wide orientation, as the step has it: with theta = 0, lr = 1 and no
+    decay theta' = -(scale O) rounded once, which gives O back exactly."""
+    th = [torch.zeros(x.numel(), device=DEV) for x in g]
+    m = [x.clone() for x in m]
+    ctx = B.AdaGC([r * c for r, c in shapes], B.ADAGC_OPT_MUON, B.ADAGC_GRAD_F32)
+    ctx.muon_attach(shapes)
+    gamma = torch.full((len(shapes),), 1e9, dtype=torch.float32, device=DEV)                      # nothing clipped
+    ctx.muon_step(th, g, m, gamma, B.make_hyper(lr=1.0, weight_decay=0.0, t_start=0), B.make_muon_hyper(ns_steps=ns_steps), 3)
     torch.cuda.synchronize()
-    hx, hA, hB, hX2 = host64(x), host64(A), host64(Bm), host64(X2)
-    assert np.array_equal(hA, hA.T) and np.array_equal(hB, hB.T)
-    assert torch.equal(Y2, X2.t().contiguous())
-    rows = [0, 1, 127, 128, 2047, 2048, 3000, 4095]
-    _sampled_rows_check("A = X X^T", hx, hx, 1.0, 0.0, None, hA, rows)
-    _sampled_rows_check("B = b A + c A A", hA, hA, c_, b_, hA, hB, rows)
-    _sampled_rows_check("X' = a X + B X", hB, hx.T.copy(), 1.0, a_, hx, hX2, rows)
-    say("Newton-Schulz products at 4096 x 14336: %d sampled rows of each product agree with the oracle" % len(rows))
+    ctx.close()
+    out = []
+    for t, s in zip(th, shapes):
+        o = (-t.double() / OM.update_scale(*s)).float().to(torch.bfloat16).view(s)
+        out.append(o.t().contiguous() if s[0] > s[1] else o)
+    return out
+
+
+def _muon_device_inputs(shapes, seed):
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    randn = lambda r, c: torch.randn(r * c, generator=gen, device=DEV)
+    return [randn(*s) * 0.01 for s in shapes], [randn(*s) * 0.005 for s in shapes]
+
+
+def _exported_step(x):
+    """One step of the iteration on one matrix by the exported product, with X and its transpose as operands."""
+    m, n = x.shape
+    mp, np_ = (m + 127) // 128 * 128, (n + 127) // 128 * 128
+    X = torch.zeros((mp, np_), dtype=torch.bfloat16, device=DEV)
+    X[:m, :n] = x
+    Xt = X.t().contiguous()
+    A, Bm, X2 = (torch.empty(s, dtype=torch.bfloat16, device=DEV) for s in ((mp, mp), (mp, mp), (mp, np_)))
+    B.adagc_muon_gemm_nt(X, X, 1.0, 0.0, None, None, A, symmetric=True)
+    B.adagc_muon_gemm_nt(A, A, 2.0315, -4.7750, A, None, Bm, symmetric=True)
+    B.adagc_muon_gemm_nt(Xt, Bm, 1.0, 3.4445, X, None, X2)                        # X'^T = a X^T + X^T B
+    torch.cuda.synchronize()
+    return A, Bm, X2[:m, :n]
+
+
+# tests/muon_plan_check.cpp holds the tiles named here against the plan
+@pytest.mark.parametrize("shapes", [
+    [(100, 250), (128, 128), (250, 300), (512, 384), (500, 640), (640, 896), (1024, 768), (1400, 1500)],   # 128-tiles, depths 128 .. 1408
+    [(640, 1408), (1400, 600)] * 10,                                              # 128-tiles, three to a workgroup
+    [(768, 2304), (2304, 768), (700, 2250), (2290, 641)] * 8 + [(640, 1400), (1400, 600), (630, 1408)],    # a X + B X on both tiles, two launches
+    [(256, 4096), (4000, 250)] * 16,                                              # a X + B X on 256-tiles of depth 256
+    [(512, 4096)] * 32,                                                           # ... of depth 512, four to a workgroup
+    [(1280, 2560), (2500, 1270)] * 8,                                             # all products on 256-tiles
+    [(64 + 128 * i, 300 + 128 * (i % 5) + 128 * i) for i in range(12)]],          # more padded shapes than a launch takes
+    ids=["depths", "several_128", "both_tiles", "256_deep_256", "256_deep_512", "all_256", "twelve_shapes"])
+def test_products_of_the_step_equal_the_exported_ones(shapes):
+    """The step's products run as planned launches over several groups of matrices, a X + B X with X read transposed: kernels that
+    adagc_muon_gemm_nt does not run.  Every sum runs over k in order in all of them, so the step's X must be, value for value, what
+    the exported products (checked against exact sums above) give from the step's X before."""
+    g, m = _muon_device_inputs(shapes, 17)
+    before = _x_after(shapes, g, m, 0)
+    for k in (1, 2):
+        after = _x_after(shapes, g, m, k)
+        for i, (x0, x1) in enumerate(zip(before, after)):
+            assert (x0 != 0).any() and (x1 != x0).any()
+            assert torch.equal(x1, _exported_step(x0)[2]), "step %d, matrix %d %s" % (k, i, shapes[i])
+        before = after
+
+
+@pytest.mark.parametrize("shapes", [[(4096, 14336)], [(14336, 4096), (4096, 14336), (4096, 4096)]])
+def test_newton_schulz_products_at_llama3_8b_ffn_shape(shapes):
+    """One step's three products at the size of a 4096 x 14336 weight, as the step runs them for one such matrix (a X + B X on 128-tiles)
+    and for a list (256-tiles): the step's X' is checked on sampled rows that the oracle computes one by one from the GPU's own
+    operands; A and B, which the step keeps to itself, as the exported products give them from the same X, the symmetric ones for exact
+    symmetry, and X' of the exported product must be the step's value for value."""
+    a_, b_, c_ = 3.4445, -4.7750, 2.0315
+    g, m = _muon_device_inputs(shapes, 9)
+    before, after = _x_after(shapes, g, m, 0), _x_after(shapes, g, m, 1)
+    for i in range(len(shapes)):
+        A, Bm, X2 = _exported_step(before[i])
+        assert torch.equal(X2, after[i])
+        hx, hA, hB, hX2 = host64(before[i]), host64(A), host64(Bm), host64(after[i])
+        assert np.array_equal(hA, hA.T) and np.array_equal(hB, hB.T)
+        rows = [0, 1, 127, 128, 2047, 2048, 3000, 4095]
+        _sampled_rows_check("A = X X^T", hx, hx, 1.0, 0.0, None, hA, rows)
+        _sampled_rows_check("B = b A + c A A", hA, hA, c_, b_, hA, hB, rows)
+        _sampled_rows_check("X' = a X + B X", hB, hx.T.copy(), 1.0, a_, hx, hX2, rows)
+    say("Newton-Schulz products of %s: sampled rows agree with the oracle" % (shapes,))
 
 
 def test_muon_step_at_llama3_8b_attention_shapes():
@@ -862,7 +918,7 @@ def test_matrix_core_product_when_workgroups_take_several_tiles(batch, M, N, K, 
 def test_muon_results_do_not_depend_on_the_size_of_the_tiles(ns_steps):
     """32 matrices of 768 rows run on 256 x 256 tiles, one of them alone on 128 x 128 tiles.  Every sum runs over k in order, in
     whichever tile, so the bits must be the same: parameters of a wide matrix, of a tall one, and of one whose extents end inside a
-    tile."""
+    tile.  (tests/muon_plan_check.cpp holds the two sizes against the plan.)"""
     shapes = [(768, 2304), (2304, 768), (700, 2250), (2290, 641)] * 8
     g, m, th = _inputs(21, shapes)
     gamma = np.array([oracle.l2_norm(x.reshape(-1)) for x in g], np.float32)
