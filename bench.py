@@ -39,7 +39,7 @@ def algorithmic_bytes(workload_name):
 
 def kernel_source_hash():
     h = hashlib.sha256()
-    for name in ("kernels.hip", "adagc_internal.h", "adagc_device.h"):
+    for name in ("kernels.hip", "adagc_internal.h", "adagc_device.h", "walk_lines.h"):
         with open(os.path.join(ROOT, "paper_2502_11034_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]

@@ -366,12 +366,13 @@ typedef struct {
  * Give the context the matrices' shapes and allocate the Newton-Schulz workspace.  Once per context.
  * Matrices whose extents, rounded up to multiples of 128, are equal are iterated together, up to 32 at a time
  * (fewer if 32 would need more than 24 GiB, or more than the device can give), by batched launches of the
- * matrix-core product: one launch over many matrices fills the GPU where one matrix has too few tiles.  The workspace (bf16) holds four
- * arrays of the padded min x max extent and two of min x min per matrix of the largest such batch (adagc_muon_workspace_bytes
- * tells the total).  A matrix's result does not depend on which others share its batch.
+ * matrix-core product: one launch over many matrices fills the GPU where one matrix has too few tiles.  The workspace (bf16) has the
+ * size of four arrays of the padded min x max extent and two of min x min per matrix of the largest such batch
+ * (adagc_muon_workspace_bytes tells the total); a batch takes two and two of them per matrix, and batches that fit into it
+ * together share launches.  A matrix's result does not depend on which others share its batch or its launches.
  *   shapes  HOST  n_tensors entries, copied
  * Errors: INVALID_ARG (shape does not match numel), STATE (context not ADAGC_OPT_MUON, or attached already),
- * TOO_LARGE (a padded dimension beyond 2^31-1), OOM, HIP.
+ * TOO_LARGE (a dimension beyond 4194176), OOM, HIP.
  */
 int adagc_muon_attach(adagc_ctx* ctx, const adagc_matrix_shape* shapes);
 
@@ -391,7 +392,7 @@ int adagc_muon_step(adagc_ctx* ctx, void* const* params, const void* const* grad
                     float* ema_norms, const adagc_hyper* hp, const adagc_muon_hyper* mh, int64_t step, void* stream);
 
 /*
- * Building block of the Muon path, exported so that it can be checked on its own: the bf16 matrix-core
+ * Building block of the Muon path, exported so that it can be checked and measured on its own: the bf16 matrix-core
  * product of the Newton-Schulz iteration (the orthogonalisation step of Muon, the optimizer the paper pairs
  * AdaGC with in "Optimizer Compatibility: Muon and Lion", Sec. 5.4; the iteration itself is not printed there),
  *     C[i][j] = bf16( alpha * sum_k P[i][k] Q[j][k] + beta * D[i][j] ),   fp32 accumulation,
@@ -409,8 +410,9 @@ int adagc_muon_gemm_nt(const void* P, int64_t ldp, const void* Q, int64_t ldq, i
                        int64_t ldct, int32_t symmetric, void* stream);
 
 /*
- * The same product for `batch` (>= 1) sets of matrices of one shape in a single launch, as adagc_muon_step issues
- * it: matrix z of every array starts z * its stride (in elements, a multiple of 8, >= 0) after the pointer given.
+ * The same product for `batch` (>= 1) sets of matrices of one shape in a single launch.  (adagc_muon_step runs its products as
+ * planned launches over matrices of several shapes, X' = a X + B X with X read transposed; the results are these ones' bit for bit.)
+ * Matrix z of every array starts z * its stride (in elements, a multiple of 8, >= 0) after the pointer given.
  * strides  HOST array of 5: for P, Q, Dt, C, Ct in this order (entries of absent arrays are ignored; with
  *          symmetric = 1 the strides of P and Q must be equal).  The caller sees to it that the batch's outputs do
  *          not overlap.  Every matrix's result is the one adagc_muon_gemm_nt gives for it alone.

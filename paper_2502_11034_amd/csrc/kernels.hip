@@ -714,8 +714,8 @@ void update_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items, const Step
                 // agree on their place in a line, every tile of the tensor is taken `shift` elements earlier: a chunk's first tile has
                 // the end of the chunk before it, the tensor's last tile what is left, one by one.  Tensors laid end to end (1500 of
                 // up to 4 M elements): 2290 us per step without, 2062 with.  (Not with telemetry: its partial sums
-                // would have the elements in another order than on tensors that lie apart.)  Lists that lie on lines have a kernel
-                // without the shift: 5000 small ones 102 us there, 112 here.
+                // would have the elements in another order than on tensors that lie apart.)  Lists that lie on lines, small lists and
+                // small launches (walk_lines.h) have a kernel without the shift: 5000 small tensors 102 us there, 112 here.
                 const int shift = LINES ? (int)ta.line_offset : 0;
                 const bool starts = LINES && c.index == 0, ends = !LINES || c.index + 1 == ta.chunk_count;
                 const auto p4 = (ADAGC_GLOBAL f32x4_any*)(p - shift);

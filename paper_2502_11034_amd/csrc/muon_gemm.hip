@@ -24,7 +24,8 @@
 // from global memory straight into LDS (global_load_lds_dwordx4, no staging registers), swizzled against bank conflicts, by
 // halves into a ring of five places (see "Main loop").  A compute unit's workgroups stay and take tile after tile: the next
 // tile's first loads are on their way while this one's results are stored (see "Between tiles").  The 256-tile kernels are at the
-// register limit of 256; the one that reads P transposed spills a few around the loop, none inside it.
+// register limit of 256.  The loop spills none, but those with D spill 8 registers (the one that reads P transposed 12) in the last
+// operand tile of an output tile, and each of the two (three) places where they are read back waits for all of the wave's loads.
 
 #include <algorithm>
 #include <type_traits>
@@ -199,7 +200,8 @@ __device__ __forceinline__ void load_to_lds_16(const void* base, uint64_t off, c
 // block: 8 bytes along a row of Ct.  Exchanging half of the lanes' values between two neighbouring blocks (v_permlane16_swap) makes
 // 16 bytes of it, stored without a detour through LDS; C, whose rows run the other way, is transposed through the wave's own part
 // of a place of the ring (ds_read_b64_tr_b16).  Where a quadrant of D has been used, the next tile's groups are loaded.  The stores
-// complete during the next tile's first half steps.
+// complete during the next tile's first half steps.  (On 256-tiles the waits for spilled registers, above, come while D's last quadrants
+// are on their way: those have less than three and a half half steps.)
 // Measured: one workgroup per tile and all of LDS as the staging tile, 12 products of 4096 x 14336 x 4096 with D, C and Ct 4866 us,
 // with workgroups that stay 4706; X X^T as above 2373, 2296.  D loaded to registers after the sums, with the waits that takes, against
 // the ring: b A + c A A of 48 matrices of 768 rows on 256-tiles 61, 52 us, of 6 of 2048 rows 59, 54, a X + B X of 32 of 1024 rows

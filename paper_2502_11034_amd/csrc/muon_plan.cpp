@@ -126,6 +126,8 @@ PlannedLaunch plan_launch(MuonProduct product, const std::vector<MuonExtent>& ex
 //   6 of 2048 x 2560                                       gram 78 / 62        poly 61 / 54        next 129 / 108
 //   1 of 1024 x 4096                                       gram 30 / 75        poly 11 / 28        next 15 / 28
 //   12 of 4096 x 14336, 8 of 4096 x 4096, 8 of 1024 x 4096 gram 3956 / 2638    poly 1459 / 1184    next 8039 / 5220
+// The estimate takes the faster side everywhere but in X X^T of the first list (75 / 73 estimated: 256-tiles, 3 us slower).  It knows
+// nothing of operand traffic, and is far too low for large matrices on 128-tiles (a X + B X of the last list 5387).
 // A launch for each group instead of one for all: 141 against 77, 85 against 52 and 185 against 178 on the first list (256-tiles),
 // 2801 against 2638, 1238 against 1184 and 5080 against 5220 on the last.
 std::vector<PlannedLaunch> plan_muon_product(MuonProduct product, const std::vector<MuonExtent>& extents)
