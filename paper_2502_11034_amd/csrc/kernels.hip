@@ -517,6 +517,10 @@ struct ElemState {
 // vector ALU active 15 % of the time), so double arithmetic costs no time (measured: 37.9 ms with
 // either precision) and makes the result the correctly rounded value of Alg. 1's statements, not
 // an accumulation of fp32 roundings.
+// Every sum of products is written as the fma it is to become: where the compiler may choose which of two products it fuses, it chooses
+// differently from kernel to kernel and from element to element of one, and a value then depends (in its last bit, about once in
+// 10^9) on where its tensor lies.  beta * state is exact in double (both come from fp32), so fma(beta, state, x) has the bits
+// of the separately rounded sum.
 
 // AdamW statements of Alg. 1 on the clipped gradient h*g; the bias corrections are folded into two
 // host-computed scalars (step_size = lr / (1 - beta1^t), inv_bias2 = 1 / (1 - beta2^t)).
@@ -524,31 +528,31 @@ struct ElemState {
 __device__ __forceinline__ void adamw_elem(const UpdateArgs& a, double h, double uc, float g, ElemState& s)
 {
     const double gh = h * (double)g;
-    const double m = a.beta1 * (double)s.m + a.one_minus_beta1 * gh;
-    const double v = a.beta2 * (double)s.v + a.one_minus_beta2 * gh * gh;
+    const double m = fma(a.beta1, (double)s.m, a.one_minus_beta1 * gh);
+    const double v = fma(a.beta2, (double)s.v, a.one_minus_beta2 * gh * gh);
     const double denom = sqrt(v * a.inv_bias2) + a.eps;
     const double th = (double)s.p;
-    s.p = (float)(th - a.lr_wd * th - uc * (a.step_size * m / denom));
+    s.p = (float)fma(-uc, a.step_size * m / denom, fma(-a.lr_wd, th, th));
     s.m = (float)m;
     s.v = (float)v;
 }
 
 // Lion (rule of Chen et al.; the paper only cites it).  The sign is a discrete decision: the
-// interpolation c is evaluated with separately rounded operations, the sequence a plain C
+// interpolation c has the bits of the sequence of separately rounded operations that a plain C
 // implementation without contraction produces.
 __device__ __forceinline__ double lion_sign(const UpdateArgs& a, double gh, float m)
 {
-    const double c = __dadd_rn(__dmul_rn(a.beta1, (double)m), __dmul_rn(a.one_minus_beta1, gh));
+    const double c = fma(a.beta1, (double)m, a.one_minus_beta1 * gh);
     return (c > 0.0) ? 1.0 : ((c < 0.0) ? -1.0 : 0.0);
 }
 
 __device__ __forceinline__ void lion_elem(const UpdateArgs& a, double h, double uc, float g, ElemState& s)
 {
-    const double gh = __dmul_rn(h, (double)g);
+    const double gh = h * (double)g;
     const double sgn = lion_sign(a, gh, s.m);
     const double th = (double)s.p;
-    s.p = (float)(th - a.lr * (uc * sgn + a.weight_decay * th));
-    s.m = (float)(a.beta2 * (double)s.m + a.one_minus_beta2 * gh);
+    s.p = (float)fma(-a.lr, fma(a.weight_decay, th, uc * sgn), th);
+    s.m = (float)fma(a.beta2, (double)s.m, a.one_minus_beta2 * gh);
 }
 
 template <int OPT>
@@ -866,8 +870,8 @@ __device__ __forceinline__ double direction_elem(const UpdateArgs& a, float g, f
 {
     const double gd = (double)g;
     if constexpr (OPT == ADAGC_OPT_ADAMW) {
-        const double m = a.beta1 * (double)m_prev + a.one_minus_beta1 * gd;
-        const double v = a.beta2 * (double)v_prev + a.one_minus_beta2 * gd * gd;
+        const double m = fma(a.beta1, (double)m_prev, a.one_minus_beta1 * gd);
+        const double v = fma(a.beta2, (double)v_prev, a.one_minus_beta2 * gd * gd);
         return (m * a.inv_bias1) / (sqrt(v * a.inv_bias2) + a.eps);
     } else {
         return lion_sign(a, gd, m_prev);

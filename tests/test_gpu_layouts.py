@@ -2,6 +2,9 @@
 element, as in flat parameter buffers), must be bit for bit the step on the same tensors in allocations of their own: the kernels
 take both through the same vectors, and neither the address nor the place in the visiting order enters a result.  The step on
 separate allocations is held against the oracle elsewhere."""
+import functools
+from fractions import Fraction
+
 import numpy as np
 import pytest
 import torch
@@ -390,3 +393,93 @@ def test_a_context_whose_tensors_move_on_and_off_the_lines():
         results.append([torch.cat(x[k]) for x in (flat, apart) for k in "pmv"] + [gamma])
     for x, y in zip(*results):
         assert torch.equal(x, y)
+
+
+def _state_next_to_a_tie(beta, t, exact):
+    """An fp32 state x > 0 for which beta x + t and beta x + exact, each rounded to double and then to fp32, differ, `exact` (a Fraction)
+    being the product that t rounds to double: which of the two a kernel computes is decided by the product that it fuses.  Searched among the
+    x whose sum with t lies within a unit of its exact arithmetic of a tie between two fp32 values.  0 if there is none."""
+    b, eb = int(beta * 2 ** 30), -30                                                # beta is an fp32 value
+    while b % 2 == 0:
+        b, eb = b // 2, eb + 1
+    for e in range(int(np.floor(np.log2(t))) - 27, int(np.floor(np.log2(t))) - 18): # of x's unit: x is between t / 16 and 16 t
+        units = int(round(t / 2.0 ** (eb + e)))
+        for bits in range(b.bit_length() + 23, b.bit_length() + 29):                # of the sum, in units of 2^(eb + e)
+            q = bits - 24                                                           # of its fp32 unit
+            x = pow(b, -1, 2 ** q) * (2 ** (q - 1) - units) % 2 ** q
+            x += -(-max(2 ** 23 - x, 0) // 2 ** q) * 2 ** q
+            if x < 2 ** 24 and (b * x + units).bit_length() == bits:
+                x = x * 2.0 ** e
+                if np.float32(beta * x + t) != np.float32(float(Fraction(beta * x) + exact)):
+                    return x
+    return 0.0
+
+
+TIES = [1, 5, 37, 1000, 1030] + [4099, 8191, 12289, 16385, 20001, 33001] * 5
+
+
+@functools.lru_cache(maxsize=None)
+def _ties(beta_m, beta_v):
+    """Gradients (integers, so that the norms' sums of squares are exact), m and v next to ties where the coefficient of a clipped tensor
+    with gamma 1 allows any, and m' and v' by the formulas in double without fusing."""
+    rng = np.random.default_rng(12)
+    b_m, b_v = float(np.float32(beta_m)), float(np.float32(beta_v))
+    out, telling = [], [0, 0]
+    for n in TIES:
+        x = (2.0 * rng.integers(0, 128, n) + 1.0) * rng.choice([-1.0, 1.0], n)
+        x[0] = 77.0
+        h = float(np.float32(1.04)) / np.sqrt(np.sum(x * x))
+        assert h < 1.0
+        m, v = rng.random(n).astype(np.float32).astype(np.float64), rng.random(n).astype(np.float32).astype(np.float64)
+        for a in np.unique(np.abs(x)):
+            gh, at = h * a, np.abs(x) == a
+            for q, (s, b, t, exact) in enumerate(((m, b_m, (1.0 - b_m) * gh, Fraction(1.0 - b_m) * Fraction(gh)),
+                                                  (v, b_v, (1.0 - b_v) * gh * gh, Fraction((1.0 - b_v) * gh) * Fraction(gh)))):
+                y = _state_next_to_a_tie(b, t, exact)
+                if y:
+                    s[at] = y
+                    telling[q] += int(at.sum())
+        m *= np.sign(x)
+        gh = h * x
+        out.append([y.astype(np.float32) for y in (x, m, v, b_m * m + (1.0 - b_m) * gh, b_v * v + (1.0 - b_v) * gh * gh)])
+    return out, telling
+
+
+@pytest.mark.parametrize("optimizer,grad_dtype,copy", [(o, g, c) for o in (B.ADAGC_OPT_ADAMW, B.ADAGC_OPT_LION)
+                                                       for g in (B.ADAGC_GRAD_F32, B.ADAGC_GRAD_BF16) for c in (False, True)])
+def test_moments_next_to_ties_have_the_bits_of_separately_rounded_sums(optimizer, grad_dtype, copy):
+    """beta m + (1 - beta) h g and beta v + (1 - beta) (h g)^2 are sums of two products: which of them is fused decides the last bit of a
+    value next to a tie.  It must not depend on the kernel or the place: short and long tensors, apart from each other and end to end
+    (in whole lines, for the sake of a large tensor of zeros), against the formulas without fusing."""
+    lion = optimizer == B.ADAGC_OPT_LION
+    beta1, beta2 = (0.9, 0.99) if lion else (0.9, 0.95)
+    data, telling = _ties(beta2 if lion else beta1, beta2)
+    assert min(telling) >= 300, telling
+    hp = B.make_hyper(lr=1e-3, beta1=beta1, beta2=beta2, t_start=0)
+    for flat in (False, True):
+        sizes = TIES + [8400001] if flat else TIES
+        pad = 1 if flat else 128
+        starts = [3 if flat else 0]
+        for n in sizes:
+            starts.append(starts[-1] + -(-n // pad) * pad)
+        host = {k: np.zeros(starts[-1], dtype=np.float32) for k in "pgmv"}
+        for a, n, rows in zip(starts, TIES, data):
+            for k, x in zip("gmv", rows):
+                host[k][a:a + n] = x
+        buf = {k: torch.from_numpy(x).to(DEV) for k, x in host.items()}
+        if grad_dtype == B.ADAGC_GRAD_BF16:
+            buf["g"] = buf["g"].to(torch.bfloat16)
+        buf["c"] = torch.zeros(starts[-1], dtype=torch.bfloat16, device=DEV)
+        lists = {k: [x[a:a + n] for a, n in zip(starts, sizes)] for k, x in buf.items()}
+        ctx = B.AdaGC(sizes, optimizer, grad_dtype, copy)
+        if copy:
+            ctx.set_param_copies(lists["c"])
+        gamma = torch.ones(len(sizes), dtype=torch.float32, device=DEV)
+        ctx.step(lists["p"], lists["g"], lists["m"], None if lion else lists["v"], gamma, hp, 7)
+        torch.cuda.synchronize()
+        ctx.close()
+        for i, n in enumerate(TIES):
+            for k, ref in zip("m" if lion else "mv", data[i][3:]):
+                wrong = (lists[k][i].cpu().numpy() != ref).nonzero()[0]
+                assert not len(wrong), "%s of tensor %d (%d elements), %s: %d values, first at %s" % (
+                    k, i, n, "end to end" if flat else "apart", len(wrong), wrong[:5])
