@@ -309,8 +309,9 @@ __device__ __forceinline__ bool arrive_last(uint32_t* counter, uint32_t total)
     return true;
 }
 
-// AdaGC branch of Alg. 1 / Eq. 3 for a tensor with sum of squares s and threshold state gamma_prev, in double, with
-// separately rounded operations.
+// AdaGC branch of Alg. 1 / Eq. 3 for a tensor with sum of squares s and threshold state gamma_prev, in double, with the
+// bits of separately rounded operations: products that are fused are those of fp32 values, which are exact.  (HIP's __dmul_rn and
+// __dadd_rn are ordinary operators, which the compiler does fuse, one product of two as it likes: hence the fma.)
 struct TensorRule {
     double norm, h, gamma_new;
     bool   active;
@@ -324,7 +325,7 @@ __device__ __forceinline__ TensorRule adagc_rule(const RuleArgs& r, double s, do
     o.active = o.norm > threshold;                        // strict; false if either side is NaN
     o.h = o.active ? __ddiv_rn(threshold, o.norm) : 1.0;
     const double clipped_norm = o.active ? threshold : o.norm;
-    o.gamma_new = __dadd_rn(__dmul_rn(r.ema_beta, gamma_prev), __dmul_rn(__dsub_rn(1.0, r.ema_beta), clipped_norm));
+    o.gamma_new = fma(r.ema_beta, gamma_prev, __dmul_rn(__dsub_rn(1.0, r.ema_beta), clipped_norm));
     return o;
 }
 
@@ -365,8 +366,7 @@ __device__ __forceinline__ void global_rule(const DeviceTables& t, float* ema, c
         active = gnorm > threshold;
         h = active ? __ddiv_rn(threshold, gnorm) : 1.0;
         const double clipped_norm = active ? threshold : gnorm;
-        ema[0] = (float)__dadd_rn(__dmul_rn(r.ema_beta, gamma_prev),
-                                  __dmul_rn(__dsub_rn(1.0, r.ema_beta), clipped_norm));
+        ema[0] = (float)fma(r.ema_beta, gamma_prev, __dmul_rn(__dsub_rn(1.0, r.ema_beta), clipped_norm));
         clipped = active;
     } else if (r.mode == ADAGC_MODE_ZCLIP && !r.warmup) {
         // Table 2's ZClip row on the model's norm: z-score against the moving mean and deviation,
@@ -379,11 +379,10 @@ __device__ __forceinline__ void global_rule(const DeviceTables& t, float* ema, c
         const double tau = __dadd_rn(mu_prev, __dmul_rn(xi, sigma));
         h = active ? __ddiv_rn(tau, gnorm) : 1.0;
         const double clipped_norm = active ? tau : gnorm;
-        const double mu = __dadd_rn(__dmul_rn(r.ema_beta, mu_prev), __dmul_rn(__dsub_rn(1.0, r.ema_beta), clipped_norm));
+        const double mu = fma(r.ema_beta, mu_prev, __dmul_rn(__dsub_rn(1.0, r.ema_beta), clipped_norm));
         const double dev = __dsub_rn(clipped_norm, mu);
         ema[0] = (float)mu;
-        ema[1] = (float)__dadd_rn(__dmul_rn(r.ema_beta, var_prev),
-                                  __dmul_rn(__dmul_rn(__dsub_rn(1.0, r.ema_beta), dev), dev));
+        ema[1] = (float)fma(r.ema_beta, var_prev, __dmul_rn(__dmul_rn(__dsub_rn(1.0, r.ema_beta), dev), dev));
         clipped = active;
     } else {
         active = gnorm > r.lambda_abs;
@@ -402,9 +401,9 @@ __device__ __forceinline__ void global_rule(const DeviceTables& t, float* ema, c
             double mu = clipped_norm, var = 0.0;
             if (!r.first_step) {
                 const double mu_prev = (double)ema[0], var_prev = (double)ema[1];
-                mu = __dadd_rn(__dmul_rn(r.ema_beta, mu_prev), __dmul_rn(__dsub_rn(1.0, r.ema_beta), clipped_norm));
+                mu = fma(r.ema_beta, mu_prev, __dmul_rn(__dsub_rn(1.0, r.ema_beta), clipped_norm));
                 const double dev = __dsub_rn(clipped_norm, mu);
-                var = __dadd_rn(__dmul_rn(r.ema_beta, var_prev), __dmul_rn(__dmul_rn(__dsub_rn(1.0, r.ema_beta), dev), dev));
+                var = fma(r.ema_beta, var_prev, __dmul_rn(__dmul_rn(__dsub_rn(1.0, r.ema_beta), dev), dev));
             }
             ema[0] = (float)mu;
             ema[1] = (float)var;

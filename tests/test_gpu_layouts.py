@@ -483,3 +483,39 @@ def test_moments_next_to_ties_have_the_bits_of_separately_rounded_sums(optimizer
                 wrong = (lists[k][i].cpu().numpy() != ref).nonzero()[0]
                 assert not len(wrong), "%s of tensor %d (%d elements), %s: %d values, first at %s" % (
                     k, i, n, "end to end" if flat else "apart", len(wrong), wrong[:5])
+
+
+@pytest.mark.parametrize("entry", [STEP, GRAPH, STATIC])
+@pytest.mark.parametrize("filler", [0, 6000001])
+def test_gamma_next_to_ties_has_the_bits_of_separately_rounded_operations(filler, entry):
+    """beta gamma + (1 - beta) norm next to ties, on a list whose rule is evaluated in the update kernel and on one with a rules kernel: the
+    formula in double, without fusing.  (1 - beta) norm is rounded; integers as gradients, so that the norms are known."""
+    rng = np.random.default_rng(5)
+    beta = float(np.float32(0.9))
+    grads, gammas = [], []
+    while len(grads) < 40:
+        x = (2.0 * rng.integers(0, 128, rng.integers(2, 60)) + 1.0) * rng.choice([-1.0, 1.0])
+        norm = float(np.sqrt(np.sum(x * x)))
+        gamma = _state_next_to_a_tie(beta, (1.0 - beta) * norm, Fraction(1.0 - beta) * Fraction(norm))
+        if gamma:
+            grads.append(x)
+            gammas.append(gamma)
+    want = [np.float32(beta * y + (1.0 - beta) * float(np.sqrt(np.sum(x * x)))) for x, y in zip(grads, gammas)]
+    hp = B.make_hyper(lr=1e-3, ema_beta=0.9, lambda_rel=1e6, t_start=0)                 # nothing clipped
+    g = [torch.from_numpy(x.astype(np.float32)).to(DEV) for x in grads] + ([torch.zeros(filler, device=DEV)] if filler else [])
+    p, m, v = ([torch.zeros_like(x) for x in g] for _ in range(3))
+    ema = torch.tensor(gammas + [1.0] * bool(filler), dtype=torch.float32, device=DEV)
+    assert ema[:40].double().cpu().tolist() == gammas                                  # fp32 values
+    numels = [x.numel() for x in g]
+    if entry == STATIC:
+        B.adagc_step_static(numels, p, g, m, v, ema, hp, 7)
+    else:
+        ctx = B.AdaGC(numels)
+        if entry == GRAPH:
+            ctx.step_graph(p, g, m, v, ema, torch.frombuffer(bytearray(B.step_params_bytes(hp, 7)), dtype=torch.uint8).to(DEV))
+        else:
+            ctx.step(p, g, m, v, ema, hp, 7)
+        torch.cuda.synchronize()
+        ctx.close()
+    torch.cuda.synchronize()
+    assert np.array_equal(ema[:40].cpu().numpy(), np.array(want))
