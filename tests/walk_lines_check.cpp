@@ -9,7 +9,8 @@ int main()
 {
     int opt, bf16, copy;
     int64_t tensors, elems, off, workgroups, items;
-    while (std::scanf("%d %d %d %" SCNd64 " %" SCNd64 " %" SCNd64 " %" SCNd64 " %" SCNd64, &opt, &bf16, &copy, &tensors, &elems, &off, &workgroups, &items) == 8)
+    while (std::scanf("%d %d %d %" SCNd64 " %" SCNd64 " %" SCNd64 " %" SCNd64 " %" SCNd64, &opt, &bf16, &copy, &tensors, &elems, &off,
+                      &workgroups, &items) == 8)
         std::printf("%d\n", adagc::walk_lines(opt, bf16 != 0, copy != 0, tensors, elems, off, workgroups, items) ? 1 : 0);
     return 0;
 }
