@@ -107,15 +107,15 @@ typedef struct {
                                      b, b+grid, ...; default: one work item per workgroup (a chunk in the
                                      norm kernel; a chunk or a part of one in the update kernel) */
     int32_t unroll;               /* 128-bit vectors per lane per array kept in flight by the update kernel:
-                                     1, 2 or 4 (default: AdamW 4, Lion 2) */
+                                     1, 2 or 4 (default: 2) */
     int32_t nontemporal;          /* streaming (non-temporal) loads and stores of the update kernel, and of the norm kernel
                                      on lists with more than 8 GiB of gradients: 1 = on (default), 2 = off */
     int32_t schedule;             /* visiting order of the chunks, see adagc_build_visiting_order: number of
                                      contiguous parts the list is cut into (default 2; 1 = list order) */
     int32_t update_split;         /* work items of the update kernel per chunk: 1 = whole chunks, or 2, 4, ...
                                      up to chunk_elems / (unroll*1024), chunk_elems / 4096 where unroll
-                                     is 0.  Default (0): 4096-element items
-                                     for AdamW, 2048 for Lion
+                                     is 0.  Default (0): 2048-element items
+                                     (with unroll 4: 4096)
                                      (small items shorten the tail of the launch and give short lists more
                                      workgroups; whole chunks cost the fewest dispatches) */
     int32_t schedule_run;         /* visiting order: chunks an XCD takes in a row (default 8) */

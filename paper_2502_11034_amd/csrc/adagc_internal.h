@@ -50,12 +50,15 @@ inline uint32_t line_offset_of(const TensorArgs& a)
 
 // One chunk, in the order in which the streaming kernels visit them: all that a workgroup needs to find its elements
 // besides the tensor's own record, in one 16-byte load.
+// Or one work item of it: the item's number inside the chunk in the upper half of `len`.
 struct WorkRef {
     uint32_t tensor;  // owning tensor
     uint32_t slot;    // number in list order: its slot of the partial results
     uint32_t index;   // position inside the tensor: first element = index * kChunkElems
     uint32_t len;     // elements, 1 .. kChunkElems
 };
+inline constexpr uint32_t kPartShift = 16;
+static_assert(kChunkElems < (1 << kPartShift), "a chunk's length and an item's number share a word");
 
 // Scalars of the per-tensor rule (Eq. 3 / warm-up branch of Alg. 1), all widened from the
 // caller's fp32 hyper-parameters so that decisions are taken in double.
@@ -97,8 +100,9 @@ struct StepScalars {
 };
 
 struct DeviceTables {
-    const WorkRef*    work;       // the chunks in visiting order: the n_long that are more than one work item of the
-                                  // update kernel, then those that are one, the n_tiny that one wave handles last
+    const WorkRef*    work;       // the chunks in visiting order: the n_long long ones, then the short ones, the n_tiny that one wave
+                                  // handles last (chunk_kind)
+    const WorkRef*    items;      // the n_short work items of the short chunks
     const TensorArgs* targs;
     double*           partials;   // one per chunk
     double*           sumsq;      // one per tensor
@@ -117,38 +121,60 @@ struct DeviceTables {
     double*           ucoef64;        // update clipping: per-tensor coefficient of the direction, or null
     uint32_t          n_chunks;
     uint32_t          n_long;
+    uint32_t          n_short;
     uint32_t          n_tiny;
     uint32_t          n_tensors;
     uint32_t          off_lines;  // host: the update kernel walks whole lines (walk_lines)
 };
 
 // Vectors per lane and array that the update kernel keeps in flight, and the work items of a full chunk (one round of those
-// each), unless the caller chooses.  AdamW: 4, items of 4096 elements; in whole chunks a launch has too long a tail (GPT-2-small
-// shapes 639 us per step against 685, 5000-tensor lists have too few workgroups), in halves 676, as 2 and 2048 elements 637 (and
-// 1.5 % slower on lists of GBs).  Lion: 2, items of 2048 elements: it moves 10 instead of 16 bytes per element each way, and
-// more, smaller items suit it (Llama-3-8B shapes, 4 layers, two placements: 7.23 -> 6.84 ms, 6.65 -> 6.55 ms).
-constexpr int default_unroll(int optimizer) { return optimizer == ADAGC_OPT_LION ? 2 : 4; }
+// each), unless the caller chooses: 2, and items of 2048 elements.  With four waves per SIMD (kUpdateWaves) AdamW has as many loads
+// in flight as with 4, items of 4096 and two waves, in smaller pieces, which fill the compute units more evenly and end sooner.
+// us per step with 4 and 4096 / with 2 and 2048, tensors of 0.5 to 1.5 M elements: 1.5 M parameters 16.4 / 15.3, 7 M 42.4 / 41.0, 17 M
+// 87.8 / 85.9, 64 M 314 / 308, 132 M 661 / 658, 500 M 2642 / 2666, 1.9 G 9306 / 9298; with bf16 gradients and the copy 17.1 / 15.3,
+// 46.3 / 44.2, 93.1 / 91.1, 315 / 311, 600 / 591, 2437 / 2434, 8747 / 8755.  In whole chunks a launch has too long a tail and short lists
+// too few workgroups.  Lion moves 10 instead of 16 bytes per element each way (Llama-3-8B shapes, 4 layers, two placements, 4 and
+// 4096 / 2 and 2048: 7.23 / 6.84 ms, 6.65 / 6.55).
+constexpr int default_unroll(int) { return 2; }
 constexpr int default_items(int unroll) { return kVecPerLane >= unroll ? kVecPerLane / unroll : 1; }
 
 // How the streaming kernels work on a chunk of `len` elements, in the order in which the work table has them:
-//   long   more than one work item of the update kernel (items_per_chunk of them make a full chunk)
-//   short  one work item
+//   long   items_per_chunk work items of the update kernel, numbered with those of other chunks; the last ones may be empty, and an
+//          empty workgroup costs its dispatch and a chain of loads all the same
+//   short  up to short_items items; the update kernel has a table of them (DeviceTables::items)
 //   tiny   one round of a single wave's loads: four chunks to a workgroup.  Most tensors of a list of adapters, biases and norm
 //          weights are of this size, and a workgroup of its own for each costs more than its work (5000 tensors, two thirds of
 //          them tiny: 108 us per step, now 100).
 enum ChunkKind { kLongChunk, kShortChunk, kTinyChunk };
 constexpr int kTinyMax = 1024;             // the norm kernel's round for one wave
-__host__ __device__ inline ChunkKind chunk_kind(int64_t len, int items_per_chunk, int unroll)
+__host__ __device__ inline int chunk_items(int64_t len, int items_per_chunk)
 {
-    if (items_per_chunk == 1 || len > kChunkElems / items_per_chunk) return kLongChunk;
+    const int64_t item = kChunkElems / items_per_chunk;
+    return (int)((len + item - 1) / item);
+}
+__host__ __device__ inline ChunkKind chunk_kind(int64_t len, int items_per_chunk, int unroll, int short_items)
+{
+    if (items_per_chunk == 1 || chunk_items(len, items_per_chunk) > short_items) return kLongChunk;
     return len <= unroll * 256 && len <= kTinyMax ? kTinyChunk : kShortChunk;
 }
 
-// Workgroups' worth of work: items_per_chunk for every long chunk (in groups of 8 chunks), one for a short chunk, one for four
-// tiny ones.
-inline int64_t count_work_items(int64_t n_chunks, int64_t n_long, int64_t n_tiny, int items_per_chunk)
+// The most items of a short chunk.  Half a chunk's in lists of small tensors and in small lists, where empty workgroups are
+// what a launch waits for; one elsewhere, because short chunks, visited after the long ones, are far from their neighbours in memory.
+// us per step, one / half a chunk's, AdamW with fp32 gradients: 5333 tensors, mean 3000 elements, 122 / 86, 10 666 of them 236 / 164;
+// mean 12 000: 4 M parameters 29.6 / 26.8, 16 M 88 / 85, 128 M 664 / 668; mean 30 000: 16 M 83.6 / 80.9, 128 M 642 / 648, 300 M
+// 1567 / 1600; mean 200 000: 16 M 85.7 / 83.7.  Lion, bf16: mean 3000: 105 / 74, 209 / 138; mean 30 000: 300 M 1045 / 1052.  (The rule in the
+// update kernel, below, has a part in the gain of the lists up to 16 M.)  All chunks that are not full ones short: mean 30 000, 300 M 1621; in
+// the order of the long ones, so that their items no longer stay on one XCD: 1669.
+constexpr int most_short_items(int64_t n_tensors, int64_t elems, int items_per_chunk)
 {
-    return (n_long + 7) / 8 * 8 * items_per_chunk + (n_chunks - n_long - n_tiny) + (n_tiny + 3) / 4;
+    return items_per_chunk > 1 && (elems <= ((int64_t)32 << 20) || elems < 8192 * n_tensors) ? items_per_chunk / 2 : 1;
+}
+
+// Workgroups' worth of work: items_per_chunk for every long chunk (in groups of 8 chunks), those of the short chunks, one for four
+// tiny ones.
+inline int64_t count_work_items(int64_t n_long, int64_t n_short, int64_t n_tiny, int items_per_chunk)
+{
+    return (n_long + 7) / 8 * 8 * items_per_chunk + n_short + (n_tiny + 3) / 4;
 }
 
 // Whether the norm kernel reads the gradients past the memory-side cache: lists of more than 8 GiB of them, 32 times what
@@ -156,13 +182,13 @@ inline int64_t count_work_items(int64_t n_chunks, int64_t n_long, int64_t n_tiny
 // (figures at the kernel).
 inline bool stream_gradients(int64_t total_elems, bool grad_bf16) { return total_elems > ((int64_t)1 << 33) / (grad_bf16 ? 2 : 4); }
 
-// Small lists evaluate the per-tensor rule (Eq. 3) inside the update kernel, every wave for its own chunk, from the tensor's
-// partial sums and a copy of gamma that the norm kernel makes: one launch less, for one more load per wave.  That pays while
-// the update kernel is only a few rounds of workgroups, and needs tensors whose slots one wave can sum in the rules kernel's
-// order (see rule_in_update).  us per step, in the rules kernel / in the update: 64 work items 11.9 / 9.8, 512: 18.0 / 15.4,
-// 1024: 28.4 / 25.9, 2048: 47.2 / 45.4, 4096: 88.9 / 87.3, 8192: 164.0 / 163.9.  So the line lies well inside the range that
-// gains, where the launch is still a tenth of the step.
-constexpr int64_t kFusedMaxItems = 1024;
+// Small lists evaluate the per-tensor rule (Eq. 3) inside the update kernel, every wave for its own tensor, from the tensor's
+// partial sums and a copy of gamma that the norm kernel makes: one launch less, for one more load per wave.  It needs tensors whose
+// slots one wave can sum in the rules kernel's order (see rule_in_update).  us per step, in the rules kernel / in the update, AdamW fp32:
+// 0.5 M parameters 12.7 / 9.2, 2 M 18.8 / 16.5, 4 M 28.7 / 26.7, 8 M 48.2 / 46.1, 16 M 83.8 / 81.7, 31 M 156.8 / 155.2; in tensors of 3000:
+// 4 M 29.6 / 27.5, 16 M 88.2 / 85.1, 32 M 165.0 / 161.1.  Lion, bf16: 0.5 M 12.5 / 9.1, 4 M 26.4 / 24.4, 16 M 65.1 / 63.5, 31 M 116.1 / 115.3;
+// in tensors of 3000: 4 M 25.6 / 24.1, 16 M 73.7 / 73.9, 32 M 137.8 / 140.9.  Work items: about one for 2048 elements.
+constexpr int64_t fused_max_items(int optimizer) { return optimizer == ADAGC_OPT_LION ? 8192 : 16384; }
 constexpr int64_t kFusedMaxChunks = 64;        // of one tensor
 struct FusedRule {
     float*   ema;        // null: the rules kernel has run, coefficients are in coef64

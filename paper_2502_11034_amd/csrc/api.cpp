@@ -210,13 +210,17 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
         const int64_t rest = c->numel[chunk_tensor[k]] - (int64_t)chunk_index[k] * kChunkElems;
         return rest < kChunkElems ? rest : (int64_t)kChunkElems;
     };
-    auto kind_of = [&](size_t k) { return chunk_kind(chunk_len(k), c->items_per_chunk, c->unroll); };
-    int64_t n_long = 0, n_tiny = 0;
+    for (int64_t i = 0; i < n_tensors; ++i) c->total_elems += descs[i].numel;
+    const int short_items = most_short_items(n_tensors, c->total_elems, c->items_per_chunk);
+    auto kind_of = [&](size_t k) { return chunk_kind(chunk_len(k), c->items_per_chunk, c->unroll, short_items); };
+    int64_t n_long = 0, n_short = 0, n_tiny = 0;           // n_short: work items
     for (size_t k = 0; k < chunk_tensor.size(); ++k) {
-        n_long += kind_of(k) == kLongChunk ? 1 : 0;
-        n_tiny += kind_of(k) == kTinyChunk ? 1 : 0;
+        const ChunkKind kind = kind_of(k);
+        if (kind == kLongChunk) ++n_long;
+        else if (kind == kTinyChunk) ++n_tiny;
+        else n_short += chunk_items(chunk_len(k), c->items_per_chunk);
     }
-    const int64_t tiles = count_work_items(c->n_chunks, n_long, n_tiny, c->items_per_chunk);
+    const int64_t tiles = count_work_items(n_long, n_short, n_tiny, c->items_per_chunk);
     auto grid_for = [cfg](int64_t items) {
         int64_t want = cfg->grid_blocks > 0 ? (int64_t)cfg->grid_blocks : items;
         if (want > items) want = items;
@@ -226,10 +230,9 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     for (int64_t i = 0; i < n_tensors; ++i) {
         const int64_t n = c->chunk_begin[(size_t)i + 1] - c->chunk_begin[(size_t)i];
         if (n > most_chunks) most_chunks = n;
-        c->total_elems += descs[i].numel;
     }
     c->stream_grads = c->nontemporal && stream_gradients(c->total_elems, cfg->grad_dtype == ADAGC_GRAD_BF16);
-    c->small_list = tiles <= kFusedMaxItems && most_chunks <= kFusedMaxChunks;
+    c->small_list = tiles <= fused_max_items(cfg->optimizer) && most_chunks <= kFusedMaxChunks;
     c->grid_norm = grid_for(c->n_chunks - n_tiny + (n_tiny + 3) / 4);
     c->n_items = tiles;
     c->grid_update = grid_for(tiles);
@@ -239,6 +242,7 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     size_t off = 0;
     auto carve = [&off](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
     const size_t o_work = carve(nc * sizeof(WorkRef));
+    const size_t o_items = carve((size_t)n_short * sizeof(WorkRef));
     const size_t o_targs = carve(nt * sizeof(TensorArgs));
     const size_t o_partials = carve(nc * sizeof(double));
     const size_t o_sumsq = carve(nt * sizeof(double));
@@ -271,7 +275,7 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     // The chunks in visiting order (see adagc_build_visiting_order): the long ones, then the short and the tiny ones in list
     // order.
     {
-        std::vector<WorkRef> work;
+        std::vector<WorkRef> work, items;
         try {
             std::vector<uint32_t> longer, order;
             longer.reserve((size_t)n_long);
@@ -289,8 +293,15 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
             for (ChunkKind kind : {kShortChunk, kTinyChunk})
                 for (size_t k = 0; k < nc; ++k)
                     if (kind_of(k) == kind) append((uint32_t)k);
+            items.reserve((size_t)n_short);
+            for (size_t k = (size_t)n_long; k < nc - (size_t)n_tiny; ++k)
+                for (int part = 0; part < chunk_items(work[k].len, c->items_per_chunk); ++part) {
+                    items.push_back(work[k]);
+                    items.back().len |= (uint32_t)part << kPartShift;
+                }
         } catch (const std::bad_alloc&) { free_ctx(c); return ADAGC_ERR_OOM; }
-        if (hipMemcpy(base + o_work, work.data(), nc * sizeof(WorkRef), hipMemcpyHostToDevice) != hipSuccess) {
+        if (hipMemcpy(base + o_work, work.data(), nc * sizeof(WorkRef), hipMemcpyHostToDevice) != hipSuccess ||
+            (n_short > 0 && hipMemcpy(base + o_items, items.data(), items.size() * sizeof(WorkRef), hipMemcpyHostToDevice) != hipSuccess)) {
             free_ctx(c);
             return ADAGC_ERR_HIP;
         }
@@ -312,6 +323,7 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     c->d_targs = reinterpret_cast<TensorArgs*>(base + o_targs);
     DeviceTables& t = c->tables;
     t.work = reinterpret_cast<const WorkRef*>(base + o_work);
+    t.items = reinterpret_cast<const WorkRef*>(base + o_items);
     t.targs = c->d_targs;
     t.partials = reinterpret_cast<double*>(base + o_partials);
     t.sumsq = reinterpret_cast<double*>(base + o_sumsq);
@@ -329,6 +341,7 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     t.ucoef64 = cfg->update_clipping ? reinterpret_cast<double*>(base + o_ucoef64) : nullptr;
     t.n_chunks = (uint32_t)c->n_chunks;
     t.n_long = (uint32_t)n_long;
+    t.n_short = (uint32_t)n_short;
     t.n_tiny = (uint32_t)n_tiny;
     t.n_tensors = (uint32_t)c->n_tensors;
 

@@ -7,8 +7,8 @@
 //                           model's norm; "Ablation Study", Sec. 5.6), ZClip
 //   global_rule_kernel / finalize_global_kernel
 //                           those model-wide rules on long lists
-//   update_kernel           per work item (a quarter of a chunk, an eighth for Lion; chunks of up to 1024, Lion 512, elements
-//                           go four to a workgroup): clipped gradient into AdamW / Lion  (Alg. 1)
+//   update_kernel           per work item (an eighth of a chunk; chunks of up to 512 elements go four to a workgroup):
+//                           clipped gradient into AdamW / Lion  (Alg. 1)
 //   direction_stats_kernel / finalize_update_clip_kernel
 //                           update clipping (AGC and Clippy rows of Table 2): norms of theta and of the
 //                           optimizer's direction per tensor, and the coefficient that scales the direction
@@ -603,49 +603,57 @@ __device__ __forceinline__ void tele_vec(double (&acc)[3], f32x4 p_old, f32x4 p_
 // eight consecutive workgroups work on eight consecutive positions of the visiting order (one from each of
 // its parts) and the items of one chunk all go to the same XCD:
 //   item T  ->  position 8*(T / (8*I)) + T % 8,  item (T / 8) % I of that chunk      (I = items_per_chunk, a power of two).
-// Chunks of one item come after the others, one item each: in a list of many small tensors three of a chunk's four items
-// would be empty, and an empty workgroup costs its dispatch and its chain of loads all the same.  Tiny chunks, last, go four
-// to a workgroup (the direction's norms take them as short ones).
+// The items of short chunks follow, from a table of their own.  Tiny chunks, last, go four to a workgroup (the direction's norms
+// take them one by one).
 
 struct WorkItem {
     WorkRef chunk;
     int     part;     // which item of the chunk
 };
 
-__device__ __forceinline__ uint64_t work_items(const DeviceTables& t, uint32_t log2_items)
+__device__ __forceinline__ uint64_t long_items(const DeviceTables& t, uint32_t log2_items)
 {
-    return ((((uint64_t)t.n_long + 7u) & ~(uint64_t)7u) << log2_items) + (t.n_chunks - t.n_long);
+    return (((uint64_t)t.n_long + 7u) & ~(uint64_t)7u) << log2_items;
 }
 
-// False: this number is only there to fill a group of eight.
+// Item number `item` of the long and short chunks.  False: this number is only there to fill a group of eight.
 __device__ __forceinline__ bool work_item(const DeviceTables& t, uint64_t item, uint32_t log2_items, WorkItem& w)
 {
-    const uint64_t in_long = (((uint64_t)t.n_long + 7u) & ~(uint64_t)7u) << log2_items;
-    uint32_t k;
+    const uint64_t in_long = long_items(t, log2_items);
     if (item < in_long) {
-        k = (uint32_t)(item >> (3 + log2_items)) * 8u + ((uint32_t)item & 7u);
-        w.part = (int)(((uint32_t)item >> 3) & ((1u << log2_items) - 1u));
+        const uint32_t k = (uint32_t)(item >> (3 + log2_items)) * 8u + ((uint32_t)item & 7u);
         if (k >= t.n_long) return false;
+        w.part = (int)(((uint32_t)item >> 3) & ((1u << log2_items) - 1u));
+        w.chunk = load_work(t.work, k);
     } else {
-        k = t.n_long + (uint32_t)(item - in_long);
-        w.part = 0;
+        w.chunk = load_work(t.items, (uint32_t)(item - in_long));
+        w.part = (int)(w.chunk.len >> kPartShift);
+        w.chunk.len &= (1u << kPartShift) - 1u;
     }
-    w.chunk = load_work(t.work, k);
     return true;
 }
 
 // The per-tensor rule inside the update kernel (FusedRule); all 64 lanes.  A tensor has at most 64 partial sums: one to a
 // lane, the other lanes' and waves' shares of the rules kernel's order are zeros there too, so the sum is the same bit for bit.
-// The lane with the tensor's first element stores the results (`stores`).
-// 27 tensors of 0.5 M parameters: 14.7 us per step with the rules in a kernel of their own, 11.4 so; 100 tensors of 3.6 M
-// parameters (1000 work items) 29, 25.8.
-__device__ __forceinline__ double rule_in_update(const DeviceTables& t, const FusedRule& rule, uint32_t tensor, const TensorArgs& ta,
-                                                 bool stores)
+// The lane with the tensor's first element stores the results (`stores`).  What it needs is loaded before the elements, and the rule
+// evaluated while they are on their way.
+struct RuleInputs {
+    double partial;
+    float  gamma;
+};
+__device__ __forceinline__ RuleInputs load_rule_inputs(const DeviceTables& t, uint32_t tensor, const TensorArgs& ta)
 {
     const uint32_t lane = threadIdx.x & 63u;
-    const double mine = lane < ta.chunk_count ? t.partials[ta.chunk_begin + lane] : 0.0;
-    const double s = wave_sum_f64(mine);
-    const TensorRule o = adagc_rule(rule.r, s, (double)uniform_load(t.ema_before + tensor));
+    RuleInputs in;
+    in.partial = lane < ta.chunk_count ? t.partials[ta.chunk_begin + lane] : 0.0;
+    in.gamma = uniform_load(t.ema_before + tensor);
+    return in;
+}
+__device__ __forceinline__ double rule_in_update(const DeviceTables& t, const FusedRule& rule, uint32_t tensor, const RuleInputs& in,
+                                                 bool stores)
+{
+    const double s = wave_sum_f64(in.partial);
+    const TensorRule o = adagc_rule(rule.r, s, (double)in.gamma);
     if (stores) store_rule(t, rule.ema, tensor, s, o);
     return o.h;
 }
@@ -663,16 +671,20 @@ __device__ __forceinline__ void wait_for_loads()
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// Waves per SIMD that the update kernel may have in flight.  One wave holds 16 loads of 1 KiB, so two are enough to cover
-// the latency, and more only open more DRAM rows at once: AdamW on GPT-2-small shapes 657 us per step with 2, 667 with 3, 670
-// with 4 (Llama-3-8B shapes 10.75, 10.90, 10.87 ms for 4 layers).  Lion has fewer arrays in flight and wants 3: GPT-2-small
-// shapes 476 us with 2, 448 with 3, 448 with 4; 1500 ragged tensors 1518, 1450, 1495; Llama-3-8B shapes with bf16 gradients and
-// copies 7.10, 6.65, 6.97 ms (5000 small tensors 88, 77, 72 us).
-template <int OPT>
-constexpr int kUpdateWaves = OPT == ADAGC_OPT_ADAMW ? 2 : 3;
+// Waves per SIMD that the update kernel may have in flight.  With 4 vectors of each array one wave holds 16 loads of 1 KiB, so two
+// are enough to cover the latency, and more only open more DRAM rows at once: AdamW on GPT-2-small shapes 657 us per step with 2, 667
+// with 3, 670 with 4 (Llama-3-8B shapes 10.75, 10.90, 10.87 ms for 4 layers).  With 2 vectors AdamW has 4: 5000 small tensors 94 us with 4, 98
+// with 3; GPT-2-small 616 - 630, 622; 133 M parameters with bf16 gradients and copies 630, 640 (ragged tensors end to end 2085, 2035).  Lion
+// has fewer arrays in flight and wants 3: GPT-2-small shapes 476 us with 2, 448 with 3, 448 with 4; 1500 ragged tensors 1518, 1450,
+// 1495; Llama-3-8B shapes with bf16 gradients and copies 7.10, 6.65, 6.97 ms (5000 small tensors 88, 77, 72 us).
+template <int OPT, int U>
+constexpr int kUpdateWaves = OPT == ADAGC_OPT_ADAMW ? (U == 4 ? 2 : 4) : 3;
 
-template <int OPT, bool BF16G, bool COPY, int U, bool NT, bool TELE, bool LINES>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kUpdateWaves<OPT>, kUpdateWaves<OPT>)))
+// Whether the per-tensor rule is evaluated here: known where the launch is one of the library's own choice, else asked.
+enum RuleHere { kRuleNo, kRuleYes, kRuleAsk };
+
+template <int OPT, bool BF16G, bool COPY, int U, bool NT, bool TELE, bool LINES, RuleHere RULE>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kUpdateWaves<OPT, U>, kUpdateWaves<OPT, U>)))
 void update_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items, const StepScalars* device_scalars, FusedRule rule)
 {
     static_assert(kVecPerLane % U == 0, "a chunk is a whole number of tiles");
@@ -696,8 +708,14 @@ void update_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items, const Step
         const int64_t first = first_element(c);
         const TensorArgs ta = load_tensor(t.targs, tensor);
         // the tensor's coefficient as computed, in double
-        const double h = rule.ema ? rule_in_update(t, rule, tensor, ta, c.index == 0 && first_tile == 0 && lane == 0)
-                                  : uniform_load(t.coef64 + tensor);
+        const bool rule_here = RULE == kRuleYes || (RULE == kRuleAsk && rule.ema);
+        double h = 1.0;
+        RuleInputs rule_inputs{0.0, 0.f};
+        if (rule_here) rule_inputs = load_rule_inputs(t, tensor, ta);
+        else h = uniform_load(t.coef64 + tensor);
+        auto evaluate_rule = [&]() __attribute__((always_inline)) {
+            if (rule_here) h = rule_in_update(t, rule, tensor, rule_inputs, c.index == 0 && first_tile == 0 && lane == 0);
+        };
         const double uc = a.update_clip ? uniform_load(t.ucoef64 + tensor) : 1.0;   // update clipping: scales the direction
         const gcbytes g = grad_at<BF16G>(ta.grad, first);
         const gfloat p = (gfloat)ta.param + first;
@@ -762,6 +780,7 @@ void update_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items, const Step
                         if constexpr (kHasV) vv[u] = ld<NTL>(v4 + idx);
                         else vv[u] = f32x4{0.f, 0.f, 0.f, 0.f};
                     }
+                    if (tt == 0) evaluate_rule();
                     if constexpr (kHasV && COPY) wait_for_loads();
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
@@ -776,6 +795,8 @@ void update_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items, const Step
                         if constexpr (kHasV) st<NTS>(v4 + idx, vv[u]);
                         if constexpr (COPY) st<NTS>(c4 + idx, pack_bf16x4(pp[u]));
                     }
+                } else if (tt == 0) {
+                    evaluate_rule();
                 }
                 if (single) {
                     const float p_old = s.p;
@@ -787,6 +808,7 @@ void update_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items, const Step
                     if constexpr (COPY) pc[j] = (uint16_t)float_to_bf16_bits(s.p);
                 }
             } else {
+                if (tt == 0) evaluate_rule();
                 for (int j = e0 + lane; j < e1; j += kLanes) {
                     ElemState s = {p[j], m[j], kHasV ? v[j] : 0.f};
                     const float p_old = s.p;
@@ -804,8 +826,7 @@ void update_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items, const Step
 
     const int tiles_per_item = kTiles >> log2_items;
     const uint32_t n_wide = t.n_chunks - t.n_tiny;
-    const uint64_t in_long = (((uint64_t)t.n_long + 7u) & ~(uint64_t)7u) << log2_items;
-    const uint64_t n_wide_items = in_long + (n_wide - t.n_long), n_items = n_wide_items + (t.n_tiny + 3u) / 4u;
+    const uint64_t n_wide_items = long_items(t, log2_items) + t.n_short, n_items = n_wide_items + (t.n_tiny + 3u) / 4u;
     for (uint64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
         double tele[3] = {0.0, 0.0, 0.0};
         if (item >= n_wide_items) {            // four tiny chunks, one to a wave
@@ -850,7 +871,7 @@ void update_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items, const Step
 // Update clipping (AGC and Clippy rows of Table 2).  The coefficient of a tensor's update needs the norms
 // of theta and of the whole tensor's direction Delta, so the direction is evaluated twice: here for its
 // norms (nothing is written but two partial results per work item), then by update_kernel, which scales it.
-// Work items are those of update_kernel.  LINF selects maxima of |.| (Clippy) instead of sums of squares (AGC).
+// Work items are those of update_kernel, or several of them (log2_stats_items).  LINF selects maxima of |.| (Clippy) instead of sums of squares (AGC).
 
 // All 64 lanes must be active.  Returns the same value in every lane.  Maxima are exact in any order.
 __device__ __forceinline__ double wave_max_f64(double x)
@@ -890,21 +911,39 @@ __device__ __forceinline__ void stat_acc(double (&acc)[2], float theta, double d
     }
 }
 
+// Vectors per lane and array in flight.  AdamW: 4, as the update kernel once had; with its 2 and 2048 elements at a time
+// 133 M parameters under AGC take 932 us per step, so 919.
+template <int OPT>
+constexpr int kStatsUnroll = OPT == ADAGC_OPT_ADAMW ? 4 : 2;
+
+// Items of a long chunk, where the update kernel has 1 << log2_items: none smaller than a tile.
+template <int OPT>
+__host__ __device__ constexpr uint32_t log2_stats_items(uint32_t log2_items)
+{
+    constexpr uint32_t kMost = kVecPerLane / kStatsUnroll<OPT>;
+    static_assert((kMost & (kMost - 1)) == 0, "a power of two");
+    return (1u << log2_items) < kMost ? log2_items : (uint32_t)__builtin_ctz(kMost);
+}
+
 template <int OPT, bool BF16G, bool LINF, bool NT>
 __global__ __launch_bounds__(kBlock) void direction_stats_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items)
 {
-    constexpr int U = default_unroll(OPT);
+    constexpr int U = kStatsUnroll<OPT>;
     constexpr bool kHasV = (OPT == ADAGC_OPT_ADAMW);
     constexpr int kTileVecs = U * kBlock;
     constexpr int kTileElems = kTileVecs * 4;
     const int tid = threadIdx.x;
     __shared__ double wave_part[2][kWavesPerBlock];
 
-    const int item_elems = kChunkElems >> log2_items;      // may be less than a tile: the caller chooses
-    const uint64_t n_items = work_items(t, log2_items);
+    // a long chunk's items are taken as many at a time as make a tile, for the slot of the first of them
+    const uint32_t log2_long = log2_stats_items<OPT>(log2_items);
+    const uint64_t in_long = long_items(t, log2_long), n_wide_items = in_long + t.n_short, n_items = n_wide_items + t.n_tiny;
     for (uint64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
         WorkItem w;
-        if (!work_item(t, item, log2_items, w)) continue;
+        if (item >= n_wide_items) w = {load_work(t.work, t.n_chunks - t.n_tiny + (uint32_t)(item - n_wide_items)), 0};
+        else if (!work_item(t, item, log2_long, w)) continue;
+        if (item < in_long) w.part <<= log2_items - log2_long;
+        const int item_elems = kChunkElems >> (item < in_long ? log2_long : log2_items);         // may be less than a tile: the caller chooses
         const int len = (int)w.chunk.len;
         const int64_t first = first_element(w.chunk);
         const TensorArgs ta = load_tensor(t.targs, w.chunk.tensor);
@@ -914,7 +953,7 @@ __global__ __launch_bounds__(kBlock) void direction_stats_kernel(DeviceTables t,
         const gcfloat v = kHasV ? (gcfloat)ta.exp_avg_sq + first : nullptr;
         double acc[2] = {0.0, 0.0};
 
-        const int item_begin = w.part * item_elems;
+        const int item_begin = w.part * (kChunkElems >> log2_items);
         const int item_end = len < item_begin + item_elems ? len : item_begin + item_elems;
 #pragma unroll 1
         for (int e0 = item_begin; e0 < item_end; e0 += kTileElems) {
@@ -1042,36 +1081,38 @@ __global__ __launch_bounds__(kBlock) void finalize_telemetry_kernel(DeviceTables
 
 using UpdateFn = void (*)(DeviceTables, UpdateArgs, uint32_t, const StepScalars*, FusedRule);
 
-// lines: only with the number of vectors in flight that is not chosen otherwise, and where whole lines ever pay
-template <int OPT, bool BF16G, bool COPY, int U>
+// The launches of the library's own choice (the vectors in flight that are not chosen otherwise, streaming) have kernels with and
+// without the rule, and with whole lines where those ever pay.
+template <int OPT, bool BF16G, bool COPY, int U, RuleHere RULE>
 UpdateFn select_update_flags(int nt, int tele, bool lines)
 {
     if constexpr (U == default_unroll(OPT) && line_limits(OPT, BF16G, COPY).elems > 0)
-        if (lines && nt && !tele) return update_kernel<OPT, BF16G, COPY, U, true, false, true>;
-    if (nt) return tele ? update_kernel<OPT, BF16G, COPY, U, true, true, false> : update_kernel<OPT, BF16G, COPY, U, true, false, false>;
-    return tele ? update_kernel<OPT, BF16G, COPY, U, false, true, false> : update_kernel<OPT, BF16G, COPY, U, false, false, false>;
+        if (lines && nt && !tele) return update_kernel<OPT, BF16G, COPY, U, true, false, true, RULE>;
+    if (nt) return tele ? update_kernel<OPT, BF16G, COPY, U, true, true, false, RULE> : update_kernel<OPT, BF16G, COPY, U, true, false, false, RULE>;
+    return tele ? update_kernel<OPT, BF16G, COPY, U, false, true, false, kRuleAsk> : update_kernel<OPT, BF16G, COPY, U, false, false, false, kRuleAsk>;
 }
 
 template <int OPT, bool BF16G, bool COPY>
-UpdateFn select_update_variant(int unroll, int nt, int tele, bool lines)
+UpdateFn select_update_variant(int unroll, int nt, int tele, bool lines, bool rule)
 {
-    if (unroll == 4) return select_update_flags<OPT, BF16G, COPY, 4>(nt, tele, lines);
-    if (unroll == 2) return select_update_flags<OPT, BF16G, COPY, 2>(nt, tele, lines);
-    return select_update_flags<OPT, BF16G, COPY, 1>(nt, tele, lines);
+    static_assert(default_unroll(OPT) == 2, "the kernels below");
+    if (unroll == 4) return select_update_flags<OPT, BF16G, COPY, 4, kRuleAsk>(nt, tele, lines);
+    if (unroll == 1) return select_update_flags<OPT, BF16G, COPY, 1, kRuleAsk>(nt, tele, lines);
+    return rule ? select_update_flags<OPT, BF16G, COPY, 2, kRuleYes>(nt, tele, lines) : select_update_flags<OPT, BF16G, COPY, 2, kRuleNo>(nt, tele, lines);
 }
 
-UpdateFn select_update(int optimizer, int grad_bf16, int with_copy, int unroll, int nt, int tele, bool lines)
+UpdateFn select_update(int optimizer, int grad_bf16, int with_copy, int unroll, int nt, int tele, bool lines, bool rule)
 {
     const int key = (optimizer == ADAGC_OPT_LION ? 4 : 0) | (grad_bf16 ? 2 : 0) | (with_copy ? 1 : 0);
     switch (key) {
-    case 0: return select_update_variant<ADAGC_OPT_ADAMW, false, false>(unroll, nt, tele, lines);
-    case 1: return select_update_variant<ADAGC_OPT_ADAMW, false, true>(unroll, nt, tele, lines);
-    case 2: return select_update_variant<ADAGC_OPT_ADAMW, true, false>(unroll, nt, tele, lines);
-    case 3: return select_update_variant<ADAGC_OPT_ADAMW, true, true>(unroll, nt, tele, lines);
-    case 4: return select_update_variant<ADAGC_OPT_LION, false, false>(unroll, nt, tele, lines);
-    case 5: return select_update_variant<ADAGC_OPT_LION, false, true>(unroll, nt, tele, lines);
-    case 6: return select_update_variant<ADAGC_OPT_LION, true, false>(unroll, nt, tele, lines);
-    default: return select_update_variant<ADAGC_OPT_LION, true, true>(unroll, nt, tele, lines);
+    case 0: return select_update_variant<ADAGC_OPT_ADAMW, false, false>(unroll, nt, tele, lines, rule);
+    case 1: return select_update_variant<ADAGC_OPT_ADAMW, false, true>(unroll, nt, tele, lines, rule);
+    case 2: return select_update_variant<ADAGC_OPT_ADAMW, true, false>(unroll, nt, tele, lines, rule);
+    case 3: return select_update_variant<ADAGC_OPT_ADAMW, true, true>(unroll, nt, tele, lines, rule);
+    case 4: return select_update_variant<ADAGC_OPT_LION, false, false>(unroll, nt, tele, lines, rule);
+    case 5: return select_update_variant<ADAGC_OPT_LION, false, true>(unroll, nt, tele, lines, rule);
+    case 6: return select_update_variant<ADAGC_OPT_LION, true, false>(unroll, nt, tele, lines, rule);
+    default: return select_update_variant<ADAGC_OPT_LION, true, true>(unroll, nt, tele, lines, rule);
     }
 }
 
@@ -1126,7 +1167,10 @@ hipError_t launch_update_clip_rule(const DeviceTables& t, const UpdateArgs& u, c
     const bool lion = optimizer == ADAGC_OPT_LION;
     const StatsFn fn = grad_bf16 ? (lion ? select_stats_flags<ADAGC_OPT_LION, true> : select_stats_flags<ADAGC_OPT_ADAMW, true>)(linf, nt)
                                  : (lion ? select_stats_flags<ADAGC_OPT_LION, false> : select_stats_flags<ADAGC_OPT_ADAMW, false>)(linf, nt);
-    fn<<<dim3(grid), dim3(kBlock), 0, stream>>>(t, u, log2_of(items_per_chunk));
+    const uint32_t log2_items = log2_of(items_per_chunk);
+    const uint32_t log2_long = lion ? log2_stats_items<ADAGC_OPT_LION>(log2_items) : log2_stats_items<ADAGC_OPT_ADAMW>(log2_items);
+    const int64_t items = ((((int64_t)t.n_long + 7) & ~(int64_t)7) << log2_long) + t.n_short + t.n_tiny;
+    fn<<<dim3((uint32_t)(items < grid ? items : grid)), dim3(kBlock), 0, stream>>>(t, u, log2_items);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     finalize_update_clip_kernel<<<dim3(t.n_tensors), dim3(kBlock), 0, stream>>>(t, r, (uint32_t)items_per_chunk);
@@ -1137,7 +1181,7 @@ hipError_t launch_update(const DeviceTables& t, const UpdateArgs& a, int optimiz
                          int with_copy, int unroll, int items_per_chunk, int nt, int tele, int grid,
                          hipStream_t stream, bool device_scalars, const FusedRule& rule)
 {
-    select_update(optimizer, grad_bf16, with_copy, unroll, nt, tele, t.off_lines != 0)<<<dim3(grid), dim3(kBlock), 0, stream>>>(
+    select_update(optimizer, grad_bf16, with_copy, unroll, nt, tele, t.off_lines != 0, rule.ema != nullptr)<<<dim3(grid), dim3(kBlock), 0, stream>>>(
         t, a, log2_of(items_per_chunk), device_scalars ? t.scalars : nullptr, rule);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !tele) return e;

@@ -21,7 +21,10 @@ constexpr size_t kMaxT = ADAGC_STATIC_MAX_TENSORS;
 constexpr size_t kMaxC = ADAGC_STATIC_MAX_CHUNKS;
 constexpr size_t kOffTargs = 0;
 constexpr size_t kOffWork = kOffTargs + align256(kMaxT * sizeof(TensorArgs));
-constexpr size_t kOffPartials = kOffWork + align256(kMaxC * sizeof(WorkRef));
+constexpr int kMostShortItems = default_items(default_unroll(ADAGC_OPT_LION)) / 2;         // of a tensor, in its last chunk
+constexpr size_t kOffItems = kOffWork + align256(kMaxC * sizeof(WorkRef));
+constexpr size_t kOffPartials = kOffItems + align256(kMaxT * kMostShortItems * sizeof(WorkRef));
+static_assert(default_items(default_unroll(ADAGC_OPT_ADAMW)) / 2 <= kMostShortItems, "see above");
 constexpr size_t kOffSumsq = kOffPartials + align256(kMaxC * sizeof(double));
 constexpr size_t kOffCoef64 = kOffSumsq + align256(kMaxT * sizeof(double));
 constexpr size_t kOffGlobal = kOffCoef64 + align256(kMaxT * sizeof(double));
@@ -56,31 +59,55 @@ hipError_t scratch_address(int device, unsigned char** out)
     return hipSuccess;
 }
 
-// Tensor records travel as kernel arguments, a batch per launch (the argument block is limited to 4 KiB).
-constexpr int kBatch = 56;
-struct TensorBatch {
-    TensorArgs t[kBatch];
-    uint32_t   long_at[kBatch];    // where the tensor's long chunks go in the work table, and its last one if that is no long one
-    uint32_t   last_at[kBatch];
-    uint32_t   first;    // list index of t[0]
-    uint32_t   count;
+// Tensor records travel as kernel arguments, a batch per launch: as many as the argument block, 4 KiB, holds.
+struct TensorInBatch {
+    void*       param;
+    const void* grad;
+    void*       exp_avg;
+    void*       exp_avg_sq;
+    void*       param_copy;
+    uint64_t    numel;         // and from kVecOkBit and kLineOffsetBit on those two
+    uint32_t    chunk_begin;
+    uint32_t    long_at;       // where the tensor's long chunks go in the work table, its last chunk if that is no long one, and
+    uint32_t    last_at;       // that one's work items if it is a short one
+    uint32_t    item_at;
 };
-static_assert(sizeof(TensorBatch) + 3 * sizeof(void*) <= 4096, "a batch fits the kernel-argument block");
+constexpr int kBatch = 63, kVecOkBit = 48, kLineOffsetBit = 49;
+static_assert(kMaxC * kChunkElems < (size_t)1 << kVecOkBit, "the largest tensor's size leaves the upper bits alone");
+struct TensorBatch {
+    TensorInBatch t[kBatch];
+    uint32_t      first;       // list index of t[0]
+    uint32_t      count;
+};
+static_assert(sizeof(TensorInBatch) == 64 && sizeof(TensorBatch) + 3 * sizeof(void*) + 3 * sizeof(int) <= 4096, "a batch fits the kernel-argument block");
 
 // Workgroup b stores the record of tensor first+b and writes that tensor's rows of the work table.
 __global__ __launch_bounds__(kBlock) void store_tensor_batch_kernel(TensorBatch batch, TensorArgs* targs, WorkRef* work,
-                                                                    int items_per_chunk, int unroll)
+                                                                    WorkRef* items, int items_per_chunk, int unroll, int short_items)
 {
     const uint32_t b = blockIdx.x;
     if (b >= batch.count) return;
-    const TensorArgs a = batch.t[b];
+    const TensorInBatch& t = batch.t[b];
     const uint32_t i = batch.first + b;
+    TensorArgs a;
+    a.param = t.param;
+    a.grad = t.grad;
+    a.exp_avg = t.exp_avg;
+    a.exp_avg_sq = t.exp_avg_sq;
+    a.param_copy = t.param_copy;
+    a.numel = (int64_t)(t.numel & (((uint64_t)1 << kVecOkBit) - 1));
+    a.chunk_begin = t.chunk_begin;
+    a.chunk_count = (uint32_t)((a.numel + kChunkElems - 1) / kChunkElems);
+    a.vec_ok = (uint32_t)(t.numel >> kVecOkBit) & 1u;
+    a.line_offset = (uint32_t)(t.numel >> kLineOffsetBit);
     if (threadIdx.x == 0) targs[i] = a;
     const uint32_t last = a.chunk_count - 1;
     const int64_t last_len = a.numel - (int64_t)last * kChunkElems;
-    const bool last_is_long = chunk_kind(last_len, items_per_chunk, unroll) == kLongChunk;
+    const ChunkKind last_kind = chunk_kind(last_len, items_per_chunk, unroll, short_items);
+    if (last_kind == kShortChunk && (int)threadIdx.x < chunk_items(last_len, items_per_chunk))
+        items[t.item_at + threadIdx.x] = WorkRef{i, a.chunk_begin + last, last, (uint32_t)last_len | threadIdx.x << kPartShift};
     for (uint32_t k = threadIdx.x; k < a.chunk_count; k += kBlock) {
-        const uint32_t at = k < last || last_is_long ? batch.long_at[b] + k : batch.last_at[b];
+        const uint32_t at = k < last || last_kind == kLongChunk ? t.long_at + k : t.last_at;
         work[at] = WorkRef{i, a.chunk_begin + k, k, k < last ? (uint32_t)kChunkElems : (uint32_t)last_len};
     }
 }
@@ -115,13 +142,11 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
     if (!hyper_ok(*hp, cfg->optimizer) || hp->clip_mode > ADAGC_MODE_ZCLIP) return ADAGC_ERR_INVALID_ARG;
     if (n_tensors > (int64_t)kMaxT) return ADAGC_ERR_TOO_LARGE;
 
-    // Everything is validated before anything is enqueued: one pass over the list.
+    // Everything is validated before anything is enqueued.
     const int unroll = default_unroll(cfg->optimizer), items_per_chunk = default_items(unroll);
-    uint64_t n_chunks = 0, n_long = 0, n_tiny = 0;
+    uint64_t n_chunks = 0, n_long = 0, n_short = 0, n_tiny = 0;          // n_short: work items
     bool small_tensors = true;
     int64_t total_elems = 0;
-    // the kind of tensor i's last chunk (all others are long)
-    auto last_kind = [&](int64_t i) { return chunk_kind((descs[i].numel - 1) % kChunkElems + 1, items_per_chunk, unroll); };
     for (int64_t i = 0; i < n_tensors; ++i) {
         if (descs[i].numel <= 0 || descs[i].flags != 0 || descs[i].reserved != 0) return ADAGC_ERR_INVALID_ARG;
         if (!params[i] || !grads[i] || !exp_avg[i] || (adamw && !exp_avg_sq[i]) || (copy && !params_bf16[i]))
@@ -130,8 +155,16 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
         if (n_chunks > (uint64_t)kMaxC) return ADAGC_ERR_TOO_LARGE;
         if (descs[i].numel > kFusedMaxChunks * kChunkElems) small_tensors = false;
         total_elems += descs[i].numel;
-        n_long += (uint64_t)((descs[i].numel - 1) / kChunkElems) + (last_kind(i) == kLongChunk ? 1 : 0);
-        n_tiny += last_kind(i) == kTinyChunk ? 1 : 0;
+    }
+    const int short_items = most_short_items(n_tensors, total_elems, items_per_chunk);
+    // the kind of tensor i's last chunk (all others are long)
+    auto last_len = [&](int64_t i) { return (descs[i].numel - 1) % kChunkElems + 1; };
+    auto last_kind = [&](int64_t i) { return chunk_kind(last_len(i), items_per_chunk, unroll, short_items); };
+    for (int64_t i = 0; i < n_tensors; ++i) {
+        const ChunkKind kind = last_kind(i);
+        n_long += (uint64_t)((descs[i].numel - 1) / kChunkElems) + (kind == kLongChunk ? 1 : 0);
+        n_short += kind == kShortChunk ? (uint64_t)chunk_items(last_len(i), items_per_chunk) : 0;
+        n_tiny += kind == kTinyChunk ? 1 : 0;
     }
 
     int device = -1;
@@ -144,7 +177,9 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
     DeviceTables t{};
     TensorArgs* d_targs = reinterpret_cast<TensorArgs*>(base + kOffTargs);
     WorkRef* d_work = reinterpret_cast<WorkRef*>(base + kOffWork);
+    WorkRef* d_items = reinterpret_cast<WorkRef*>(base + kOffItems);
     t.work = d_work;
+    t.items = d_items;
     t.targs = d_targs;
     t.partials = reinterpret_cast<double*>(base + kOffPartials);
     t.sumsq = reinterpret_cast<double*>(base + kOffSumsq);
@@ -160,10 +195,11 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
     t.scalars = nullptr;
     t.n_chunks = (uint32_t)n_chunks;
     t.n_long = (uint32_t)n_long;
+    t.n_short = (uint32_t)n_short;
     t.n_tiny = (uint32_t)n_tiny;
     t.n_tensors = (uint32_t)n_tensors;
 
-    const int64_t items = count_work_items((int64_t)n_chunks, (int64_t)n_long, (int64_t)n_tiny, items_per_chunk);
+    const int64_t items = count_work_items((int64_t)n_long, (int64_t)n_short, (int64_t)n_tiny, items_per_chunk);
     const int64_t max_grid = (int64_t)(0xFFFFFFFFu / (uint32_t)kBlock);
     const int64_t groups = (int64_t)(n_chunks - n_tiny + (n_tiny + 3) / 4);
     const int grid_norm = (int)(groups > max_grid ? max_grid : groups);
@@ -177,40 +213,38 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
     // Tensor records and chunk table, a batch of tensors per launch.
     const uintptr_t grad_align = bf16g ? 2 : 4;
     int64_t off_lines = 0;
-    uint32_t chunk_begin = 0, long_at = 0, short_at = (uint32_t)n_long, tiny_at = (uint32_t)(n_chunks - n_tiny);
+    uint32_t chunk_begin = 0, long_at = 0, short_at = (uint32_t)n_long, item_at = 0, tiny_at = (uint32_t)(n_chunks - n_tiny);
     TensorBatch batch;
     for (int64_t first = 0; first < n_tensors; first += kBatch) {
         const int64_t count = (n_tensors - first) < kBatch ? (n_tensors - first) : kBatch;
         for (int64_t b = 0; b < count; ++b) {
             const int64_t i = first + b;
-            TensorArgs& a = batch.t[b];
+            TensorArgs a{};
             a.param = params[i];
             a.grad = grads[i];
             a.exp_avg = exp_avg[i];
             a.exp_avg_sq = adamw ? exp_avg_sq[i] : nullptr;
             a.param_copy = copy ? params_bf16[i] : nullptr;
-            a.numel = descs[i].numel;
-            a.chunk_begin = chunk_begin;
-            a.chunk_count = (uint32_t)((descs[i].numel + kChunkElems - 1) / kChunkElems);
             a.vec_ok = (aligned(a.param, 4) && aligned(a.exp_avg, 4) && aligned(a.grad, grad_align) &&
                         (!adamw || aligned(a.exp_avg_sq, 4)) && (!copy || aligned(a.param_copy, 2)))
                            ? 1u : 0u;
             a.line_offset = may_walk ? line_offset_of(a) : 0u;
-            if (a.line_offset) off_lines += a.numel;
-            chunk_begin += a.chunk_count;
+            if (a.line_offset) off_lines += descs[i].numel;
             const ChunkKind kind = last_kind(i);
-            batch.long_at[b] = long_at;
-            long_at += kind == kLongChunk ? a.chunk_count : a.chunk_count - 1;
-            batch.last_at[b] = kind == kShortChunk ? short_at++ : (kind == kTinyChunk ? tiny_at++ : 0u);
+            const uint32_t chunks = (uint32_t)((descs[i].numel + kChunkElems - 1) / kChunkElems);
+            batch.t[b] = TensorInBatch{a.param, a.grad, a.exp_avg, a.exp_avg_sq, a.param_copy,
+                                       (uint64_t)descs[i].numel | (uint64_t)a.vec_ok << kVecOkBit | (uint64_t)a.line_offset << kLineOffsetBit,
+                                       chunk_begin, long_at,
+                                       kind == kShortChunk ? short_at++ : (kind == kTinyChunk ? tiny_at++ : 0u), item_at};
+            chunk_begin += chunks;
+            long_at += kind == kLongChunk ? chunks : chunks - 1;
+            if (kind == kShortChunk) item_at += (uint32_t)chunk_items(last_len(i), items_per_chunk);
         }
-        for (int64_t b = count; b < kBatch; ++b) {
-            batch.t[b] = TensorArgs{};
-            batch.long_at[b] = batch.last_at[b] = 0;
-        }
+        for (int64_t b = count; b < kBatch; ++b) batch.t[b] = TensorInBatch{};
         batch.first = (uint32_t)first;
         batch.count = (uint32_t)count;
-        store_tensor_batch_kernel<<<dim3((uint32_t)count), dim3(kBlock), 0, stream>>>(batch, d_targs, d_work, items_per_chunk,
-                                                                                      unroll);
+        store_tensor_batch_kernel<<<dim3((uint32_t)count), dim3(kBlock), 0, stream>>>(batch, d_targs, d_work, d_items,
+                                                                                      items_per_chunk, unroll, short_items);
         if (hipGetLastError() != hipSuccess) return ADAGC_ERR_HIP;
     }
 
@@ -219,7 +253,7 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
     host_step_scalars(*hp, step, r, u);
     t.off_lines = walks(off_lines);
     FusedRule rule{};
-    if (small_tensors && items <= kFusedMaxItems && !r.warmup && r.mode == ADAGC_MODE_ADAGC) rule = FusedRule{ema_norms, r};
+    if (small_tensors && items <= fused_max_items(cfg->optimizer) && !r.warmup && r.mode == ADAGC_MODE_ADAGC) rule = FusedRule{ema_norms, r};
     if (launch_sumsq_partials(t, bf16g, stream_gradients(total_elems, bf16g), grid_norm, stream, nullptr, 0, rule.ema) != hipSuccess)
         return ADAGC_ERR_HIP;
     if (!rule.ema && launch_rules(t, ema_norms, r, stream) != hipSuccess) return ADAGC_ERR_HIP;

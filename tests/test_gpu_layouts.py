@@ -240,6 +240,47 @@ def test_rule_in_the_update_equals_the_rules_kernel(optimizer, numels):
             assert ((x - y).abs() <= 2e-7 * y.abs()).all()
 
 
+# chunks of every number of work items, one element below, at and above it
+ITEMS = [k * 2048 + d for k in range(1, 9) for d in (-1, 0, 1)]
+MI = 1 << 20
+ITEM_LISTS = {"a small list": ITEMS,                                      # short chunks: up to half of a chunk's items
+              "a large list": ITEMS + [33 * MI],                          # one item
+              "a large list of small tensors": ITEMS + [5600] * 6100,     # half again
+              "the rule in the update kernel, AdamW": [64 * 16384] * 32, "one more": [64 * 16384] * 32 + [1],
+              "the rule in the update kernel, Lion": [64 * 16384] * 16, "Lion, one more": [1] + [64 * 16384] * 16}
+
+
+@pytest.mark.parametrize("optimizer", [B.ADAGC_OPT_ADAMW, B.ADAGC_OPT_LION])
+@pytest.mark.parametrize("name", ITEM_LISTS)
+def test_work_items_of_every_chunk(name, optimizer):
+    """Which chunks are cut into items of a table, which are numbered with empty ones, and whether the rule is in the update kernel depends
+    on the list; the results do not: the library's own choice, whole chunks, and the entry point that builds its tables on the GPU."""
+    numels, results = ITEM_LISTS[name], []
+    gen = torch.Generator(device=DEV).manual_seed(11)
+    total = sum(numels)
+    host = {"p": 0.02, "g": 0.01, "m": 0.002, "v": 1e-4}
+    host = {k: torch.randn(total, generator=gen, device=DEV).mul_(x) for k, x in host.items()}
+    host["v"].square_()
+    hp = B.make_hyper(lr=1e-3, t_start=0)
+    for kw in ({}, dict(update_split=1, unroll=4), None):
+        lists = {k: [y.clone() for y in x.split(numels)] for k, x in host.items()}
+        gamma = torch.tensor([(0.012, 0.009)[i % 2] * n ** 0.5 for i, n in enumerate(numels)], dtype=torch.float32, device=DEV)
+        v = lists["v"] if optimizer == B.ADAGC_OPT_ADAMW else None
+        norms, coefs = torch.zeros(len(numels), device=DEV), torch.zeros(len(numels), device=DEV)
+        if kw is None:
+            B.adagc_step_static(numels, lists["p"], lists["g"], lists["m"], v, gamma, hp, 7, optimizer=optimizer, out_norms=norms, out_coefs=coefs)
+        else:
+            ctx = B.AdaGC(numels, optimizer, **kw)
+            ctx.step(lists["p"], lists["g"], lists["m"], v, gamma, hp, 7)
+            norms, coefs = (torch.from_numpy(x).to(DEV) for x in ctx.get_norms()[:2])
+            ctx.close()
+        results.append([torch.cat(lists[k]) for k in ("p", "m", "v")] + [gamma, norms, coefs])
+    assert (results[0][0] != host["p"]).float().mean() > 0.999 and (results[0][5] < 1).any() and (results[0][5] == 1).any()
+    for other in results[1:]:
+        for k, (x, y) in enumerate(zip(results[0], other)):
+            assert torch.equal(x, y), "array %d" % k
+
+
 # sizes around the ends of vectors, lines, tiles (512, 1024, 2048, 4096 elements) and chunks (16384); the last brings the list above
 # what walk_lines.h asks for (8 Mi elements for Lion, and the mean of 16384)
 LINES = [1, 2, 3, 4, 5, 31, 32, 33, 34, 63, 511, 513, 1023, 1024, 1025, 1056, 2047, 2049, 4064, 4095, 4096, 4097, 4128, 8190, 16353, 16383,
