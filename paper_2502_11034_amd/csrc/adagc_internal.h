@@ -195,6 +195,34 @@ struct FusedRule {
     RuleArgs r;
 };
 
+// The smallest lists have a single launch: the workgroups of the update kernel sum the chunks for themselves and tell each other
+// (Exchange).  Every workgroup of a chunk reads all of its gradient, eight times what the norm kernel reads, and waits for the others of
+// its tensor, so this is for launches that the chip holds at once and that the host issues one by one: it is the second launch's issue
+// that is saved, the GPU is as long at it as at two kernels or a little longer.  While a stream is captured there are two.
+// us per step issued / with the GPU waited for, two launches / one: AdamW fp32, 0.14 M parameters (70 work items) 11.4 / 8.3 and
+// 22.8 / 23.0, 0.3 M 11.3 / 8.3 and 23.5 / 23.0, 27 tensors of 0.53 M (261) 11.4 / 8.2, 0.5 M (255) 11.1 / 9.5 and 24.2 / 24.6; with bf16
+// gradients and the copy 11.3 / 9.2, 11.7 / 8.7, 11.5 / 10.7 (0.5 M); beyond: 360 items 11.2 / 11.0 and 11.5 / 11.4, and where the chip does not
+// hold the launch, waits that nobody ends: 575 items 11.5 / 57.
+constexpr int64_t kOneLaunchItems = 288;
+// A stream that is being captured (or cannot be asked): its launches are issued only once.
+inline bool issues_now(hipStream_t stream)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(stream, &status) == hipSuccess && status == hipStreamCaptureStatusNone;
+}
+
+// What the workgroups of a launch tell each other: a chunk's sum of squares and a tensor's gamma, in 64-bit words of which the lower
+// half is a half of the value and the upper half the launch's number, so that a word is complete by itself and one of an earlier launch is
+// not taken for this one's.  Words are stored and loaded with agent-scope accesses (the L2s of the XCDs are not coherent).  Nobody
+// waits for long: after `polls` looks a wave computes what it is missing, to the same bits, so that workgroups which are
+// not running yet, because other work fills the chip, hold up nothing.
+struct Exchange {
+    uint64_t* words;         // two for each chunk, then one for each tensor; null: there is a norm kernel
+    uint32_t* launches;      // one for each wave, which counts its launches for itself; null: the words are clear, the number is 1
+    uint32_t  polls;
+};
+constexpr uint32_t kPolls = 200;           // a look takes about 1 us
+
 // What every step entry point accepts as hyper-parameters.
 inline bool hyper_ok(const adagc_hyper& h, int optimizer)
 {
@@ -248,7 +276,7 @@ hipError_t launch_rules(const DeviceTables& t, float* ema, const RuleArgs& r, hi
                         const adagc_step_params* params = nullptr, int optimizer = 0);
 hipError_t launch_update(const DeviceTables& t, const UpdateArgs& u, int optimizer, int grad_bf16,
                          int with_copy, int unroll, int items_per_chunk, int nt, int tele, int grid,
-                         hipStream_t stream, bool device_scalars = false, const FusedRule& rule = FusedRule{});
+                         hipStream_t stream, bool device_scalars = false, const FusedRule& rule = FusedRule{}, const Exchange& exchange = Exchange{});
 // Update-clipping modes (AGC, Clippy): norms of theta and of the direction per work item, then one workgroup
 // per tensor turns them into the tensor's update coefficient.
 hipError_t launch_update_clip_rule(const DeviceTables& t, const UpdateArgs& u, const RuleArgs& r, int optimizer,

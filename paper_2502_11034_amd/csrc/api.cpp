@@ -27,6 +27,7 @@ struct adagc_ctx {
     int          items_per_chunk = 1;   // work items of the update kernel per chunk
     bool         stream_grads = false;  // the norm kernel reads past the memory-side cache
     bool         small_list = false;    // the per-tensor rule goes into the update kernel (FusedRule)
+    Exchange     exchange{};            // and the norms too, in a single launch
 
     std::vector<int64_t>    numel;
     std::vector<int64_t>    chunk_begin;      // n_tensors + 1
@@ -233,6 +234,10 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     }
     c->stream_grads = c->nontemporal && stream_gradients(c->total_elems, cfg->grad_dtype == ADAGC_GRAD_BF16);
     c->small_list = tiles <= fused_max_items(cfg->optimizer) && most_chunks <= kFusedMaxChunks;
+    // (with the library's own choice of work items, a workgroup for each)
+    const bool one_launch = c->small_list && tiles <= kOneLaunchItems && cfg->grid_blocks == 0 && cfg->optimizer != ADAGC_OPT_MUON &&
+                            c->unroll == default_unroll(cfg->optimizer) && c->items_per_chunk == default_items(c->unroll) && c->nontemporal &&
+                            !cfg->telemetry;
     c->grid_norm = grid_for(c->n_chunks - n_tiny + (n_tiny + 3) / 4);
     c->n_items = tiles;
     c->grid_update = grid_for(tiles);
@@ -265,6 +270,8 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     const size_t o_tele_partials = carve(cfg->telemetry ? 3 * nc * tiles_per_chunk * sizeof(double) : 0);
     const size_t o_ustat = carve(cfg->update_clipping ? 2 * nc * tiles_per_chunk * sizeof(double) : 0);
     const size_t o_ucoef64 = carve(cfg->update_clipping ? nt * sizeof(double) : 0);
+    const size_t o_words = carve(one_launch ? (2 * nc + nt) * sizeof(uint64_t) : 0);
+    const size_t o_launches = carve(one_launch ? (size_t)tiles * kWavesPerBlock * sizeof(uint32_t) : 0);
     const size_t slab_bytes = off;
 
     hipError_t e = hipMalloc(&c->slab, slab_bytes);
@@ -339,6 +346,7 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     t.tele_norm = cfg->telemetry ? reinterpret_cast<float*>(base + o_tele_norm) : nullptr;
     t.ustat_partials = cfg->update_clipping ? reinterpret_cast<double*>(base + o_ustat) : nullptr;
     t.ucoef64 = cfg->update_clipping ? reinterpret_cast<double*>(base + o_ucoef64) : nullptr;
+    if (one_launch) c->exchange = {reinterpret_cast<uint64_t*>(base + o_words), reinterpret_cast<uint32_t*>(base + o_launches), kPolls};
     t.n_chunks = (uint32_t)c->n_chunks;
     t.n_long = (uint32_t)n_long;
     t.n_short = (uint32_t)n_short;
@@ -347,6 +355,15 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
 
     *out = c;
     return ADAGC_OK;
+}
+
+// For tests (not in the header): how often a wave of a single-launch step looks for what others tell before it computes that itself.
+// False: the context's steps are not of that kind.
+extern "C" int adagc_internal_set_polls(adagc_ctx* ctx, uint32_t polls)
+{
+    if (!ctx || !ctx->exchange.words) return 0;
+    ctx->exchange.polls = polls;
+    return 1;
 }
 
 extern "C" void adagc_destroy(adagc_ctx* ctx)
@@ -458,6 +475,7 @@ extern "C" int adagc_step(adagc_ctx* ctx, void* const* params, const void* const
     UpdateArgs u;
     host_step_scalars(*hp, step, r, u);
     FusedRule  rule{};
+    Exchange   exchange{};
     ctx->device_scalars_used = false;
     const bool prof = ctx->prof_steps < ctx->prof_capacity;
     hipEvent_t* ev = prof ? &ctx->prof_events[(size_t)ctx->prof_steps * 4] : nullptr;
@@ -473,14 +491,16 @@ extern "C" int adagc_step(adagc_ctx* ctx, void* const* params, const void* const
             return ADAGC_ERR_HIP;
     } else {
         if (ctx->small_list && !r.warmup && r.mode == ADAGC_MODE_ADAGC) rule = FusedRule{ema_norms, r};
-        if (launch_sumsq_partials(ctx->tables, bf16g, ctx->stream_grads, ctx->grid_norm, stream, nullptr, 0, rule.ema) != hipSuccess)
+        if (rule.ema && ctx->exchange.words && !prof && issues_now(stream)) exchange = ctx->exchange;      // (profiled steps keep a norm kernel to time)
+        if (!exchange.words &&
+            launch_sumsq_partials(ctx->tables, bf16g, ctx->stream_grads, ctx->grid_norm, stream, nullptr, 0, rule.ema) != hipSuccess)
             return ADAGC_ERR_HIP;
         if (prof && hipEventRecord(ev[1], stream) != hipSuccess) return ADAGC_ERR_HIP;
         if (!rule.ema && launch_rules(ctx->tables, ema_norms, r, stream) != hipSuccess) return ADAGC_ERR_HIP;
         if (prof && hipEventRecord(ev[2], stream) != hipSuccess) return ADAGC_ERR_HIP;
     }
     if (launch_update(ctx->tables, u, ctx->cfg.optimizer, bf16g, copy, ctx->unroll, ctx->items_per_chunk,
-                      ctx->nontemporal, ctx->cfg.telemetry, ctx->grid_update, stream, false, rule) != hipSuccess)
+                      ctx->nontemporal, ctx->cfg.telemetry, ctx->grid_update, stream, false, rule, exchange) != hipSuccess)
         return ADAGC_ERR_HIP;
     if (prof) {
         if (hipEventRecord(ev[3], stream) != hipSuccess) return ADAGC_ERR_HIP;

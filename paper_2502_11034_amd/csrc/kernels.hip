@@ -137,15 +137,12 @@ __device__ __forceinline__ void acc4(double (&acc)[4], f32x4 g)
     acc[3] = fma(w, w, acc[3]);
 }
 
-// A chunk of at most kTinyMax elements, by one wave.
+// Sum of squares of a chunk of at most kTinyMax elements, by one wave (all its lanes get it).
 template <bool BF16>
-__device__ __forceinline__ void tiny_chunk_sumsq(const DeviceTables& t, const WorkRef& w, int lane)
+__device__ __forceinline__ double tiny_chunk_sumsq(const gcbytes g, int len, bool vec_ok, int lane)
 {
-    const TensorArgs ta = load_tensor(t.targs, w.tensor);
-    const int len = (int)w.len;
-    const gcbytes g = grad_at<BF16>(ta.grad, first_element(w));
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    if (ta.vec_ok) {
+    if (vec_ok) {
         constexpr int kRound = kTinyMax / 256;
         const int nvec = len >> 2;
         const int j = (nvec << 2) + lane;
@@ -166,8 +163,47 @@ __device__ __forceinline__ void tiny_chunk_sumsq(const DeviceTables& t, const Wo
             acc[0] = fma(x, x, acc[0]);
         }
     }
-    const double s = wave_sum_f64((acc[0] + acc[1]) + (acc[2] + acc[3]));
-    if (lane == 0) t.partials[w.slot] = s;
+    return wave_sum_f64((acc[0] + acc[1]) + (acc[2] + acc[3]));
+}
+
+// Lane `tid` of a workgroup's share of the sum of squares of any other chunk.
+template <bool BF16, bool NTL>
+__device__ __forceinline__ double chunk_sumsq_share(const gcbytes g, int len, bool vec_ok, int tid)
+{
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    if (vec_ok) {
+        if (len == kChunkElems) {
+            f32x4 r[kVecPerLane];
+#pragma unroll
+            for (int u = 0; u < kVecPerLane; ++u) r[u] = load_grad4<BF16, NTL>(g, u * kBlock + tid);
+#pragma unroll
+            for (int u = 0; u < kVecPerLane; ++u) acc4(acc, r[u]);
+        } else {
+            // four loads at a time; a vector past the end counts as zeros, which add nothing to a sum of squares
+            constexpr int kFlight = kVecPerLane < 4 ? kVecPerLane : 4;
+            const int nvec = len >> 2;
+            const int j = (nvec << 2) + tid;
+            const float last = j < len ? load_grad1<BF16>(g, j) : 0.f;
+            for (int v0 = 0; v0 < nvec; v0 += kFlight * kBlock) {
+                f32x4 r[kFlight];
+#pragma unroll
+                for (int u = 0; u < kFlight; ++u) {
+                    const int v = v0 + u * kBlock + tid;
+                    r[u] = v < nvec ? load_grad4<BF16, NTL>(g, v) : f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+#pragma unroll
+                for (int u = 0; u < kFlight; ++u) acc4(acc, r[u]);
+            }
+            const double x = (double)last;
+            acc[0] = fma(x, x, acc[0]);
+        }
+    } else {
+        for (int j = tid; j < len; j += kBlock) {
+            double x = (double)load_grad1<BF16>(g, j);
+            acc[0] = fma(x, x, acc[0]);
+        }
+    }
+    return (acc[0] + acc[1]) + (acc[2] + acc[3]);
 }
 
 // NTL: streaming loads, for lists whose gradients are many times the 256 MB of the memory-side cache (stream_gradients).  On
@@ -198,7 +234,9 @@ __global__ __launch_bounds__(kBlock) void sumsq_partials_kernel(DeviceTables t, 
             if (at < t.n_chunks) {
                 const WorkRef w = load_work(t.work, at);
                 if (ema_to_keep && w.index == 0 && (tid & 63) == 0) t.ema_before[w.tensor] = ema_to_keep[w.tensor];
-                tiny_chunk_sumsq<BF16>(t, w, tid & 63);
+                const TensorArgs ta = load_tensor(t.targs, w.tensor);
+                const double s = tiny_chunk_sumsq<BF16>(grad_at<BF16>(ta.grad, first_element(w)), (int)w.len, ta.vec_ok != 0, tid & 63);
+                if ((tid & 63) == 0) t.partials[w.slot] = s;
             }
             continue;
         }
@@ -207,42 +245,7 @@ __global__ __launch_bounds__(kBlock) void sumsq_partials_kernel(DeviceTables t, 
         const TensorArgs ta = load_tensor(t.targs, w.tensor);
         const int len = (int)w.len;
         const gcbytes g = grad_at<BF16>(ta.grad, first_element(w));
-        double acc[4] = {0.0, 0.0, 0.0, 0.0};
-
-        if (ta.vec_ok) {
-            if (len == kChunkElems) {
-                f32x4 r[kVecPerLane];
-#pragma unroll
-                for (int u = 0; u < kVecPerLane; ++u) r[u] = load_grad4<BF16, NTL>(g, u * kBlock + tid);
-#pragma unroll
-                for (int u = 0; u < kVecPerLane; ++u) acc4(acc, r[u]);
-            } else {
-                // four loads at a time; a vector past the end counts as zeros, which add nothing to a sum of squares
-                constexpr int kFlight = kVecPerLane < 4 ? kVecPerLane : 4;
-                const int nvec = len >> 2;
-                const int j = (nvec << 2) + tid;
-                const float last = j < len ? load_grad1<BF16>(g, j) : 0.f;
-                for (int v0 = 0; v0 < nvec; v0 += kFlight * kBlock) {
-                    f32x4 r[kFlight];
-#pragma unroll
-                    for (int u = 0; u < kFlight; ++u) {
-                        const int v = v0 + u * kBlock + tid;
-                        r[u] = v < nvec ? load_grad4<BF16, NTL>(g, v) : f32x4{0.f, 0.f, 0.f, 0.f};
-                    }
-#pragma unroll
-                    for (int u = 0; u < kFlight; ++u) acc4(acc, r[u]);
-                }
-                const double x = (double)last;
-                acc[0] = fma(x, x, acc[0]);
-            }
-        } else {
-            for (int j = tid; j < len; j += kBlock) {
-                double x = (double)load_grad1<BF16>(g, j);
-                acc[0] = fma(x, x, acc[0]);
-            }
-        }
-
-        double s = wave_sum_f64((acc[0] + acc[1]) + (acc[2] + acc[3]));
+        double s = wave_sum_f64(chunk_sumsq_share<BF16, NTL>(g, len, ta.vec_ok != 0, tid));
         if ((tid & 63) == 0) wave_sums[tid >> 6] = s;
         __syncthreads();
         if (tid == 0) {
@@ -658,6 +661,84 @@ __device__ __forceinline__ double rule_in_update(const DeviceTables& t, const Fu
     return o.h;
 }
 
+// A chunk's sum of squares by a single wave, in the norm kernel's order: four lanes' shares one after another.
+template <bool BF16, int UNROLL>
+__device__ __forceinline__ double chunk_sumsq_by_wave(const TensorArgs& ta, uint32_t index, int lane)
+{
+    const int64_t first = (int64_t)index * kChunkElems, rest = ta.numel - first;
+    const int len = rest < kChunkElems ? (int)rest : kChunkElems;
+    const gcbytes g = grad_at<BF16>(ta.grad, first);
+    if (chunk_kind(len, default_items(UNROLL), UNROLL, 1) == kTinyChunk) return tiny_chunk_sumsq<BF16>(g, len, ta.vec_ok != 0, lane);
+    double total = wave_sum_f64(chunk_sumsq_share<BF16, false>(g, len, ta.vec_ok != 0, lane));
+#pragma unroll 1
+    for (int w = 1; w < kWavesPerBlock; ++w) total += wave_sum_f64(chunk_sumsq_share<BF16, false>(g, len, ta.vec_ok != 0, w * 64 + lane));
+    return total;
+}
+
+// The rule of a single launch (Exchange), by one wave that has the sum of its chunk: `own`.  publishes: this wave is the one of the
+// chunk's that tells it to the others; the one of the tensor's first chunk tells gamma as well, before it may store the new one (`stores`).
+// At most 64 chunks, a lane for each.
+struct OneLaunchInputs {
+    float    gamma;
+    uint32_t before;         // (lane 0) launches of this wave so far
+};
+__device__ __forceinline__ OneLaunchInputs load_one_launch_inputs(const FusedRule& rule, const Exchange& x, uint32_t tensor, bool alone, uint32_t wave)
+{
+    OneLaunchInputs in{load_shared(rule.ema + tensor), 0u};
+    if (!alone && x.launches && (threadIdx.x & 63u) == 0)
+        in.before = __hip_atomic_fetch_add(x.launches + wave, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return in;
+}
+
+template <bool BF16, int UNROLL>
+__device__ __forceinline__ double rule_in_one_launch(const DeviceTables& t, const FusedRule& rule, const Exchange& x, const WorkRef& c,
+                                                     const TensorArgs& ta, const OneLaunchInputs& in, double own, bool alone, bool publishes)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    float gamma = in.gamma;
+    double mine = lane == c.index ? own : 0.0;
+    if (!alone) {
+        const uint32_t launch = 1u + (uint32_t)__builtin_amdgcn_readfirstlane((int)in.before);
+        asm volatile("" : "+v"(gamma) : : "memory");       // it is here before the first look
+        const uint64_t number = (uint64_t)launch << 32;
+        uint64_t* const sums = x.words + 2 * (size_t)ta.chunk_begin;
+        uint64_t* const gammas = x.words + 2 * (size_t)t.n_chunks;
+        if (publishes && lane == 0) {
+            store_shared(sums + 2 * c.index, number | (uint32_t)__double2loint(own));
+            store_shared(sums + 2 * c.index + 1, number | (uint32_t)__double2hiint(own));
+            if (c.index == 0) store_shared(gammas + c.tensor, number | __float_as_uint(gamma));
+        }
+        bool missing = lane < ta.chunk_count && lane != c.index, gamma_missing = !(publishes && c.index == 0);
+        for (uint32_t look = 0;; ++look) {
+            const uint32_t at = lane < ta.chunk_count ? lane : 0;
+            const uint64_t lo = load_shared(sums + 2 * at), hi = load_shared(sums + 2 * at + 1), g = load_shared(gammas + c.tensor);
+            if (missing && (lo >> 32) == launch && (hi >> 32) == launch) {
+                mine = __hiloint2double((int)(uint32_t)hi, (int)(uint32_t)lo);
+                missing = false;
+            }
+            if (gamma_missing && (g >> 32) == launch) {
+                gamma = __uint_as_float((uint32_t)g);
+                gamma_missing = false;
+            }
+            // (a gamma that has not been told has not been replaced either: what was read above stands)
+            if (!__any(missing || gamma_missing) || look >= x.polls) break;
+        }
+        for (uint64_t left = __ballot(missing); left; left &= left - 1) {
+            const uint32_t k = (uint32_t)__builtin_ctzll(left);
+            const double s = chunk_sumsq_by_wave<BF16, UNROLL>(ta, k, (int)lane);
+            if (lane == k) mine = s;
+        }
+        // what this wave has told is there for all before the new gamma can be
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (0xF << 8));
+        asm volatile("" ::: "memory");
+    }
+    const double s = wave_sum_f64(mine);
+    const TensorRule o = adagc_rule(rule.r, s, (double)gamma);
+    if (publishes && c.index == 0 && lane == 0) store_rule(t, rule.ema, c.tensor, s, o);
+    return o.h;
+}
+
 // All loads of this wave are there before anything else is done.  With seven arrays and a copy to write, stores that start
 // while the item's last loads are still on their way cost a little more in read/write turnaround than they gain.  AdamW with the
 // copy, without / with the wait: GPT-2-small shapes 686 / 679 us per step, 133 M parameters with bf16 gradients 639 / 635 (664 /
@@ -671,7 +752,7 @@ __device__ __forceinline__ void wait_for_loads()
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// Waves per SIMD that the update kernel may have in flight.  With 4 vectors of each array one wave holds 16 loads of 1 KiB, so two
+// Waves per SIMD that the update kernel may have in flight.  (A single launch, of a round of workgroups at most, has the registers of two.)  With 4 vectors of each array one wave holds 16 loads of 1 KiB, so two
 // are enough to cover the latency, and more only open more DRAM rows at once: AdamW on GPT-2-small shapes 657 us per step with 2, 667
 // with 3, 670 with 4 (Llama-3-8B shapes 10.75, 10.90, 10.87 ms for 4 layers).  With 2 vectors AdamW has 4: 5000 small tensors 94 us with 4, 98
 // with 3; GPT-2-small 616 - 630, 622; 133 M parameters with bf16 gradients and copies 630, 640 (ragged tensors end to end 2085, 2035).  Lion
@@ -681,11 +762,12 @@ template <int OPT, int U>
 constexpr int kUpdateWaves = OPT == ADAGC_OPT_ADAMW ? (U == 4 ? 2 : 4) : 3;
 
 // Whether the per-tensor rule is evaluated here: known where the launch is one of the library's own choice, else asked.
-enum RuleHere { kRuleNo, kRuleYes, kRuleAsk };
+// kRuleOne: and the chunks' sums of squares as well (Exchange).
+enum RuleHere { kRuleNo, kRuleYes, kRuleAsk, kRuleOne };
 
 template <int OPT, bool BF16G, bool COPY, int U, bool NT, bool TELE, bool LINES, RuleHere RULE>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kUpdateWaves<OPT, U>, kUpdateWaves<OPT, U>)))
-void update_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items, const StepScalars* device_scalars, FusedRule rule)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RULE == kRuleOne ? 2 : kUpdateWaves<OPT, U>, RULE == kRuleOne ? 2 : kUpdateWaves<OPT, U>)))
+void update_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items, const StepScalars* device_scalars, FusedRule rule, Exchange exchange)
 {
     static_assert(kVecPerLane % U == 0, "a chunk is a whole number of tiles");
     if (device_scalars) {                      // adagc_step_graph: this step's scalars live in device memory
@@ -697,6 +779,7 @@ void update_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items, const Step
     constexpr int kTiles = kVecPerLane / U;
     const int tid = threadIdx.x;
     __shared__ double tele_sums[3][kWavesPerBlock];
+    __shared__ double one_sums[kWavesPerBlock + 1];        // a single launch: the waves' sums, then the coefficient
 
     // Tiles first_tile .. first_tile + n_tiles - 1 of a chunk, by LANES lanes (a workgroup, or a wave of it).
     auto update_tiles = [&](auto LANES, const WorkRef& c, int first_tile, int n_tiles, int lane, double (&tele)[3])
@@ -712,8 +795,32 @@ void update_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items, const Step
         double h = 1.0;
         RuleInputs rule_inputs{0.0, 0.f};
         if (rule_here) rule_inputs = load_rule_inputs(t, tensor, ta);
-        else h = uniform_load(t.coef64 + tensor);
+        else if constexpr (RULE != kRuleOne) h = uniform_load(t.coef64 + tensor);
         auto evaluate_rule = [&]() __attribute__((always_inline)) {
+            if constexpr (RULE == kRuleOne) {
+                const gcbytes chunk = grad_at<BF16G>(ta.grad, first);
+                const bool alone = ta.chunk_count == 1 && len <= kTiles / default_items(U) * U * kBlock * 4;
+                const uint32_t wave = blockIdx.x * kWavesPerBlock + (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
+                OneLaunchInputs in{};
+                if (lane < 64) in = load_one_launch_inputs(rule, exchange, tensor, alone, wave);
+                if constexpr (kLanes == 64) {
+                    const double own = tiny_chunk_sumsq<BF16G>(chunk, len, ta.vec_ok != 0, lane);
+                    h = rule_in_one_launch<BF16G, U>(t, rule, exchange, c, ta, in, own, alone, true);
+                } else {
+                    const double share = wave_sum_f64(chunk_sumsq_share<BF16G, false>(chunk, len, ta.vec_ok != 0, lane));
+                    if ((lane & 63) == 0) one_sums[lane >> 6] = share;
+                    __syncthreads();
+                    if (lane < 64) {
+                        double own = one_sums[0];
+#pragma unroll
+                        for (int w = 1; w < kWavesPerBlock; ++w) own += one_sums[w];
+                        const double coef = rule_in_one_launch<BF16G, U>(t, rule, exchange, c, ta, in, own, alone, first_tile == 0);
+                        if (lane == 0) one_sums[kWavesPerBlock] = coef;
+                    }
+                    __syncthreads();
+                    h = one_sums[kWavesPerBlock];
+                }
+            }
             if (rule_here) h = rule_in_update(t, rule, tensor, rule_inputs, c.index == 0 && first_tile == 0 && lane == 0);
         };
         const double uc = a.update_clip ? uniform_load(t.ucoef64 + tensor) : 1.0;   // update clipping: scales the direction
@@ -1079,7 +1186,7 @@ __global__ __launch_bounds__(kBlock) void finalize_telemetry_kernel(DeviceTables
     if (threadIdx.x == 0) t.tele_norm[(size_t)q * t.n_tensors + i] = (float)sqrt(s);
 }
 
-using UpdateFn = void (*)(DeviceTables, UpdateArgs, uint32_t, const StepScalars*, FusedRule);
+using UpdateFn = void (*)(DeviceTables, UpdateArgs, uint32_t, const StepScalars*, FusedRule, Exchange);
 
 // The launches of the library's own choice (the vectors in flight that are not chosen otherwise, streaming) have kernels with and
 // without the rule, and with whole lines where those ever pay.
@@ -1093,26 +1200,27 @@ UpdateFn select_update_flags(int nt, int tele, bool lines)
 }
 
 template <int OPT, bool BF16G, bool COPY>
-UpdateFn select_update_variant(int unroll, int nt, int tele, bool lines, bool rule)
+UpdateFn select_update_variant(int unroll, int nt, int tele, bool lines, bool rule, bool one)
 {
+    if (one) return update_kernel<OPT, BF16G, COPY, default_unroll(OPT), true, false, false, kRuleOne>;
     static_assert(default_unroll(OPT) == 2, "the kernels below");
     if (unroll == 4) return select_update_flags<OPT, BF16G, COPY, 4, kRuleAsk>(nt, tele, lines);
     if (unroll == 1) return select_update_flags<OPT, BF16G, COPY, 1, kRuleAsk>(nt, tele, lines);
     return rule ? select_update_flags<OPT, BF16G, COPY, 2, kRuleYes>(nt, tele, lines) : select_update_flags<OPT, BF16G, COPY, 2, kRuleNo>(nt, tele, lines);
 }
 
-UpdateFn select_update(int optimizer, int grad_bf16, int with_copy, int unroll, int nt, int tele, bool lines, bool rule)
+UpdateFn select_update(int optimizer, int grad_bf16, int with_copy, int unroll, int nt, int tele, bool lines, bool rule, bool one)
 {
     const int key = (optimizer == ADAGC_OPT_LION ? 4 : 0) | (grad_bf16 ? 2 : 0) | (with_copy ? 1 : 0);
     switch (key) {
-    case 0: return select_update_variant<ADAGC_OPT_ADAMW, false, false>(unroll, nt, tele, lines, rule);
-    case 1: return select_update_variant<ADAGC_OPT_ADAMW, false, true>(unroll, nt, tele, lines, rule);
-    case 2: return select_update_variant<ADAGC_OPT_ADAMW, true, false>(unroll, nt, tele, lines, rule);
-    case 3: return select_update_variant<ADAGC_OPT_ADAMW, true, true>(unroll, nt, tele, lines, rule);
-    case 4: return select_update_variant<ADAGC_OPT_LION, false, false>(unroll, nt, tele, lines, rule);
-    case 5: return select_update_variant<ADAGC_OPT_LION, false, true>(unroll, nt, tele, lines, rule);
-    case 6: return select_update_variant<ADAGC_OPT_LION, true, false>(unroll, nt, tele, lines, rule);
-    default: return select_update_variant<ADAGC_OPT_LION, true, true>(unroll, nt, tele, lines, rule);
+    case 0: return select_update_variant<ADAGC_OPT_ADAMW, false, false>(unroll, nt, tele, lines, rule, one);
+    case 1: return select_update_variant<ADAGC_OPT_ADAMW, false, true>(unroll, nt, tele, lines, rule, one);
+    case 2: return select_update_variant<ADAGC_OPT_ADAMW, true, false>(unroll, nt, tele, lines, rule, one);
+    case 3: return select_update_variant<ADAGC_OPT_ADAMW, true, true>(unroll, nt, tele, lines, rule, one);
+    case 4: return select_update_variant<ADAGC_OPT_LION, false, false>(unroll, nt, tele, lines, rule, one);
+    case 5: return select_update_variant<ADAGC_OPT_LION, false, true>(unroll, nt, tele, lines, rule, one);
+    case 6: return select_update_variant<ADAGC_OPT_LION, true, false>(unroll, nt, tele, lines, rule, one);
+    default: return select_update_variant<ADAGC_OPT_LION, true, true>(unroll, nt, tele, lines, rule, one);
     }
 }
 
@@ -1179,10 +1287,10 @@ hipError_t launch_update_clip_rule(const DeviceTables& t, const UpdateArgs& u, c
 
 hipError_t launch_update(const DeviceTables& t, const UpdateArgs& a, int optimizer, int grad_bf16,
                          int with_copy, int unroll, int items_per_chunk, int nt, int tele, int grid,
-                         hipStream_t stream, bool device_scalars, const FusedRule& rule)
+                         hipStream_t stream, bool device_scalars, const FusedRule& rule, const Exchange& exchange)
 {
-    select_update(optimizer, grad_bf16, with_copy, unroll, nt, tele, t.off_lines != 0, rule.ema != nullptr)<<<dim3(grid), dim3(kBlock), 0, stream>>>(
-        t, a, log2_of(items_per_chunk), device_scalars ? t.scalars : nullptr, rule);
+    select_update(optimizer, grad_bf16, with_copy, unroll, nt, tele, t.off_lines != 0, rule.ema != nullptr, exchange.words != nullptr)<<<dim3(grid), dim3(kBlock), 0, stream>>>(
+        t, a, log2_of(items_per_chunk), device_scalars ? t.scalars : nullptr, rule, exchange);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !tele) return e;
     finalize_telemetry_kernel<<<dim3(t.n_tensors, 3), dim3(kBlock), 0, stream>>>(t, (uint32_t)items_per_chunk);

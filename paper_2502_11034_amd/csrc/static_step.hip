@@ -33,7 +33,10 @@ constexpr size_t kOffEmaBefore = kOffArrivals + align256(sizeof(uint32_t));
 constexpr size_t kOffNorm = kOffEmaBefore + align256(kMaxT * sizeof(float));
 constexpr size_t kOffCoef = kOffNorm + align256(kMaxT * sizeof(float));
 constexpr size_t kOffFlag = kOffCoef + align256(kMaxT * sizeof(float));
-constexpr size_t kScratchBytes = kOffFlag + align256(kMaxT);
+constexpr size_t kOffWords = kOffFlag + align256(kMaxT);
+// of a single launch (Exchange): two for each chunk and one for each tensor, of both up to four for each work item (tiny chunks)
+constexpr size_t kMaxWords = (2 + 1) * 4 * kOneLaunchItems;
+constexpr size_t kScratchBytes = kOffWords + align256(kMaxWords * sizeof(uint64_t));
 
 // In host code this name is only a handle for hipGetSymbolAddress, never an address to hand to a kernel.
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
@@ -79,11 +82,13 @@ struct TensorBatch {
     uint32_t      first;       // list index of t[0]
     uint32_t      count;
 };
-static_assert(sizeof(TensorInBatch) == 64 && sizeof(TensorBatch) + 3 * sizeof(void*) + 3 * sizeof(int) <= 4096, "a batch fits the kernel-argument block");
+static_assert(sizeof(TensorInBatch) == 64 && sizeof(TensorBatch) + 4 * sizeof(void*) + 4 * sizeof(int) <= 4096, "a batch fits the kernel-argument block");
 
-// Workgroup b stores the record of tensor first+b and writes that tensor's rows of the work table.
+// Workgroup b stores the record of tensor first+b and writes that tensor's rows of the work table.  words: null, or what the
+// workgroups of a single launch tell each other, of a list of n_chunks chunks: cleared.
 __global__ __launch_bounds__(kBlock) void store_tensor_batch_kernel(TensorBatch batch, TensorArgs* targs, WorkRef* work,
-                                                                    WorkRef* items, int items_per_chunk, int unroll, int short_items)
+                                                                    WorkRef* items, int items_per_chunk, int unroll, int short_items,
+                                                                    uint64_t* words, uint32_t n_chunks)
 {
     const uint32_t b = blockIdx.x;
     if (b >= batch.count) return;
@@ -101,6 +106,10 @@ __global__ __launch_bounds__(kBlock) void store_tensor_batch_kernel(TensorBatch 
     a.vec_ok = (uint32_t)(t.numel >> kVecOkBit) & 1u;
     a.line_offset = (uint32_t)(t.numel >> kLineOffsetBit);
     if (threadIdx.x == 0) targs[i] = a;
+    if (words) {
+        if (threadIdx.x == 0) words[2 * (size_t)n_chunks + i] = 0;
+        for (uint32_t k = threadIdx.x; k < 2 * a.chunk_count; k += kBlock) words[2 * (size_t)a.chunk_begin + k] = 0;
+    }
     const uint32_t last = a.chunk_count - 1;
     const int64_t last_len = a.numel - (int64_t)last * kChunkElems;
     const ChunkKind last_kind = chunk_kind(last_len, items_per_chunk, unroll, short_items);
@@ -210,6 +219,14 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
     };
     const bool may_walk = walks(total_elems);        // wherever its tensors start
 
+    RuleArgs r;
+    UpdateArgs u;
+    host_step_scalars(*hp, step, r, u);
+    FusedRule rule{};
+    if (small_tensors && items <= fused_max_items(cfg->optimizer) && !r.warmup && r.mode == ADAGC_MODE_ADAGC) rule = FusedRule{ema_norms, r};
+    const bool one_launch = rule.ema && items <= kOneLaunchItems && 2 * n_chunks + (uint64_t)n_tensors <= kMaxWords && issues_now(stream);
+    uint64_t* const words = one_launch ? reinterpret_cast<uint64_t*>(base + kOffWords) : nullptr;
+
     // Tensor records and chunk table, a batch of tensors per launch.
     const uintptr_t grad_align = bf16g ? 2 : 4;
     int64_t off_lines = 0;
@@ -244,20 +261,17 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
         batch.first = (uint32_t)first;
         batch.count = (uint32_t)count;
         store_tensor_batch_kernel<<<dim3((uint32_t)count), dim3(kBlock), 0, stream>>>(batch, d_targs, d_work, d_items,
-                                                                                      items_per_chunk, unroll, short_items);
+                                                                                      items_per_chunk, unroll, short_items, words, t.n_chunks);
         if (hipGetLastError() != hipSuccess) return ADAGC_ERR_HIP;
     }
 
-    RuleArgs r;
-    UpdateArgs u;
-    host_step_scalars(*hp, step, r, u);
     t.off_lines = walks(off_lines);
-    FusedRule rule{};
-    if (small_tensors && items <= fused_max_items(cfg->optimizer) && !r.warmup && r.mode == ADAGC_MODE_ADAGC) rule = FusedRule{ema_norms, r};
-    if (launch_sumsq_partials(t, bf16g, stream_gradients(total_elems, bf16g), grid_norm, stream, nullptr, 0, rule.ema) != hipSuccess)
+    if (!one_launch &&
+        launch_sumsq_partials(t, bf16g, stream_gradients(total_elems, bf16g), grid_norm, stream, nullptr, 0, rule.ema) != hipSuccess)
         return ADAGC_ERR_HIP;
     if (!rule.ema && launch_rules(t, ema_norms, r, stream) != hipSuccess) return ADAGC_ERR_HIP;
-    if (launch_update(t, u, cfg->optimizer, bf16g, copy, unroll, items_per_chunk, 1, 0, grid_update, stream, false, rule) != hipSuccess)
+    if (launch_update(t, u, cfg->optimizer, bf16g, copy, unroll, items_per_chunk, 1, 0, grid_update, stream, false, rule,
+                      Exchange{words, nullptr, kPolls}) != hipSuccess)
         return ADAGC_ERR_HIP;
     return ADAGC_OK;
 }

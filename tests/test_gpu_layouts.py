@@ -2,6 +2,7 @@
 element, as in flat parameter buffers), must be bit for bit the step on the same tensors in allocations of their own: the kernels
 take both through the same vectors, and neither the address nor the place in the visiting order enters a result.  The step on
 separate allocations is held against the oracle elsewhere."""
+import ctypes
 import functools
 from fractions import Fraction
 
@@ -279,6 +280,114 @@ def test_work_items_of_every_chunk(name, optimizer):
     for other in results[1:]:
         for k, (x, y) in enumerate(zip(results[0], other)):
             assert torch.equal(x, y), "array %d" % k
+
+
+# Up to 288 work items (2048 elements; a long chunk has eight, in groups of eight chunks) without telemetry a step is a single launch, whose
+# workgroups tell each other their sums; one item more, and steps that are profiled, have the norm kernel.
+ONE_LAUNCH = {"every size": [1, 5, 511, 512, 513, 1024, 2047, 2048, 2049, 4096, 16384, 16385, 16384 + 300, 40000, 5],
+              "a chunk to a lane": [32 * 16384 - 5], "a transformer": [131072] + [16384, 65536, 128] * 2 + [300, 40000],
+              "waves": [500] * 600 + [3000] * 60, "at the limit": [2048] * 288, "one more": [2048] * 289}
+
+
+@pytest.mark.parametrize("optimizer,grad_dtype,copy", [(B.ADAGC_OPT_ADAMW, B.ADAGC_GRAD_F32, False), (B.ADAGC_OPT_ADAMW, B.ADAGC_GRAD_BF16, True),
+                                                       (B.ADAGC_OPT_LION, B.ADAGC_GRAD_F32, True), (B.ADAGC_OPT_LION, B.ADAGC_GRAD_BF16, False)])
+@pytest.mark.parametrize("name", ONE_LAUNCH)
+def test_a_single_launch_equals_the_norm_kernel_and_the_update(name, optimizer, grad_dtype, copy):
+    """Three steps each: profiled (two launches), as they are, without any waiting (every wave computes all that it was not told before it
+    looked), a captured step replayed, from odd addresses, and the entry point that builds its tables on the GPU."""
+    numels, results = ONE_LAUNCH[name], []
+    total, lion = sum(numels), optimizer == B.ADAGC_OPT_LION
+    set_polls = B.lib().adagc_internal_set_polls
+    set_polls.argtypes = [ctypes.c_void_p, ctypes.c_uint32]
+    hp = B.make_hyper(lr=1e-3, t_start=0)
+    for kind in ("profiled", "one", "no waiting", "captured", "odd", "static"):
+        gen = torch.Generator(device=DEV).manual_seed(3)
+        flat = {k: torch.randn(total, generator=gen, device=DEV) * x for k, x in (("p", 0.02), ("g", 0.01), ("m", 0.002), ("v", 0.01))}
+        flat["v"].square_()
+        flat["c"] = torch.zeros(total, dtype=torch.bfloat16, device=DEV)
+        if grad_dtype == B.ADAGC_GRAD_BF16:
+            flat["g"] = flat["g"].to(torch.bfloat16)
+        lists = {k: [y.clone() for y in x.split(numels)] for k, x in flat.items()}
+        held = lists["m"]
+        if kind == "odd":                          # the momentum at an odd byte
+            held = [torch.zeros(4 * n + 8, dtype=torch.uint8, device=DEV) for n in numels]
+            for buf, x in zip(held, lists["m"]):
+                buf[3:3 + 4 * x.numel()] = x.view(torch.uint8)
+        m = [buf.data_ptr() + 3 for buf in held] if kind == "odd" else held
+        v = None if lion else lists["v"]
+        gamma = torch.tensor([(0.009, 0.012)[i % 2] * n ** 0.5 for i, n in enumerate(numels)], dtype=torch.float32, device=DEV)
+        norms, coefs, clipped = (torch.zeros(len(numels), dtype=t, device=DEV) for t in (torch.float32, torch.float32, torch.uint8))
+        reports = []
+        ctx = None if kind == "static" else B.AdaGC(numels, optimizer, grad_dtype, copy)
+        if ctx:
+            assert set_polls(ctx._ctx, 0 if kind == "no waiting" else 200) == (name != "one more")
+            if copy:
+                ctx.set_param_copies(lists["c"])
+            if kind == "profiled":
+                ctx.profile_begin(3)
+        for step in range(3):
+            if kind == "static":
+                B.adagc_step_static(numels, lists["p"], lists["g"], m, v, gamma, hp, 7, optimizer=optimizer, grad_dtype=grad_dtype,
+                                    params_bf16=lists["c"] if copy else None, out_norms=norms, out_coefs=coefs, out_clipped=clipped)
+                reports += [norms.cpu(), coefs.cpu(), clipped.cpu()]
+            elif kind == "captured" and step:
+                if step == 1:
+                    graph = torch.cuda.CUDAGraph()
+                    torch.cuda.synchronize()
+                    with torch.cuda.graph(graph):
+                        ctx.step(lists["p"], lists["g"], m, v, gamma, hp, 7, stream=torch.cuda.current_stream().cuda_stream)
+                graph.replay()
+                torch.cuda.synchronize()
+            else:
+                ctx.step(lists["p"], lists["g"], m, v, gamma, hp, 7)
+            if ctx:
+                reports += [torch.from_numpy(x.copy()) for x in ctx.get_norms()]
+            reports.append(gamma.cpu())
+        torch.cuda.synchronize()
+        if ctx:
+            ctx.close()
+        if kind == "odd":
+            assert all((buf[:3] == 0).all() and (buf[3 + 4 * n:] == 0).all() for buf, n in zip(held, numels))
+            held = [buf[3:3 + 4 * n].clone().view(torch.float32) for buf, n in zip(held, numels)]
+        results.append(reports + [torch.cat(lists["p"]), torch.cat(held), torch.cat(lists["v"]), torch.cat(lists["c"])])
+        if kind == "odd":                          # its sums run element by element, in another order: no bits to compare
+            for x, y in zip(results.pop(), results[0]):
+                assert torch.allclose(x.double(), y.double(), rtol=1e-5 if x.dtype != torch.bfloat16 else 2 ** -7, atol=0)
+            continue
+        for k, (x, y) in enumerate(zip(results[-1], results[0])):
+            assert torch.equal(x, y), "%s: array %d" % (kind, k)
+    assert (results[0][1] < 1).any() and (len(numels) == 1 or (results[0][1] == 1).any())
+
+
+def test_single_launches_that_overlap_leave_nothing_behind():
+    """Steps of one context on two streams at once, which is not allowed and leaves any state, hold nobody up and leave nothing that a later
+    step on its own could take for its own sums."""
+    numels = ONE_LAUNCH["a transformer"]
+    gen = torch.Generator(device=DEV).manual_seed(4)
+    hp = B.make_hyper(lr=1e-3, t_start=0)
+    ctx, other = B.AdaGC(numels), B.AdaGC(numels)
+    def state():
+        s = {k: [torch.randn(n, generator=gen, device=DEV) * x for n in numels] for k, x in (("p", 0.02), ("g", 0.01), ("m", 0.002))}
+        s["v"] = [torch.rand(n, generator=gen, device=DEV) * 1e-4 for n in numels]
+        s["gamma"] = torch.tensor([0.009 * n ** 0.5 for n in numels], dtype=torch.float32, device=DEV)
+        return s
+    a = state()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    for k in range(40):
+        ctx.step(a["p"], a["g"], a["m"], a["v"], a["gamma"], hp, 7, stream=streams[k % 2].cuda_stream)
+    torch.cuda.synchronize()
+    b = state()
+    c = {k: [x.clone() for x in y] if k != "gamma" else y.clone() for k, y in b.items()}
+    for step in range(7, 12):
+        ctx.step(b["p"], b["g"], b["m"], b["v"], b["gamma"], hp, step)
+        other.step(c["p"], c["g"], c["m"], c["v"], c["gamma"], hp, step)
+    torch.cuda.synchronize()
+    for k in b:
+        for x, y in zip(b[k], c[k]):
+            assert torch.equal(x, y)
+    ctx.close()
+    other.close()
 
 
 # sizes around the ends of vectors, lines, tiles (512, 1024, 2048, 4096 elements) and chunks (16384); the last brings the list above
