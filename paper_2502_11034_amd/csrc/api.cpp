@@ -773,24 +773,25 @@ extern "C" int adagc_muon_step(adagc_ctx* ctx, void* const* params, const void* 
         MuonGroup groups[kMaxGroups];
         const size_t n = round.groups.size();
         std::copy(round.groups.begin(), round.groups.end(), groups);
+        MuonSpans spans{};
         for (size_t i = 0; i < n; ++i) {
             const MuonGroup& g = groups[i];
-            if (launch_muon_normalise(t, ctx->muon_matrices + ctx->muon_batches[round.batches[i]].first, g.count, g.mp, g.np, mu, mh->nesterov,
-                                      bf16g, g.x, stream) != hipSuccess)
-                return ADAGC_ERR_HIP;
+            add_span(spans, ctx->muon_matrices + ctx->muon_batches[round.batches[i]].first, g.x, g.mp, g.np, g.count,
+                     muon_normalise_blocks(g.mp, g.np));
         }
+        if (launch_muon_normalise(t, spans, mu, mh->nesterov, bf16g, stream) != hipSuccess) return ADAGC_ERR_HIP;
         for (int k = 0; k < mh->ns_steps; ++k) {
             for (int p = 0; p < 3; ++p)
                 for (const MuonLaunch& l : round.launches[p])
                     if (launch_muon_product((MuonProduct)p, l, groups, stream) != hipSuccess) return ADAGC_ERR_HIP;
             for (size_t i = 0; i < n; ++i) std::swap(groups[i].x, groups[i].x2);
         }
+        spans = MuonSpans{};
         for (size_t i = 0; i < n; ++i) {
             const adagc_ctx::MuonBatch& bt = ctx->muon_batches[round.batches[i]];
-            if (launch_muon_apply(t, ctx->muon_matrices + bt.first, groups[i].count, bt.apply_blocks, bt.mp, bt.np, groups[i].x, (double)h.lr,
-                                  (double)h.weight_decay, copy, stream) != hipSuccess)
-                return ADAGC_ERR_HIP;
+            add_span(spans, ctx->muon_matrices + bt.first, groups[i].x, bt.mp, bt.np, groups[i].count, bt.apply_blocks);
         }
+        if (launch_muon_apply(t, spans, (double)h.lr, (double)h.weight_decay, copy, stream) != hipSuccess) return ADAGC_ERR_HIP;
     }
     if (prof) {
         if (hipEventRecord(ev[3], stream) != hipSuccess) return ADAGC_ERR_HIP;
