@@ -182,6 +182,15 @@ inline int64_t count_work_items(int64_t n_long, int64_t n_short, int64_t n_tiny,
 // (figures at the kernel).
 inline bool stream_gradients(int64_t total_elems, bool grad_bf16) { return total_elems > ((int64_t)1 << 33) / (grad_bf16 ? 2 : 4); }
 
+// Large lists are stepped group by group (norms, rules, update of one, then of the next) where the rule is per tensor, so that the update
+// finds gradients of its group in the memory-side cache: runs of whole tensors of up to so many bytes of gradients, or a
+// larger one.
+// us per step, whole / in groups, AdamW fp32: 108 M parameters (433 MB of gradients) 535 / 524 in tensors of 1 M, 522 / 531 in tensors of
+// 30 000; 133 M 664 / 647, 181 M 908 / 866, 296 M 1533 / 1422; with the copy 1.5 G 7962 / 7319; bf16 and the copy 260 M 1240 / 1206, 583 M
+// 2931 / 2669; Lion fp32 108 M 387 / 390, 133 M 483 / 473, 296 M 1075 / 1057, bf16 and the copy 583 M 2005 / 1883.  Groups of 128, 256, 512 and 1024 MiB:
+// 1500 ragged tensors of 1.6 GB of gradients 1965, 1905, 1994, 2007 (whole 2039), Llama shapes 9.93, 9.86, 9.95, 10.08 ms (10.22).
+constexpr int64_t kGroupBytes = (int64_t)256 << 20, kGroupedBytes = (int64_t)450 << 20;
+
 // Small lists evaluate the per-tensor rule (Eq. 3) inside the update kernel, every wave for its own tensor, from the tensor's
 // partial sums and a copy of gamma that the norm kernel makes: one launch less, for one more load per wave.  It needs tensors whose
 // slots one wave can sum in the rules kernel's order (see rule_in_update).  us per step, in the rules kernel / in the update, AdamW fp32:
@@ -274,6 +283,8 @@ hipError_t launch_sumsq_partials(const DeviceTables& t, int grad_bf16, bool stre
                                  const adagc_step_params* params = nullptr, int optimizer = 0, const float* ema_to_keep = nullptr);
 hipError_t launch_rules(const DeviceTables& t, float* ema, const RuleArgs& r, hipStream_t stream,
                         const adagc_step_params* params = nullptr, int optimizer = 0);
+// The per-tensor rule of tensors first .. first + count - 1 only.
+hipError_t launch_tensor_rules(const DeviceTables& t, float* ema, const RuleArgs& r, uint32_t first, uint32_t count, hipStream_t stream);
 hipError_t launch_update(const DeviceTables& t, const UpdateArgs& u, int optimizer, int grad_bf16,
                          int with_copy, int unroll, int items_per_chunk, int nt, int tele, int grid,
                          hipStream_t stream, bool device_scalars = false, const FusedRule& rule = FusedRule{}, const Exchange& exchange = Exchange{});

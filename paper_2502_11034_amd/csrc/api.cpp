@@ -29,6 +29,18 @@ struct adagc_ctx {
     bool         small_list = false;    // the per-tensor rule goes into the update kernel (FusedRule)
     Exchange     exchange{};            // and the norms too, in a single launch
 
+    // A run of tensors with a work table of its own (kGroupBytes)
+    struct TensorGroup {
+        int64_t  first = 0, count = 0;
+        int64_t  elems = 0;
+        size_t   work_at = 0, items_at = 0;    // its places in the groups' tables
+        uint32_t n_chunks = 0, n_long = 0, n_short = 0, n_tiny = 0;
+        int      grid_norm = 0, grid_update = 0;
+    };
+    std::vector<TensorGroup> tensor_groups;   // empty: the list is stepped as a whole
+    const WorkRef* group_work = nullptr;      // device
+    const WorkRef* group_items = nullptr;
+
     std::vector<int64_t>    numel;
     std::vector<int64_t>    chunk_begin;      // n_tensors + 1
     std::vector<void*>      param_copies;     // device pointers, empty until set
@@ -242,6 +254,10 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     c->n_items = tiles;
     c->grid_update = grid_for(tiles);
 
+    const int64_t grad_bytes = c->total_elems * (cfg->grad_dtype == ADAGC_GRAD_BF16 ? 2 : 4);
+    const bool grouped = grad_bytes >= kGroupedBytes && cfg->grid_blocks == 0 && cfg->optimizer != ADAGC_OPT_MUON && c->nontemporal &&
+                         !cfg->telemetry;
+
     // One slab, carved into 256-byte aligned arrays.
     const size_t nt = (size_t)n_tensors, nc = (size_t)c->n_chunks;
     size_t off = 0;
@@ -272,6 +288,8 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     const size_t o_ucoef64 = carve(cfg->update_clipping ? nt * sizeof(double) : 0);
     const size_t o_words = carve(one_launch ? (2 * nc + nt) * sizeof(uint64_t) : 0);
     const size_t o_launches = carve(one_launch ? (size_t)tiles * kWavesPerBlock * sizeof(uint32_t) : 0);
+    const size_t o_group_work = carve(grouped ? nc * sizeof(WorkRef) : 0);
+    const size_t o_group_items = carve(grouped ? (size_t)n_short * sizeof(WorkRef) : 0);
     const size_t slab_bytes = off;
 
     hipError_t e = hipMalloc(&c->slab, slab_bytes);
@@ -280,38 +298,75 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     if (hipMemset(c->slab, 0, slab_bytes) != hipSuccess) { free_ctx(c); return ADAGC_ERR_HIP; }
 
     // The chunks in visiting order (see adagc_build_visiting_order): the long ones, then the short and the tiny ones in list
-    // order.
+    // order; and the work items of the short ones.  Of chunks `from` to `to`, appended.
     {
-        std::vector<WorkRef> work, items;
-        try {
+        std::vector<WorkRef> work, items, group_work, group_items;
+        auto append_range = [&](size_t from, size_t to, std::vector<WorkRef>& to_work, std::vector<WorkRef>& to_items,
+                                adagc_ctx::TensorGroup& g) {
             std::vector<uint32_t> longer, order;
-            longer.reserve((size_t)n_long);
-            for (size_t k = 0; k < nc; ++k)
+            for (size_t k = from; k < to; ++k)
                 if (kind_of(k) == kLongChunk) longer.push_back((uint32_t)k);
-            order.resize((size_t)n_long);
-            if (n_long > 0) {
-                rc = adagc_build_visiting_order(n_long, cfg->schedule ? cfg->schedule : 2, cfg->schedule_run ? cfg->schedule_run : 8,
-                                                order.data());
-                if (rc != ADAGC_OK) { free_ctx(c); return rc; }
-            }
-            work.reserve(nc);
-            auto append = [&](uint32_t k) { work.push_back(WorkRef{chunk_tensor[k], k, chunk_index[k], (uint32_t)chunk_len(k)}); };
+            order.resize(longer.size());
+            int made = ADAGC_OK;
+            if (!longer.empty())
+                made = adagc_build_visiting_order((int64_t)longer.size(), cfg->schedule ? cfg->schedule : 2,
+                                                  cfg->schedule_run ? cfg->schedule_run : 8, order.data());
+            if (made != ADAGC_OK) return made;
+            g.work_at = to_work.size();
+            g.items_at = to_items.size();
+            auto append = [&](uint32_t k) { to_work.push_back(WorkRef{chunk_tensor[k], k, chunk_index[k], (uint32_t)chunk_len(k)}); };
             for (uint32_t o : order) append(longer[o]);
             for (ChunkKind kind : {kShortChunk, kTinyChunk})
-                for (size_t k = 0; k < nc; ++k)
-                    if (kind_of(k) == kind) append((uint32_t)k);
-            items.reserve((size_t)n_short);
-            for (size_t k = (size_t)n_long; k < nc - (size_t)n_tiny; ++k)
-                for (int part = 0; part < chunk_items(work[k].len, c->items_per_chunk); ++part) {
-                    items.push_back(work[k]);
-                    items.back().len |= (uint32_t)part << kPartShift;
+                for (size_t k = from; k < to; ++k) {
+                    if (kind_of(k) != kind) continue;
+                    append((uint32_t)k);
+                    if (kind == kTinyChunk) {
+                        ++g.n_tiny;
+                        continue;
+                    }
+                    for (int part = 0; part < chunk_items(chunk_len(k), c->items_per_chunk); ++part) {
+                        to_items.push_back(to_work.back());
+                        to_items.back().len |= (uint32_t)part << kPartShift;
+                    }
                 }
-        } catch (const std::bad_alloc&) { free_ctx(c); return ADAGC_ERR_OOM; }
-        if (hipMemcpy(base + o_work, work.data(), nc * sizeof(WorkRef), hipMemcpyHostToDevice) != hipSuccess ||
-            (n_short > 0 && hipMemcpy(base + o_items, items.data(), items.size() * sizeof(WorkRef), hipMemcpyHostToDevice) != hipSuccess)) {
+            g.n_chunks = (uint32_t)(to - from);
+            g.n_long = (uint32_t)longer.size();
+            g.n_short = (uint32_t)(to_items.size() - g.items_at);
+            g.grid_norm = grid_for((int64_t)g.n_chunks - g.n_tiny + (g.n_tiny + 3) / 4);
+            g.grid_update = grid_for(count_work_items(g.n_long, g.n_short, g.n_tiny, c->items_per_chunk));
+            return ADAGC_OK;
+        };
+        try {
+            work.reserve(nc);
+            items.reserve((size_t)n_short);
+            adagc_ctx::TensorGroup all;
+            rc = append_range(0, nc, work, items, all);
+            if (rc == ADAGC_OK && grouped) {
+                const int64_t most = kGroupBytes / (cfg->grad_dtype == ADAGC_GRAD_BF16 ? 2 : 4);
+                group_work.reserve(nc);
+                group_items.reserve((size_t)n_short);
+                for (int64_t first = 0; rc == ADAGC_OK && first < n_tensors;) {
+                    adagc_ctx::TensorGroup g;
+                    g.first = first;
+                    do {
+                        g.elems += descs[first++].numel;
+                        ++g.count;
+                    } while (first < n_tensors && g.elems + descs[first].numel <= most);
+                    rc = append_range((size_t)c->chunk_begin[(size_t)g.first], (size_t)c->chunk_begin[(size_t)first], group_work, group_items, g);
+                    c->tensor_groups.push_back(g);
+                }
+            }
+        } catch (const std::bad_alloc&) { rc = ADAGC_ERR_OOM; }
+        if (rc != ADAGC_OK) { free_ctx(c); return rc; }
+        auto upload = [&](size_t to, const std::vector<WorkRef>& from) {
+            return from.empty() || hipMemcpy(base + to, from.data(), from.size() * sizeof(WorkRef), hipMemcpyHostToDevice) == hipSuccess;
+        };
+        if (!upload(o_work, work) || !upload(o_items, items) || !upload(o_group_work, group_work) || !upload(o_group_items, group_items)) {
             free_ctx(c);
             return ADAGC_ERR_HIP;
         }
+        c->group_work = reinterpret_cast<const WorkRef*>(base + o_group_work);
+        c->group_items = reinterpret_cast<const WorkRef*>(base + o_group_items);
     }
     const size_t staging_bytes = adagc_ctx::kStagingSlots * nt * sizeof(TensorArgs);
     const size_t status_at = staging_bytes + align_up(c->results_bytes, 64);
@@ -480,6 +535,23 @@ extern "C" int adagc_step(adagc_ctx* ctx, void* const* params, const void* const
     const bool prof = ctx->prof_steps < ctx->prof_capacity;
     hipEvent_t* ev = prof ? &ctx->prof_events[(size_t)ctx->prof_steps * 4] : nullptr;
 
+    if (!prof && !ctx->tensor_groups.empty() && !r.warmup && r.mode == ADAGC_MODE_ADAGC) {       // (profiled steps time the kernels of a whole list)
+        for (const adagc_ctx::TensorGroup& g : ctx->tensor_groups) {
+            DeviceTables t = ctx->tables;
+            t.work = ctx->group_work + g.work_at;
+            t.items = ctx->group_items + g.items_at;
+            t.n_chunks = g.n_chunks;
+            t.n_long = g.n_long;
+            t.n_short = g.n_short;
+            t.n_tiny = g.n_tiny;
+            if (launch_sumsq_partials(t, bf16g, stream_gradients(g.elems, bf16g), g.grid_norm, stream) != hipSuccess ||
+                launch_tensor_rules(t, ema_norms, r, (uint32_t)g.first, (uint32_t)g.count, stream) != hipSuccess ||
+                launch_update(t, u, ctx->cfg.optimizer, bf16g, copy, ctx->unroll, ctx->items_per_chunk, ctx->nontemporal, 0, g.grid_update,
+                              stream) != hipSuccess)
+                return ADAGC_ERR_HIP;
+        }
+        return ADAGC_OK;
+    }
     if (prof && hipEventRecord(ev[0], stream) != hipSuccess) return ADAGC_ERR_HIP;
     if (update_clip) {
         // AGC / Clippy: no gradient norms; the direction's norms (timed in the norm slot together with their

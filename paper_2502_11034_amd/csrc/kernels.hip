@@ -480,6 +480,15 @@ __global__ __launch_bounds__(kBlock) void rules_kernel(DeviceTables t, float* em
     for (uint32_t k = tid; k < t.n_tensors; k += kBlock) take_global_coefficient(t, ema, r, k);
 }
 
+// The per-tensor rule of a group's tensors, the first of which is `first`.
+__global__ __launch_bounds__(kBlock) void tensor_rules_kernel(DeviceTables t, float* ema, RuleArgs r, uint32_t first)
+{
+    __shared__ double wave_sums[kWavesPerBlock];
+    const uint32_t i = first + blockIdx.x;
+    const double s = tensor_slot_sum(t, t.partials, i, wave_sums);
+    if (threadIdx.x == 0) store_rule(t, ema, i, s, adagc_rule(r, s, (double)ema[i]));
+}
+
 // Per-tensor sum of squares only.
 __global__ __launch_bounds__(kBlock) void tensor_sumsq_kernel(DeviceTables t)
 {
@@ -1248,6 +1257,12 @@ hipError_t launch_rules(const DeviceTables& t, float* ema, const RuleArgs& r, hi
     if (e != hipSuccess) return e;
     const uint32_t blocks = (t.n_tensors + kBlock - 1) / kBlock;
     finalize_global_kernel<<<dim3(blocks), dim3(kBlock), 0, stream>>>(t, ema, r, params, optimizer);
+    return hipGetLastError();
+}
+
+hipError_t launch_tensor_rules(const DeviceTables& t, float* ema, const RuleArgs& r, uint32_t first, uint32_t count, hipStream_t stream)
+{
+    tensor_rules_kernel<<<dim3(count), dim3(kBlock), 0, stream>>>(t, ema, r, first);
     return hipGetLastError();
 }
 

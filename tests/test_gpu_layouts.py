@@ -390,6 +390,62 @@ def test_single_launches_that_overlap_leave_nothing_behind():
     other.close()
 
 
+# Lists with more than 450 MiB of gradients, stepped in groups of up to 256 MiB of them: groups that are full to the byte, a tensor larger than
+# a group, chunks of every kind and single tensors at the ends of groups.
+GROUP = 256 * MI // 4
+GROUPED = {"full groups": (B.ADAGC_GRAD_F32, [GROUP // 2] * 4 + [1]), "a tensor larger than a group": (B.ADAGC_GRAD_F32, [5, GROUP + 70001, 300, 40 * MI, 2049, 12 * MI, 7]),
+           "small tensors": (B.ADAGC_GRAD_F32, ITEMS + [16384 * 3 + 511] * 2500), "bf16": (B.ADAGC_GRAD_BF16, [1000, 2 * GROUP - 1001, 2, 2 * GROUP - 2, 4099])}
+
+
+@pytest.mark.parametrize("optimizer,copy,flat", [(B.ADAGC_OPT_ADAMW, False, True), (B.ADAGC_OPT_LION, True, False)])
+@pytest.mark.parametrize("name", GROUPED)
+def test_a_list_in_groups_equals_the_list_as_a_whole(name, optimizer, copy, flat):
+    """Two steps, the second captured and replayed, against steps that are profiled, which take the list as a whole; end to end in flat buffers
+    (whole lines) or each tensor on its own.  A step of a warm-up, which is not grouped, in between."""
+    grad_dtype, numels = GROUPED[name]
+    assert sum(numels) * (2 if grad_dtype == B.ADAGC_GRAD_BF16 else 4) > 450 * MI
+    lion, total, results = optimizer == B.ADAGC_OPT_LION, sum(numels), []
+    hp = B.make_hyper(lr=1e-3, t_start=0)
+    for whole in (True, False):
+        gen = torch.Generator(device=DEV).manual_seed(6)
+        buf = {k: torch.randn(total, generator=gen, device=DEV).mul_(x) for k, x in (("p", 0.02), ("g", 0.01), ("m", 0.002)) + (() if lion else (("v", 0.01),))}
+        if not lion:
+            buf["v"].square_()
+        if grad_dtype == B.ADAGC_GRAD_BF16:
+            buf["g"] = buf["g"].to(torch.bfloat16)
+        buf["c"] = torch.zeros(total if copy else 1, dtype=torch.bfloat16, device=DEV)
+        lists = {k: list(x.split(numels)) if x.numel() == total else [] for k, x in buf.items()}
+        if not flat:
+            lists = {k: [y.clone() for y in x] for k, x in lists.items()}
+            del buf
+        gamma = torch.tensor([(0.009, 0.012)[i % 2] * n ** 0.5 for i, n in enumerate(numels)], dtype=torch.float32, device=DEV)
+        ctx = B.AdaGC(numels, optimizer, grad_dtype, copy)
+        if copy:
+            ctx.set_param_copies(lists["c"])
+        if whole:
+            ctx.profile_begin(3)
+        v, reports = None if lion else lists["v"], []
+        for step, h in ((7, hp), (8, B.make_hyper(lr=1e-3, t_start=100, lambda_abs=1.0)), (9, hp)):
+            if whole or step != 9:
+                ctx.step(lists["p"], lists["g"], lists["m"], v, gamma, h, step)
+            else:
+                graph = torch.cuda.CUDAGraph()
+                torch.cuda.synchronize()
+                with torch.cuda.graph(graph):
+                    ctx.step(lists["p"], lists["g"], lists["m"], v, gamma, h, step, stream=torch.cuda.current_stream().cuda_stream)
+                graph.replay()
+                torch.cuda.synchronize()
+            reports += [torch.from_numpy(x.copy()) for x in ctx.get_norms()] + [gamma.cpu()]
+        ctx.close()
+        results.append((reports, {k: lists[k] for k in ("p", "m", "c") + (() if lion else ("v",))}))
+    assert (results[0][0][1] < 1).any() and (results[0][0][1] == 1).any()
+    for k, (x, y) in enumerate(zip(results[0][0], results[1][0])):
+        assert torch.equal(x, y), "report %d" % k
+    for k in results[0][1]:
+        for i, (x, y) in enumerate(zip(results[0][1][k], results[1][1][k])):
+            assert torch.equal(x, y), "%s of tensor %d" % (k, i)
+
+
 # sizes around the ends of vectors, lines, tiles (512, 1024, 2048, 4096 elements) and chunks (16384); the last brings the list above
 # what walk_lines.h asks for (8 Mi elements for Lion, and the mean of 16384)
 LINES = [1, 2, 3, 4, 5, 31, 32, 33, 34, 63, 511, 513, 1023, 1024, 1025, 1056, 2047, 2049, 4064, 4095, 4096, 4097, 4128, 8190, 16353, 16383,
