@@ -268,7 +268,7 @@ int adagc_step_graph(adagc_ctx* ctx, void* const* params, const void* const* gra
  * this call allocates nothing (no hipMalloc / hipFree, no copy, no memset, no event), it only
  * launches kernels on `stream`.  The segment table, the per-chunk partial sums and the per-tensor
  * results live in a fixed array inside the library's device code, ADAGC_STATIC_MAX_* in size
- * (about 15 MB per GPU, held from the library's load until the process ends).
+ * (about 18 MB per GPU, held from the library's load until the process ends).
  *   descs, n_tensors, cfg   HOST  as for adagc_create; cfg->telemetry, cfg->update_clipping and the
  *                                 launch-tuning fields must be 0 (library defaults, chunks visited in
  *                                 list order; clip modes 0 to 3)
