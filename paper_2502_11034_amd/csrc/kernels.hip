@@ -8,7 +8,9 @@
 //   global_rule_kernel / finalize_global_kernel
 //                           those model-wide rules on long lists
 //   update_kernel           per work item (an eighth of a chunk; chunks of up to 512 elements go four to a workgroup):
-//                           clipped gradient into AdamW / Lion  (Alg. 1)
+//                           clipped gradient into AdamW / Lion  (Alg. 1); small lists with the per-tensor rule inside, the
+//                           smallest with the norms as well
+//   tensor_rules_kernel     the per-tensor rule of a group of a large list's tensors
 //   direction_stats_kernel / finalize_update_clip_kernel
 //                           update clipping (AGC and Clippy rows of Table 2): norms of theta and of the
 //                           optimizer's direction per tensor, and the coefficient that scales the direction
