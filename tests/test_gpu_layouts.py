@@ -373,6 +373,7 @@ def test_single_launches_that_overlap_leave_nothing_behind():
         return s
     a = state()
     streams = [torch.cuda.Stream() for _ in range(2)]
+    ctx.step(a["p"], a["g"], a["m"], a["v"], a["gamma"], hp, 7)          # the pointer table is uploaded once, before the steps that overlap
     torch.cuda.synchronize()
     for k in range(40):
         ctx.step(a["p"], a["g"], a["m"], a["v"], a["gamma"], hp, 7, stream=streams[k % 2].cuda_stream)
