@@ -213,11 +213,14 @@ struct FusedRule {
 // gradients and the copy 11.3 / 9.2, 11.7 / 8.7, 11.5 / 10.7 (0.5 M); beyond: 360 items 11.2 / 11.0 and 11.5 / 11.4, and where the chip does not
 // hold the launch, waits that nobody ends: 575 items 11.5 / 57.
 constexpr int64_t kOneLaunchItems = 288;
-// A stream that is being captured (or cannot be asked): its launches are issued only once.
+// A stream that is being captured (or cannot be asked, as the NULL stream while another one is captured): its launches are issued only once.
+// The error of a stream that cannot be asked is not the step's and does not stay behind for the launches, which report the thread's last one.
 inline bool issues_now(hipStream_t stream)
 {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(stream, &status) == hipSuccess && status == hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) == hipSuccess) return status == hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
 }
 
 // What the workgroups of a launch tell each other: a chunk's sum of squares and a tensor's gamma, in 64-bit words of which the lower
