@@ -205,14 +205,40 @@ struct FusedRule {
 };
 
 // The smallest lists have a single launch: the workgroups of the update kernel sum the chunks for themselves and tell each other
-// (Exchange).  Every workgroup of a chunk reads all of its gradient, eight times what the norm kernel reads, and waits for the others of
-// its tensor, so this is for launches that the chip holds at once and that the host issues one by one: it is the second launch's issue
-// that is saved, the GPU is as long at it as at two kernels or a little longer.  While a stream is captured there are two.
-// us per step issued / with the GPU waited for, two launches / one: AdamW fp32, 0.14 M parameters (70 work items) 11.4 / 8.3 and
-// 22.8 / 23.0, 0.3 M 11.3 / 8.3 and 23.5 / 23.0, 27 tensors of 0.53 M (261) 11.4 / 8.2, 0.5 M (255) 11.1 / 9.5 and 24.2 / 24.6; with bf16
-// gradients and the copy 11.3 / 9.2, 11.7 / 8.7, 11.5 / 10.7 (0.5 M); beyond: 360 items 11.2 / 11.0 and 11.5 / 11.4, and where the chip does not
-// hold the launch, waits that nobody ends: 575 items 11.5 / 57.
-constexpr int64_t kOneLaunchItems = 288;
+// (Exchange).  Every workgroup of a chunk reads all of its gradient, up to eight times what the norm kernel reads, and waits for the
+// others of its tensor, so whether the GPU is done sooner than with two launches depends on the list.  us per step on the GPU, issued
+// behind a long product (so the host is ahead), two launches / one:
+//                                        AdamW f32    AdamW bf16 + copy   Lion f32     Lion bf16 + copy
+//   288 tensors of 2048                  9.0 / 7.3    9.8 / 7.6           7.3 / 5.9    7.7 / 6.5
+//   46 of 3693 on average (111 items)    8.3 / 7.5    9.5 / 8.2           7.0 / 7.0    7.8 / 7.6
+//   27 of 14 500 (236 items)             9.0 / 8.3    10.9 / 9.5          7.4 / 7.7    8.7 / 8.8
+//   12 of 16 384 (128 items)             8.6 / 8.2    9.1 / 9.5           6.6 / 7.5    6.8 / 8.9
+//   32 of 16 384 (256 items)             8.7 / 8.6    9.5 / 10.2          7.1 / 8.0    7.3 / 9.8
+//   a two-layer transformer (258 items)  8.6 / 8.5    9.5 / 10.1          7.1 / 8.3    7.6 / 9.9
+//   17 of 28 200 (275 items)             9.1 / 9.8    11.0 / 10.9         7.8 / 8.4    9.2 / 9.7
+//   one tensor of 400 000                8.4 / 8.9    9.4 / 10.7          6.7 / 8.4    7.2 / 10.2
+// Where each tensor is one work item nobody waits and nothing is read twice.  Else it pays with AdamW while every workgroup that
+// somebody waits for has a compute unit of its own and tensors are not too long; with bf16 gradients not where most long chunks are
+// whole ones (two launches take those quickest); with Lion, whose update is short, only without long chunks.  The host saves the issue of
+// a launch besides, 2.5 to 3 us.  While a stream is captured there are two launches.
+constexpr int64_t kOneLaunchItems = 288;       // of a device with 256 compute units; an eighth more than that on others
+constexpr int64_t kOneLaunchChunks = 16;       // of one tensor
+struct LaunchShape {
+    int64_t n_long, n_short, n_tiny;           // as in DeviceTables
+    int64_t n_full;                            // chunks of kChunkElems elements
+    int64_t most_chunks;                       // of one tensor
+    bool    alone;                             // every tensor is a single work item
+};
+inline bool one_launch_pays(int optimizer, bool bf16_grads, const LaunchShape& s, int items_per_chunk, int64_t compute_units)
+{
+    const int64_t items = count_work_items(s.n_long, s.n_short, s.n_tiny, items_per_chunk);
+    if (items > kOneLaunchItems || items > compute_units + compute_units / 8) return false;
+    if (s.alone) return true;
+    if (count_work_items(s.n_long, s.n_short, 0, items_per_chunk) > compute_units) return false;
+    if (s.n_long == 0) return true;
+    return optimizer == ADAGC_OPT_ADAMW && s.most_chunks <= kOneLaunchChunks && (!bf16_grads || 2 * s.n_full <= s.n_long);
+}
+
 // A stream that is being captured (or cannot be asked, as the NULL stream while another one is captured): its launches are issued only once.
 // The error of a stream that cannot be asked is not the step's and does not stay behind for the launches, which report the thread's last one.
 inline bool issues_now(hipStream_t stream)

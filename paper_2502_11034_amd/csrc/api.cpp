@@ -27,7 +27,8 @@ struct adagc_ctx {
     int          items_per_chunk = 1;   // work items of the update kernel per chunk
     bool         stream_grads = false;  // the norm kernel reads past the memory-side cache
     bool         small_list = false;    // the per-tensor rule goes into the update kernel (FusedRule)
-    Exchange     exchange{};            // and the norms too, in a single launch
+    Exchange     exchange{};            // and the norms too, in a single launch: possible if its words are there,
+    bool         one_launch = false;    // and where it pays
 
     // A run of tensors with a work table of its own (kGroupBytes)
     struct TensorGroup {
@@ -250,6 +251,19 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     const bool one_launch = c->small_list && tiles <= kOneLaunchItems && cfg->grid_blocks == 0 && cfg->optimizer != ADAGC_OPT_MUON &&
                             c->unroll == default_unroll(cfg->optimizer) && c->items_per_chunk == default_items(c->unroll) && c->nontemporal &&
                             !cfg->telemetry;
+    if (one_launch) {
+        LaunchShape shape{n_long, n_short, n_tiny, 0, most_chunks, true};
+        for (int64_t i = 0; i < n_tensors; ++i) {
+            shape.n_full += descs[i].numel / kChunkElems;
+            shape.alone = shape.alone && descs[i].numel <= kChunkElems / c->items_per_chunk;
+        }
+        int compute_units = 0;
+        if (hipDeviceGetAttribute(&compute_units, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) {
+            free_ctx(c);
+            return ADAGC_ERR_HIP;
+        }
+        c->one_launch = one_launch_pays(cfg->optimizer, cfg->grad_dtype == ADAGC_GRAD_BF16, shape, c->items_per_chunk, compute_units);
+    }
     c->grid_norm = grid_for(c->n_chunks - n_tiny + (n_tiny + 3) / 4);
     c->n_items = tiles;
     c->grid_update = grid_for(tiles);
@@ -412,11 +426,12 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     return ADAGC_OK;
 }
 
-// For tests (not in the header): how often a wave of a single-launch step looks for what others tell before it computes that itself.
-// False: the context's steps are not of that kind.
+// For tests (not in the header): has the context step in a single launch, whether it pays or not, and sets how often a wave of it looks
+// for what others tell before it computes that itself.  False: such a step is not possible.
 extern "C" int adagc_internal_set_polls(adagc_ctx* ctx, uint32_t polls)
 {
     if (!ctx || !ctx->exchange.words) return 0;
+    ctx->one_launch = true;
     ctx->exchange.polls = polls;
     return 1;
 }
@@ -563,7 +578,7 @@ extern "C" int adagc_step(adagc_ctx* ctx, void* const* params, const void* const
             return ADAGC_ERR_HIP;
     } else {
         if (ctx->small_list && !r.warmup && r.mode == ADAGC_MODE_ADAGC) rule = FusedRule{ema_norms, r};
-        if (rule.ema && ctx->exchange.words && !prof && issues_now(stream)) exchange = ctx->exchange;      // (profiled steps keep a norm kernel to time)
+        if (rule.ema && ctx->one_launch && !prof && issues_now(stream)) exchange = ctx->exchange;      // (profiled steps keep a norm kernel to time)
         if (!exchange.words &&
             launch_sumsq_partials(ctx->tables, bf16g, ctx->stream_grads, ctx->grid_norm, stream, nullptr, 0, rule.ema) != hipSuccess)
             return ADAGC_ERR_HIP;

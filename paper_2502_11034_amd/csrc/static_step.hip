@@ -43,22 +43,26 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;
 void*      g_scratch_ptr[kMaxDevices];    // device address of `scratch` on each GPU, once looked up
+int        g_compute_units[kMaxDevices];
 bool       g_scratch_known[kMaxDevices];
 std::mutex g_scratch_mutex;
 
-// Device address of this GPU's copy of the array (`device` must be the current device).
-hipError_t scratch_address(int device, unsigned char** out)
+// Device address of this GPU's copy of the array (`device` must be the current device), and its compute units.
+hipError_t scratch_address(int device, unsigned char** out, int* compute_units)
 {
     std::lock_guard<std::mutex> lock(g_scratch_mutex);
     if (!g_scratch_known[device]) {
         void* p = nullptr;
-        const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
+        hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
         if (e != hipSuccess) return e;
         if (!p) return hipErrorInvalidSymbol;
+        e = hipDeviceGetAttribute(&g_compute_units[device], hipDeviceAttributeMultiprocessorCount, device);
+        if (e != hipSuccess) return e;
         g_scratch_ptr[device] = p;
         g_scratch_known[device] = true;
     }
     *out = static_cast<unsigned char*>(g_scratch_ptr[device]);
+    *compute_units = g_compute_units[device];
     return hipSuccess;
 }
 
@@ -154,15 +158,15 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
     // Everything is validated before anything is enqueued.
     const int unroll = default_unroll(cfg->optimizer), items_per_chunk = default_items(unroll);
     uint64_t n_chunks = 0, n_long = 0, n_short = 0, n_tiny = 0;          // n_short: work items
-    bool small_tensors = true;
-    int64_t total_elems = 0;
+    int64_t total_elems = 0, n_full = 0, largest = 0;
     for (int64_t i = 0; i < n_tensors; ++i) {
         if (descs[i].numel <= 0 || descs[i].flags != 0 || descs[i].reserved != 0) return ADAGC_ERR_INVALID_ARG;
         if (!params[i] || !grads[i] || !exp_avg[i] || (adamw && !exp_avg_sq[i]) || (copy && !params_bf16[i]))
             return ADAGC_ERR_INVALID_ARG;
         n_chunks += (uint64_t)((descs[i].numel + kChunkElems - 1) / kChunkElems);
         if (n_chunks > (uint64_t)kMaxC) return ADAGC_ERR_TOO_LARGE;
-        if (descs[i].numel > kFusedMaxChunks * kChunkElems) small_tensors = false;
+        if (descs[i].numel > largest) largest = descs[i].numel;
+        n_full += descs[i].numel / kChunkElems;
         total_elems += descs[i].numel;
     }
     const int short_items = most_short_items(n_tensors, total_elems, items_per_chunk);
@@ -180,7 +184,8 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
     if (hipGetDevice(&device) != hipSuccess) return ADAGC_ERR_HIP;
     if (device < 0 || device >= kMaxDevices) return ADAGC_ERR_HIP;
     unsigned char* base = nullptr;
-    if (scratch_address(device, &base) != hipSuccess) return ADAGC_ERR_HIP;
+    int compute_units = 0;
+    if (scratch_address(device, &base, &compute_units) != hipSuccess) return ADAGC_ERR_HIP;
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
 
     DeviceTables t{};
@@ -223,8 +228,11 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
     UpdateArgs u;
     host_step_scalars(*hp, step, r, u);
     FusedRule rule{};
-    if (small_tensors && items <= fused_max_items(cfg->optimizer) && !r.warmup && r.mode == ADAGC_MODE_ADAGC) rule = FusedRule{ema_norms, r};
-    const bool one_launch = rule.ema && items <= kOneLaunchItems && 2 * n_chunks + (uint64_t)n_tensors <= kMaxWords && issues_now(stream);
+    if (largest <= kFusedMaxChunks * kChunkElems && items <= fused_max_items(cfg->optimizer) && !r.warmup && r.mode == ADAGC_MODE_ADAGC) rule = FusedRule{ema_norms, r};
+    const LaunchShape shape{(int64_t)n_long, (int64_t)n_short, (int64_t)n_tiny, n_full, (largest + kChunkElems - 1) / kChunkElems,
+                            largest <= kChunkElems / items_per_chunk};
+    const bool one_launch = rule.ema && 2 * n_chunks + (uint64_t)n_tensors <= kMaxWords &&
+                            one_launch_pays(cfg->optimizer, bf16g, shape, items_per_chunk, compute_units) && issues_now(stream);
     uint64_t* const words = one_launch ? reinterpret_cast<uint64_t*>(base + kOffWords) : nullptr;
 
     // Tensor records and chunk table, a batch of tensors per launch.

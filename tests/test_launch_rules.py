@@ -6,6 +6,8 @@ import subprocess
 
 import pytest
 
+from paper_2502_11034_amd import binding as B
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 pytestmark = pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir(os.path.join(ROCM, "include", "hip")),
@@ -24,3 +26,41 @@ def test_a_stream_that_cannot_be_asked_leaves_no_error_behind(tmp_path):
     """The NULL stream while another stream is captured: the question fails, the step's launches must not report that."""
     res = subprocess.run([_driver(tmp_path, "issues_now_check")], capture_output=True, text=True, timeout=60)
     assert res.returncode == 0, res.stdout
+
+
+ADAMW, LION = B.ADAGC_OPT_ADAMW, B.ADAGC_OPT_LION
+LAYER = [128, 128, 49152, 16384, 65536, 65536]
+# list, and whether a single launch is the quicker step with AdamW and Lion on f32 and bf16 gradients, on 256 compute units
+ONE_LAUNCH = {
+    "one element": ([1], True, True, True, True), "tensors of one item": ([2048] * 288, True, True, True, True),
+    "one more of them": ([2048] * 289, False, False, False, False), "tiny tensors": ([500] * 1152, True, True, True, True),
+    "short chunks": ([3693] * 46, True, True, True, True), "a workgroup to a compute unit": ([2049] * 128, True, True, True, True),
+    "one more": ([2049] * 128 + [600], False, False, False, False),
+    "a two-layer transformer": ([131072] + LAYER * 2 + [128], True, False, False, False), "whole chunks": ([16384] * 32, True, False, False, False),
+    "ends of chunks": ([14500] * 27, True, True, False, False), "half of them whole": ([16384, 14500] * 8, True, True, False, False),
+    "more than half": ([16384, 14500] * 8 + [16384], True, False, False, False),
+    "a compute unit for all but ten": ([28200] * 17, False, False, False, False),
+    "16 chunks": ([16 * 16384], True, False, False, False), "17 chunks": ([16 * 16384 + 1], False, False, False, False)}
+
+
+@pytest.fixture(scope="module")
+def one_launch(tmp_path_factory):
+    exe = _driver(tmp_path_factory.mktemp("one_launch"), "one_launch_check")
+
+    def ask(optimizer, bf16, compute_units, numels):
+        line = " ".join(str(x) for x in [optimizer, bf16, compute_units, len(numels)] + numels)
+        return subprocess.run([exe], input=line, capture_output=True, text=True, check=True, timeout=60).stdout.strip() == "1"
+    return ask
+
+
+@pytest.mark.parametrize("name", ONE_LAUNCH)
+def test_a_single_launch_where_the_gpu_is_done_sooner(one_launch, name):
+    numels, *pays = ONE_LAUNCH[name]
+    assert [one_launch(o, b, 256, numels) for o in (ADAMW, LION) for b in (0, 1)] == pays
+
+
+def test_a_single_launch_that_the_device_holds_at_once(one_launch):
+    """A part of a GPU has fewer compute units: workgroups that are not running keep those that are waiting for them."""
+    assert one_launch(ADAMW, 0, 64, [2048] * 72) and not one_launch(ADAMW, 0, 64, [2048] * 73)
+    assert one_launch(ADAMW, 0, 64, [16384] * 8) and not one_launch(ADAMW, 0, 64, [16384] * 9) and not one_launch(ADAMW, 0, 32, [16384])
+    assert not one_launch(ADAMW, 0, 0, [1])
