@@ -502,7 +502,8 @@ int prepare_tables(adagc_ctx* ctx, void* const* params, const void* const* grads
         TensorArgs* stage = ctx->staging + (size_t)slot * (size_t)ctx->n_tensors;
         std::memcpy(stage, ctx->scratch_args.data(), args_bytes);
         auto walks = [&](int64_t off_lines) {
-            return walk_lines(ctx->cfg.optimizer, bf16g, copy, ctx->n_tensors, ctx->total_elems, off_lines, ctx->grid_update, ctx->n_items);
+            return lines_with_unroll(ctx->cfg.optimizer, ctx->unroll) &&
+                   walk_lines(ctx->cfg.optimizer, bf16g, copy, ctx->n_tensors, ctx->total_elems, off_lines, ctx->grid_update, ctx->n_items);
         };
         int64_t off_lines = 0;
         if (walks(ctx->total_elems))             // wherever its tensors start

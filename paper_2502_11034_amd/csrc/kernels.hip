@@ -1199,12 +1199,12 @@ __global__ __launch_bounds__(kBlock) void finalize_telemetry_kernel(DeviceTables
 
 using UpdateFn = void (*)(DeviceTables, UpdateArgs, uint32_t, const StepScalars*, FusedRule, Exchange);
 
-// The launches of the library's own choice (the vectors in flight that are not chosen otherwise, streaming) have kernels with and
-// without the rule, and with whole lines where those ever pay.
+// Where whole lines ever pay, the launches of the library's own choice (streaming, so many vectors in flight) have kernels with
+// them; those of lists that may be small have kernels with and without the rule.
 template <int OPT, bool BF16G, bool COPY, int U, RuleHere RULE>
 UpdateFn select_update_flags(int nt, int tele, bool lines)
 {
-    if constexpr (U == default_unroll(OPT) && line_limits(OPT, BF16G, COPY).elems > 0)
+    if constexpr (lines_with_unroll(OPT, U) && line_limits(OPT, BF16G, COPY).elems > 0)
         if (lines && nt && !tele) return update_kernel<OPT, BF16G, COPY, U, true, false, true, RULE>;
     if (nt) return tele ? update_kernel<OPT, BF16G, COPY, U, true, true, false, RULE> : update_kernel<OPT, BF16G, COPY, U, true, false, false, RULE>;
     return tele ? update_kernel<OPT, BF16G, COPY, U, false, true, false, kRuleAsk> : update_kernel<OPT, BF16G, COPY, U, false, false, false, kRuleAsk>;

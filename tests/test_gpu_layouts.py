@@ -466,7 +466,9 @@ LINE_RUNS = [(B.ADAGC_OPT_ADAMW, B.ADAGC_GRAD_F32, True, STEP, B.ADAGC_MODE_ADAG
              (B.ADAGC_OPT_ADAMW, B.ADAGC_GRAD_F32, True, STEP, B.ADAGC_MODE_CLIPPY, {}, [1, 15]),
              (B.ADAGC_OPT_LION, B.ADAGC_GRAD_BF16, True, STEP, B.ADAGC_MODE_CLIPPY, {}, [29]),
              (B.ADAGC_OPT_ADAMW, B.ADAGC_GRAD_F32, False, STEP, B.ADAGC_MODE_ADAGC, {"grid_blocks": 400}, [7]),
-             (B.ADAGC_OPT_LION, B.ADAGC_GRAD_BF16, True, STEP, B.ADAGC_MODE_ADAGC, {"update_split": 1}, [2])]
+             (B.ADAGC_OPT_LION, B.ADAGC_GRAD_BF16, True, STEP, B.ADAGC_MODE_ADAGC, {"update_split": 1}, [2]),
+             (B.ADAGC_OPT_ADAMW, B.ADAGC_GRAD_F32, True, STEP, B.ADAGC_MODE_ADAGC, {"unroll": 4}, [1, 31]),
+             (B.ADAGC_OPT_ADAMW, B.ADAGC_GRAD_BF16, False, GRAPH, B.ADAGC_MODE_ZCLIP, {"unroll": 4}, [7])]
 
 
 class _Lines:

@@ -64,3 +64,9 @@ def test_a_single_launch_that_the_device_holds_at_once(one_launch):
     assert one_launch(ADAMW, 0, 64, [2048] * 72) and not one_launch(ADAMW, 0, 64, [2048] * 73)
     assert one_launch(ADAMW, 0, 64, [16384] * 8) and not one_launch(ADAMW, 0, 64, [16384] * 9) and not one_launch(ADAMW, 0, 32, [16384])
     assert not one_launch(ADAMW, 0, 0, [1])
+
+
+def test_whole_lines_with_the_vectors_in_flight_that_a_library_ever_chose(tmp_path):
+    """1, 2 and 4 vectors: a caller who sets the number that has been the library's own keeps the whole lines."""
+    out = subprocess.run([_driver(tmp_path, "lines_unroll_check")], capture_output=True, text=True, check=True, timeout=60).stdout
+    assert out.split("\n")[:2] == ["0 1 1", "0 1 0"]
