@@ -138,6 +138,19 @@ struct DeviceTables {
 constexpr int default_unroll(int) { return 2; }
 constexpr int default_items(int unroll) { return kVecPerLane >= unroll ? kVecPerLane / unroll : 1; }
 
+// What adagc_config's unroll and update_split (0: the library's choice) make of a list.  Where only the split is chosen, items have 4096
+// elements or more, and AdamW's 4 vectors of each array in flight: us per step with split 4, 2 / 4 vectors: GPT-2-small 654 / 628, with bf16
+// gradients and the copy 620 / 597; 271 M parameters 1434 / 1384, 1372 / 1318.
+struct UpdateItems {
+    int unroll, per_chunk;
+};
+constexpr UpdateItems update_items(int optimizer, int unroll, int split)
+{
+    const int least = default_unroll(optimizer);
+    if (unroll == 0) unroll = split != 0 && optimizer == ADAGC_OPT_ADAMW ? 4 : least;
+    return {unroll, split ? split : default_items(unroll > least ? unroll : least)};
+}
+
 // How the streaming kernels work on a chunk of `len` elements, in the order in which the work table has them:
 //   long   items_per_chunk work items of the update kernel, numbered with those of other chunks; the last ones may be empty, and an
 //          empty workgroup costs its dispatch and a chain of loads all the same
@@ -197,7 +210,11 @@ constexpr int64_t kGroupBytes = (int64_t)256 << 20, kGroupedBytes = (int64_t)450
 // 0.5 M parameters 12.7 / 9.2, 2 M 18.8 / 16.5, 4 M 28.7 / 26.7, 8 M 48.2 / 46.1, 16 M 83.8 / 81.7, 31 M 156.8 / 155.2; in tensors of 3000:
 // 4 M 29.6 / 27.5, 16 M 88.2 / 85.1, 32 M 165.0 / 161.1.  Lion, bf16: 0.5 M 12.5 / 9.1, 4 M 26.4 / 24.4, 16 M 65.1 / 63.5, 31 M 116.1 / 115.3;
 // in tensors of 3000: 4 M 25.6 / 24.1, 16 M 73.7 / 73.9, 32 M 137.8 / 140.9.  Work items: about one for 2048 elements.
-constexpr int64_t fused_max_items(int optimizer) { return optimizer == ADAGC_OPT_LION ? 8192 : 16384; }
+// (As many fewer of larger items: the line lies at the same list.)
+constexpr int64_t fused_max_items(int optimizer, int items_per_chunk)
+{
+    return (int64_t)(optimizer == ADAGC_OPT_LION ? 1024 : 2048) * items_per_chunk;
+}
 constexpr int64_t kFusedMaxChunks = 64;        // of one tensor
 struct FusedRule {
     float*   ema;        // null: the rules kernel has run, coefficients are in coef64

@@ -163,7 +163,7 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     if (cfg->unroll != 0 && cfg->unroll != 1 && cfg->unroll != 2 && cfg->unroll != 4) return ADAGC_ERR_INVALID_ARG;
     {
         // unroll*1024-element tiles per chunk, 4096-element ones where the caller leaves unroll to the library (whose own choice
-        // depends on the optimizer and may change; it divides 4, so every such split is whole tiles)
+        // depends on the optimizer and on the split and may change; it divides 4, so every such split is whole tiles)
         const int tiles = kVecPerLane / (cfg->unroll ? cfg->unroll : 4);
         static_assert(4 % default_unroll(ADAGC_OPT_ADAMW) == 0 && 4 % default_unroll(ADAGC_OPT_LION) == 0, "see above");
         const int sp = cfg->update_split;
@@ -214,12 +214,12 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     //    -1.9 % (AdamW, 8 B parameters), -0.4 % (Lion), -1.2 % (20 001 ragged tensors).  Fewer
     //    address fronts per array mean fewer DRAM rows open at once; runs keep each XCD on
     //    its own pages.
-    c->unroll = cfg->unroll ? cfg->unroll : default_unroll(cfg->optimizer);
     c->nontemporal = cfg->nontemporal == 2 ? 0 : 1;
     //  - work items of the update kernel: see default_unroll.
     // Both streaming kernels walk their work items b, b+grid, ..., so any grid size is valid.
-    const int least_unroll = default_unroll(cfg->optimizer);
-    c->items_per_chunk = cfg->update_split ? cfg->update_split : default_items(c->unroll > least_unroll ? c->unroll : least_unroll);
+    const UpdateItems update = update_items(cfg->optimizer, cfg->unroll, cfg->update_split);
+    c->unroll = update.unroll;
+    c->items_per_chunk = update.per_chunk;
     auto chunk_len = [&](size_t k) {
         const int64_t rest = c->numel[chunk_tensor[k]] - (int64_t)chunk_index[k] * kChunkElems;
         return rest < kChunkElems ? rest : (int64_t)kChunkElems;
@@ -246,7 +246,7 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
         if (n > most_chunks) most_chunks = n;
     }
     c->stream_grads = c->nontemporal && stream_gradients(c->total_elems, cfg->grad_dtype == ADAGC_GRAD_BF16);
-    c->small_list = tiles <= fused_max_items(cfg->optimizer) && most_chunks <= kFusedMaxChunks;
+    c->small_list = tiles <= fused_max_items(cfg->optimizer, c->items_per_chunk) && most_chunks <= kFusedMaxChunks;
     // (with the library's own choice of work items, a workgroup for each)
     const bool one_launch = c->small_list && tiles <= kOneLaunchItems && cfg->grid_blocks == 0 && cfg->optimizer != ADAGC_OPT_MUON &&
                             c->unroll == default_unroll(cfg->optimizer) && c->items_per_chunk == default_items(c->unroll) && c->nontemporal &&

@@ -70,3 +70,15 @@ def test_whole_lines_with_the_vectors_in_flight_that_a_library_ever_chose(tmp_pa
     """1, 2 and 4 vectors: a caller who sets the number that has been the library's own keeps the whole lines."""
     out = subprocess.run([_driver(tmp_path, "lines_unroll_check")], capture_output=True, text=True, check=True, timeout=60).stdout
     assert out.split("\n")[:2] == ["0 1 1", "0 1 0"]
+
+
+# optimizer, unroll, update_split: vectors in flight, work items of a chunk
+UPDATE_ITEMS = [(ADAMW, 0, 0, 2, 8), (ADAMW, 0, 1, 4, 1), (ADAMW, 0, 2, 4, 2), (ADAMW, 0, 4, 4, 4), (ADAMW, 4, 0, 4, 4), (ADAMW, 2, 0, 2, 8),
+                (ADAMW, 1, 0, 1, 8), (ADAMW, 2, 4, 2, 4), (ADAMW, 1, 16, 1, 16), (LION, 0, 0, 2, 8), (LION, 0, 4, 2, 4), (LION, 0, 1, 2, 1),
+                (LION, 4, 0, 4, 4), (LION, 1, 16, 1, 16)]
+
+
+def test_a_chosen_split_has_the_vectors_in_flight_that_suit_it(tmp_path):
+    out = subprocess.run([_driver(tmp_path, "update_items_check")], input="\n".join("%d %d %d" % x[:3] for x in UPDATE_ITEMS) + "\n",
+                         capture_output=True, text=True, check=True, timeout=60).stdout
+    assert [tuple(map(int, line.split())) for line in out.splitlines()] == [x[3:] + ((16 if x[0] == LION else 32) << 20,) for x in UPDATE_ITEMS]
