@@ -141,13 +141,18 @@ constexpr int default_items(int unroll) { return kVecPerLane >= unroll ? kVecPer
 // What adagc_config's unroll and update_split (0: the library's choice) make of a list.  Where only the split is chosen, items have 4096
 // elements or more, and AdamW's 4 vectors of each array in flight: us per step with split 4, 2 / 4 vectors: GPT-2-small 654 / 628, with bf16
 // gradients and the copy 620 / 597; 271 M parameters 1434 / 1384, 1372 / 1318.
+// The largest launches (elems: the list's, or a group's: see kGroupBytes) have AdamW's 4 vectors and items of 4096, as those wait least on
+// DRAM rows that others have closed.  us per step taken whole, Llama shapes, 2 and 2048 / 4 and 4096: f32 271 M parameters 1374 / 1382, 374 M
+// 1975 / 1953, 423 M 2251 / 2229, 536 M 2828 / 2818, 941 M 5300 / 5164; bf16 and the copy 1306 / 1312, 1870 / 1854, 2136 / 2090, 2667 / 2642, 4893 / 4737;
+// in list order (adagc_step_static) 1351 / 1387, 1952 / 1947, 2236 / 2246, 2979 / 2828, 5041 / 4887.  One tensor of 525 M 2754 / 2730, 2578 / 2598.
+constexpr int64_t kWideItemsElems = (int64_t)384 << 20;
 struct UpdateItems {
     int unroll, per_chunk;
 };
-constexpr UpdateItems update_items(int optimizer, int unroll, int split)
+constexpr UpdateItems update_items(int optimizer, int unroll, int split, int64_t elems)
 {
     const int least = default_unroll(optimizer);
-    if (unroll == 0) unroll = split != 0 && optimizer == ADAGC_OPT_ADAMW ? 4 : least;
+    if (unroll == 0) unroll = (split != 0 || elems >= kWideItemsElems) && optimizer == ADAGC_OPT_ADAMW ? 4 : least;
     return {unroll, split ? split : default_items(unroll > least ? unroll : least)};
 }
 

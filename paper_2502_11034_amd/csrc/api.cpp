@@ -32,11 +32,12 @@ struct adagc_ctx {
 
     // A run of tensors with a work table of its own (kGroupBytes)
     struct TensorGroup {
-        int64_t  first = 0, count = 0;
-        int64_t  elems = 0;
-        size_t   work_at = 0, items_at = 0;    // its places in the groups' tables
-        uint32_t n_chunks = 0, n_long = 0, n_short = 0, n_tiny = 0;
-        int      grid_norm = 0, grid_update = 0;
+        int64_t     first = 0, count = 0;
+        int64_t     elems = 0;
+        UpdateItems update{};
+        size_t      work_at = 0, items_at = 0;    // its places in the groups' tables
+        uint32_t    n_chunks = 0, n_long = 0, n_short = 0, n_tiny = 0;
+        int         grid_norm = 0, grid_update = 0;
     };
     std::vector<TensorGroup> tensor_groups;   // empty: the list is stepped as a whole
     const WorkRef* group_work = nullptr;      // device
@@ -217,29 +218,87 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     c->nontemporal = cfg->nontemporal == 2 ? 0 : 1;
     //  - work items of the update kernel: see default_unroll.
     // Both streaming kernels walk their work items b, b+grid, ..., so any grid size is valid.
-    const UpdateItems update = update_items(cfg->optimizer, cfg->unroll, cfg->update_split);
+    for (int64_t i = 0; i < n_tensors; ++i) c->total_elems += descs[i].numel;
+    const UpdateItems update = update_items(cfg->optimizer, cfg->unroll, cfg->update_split, c->total_elems);
     c->unroll = update.unroll;
     c->items_per_chunk = update.per_chunk;
     auto chunk_len = [&](size_t k) {
         const int64_t rest = c->numel[chunk_tensor[k]] - (int64_t)chunk_index[k] * kChunkElems;
         return rest < kChunkElems ? rest : (int64_t)kChunkElems;
     };
-    for (int64_t i = 0; i < n_tensors; ++i) c->total_elems += descs[i].numel;
-    const int short_items = most_short_items(n_tensors, c->total_elems, c->items_per_chunk);
-    auto kind_of = [&](size_t k) { return chunk_kind(chunk_len(k), c->items_per_chunk, c->unroll, short_items); };
-    int64_t n_long = 0, n_short = 0, n_tiny = 0;           // n_short: work items
-    for (size_t k = 0; k < chunk_tensor.size(); ++k) {
-        const ChunkKind kind = kind_of(k);
-        if (kind == kLongChunk) ++n_long;
-        else if (kind == kTinyChunk) ++n_tiny;
-        else n_short += chunk_items(chunk_len(k), c->items_per_chunk);
-    }
-    const int64_t tiles = count_work_items(n_long, n_short, n_tiny, c->items_per_chunk);
     auto grid_for = [cfg](int64_t items) {
         int64_t want = cfg->grid_blocks > 0 ? (int64_t)cfg->grid_blocks : items;
         if (want > items) want = items;
         return (int)(want > kMaxGridBlocks ? kMaxGridBlocks : want);
     };
+
+    // The chunks in visiting order (see adagc_build_visiting_order): the long ones, then the short and the tiny ones in list
+    // order; and the work items of the short ones.  Of chunks `from` to `to`, appended.
+    std::vector<WorkRef> work, items, group_work, group_items;
+    auto append_range = [&](size_t from, size_t to, std::vector<WorkRef>& to_work, std::vector<WorkRef>& to_items,
+                            adagc_ctx::TensorGroup& g) {
+        const int per_chunk = g.update.per_chunk, short_items = most_short_items(n_tensors, c->total_elems, per_chunk);
+        auto kind_of = [&](size_t k) { return chunk_kind(chunk_len(k), per_chunk, g.update.unroll, short_items); };
+        std::vector<uint32_t> longer, order;
+        for (size_t k = from; k < to; ++k)
+            if (kind_of(k) == kLongChunk) longer.push_back((uint32_t)k);
+        order.resize(longer.size());
+        int made = ADAGC_OK;
+        if (!longer.empty())
+            made = adagc_build_visiting_order((int64_t)longer.size(), cfg->schedule ? cfg->schedule : 2,
+                                              cfg->schedule_run ? cfg->schedule_run : 8, order.data());
+        if (made != ADAGC_OK) return made;
+        g.work_at = to_work.size();
+        g.items_at = to_items.size();
+        auto append = [&](uint32_t k) { to_work.push_back(WorkRef{chunk_tensor[k], k, chunk_index[k], (uint32_t)chunk_len(k)}); };
+        for (uint32_t o : order) append(longer[o]);
+        for (ChunkKind kind : {kShortChunk, kTinyChunk})
+            for (size_t k = from; k < to; ++k) {
+                if (kind_of(k) != kind) continue;
+                append((uint32_t)k);
+                if (kind == kTinyChunk) {
+                    ++g.n_tiny;
+                    continue;
+                }
+                for (int part = 0; part < chunk_items(chunk_len(k), per_chunk); ++part) {
+                    to_items.push_back(to_work.back());
+                    to_items.back().len |= (uint32_t)part << kPartShift;
+                }
+            }
+        g.n_chunks = (uint32_t)(to - from);
+        g.n_long = (uint32_t)longer.size();
+        g.n_short = (uint32_t)(to_items.size() - g.items_at);
+        g.grid_norm = grid_for((int64_t)g.n_chunks - g.n_tiny + (g.n_tiny + 3) / 4);
+        g.grid_update = grid_for(count_work_items(g.n_long, g.n_short, g.n_tiny, per_chunk));
+        return ADAGC_OK;
+    };
+    const int64_t grad_bytes = c->total_elems * (cfg->grad_dtype == ADAGC_GRAD_BF16 ? 2 : 4);
+    const bool grouped = grad_bytes >= kGroupedBytes && cfg->grid_blocks == 0 && cfg->optimizer != ADAGC_OPT_MUON && c->nontemporal &&
+                         !cfg->telemetry;
+    adagc_ctx::TensorGroup all;
+    try {
+        work.reserve(chunk_tensor.size());
+        all.update = update;
+        rc = append_range(0, chunk_tensor.size(), work, items, all);
+        if (rc == ADAGC_OK && grouped) {
+            const int64_t most = kGroupBytes / (cfg->grad_dtype == ADAGC_GRAD_BF16 ? 2 : 4);
+            group_work.reserve(chunk_tensor.size());
+            for (int64_t first = 0; rc == ADAGC_OK && first < n_tensors;) {
+                adagc_ctx::TensorGroup g;
+                g.first = first;
+                do {
+                    g.elems += descs[first++].numel;
+                    ++g.count;
+                } while (first < n_tensors && g.elems + descs[first].numel <= most);
+                g.update = update_items(cfg->optimizer, cfg->unroll, cfg->update_split, g.elems);
+                rc = append_range((size_t)c->chunk_begin[(size_t)g.first], (size_t)c->chunk_begin[(size_t)first], group_work, group_items, g);
+                c->tensor_groups.push_back(g);
+            }
+        }
+    } catch (const std::bad_alloc&) { rc = ADAGC_ERR_OOM; }
+    if (rc != ADAGC_OK) { free_ctx(c); return rc; }
+    const int64_t tiles = count_work_items(all.n_long, all.n_short, all.n_tiny, c->items_per_chunk);
+
     int64_t most_chunks = 0;
     for (int64_t i = 0; i < n_tensors; ++i) {
         const int64_t n = c->chunk_begin[(size_t)i + 1] - c->chunk_begin[(size_t)i];
@@ -252,7 +311,7 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
                             c->unroll == default_unroll(cfg->optimizer) && c->items_per_chunk == default_items(c->unroll) && c->nontemporal &&
                             !cfg->telemetry;
     if (one_launch) {
-        LaunchShape shape{n_long, n_short, n_tiny, 0, most_chunks, true};
+        LaunchShape shape{all.n_long, all.n_short, all.n_tiny, 0, most_chunks, true};
         for (int64_t i = 0; i < n_tensors; ++i) {
             shape.n_full += descs[i].numel / kChunkElems;
             shape.alone = shape.alone && descs[i].numel <= kChunkElems / c->items_per_chunk;
@@ -264,20 +323,16 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
         }
         c->one_launch = one_launch_pays(cfg->optimizer, cfg->grad_dtype == ADAGC_GRAD_BF16, shape, c->items_per_chunk, compute_units);
     }
-    c->grid_norm = grid_for(c->n_chunks - n_tiny + (n_tiny + 3) / 4);
+    c->grid_norm = all.grid_norm;
     c->n_items = tiles;
-    c->grid_update = grid_for(tiles);
-
-    const int64_t grad_bytes = c->total_elems * (cfg->grad_dtype == ADAGC_GRAD_BF16 ? 2 : 4);
-    const bool grouped = grad_bytes >= kGroupedBytes && cfg->grid_blocks == 0 && cfg->optimizer != ADAGC_OPT_MUON && c->nontemporal &&
-                         !cfg->telemetry;
+    c->grid_update = all.grid_update;
 
     // One slab, carved into 256-byte aligned arrays.
     const size_t nt = (size_t)n_tensors, nc = (size_t)c->n_chunks;
     size_t off = 0;
     auto carve = [&off](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
     const size_t o_work = carve(nc * sizeof(WorkRef));
-    const size_t o_items = carve((size_t)n_short * sizeof(WorkRef));
+    const size_t o_items = carve(items.size() * sizeof(WorkRef));
     const size_t o_targs = carve(nt * sizeof(TensorArgs));
     const size_t o_partials = carve(nc * sizeof(double));
     const size_t o_sumsq = carve(nt * sizeof(double));
@@ -302,8 +357,8 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     const size_t o_ucoef64 = carve(cfg->update_clipping ? nt * sizeof(double) : 0);
     const size_t o_words = carve(one_launch ? (2 * nc + nt) * sizeof(uint64_t) : 0);
     const size_t o_launches = carve(one_launch ? (size_t)tiles * kWavesPerBlock * sizeof(uint32_t) : 0);
-    const size_t o_group_work = carve(grouped ? nc * sizeof(WorkRef) : 0);
-    const size_t o_group_items = carve(grouped ? (size_t)n_short * sizeof(WorkRef) : 0);
+    const size_t o_group_work = carve(group_work.size() * sizeof(WorkRef));
+    const size_t o_group_items = carve(group_items.size() * sizeof(WorkRef));
     const size_t slab_bytes = off;
 
     hipError_t e = hipMalloc(&c->slab, slab_bytes);
@@ -311,77 +366,15 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     char* base = static_cast<char*>(c->slab);
     if (hipMemset(c->slab, 0, slab_bytes) != hipSuccess) { free_ctx(c); return ADAGC_ERR_HIP; }
 
-    // The chunks in visiting order (see adagc_build_visiting_order): the long ones, then the short and the tiny ones in list
-    // order; and the work items of the short ones.  Of chunks `from` to `to`, appended.
-    {
-        std::vector<WorkRef> work, items, group_work, group_items;
-        auto append_range = [&](size_t from, size_t to, std::vector<WorkRef>& to_work, std::vector<WorkRef>& to_items,
-                                adagc_ctx::TensorGroup& g) {
-            std::vector<uint32_t> longer, order;
-            for (size_t k = from; k < to; ++k)
-                if (kind_of(k) == kLongChunk) longer.push_back((uint32_t)k);
-            order.resize(longer.size());
-            int made = ADAGC_OK;
-            if (!longer.empty())
-                made = adagc_build_visiting_order((int64_t)longer.size(), cfg->schedule ? cfg->schedule : 2,
-                                                  cfg->schedule_run ? cfg->schedule_run : 8, order.data());
-            if (made != ADAGC_OK) return made;
-            g.work_at = to_work.size();
-            g.items_at = to_items.size();
-            auto append = [&](uint32_t k) { to_work.push_back(WorkRef{chunk_tensor[k], k, chunk_index[k], (uint32_t)chunk_len(k)}); };
-            for (uint32_t o : order) append(longer[o]);
-            for (ChunkKind kind : {kShortChunk, kTinyChunk})
-                for (size_t k = from; k < to; ++k) {
-                    if (kind_of(k) != kind) continue;
-                    append((uint32_t)k);
-                    if (kind == kTinyChunk) {
-                        ++g.n_tiny;
-                        continue;
-                    }
-                    for (int part = 0; part < chunk_items(chunk_len(k), c->items_per_chunk); ++part) {
-                        to_items.push_back(to_work.back());
-                        to_items.back().len |= (uint32_t)part << kPartShift;
-                    }
-                }
-            g.n_chunks = (uint32_t)(to - from);
-            g.n_long = (uint32_t)longer.size();
-            g.n_short = (uint32_t)(to_items.size() - g.items_at);
-            g.grid_norm = grid_for((int64_t)g.n_chunks - g.n_tiny + (g.n_tiny + 3) / 4);
-            g.grid_update = grid_for(count_work_items(g.n_long, g.n_short, g.n_tiny, c->items_per_chunk));
-            return ADAGC_OK;
-        };
-        try {
-            work.reserve(nc);
-            items.reserve((size_t)n_short);
-            adagc_ctx::TensorGroup all;
-            rc = append_range(0, nc, work, items, all);
-            if (rc == ADAGC_OK && grouped) {
-                const int64_t most = kGroupBytes / (cfg->grad_dtype == ADAGC_GRAD_BF16 ? 2 : 4);
-                group_work.reserve(nc);
-                group_items.reserve((size_t)n_short);
-                for (int64_t first = 0; rc == ADAGC_OK && first < n_tensors;) {
-                    adagc_ctx::TensorGroup g;
-                    g.first = first;
-                    do {
-                        g.elems += descs[first++].numel;
-                        ++g.count;
-                    } while (first < n_tensors && g.elems + descs[first].numel <= most);
-                    rc = append_range((size_t)c->chunk_begin[(size_t)g.first], (size_t)c->chunk_begin[(size_t)first], group_work, group_items, g);
-                    c->tensor_groups.push_back(g);
-                }
-            }
-        } catch (const std::bad_alloc&) { rc = ADAGC_ERR_OOM; }
-        if (rc != ADAGC_OK) { free_ctx(c); return rc; }
-        auto upload = [&](size_t to, const std::vector<WorkRef>& from) {
-            return from.empty() || hipMemcpy(base + to, from.data(), from.size() * sizeof(WorkRef), hipMemcpyHostToDevice) == hipSuccess;
-        };
-        if (!upload(o_work, work) || !upload(o_items, items) || !upload(o_group_work, group_work) || !upload(o_group_items, group_items)) {
-            free_ctx(c);
-            return ADAGC_ERR_HIP;
-        }
-        c->group_work = reinterpret_cast<const WorkRef*>(base + o_group_work);
-        c->group_items = reinterpret_cast<const WorkRef*>(base + o_group_items);
+    auto upload = [&](size_t to, const std::vector<WorkRef>& from) {
+        return from.empty() || hipMemcpy(base + to, from.data(), from.size() * sizeof(WorkRef), hipMemcpyHostToDevice) == hipSuccess;
+    };
+    if (!upload(o_work, work) || !upload(o_items, items) || !upload(o_group_work, group_work) || !upload(o_group_items, group_items)) {
+        free_ctx(c);
+        return ADAGC_ERR_HIP;
     }
+    c->group_work = reinterpret_cast<const WorkRef*>(base + o_group_work);
+    c->group_items = reinterpret_cast<const WorkRef*>(base + o_group_items);
     const size_t staging_bytes = adagc_ctx::kStagingSlots * nt * sizeof(TensorArgs);
     const size_t status_at = staging_bytes + align_up(c->results_bytes, 64);
     if (hipHostMalloc(reinterpret_cast<void**>(&c->staging), status_at + sizeof(int32_t), hipHostMallocDefault) != hipSuccess) {
@@ -417,9 +410,9 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     t.ucoef64 = cfg->update_clipping ? reinterpret_cast<double*>(base + o_ucoef64) : nullptr;
     if (one_launch) c->exchange = {reinterpret_cast<uint64_t*>(base + o_words), reinterpret_cast<uint32_t*>(base + o_launches), kPolls};
     t.n_chunks = (uint32_t)c->n_chunks;
-    t.n_long = (uint32_t)n_long;
-    t.n_short = (uint32_t)n_short;
-    t.n_tiny = (uint32_t)n_tiny;
+    t.n_long = all.n_long;
+    t.n_short = all.n_short;
+    t.n_tiny = all.n_tiny;
     t.n_tensors = (uint32_t)c->n_tensors;
 
     *out = c;
@@ -562,7 +555,7 @@ extern "C" int adagc_step(adagc_ctx* ctx, void* const* params, const void* const
             t.n_tiny = g.n_tiny;
             if (launch_sumsq_partials(t, bf16g, stream_gradients(g.elems, bf16g), g.grid_norm, stream) != hipSuccess ||
                 launch_tensor_rules(t, ema_norms, r, (uint32_t)g.first, (uint32_t)g.count, stream) != hipSuccess ||
-                launch_update(t, u, ctx->cfg.optimizer, bf16g, copy, ctx->unroll, ctx->items_per_chunk, ctx->nontemporal, 0, g.grid_update,
+                launch_update(t, u, ctx->cfg.optimizer, bf16g, copy, g.update.unroll, g.update.per_chunk, ctx->nontemporal, 0, g.grid_update,
                               stream) != hipSuccess)
                 return ADAGC_ERR_HIP;
         }

@@ -156,7 +156,6 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
     if (n_tensors > (int64_t)kMaxT) return ADAGC_ERR_TOO_LARGE;
 
     // Everything is validated before anything is enqueued.
-    const int unroll = default_unroll(cfg->optimizer), items_per_chunk = default_items(unroll);
     uint64_t n_chunks = 0, n_long = 0, n_short = 0, n_tiny = 0;          // n_short: work items
     int64_t total_elems = 0, n_full = 0, largest = 0;
     for (int64_t i = 0; i < n_tensors; ++i) {
@@ -169,6 +168,8 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
         n_full += descs[i].numel / kChunkElems;
         total_elems += descs[i].numel;
     }
+    const UpdateItems update = update_items(cfg->optimizer, 0, 0, total_elems);
+    const int unroll = update.unroll, items_per_chunk = update.per_chunk;
     const int short_items = most_short_items(n_tensors, total_elems, items_per_chunk);
     // the kind of tensor i's last chunk (all others are long)
     auto last_len = [&](int64_t i) { return (descs[i].numel - 1) % kChunkElems + 1; };

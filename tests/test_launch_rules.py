@@ -79,6 +79,17 @@ UPDATE_ITEMS = [(ADAMW, 0, 0, 2, 8), (ADAMW, 0, 1, 4, 1), (ADAMW, 0, 2, 4, 2), (
 
 
 def test_a_chosen_split_has_the_vectors_in_flight_that_suit_it(tmp_path):
-    out = subprocess.run([_driver(tmp_path, "update_items_check")], input="\n".join("%d %d %d" % x[:3] for x in UPDATE_ITEMS) + "\n",
+    asked = [x[:3] + (1 << 20,) for x in UPDATE_ITEMS]
+    out = subprocess.run([_driver(tmp_path, "update_items_check")], input="\n".join("%d %d %d %d" % x for x in asked) + "\n",
                          capture_output=True, text=True, check=True, timeout=60).stdout
     assert [tuple(map(int, line.split())) for line in out.splitlines()] == [x[3:] + ((16 if x[0] == LION else 32) << 20,) for x in UPDATE_ITEMS]
+
+
+def test_the_largest_launches_have_larger_items(tmp_path):
+    """From 384 Mi elements AdamW has 4 vectors in flight and items of 4096 elements, unless the caller chooses."""
+    at = 384 << 20
+    asked = [(ADAMW, 0, 0, at - 1, 2, 8), (ADAMW, 0, 0, at, 4, 4), (ADAMW, 0, 0, 1 << 34, 4, 4), (ADAMW, 2, 0, at, 2, 8), (ADAMW, 0, 2, at, 4, 2),
+             (ADAMW, 1, 0, at, 1, 8), (LION, 0, 0, 1 << 34, 2, 8)]
+    out = subprocess.run([_driver(tmp_path, "update_items_check")], input="\n".join("%d %d %d %d" % x[:4] for x in asked) + "\n",
+                         capture_output=True, text=True, check=True, timeout=60).stdout
+    assert [tuple(map(int, line.split()))[:2] for line in out.splitlines()] == [x[4:] for x in asked]

@@ -1,4 +1,4 @@
-// Host-only driver of tests/test_launch_rules.py: update_items (csrc/adagc_internal.h) for lines of optimizer, unroll and update_split on stdin;
+// Host-only driver of tests/test_launch_rules.py: update_items (csrc/adagc_internal.h) for lines of optimizer, unroll, update_split and elements on stdin;
 // prints the vectors in flight, the work items of a chunk and the most elements in full ones of a list whose rule is in the update kernel.
 #include <cstdio>
 
@@ -7,8 +7,9 @@
 int main()
 {
     int optimizer, unroll, split;
-    while (std::scanf("%d %d %d", &optimizer, &unroll, &split) == 3) {
-        const adagc::UpdateItems u = adagc::update_items(optimizer, unroll, split);
+    long long elems;
+    while (std::scanf("%d %d %d %lld", &optimizer, &unroll, &split, &elems) == 4) {
+        const adagc::UpdateItems u = adagc::update_items(optimizer, unroll, split, elems);
         std::printf("%d %d %lld\n", u.unroll, u.per_chunk,
                     (long long)(adagc::fused_max_items(optimizer, u.per_chunk) * (adagc::kChunkElems / u.per_chunk)));
     }
