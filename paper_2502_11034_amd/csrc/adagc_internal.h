@@ -167,8 +167,8 @@ enum ChunkKind { kLongChunk, kShortChunk, kTinyChunk };
 constexpr int kTinyMax = 1024;             // the norm kernel's round for one wave
 __host__ __device__ inline int chunk_items(int64_t len, int items_per_chunk)
 {
-    const int64_t item = kChunkElems / items_per_chunk;
-    return (int)((len + item - 1) / item);
+    // = len / (kChunkElems / items_per_chunk) rounded up, without the divisions, which adagc_step_static would have several of per tensor
+    return (int)(((uint64_t)len * (uint32_t)items_per_chunk + kChunkElems - 1) / kChunkElems);
 }
 __host__ __device__ inline ChunkKind chunk_kind(int64_t len, int items_per_chunk, int unroll, int short_items)
 {

@@ -162,21 +162,21 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
         if (descs[i].numel <= 0 || descs[i].flags != 0 || descs[i].reserved != 0) return ADAGC_ERR_INVALID_ARG;
         if (!params[i] || !grads[i] || !exp_avg[i] || (adamw && !exp_avg_sq[i]) || (copy && !params_bf16[i]))
             return ADAGC_ERR_INVALID_ARG;
-        n_chunks += (uint64_t)((descs[i].numel + kChunkElems - 1) / kChunkElems);
+        n_chunks += ((uint64_t)descs[i].numel + kChunkElems - 1) / kChunkElems;
         if (n_chunks > (uint64_t)kMaxC) return ADAGC_ERR_TOO_LARGE;
         if (descs[i].numel > largest) largest = descs[i].numel;
-        n_full += descs[i].numel / kChunkElems;
+        n_full += (int64_t)((uint64_t)descs[i].numel / kChunkElems);
         total_elems += descs[i].numel;
     }
     const UpdateItems update = update_items(cfg->optimizer, 0, 0, total_elems);
     const int unroll = update.unroll, items_per_chunk = update.per_chunk;
     const int short_items = most_short_items(n_tensors, total_elems, items_per_chunk);
     // the kind of tensor i's last chunk (all others are long)
-    auto last_len = [&](int64_t i) { return (descs[i].numel - 1) % kChunkElems + 1; };
+    auto last_len = [&](int64_t i) { return (int64_t)((uint64_t)(descs[i].numel - 1) % kChunkElems) + 1; };
     auto last_kind = [&](int64_t i) { return chunk_kind(last_len(i), items_per_chunk, unroll, short_items); };
     for (int64_t i = 0; i < n_tensors; ++i) {
         const ChunkKind kind = last_kind(i);
-        n_long += (uint64_t)((descs[i].numel - 1) / kChunkElems) + (kind == kLongChunk ? 1 : 0);
+        n_long += (uint64_t)(descs[i].numel - 1) / kChunkElems + (kind == kLongChunk ? 1 : 0);
         n_short += kind == kShortChunk ? (uint64_t)chunk_items(last_len(i), items_per_chunk) : 0;
         n_tiny += kind == kTinyChunk ? 1 : 0;
     }
@@ -257,7 +257,7 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
             a.line_offset = may_walk ? line_offset_of(a) : 0u;
             if (a.line_offset) off_lines += descs[i].numel;
             const ChunkKind kind = last_kind(i);
-            const uint32_t chunks = (uint32_t)((descs[i].numel + kChunkElems - 1) / kChunkElems);
+            const uint32_t chunks = (uint32_t)(((uint64_t)descs[i].numel + kChunkElems - 1) / kChunkElems);
             batch.t[b] = TensorInBatch{a.param, a.grad, a.exp_avg, a.exp_avg_sq, a.param_copy,
                                        (uint64_t)descs[i].numel | (uint64_t)a.vec_ok << kVecOkBit | (uint64_t)a.line_offset << kLineOffsetBit,
                                        chunk_begin, long_at,
