@@ -394,9 +394,10 @@ def main():
                        "update_median": round(float(np.median(per_kernel[:, 2])), 4),
                        "update_min": round(float(per_kernel[:, 2].min()), 4),
                        "update_max": round(float(per_kernel[:, 2].max()), 4)},
+        "kernels_ms_are": "means of as many profiled steps after the timed ones; those take the list as a whole, the timed ones in groups of tensors if it is large",
         "norm_kernel_gbps": round(norm_gbps, 1),
         "tensors_clipped_last_step": int(flags.sum()),
-        "roofline": {"kernel": "update_kernel", "bound": "hbm", "achieved": round(upd_gbps, 1),
+        "roofline": {"kernel": "update_kernel", "of": "profiled steps, see kernels_ms_are", "bound": "hbm", "achieved": round(upd_gbps, 1),
                      "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": round(upd_gbps / HBM_PEAK_GBPS, 4),
                      "traffic": measured_traffic(args.workload, "update_kernel")},
     }

@@ -107,7 +107,8 @@ typedef struct {
                                      b, b+grid, ...; default: one work item per workgroup (a chunk in the
                                      norm kernel; a chunk or a part of one in the update kernel) */
     int32_t unroll;               /* 128-bit vectors per lane per array kept in flight by the update kernel:
-                                     1, 2 or 4 (default: 2) */
+                                     1, 2 or 4 (default: 2; AdamW 4 with a chosen
+                                     update_split and on launches of 384 Mi elements or more) */
     int32_t nontemporal;          /* streaming (non-temporal) loads and stores of the update kernel, and of the norm kernel
                                      on lists with more than 8 GiB of gradients: 1 = on (default), 2 = off */
     int32_t schedule;             /* visiting order of the chunks, see adagc_build_visiting_order: number of
@@ -115,7 +116,7 @@ typedef struct {
     int32_t update_split;         /* work items of the update kernel per chunk: 1 = whole chunks, or 2, 4, ...
                                      up to chunk_elems / (unroll*1024), chunk_elems / 4096 where unroll
                                      is 0.  Default (0): 2048-element items
-                                     (with unroll 4: 4096)
+                                     (with 4 vectors in flight: 4096)
                                      (small items shorten the tail of the launch and give short lists more
                                      workgroups; whole chunks cost the fewest dispatches) */
     int32_t schedule_run;         /* visiting order: chunks an XCD takes in a row (default 8) */
@@ -336,6 +337,9 @@ int adagc_get_segment_table(adagc_ctx* ctx, int64_t* chunk_begin, uint32_t* chun
  * milliseconds (norm, finalize, update; finalize is next to nothing on small lists, whose rule is part
  * of the update kernel) to ms (HOST float[3*max_steps]), the
  * number of recorded steps to n_steps, and releases the events.
+ * Profiled steps take the list as a whole, with the same results: large lists, which are otherwise
+ * stepped in groups of tensors, take longer, and the smallest ones, otherwise a single launch, have
+ * a norm kernel of their own.
  */
 int adagc_profile_begin(adagc_ctx* ctx, int32_t max_steps);
 int adagc_profile_end(adagc_ctx* ctx, float* ms, int32_t* n_steps);
