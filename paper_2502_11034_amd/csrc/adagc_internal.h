@@ -138,9 +138,11 @@ struct DeviceTables {
 constexpr int default_unroll(int) { return 2; }
 constexpr int default_items(int unroll) { return kVecPerLane >= unroll ? kVecPerLane / unroll : 1; }
 
-// What adagc_config's unroll and update_split (0: the library's choice) make of a list.  Where only the split is chosen, items have 4096
-// elements or more, and AdamW's 4 vectors of each array in flight: us per step with split 4, 2 / 4 vectors: GPT-2-small 654 / 628, with bf16
-// gradients and the copy 620 / 597; 271 M parameters 1434 / 1384, 1372 / 1318.
+// What adagc_config's unroll, update_split and grid_blocks (0: the library's choice) make of a list.  Where only the split is chosen, items
+// have 4096 elements or more, and AdamW's 4 vectors of each array in flight: us per step with split 4, 2 / 4 vectors: GPT-2-small 654 / 628,
+// with bf16 gradients and the copy 620 / 597; 271 M parameters 1434 / 1384, 1372 / 1318.  A workgroup that walks many items has 4 vectors and
+// items of 4096 too, as it fetches one after the other: GPT-2-small with 160, 1024 and 16384 workgroups, 2 and 2048 / 4 and 4096: 906 / 762,
+// 721 / 691, 662 / 657, bf16 and the copy 991 / 774, 694 / 664, 645 / 625 (320: 784 / 827, 770 / 811; lists of 64 M 444 / 446, 475 / 478).
 // The largest launches (elems: the list's, or a group's: see kGroupBytes) have AdamW's 4 vectors and items of 4096, as those wait least on
 // DRAM rows that others have closed.  us per step taken whole, Llama shapes, 2 and 2048 / 4 and 4096: f32 271 M parameters 1374 / 1382, 374 M
 // 1975 / 1953, 423 M 2251 / 2229, 536 M 2828 / 2818, 941 M 5300 / 5164; bf16 and the copy 1306 / 1312, 1870 / 1854, 2136 / 2090, 2667 / 2642, 4893 / 4737;
@@ -149,10 +151,10 @@ constexpr int64_t kWideItemsElems = (int64_t)384 << 20;
 struct UpdateItems {
     int unroll, per_chunk;
 };
-constexpr UpdateItems update_items(int optimizer, int unroll, int split, int64_t elems)
+constexpr UpdateItems update_items(int optimizer, int unroll, int split, int grid_blocks, int64_t elems)
 {
     const int least = default_unroll(optimizer);
-    if (unroll == 0) unroll = (split != 0 || elems >= kWideItemsElems) && optimizer == ADAGC_OPT_ADAMW ? 4 : least;
+    if (unroll == 0) unroll = (split != 0 || grid_blocks != 0 || elems >= kWideItemsElems) && optimizer == ADAGC_OPT_ADAMW ? 4 : least;
     return {unroll, split ? split : default_items(unroll > least ? unroll : least)};
 }
 

@@ -219,7 +219,7 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
     //  - work items of the update kernel: see default_unroll.
     // Both streaming kernels walk their work items b, b+grid, ..., so any grid size is valid.
     for (int64_t i = 0; i < n_tensors; ++i) c->total_elems += descs[i].numel;
-    const UpdateItems update = update_items(cfg->optimizer, cfg->unroll, cfg->update_split, c->total_elems);
+    const UpdateItems update = update_items(cfg->optimizer, cfg->unroll, cfg->update_split, cfg->grid_blocks, c->total_elems);
     c->unroll = update.unroll;
     c->items_per_chunk = update.per_chunk;
     auto chunk_len = [&](size_t k) {
@@ -290,7 +290,7 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
                     g.elems += descs[first++].numel;
                     ++g.count;
                 } while (first < n_tensors && g.elems + descs[first].numel <= most);
-                g.update = update_items(cfg->optimizer, cfg->unroll, cfg->update_split, g.elems);
+                g.update = update_items(cfg->optimizer, cfg->unroll, cfg->update_split, cfg->grid_blocks, g.elems);
                 rc = append_range((size_t)c->chunk_begin[(size_t)g.first], (size_t)c->chunk_begin[(size_t)first], group_work, group_items, g);
                 c->tensor_groups.push_back(g);
             }

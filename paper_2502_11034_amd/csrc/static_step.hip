@@ -168,7 +168,7 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
         n_full += (int64_t)((uint64_t)descs[i].numel / kChunkElems);
         total_elems += descs[i].numel;
     }
-    const UpdateItems update = update_items(cfg->optimizer, 0, 0, total_elems);
+    const UpdateItems update = update_items(cfg->optimizer, 0, 0, 0, total_elems);
     const int unroll = update.unroll, items_per_chunk = update.per_chunk;
     const int short_items = most_short_items(n_tensors, total_elems, items_per_chunk);
     // the kind of tensor i's last chunk (all others are long)

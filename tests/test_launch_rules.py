@@ -72,24 +72,29 @@ def test_whole_lines_with_the_vectors_in_flight_that_a_library_ever_chose(tmp_pa
     assert out.split("\n")[:2] == ["0 1 1", "0 1 0"]
 
 
-# optimizer, unroll, update_split: vectors in flight, work items of a chunk
-UPDATE_ITEMS = [(ADAMW, 0, 0, 2, 8), (ADAMW, 0, 1, 4, 1), (ADAMW, 0, 2, 4, 2), (ADAMW, 0, 4, 4, 4), (ADAMW, 4, 0, 4, 4), (ADAMW, 2, 0, 2, 8),
-                (ADAMW, 1, 0, 1, 8), (ADAMW, 2, 4, 2, 4), (ADAMW, 1, 16, 1, 16), (LION, 0, 0, 2, 8), (LION, 0, 4, 2, 4), (LION, 0, 1, 2, 1),
-                (LION, 4, 0, 4, 4), (LION, 1, 16, 1, 16)]
+# optimizer, unroll, update_split, grid_blocks: vectors in flight, work items of a chunk
+UPDATE_ITEMS = [(ADAMW, 0, 0, 0, 2, 8), (ADAMW, 0, 1, 0, 4, 1), (ADAMW, 0, 2, 0, 4, 2), (ADAMW, 0, 4, 0, 4, 4), (ADAMW, 4, 0, 0, 4, 4),
+                (ADAMW, 2, 0, 0, 2, 8), (ADAMW, 1, 0, 0, 1, 8), (ADAMW, 2, 4, 0, 2, 4), (ADAMW, 1, 16, 0, 1, 16), (ADAMW, 0, 0, 320, 4, 4),
+                (ADAMW, 2, 0, 320, 2, 8), (ADAMW, 0, 2, 320, 4, 2), (LION, 0, 0, 0, 2, 8), (LION, 0, 4, 0, 2, 4), (LION, 0, 1, 0, 2, 1),
+                (LION, 4, 0, 0, 4, 4), (LION, 1, 16, 0, 1, 16), (LION, 0, 0, 320, 2, 8)]
 
 
-def test_a_chosen_split_has_the_vectors_in_flight_that_suit_it(tmp_path):
-    asked = [x[:3] + (1 << 20,) for x in UPDATE_ITEMS]
-    out = subprocess.run([_driver(tmp_path, "update_items_check")], input="\n".join("%d %d %d %d" % x for x in asked) + "\n",
+def _update_items(tmp_path, asked):
+    """Per line (optimizer, unroll, update_split, grid_blocks, elements): vectors in flight, work items of a chunk, and the most elements in
+    full items of a list whose rule is in the update kernel."""
+    out = subprocess.run([_driver(tmp_path, "update_items_check")], input="\n".join("%d %d %d %d %d" % x for x in asked) + "\n",
                          capture_output=True, text=True, check=True, timeout=60).stdout
-    assert [tuple(map(int, line.split())) for line in out.splitlines()] == [x[3:] + ((16 if x[0] == LION else 32) << 20,) for x in UPDATE_ITEMS]
+    return [tuple(map(int, line.split())) for line in out.splitlines()]
+
+
+def test_a_chosen_split_or_grid_has_the_vectors_in_flight_that_suit_it(tmp_path):
+    got = _update_items(tmp_path, [x[:4] + (1 << 20,) for x in UPDATE_ITEMS])
+    assert got == [x[4:] + ((16 if x[0] == LION else 32) << 20,) for x in UPDATE_ITEMS]
 
 
 def test_the_largest_launches_have_larger_items(tmp_path):
     """From 384 Mi elements AdamW has 4 vectors in flight and items of 4096 elements, unless the caller chooses."""
     at = 384 << 20
-    asked = [(ADAMW, 0, 0, at - 1, 2, 8), (ADAMW, 0, 0, at, 4, 4), (ADAMW, 0, 0, 1 << 34, 4, 4), (ADAMW, 2, 0, at, 2, 8), (ADAMW, 0, 2, at, 4, 2),
-             (ADAMW, 1, 0, at, 1, 8), (LION, 0, 0, 1 << 34, 2, 8)]
-    out = subprocess.run([_driver(tmp_path, "update_items_check")], input="\n".join("%d %d %d %d" % x[:4] for x in asked) + "\n",
-                         capture_output=True, text=True, check=True, timeout=60).stdout
-    assert [tuple(map(int, line.split()))[:2] for line in out.splitlines()] == [x[4:] for x in asked]
+    asked = [(ADAMW, 0, 0, 0, at - 1, 2, 8), (ADAMW, 0, 0, 0, at, 4, 4), (ADAMW, 0, 0, 0, 1 << 34, 4, 4), (ADAMW, 2, 0, 0, at, 2, 8),
+             (ADAMW, 0, 2, 0, at, 4, 2), (ADAMW, 1, 0, 0, at, 1, 8), (LION, 0, 0, 0, 1 << 34, 2, 8)]
+    assert [x[:2] for x in _update_items(tmp_path, [x[:5] for x in asked])] == [x[5:] for x in asked]
