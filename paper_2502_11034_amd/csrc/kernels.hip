@@ -802,11 +802,13 @@ void update_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items, const Step
         const int64_t first = first_element(c);
         const TensorArgs ta = load_tensor(t.targs, tensor);
         // the tensor's coefficient as computed, in double
-        const bool rule_here = RULE == kRuleYes || (RULE == kRuleAsk && rule.ema);
         double h = 1.0;
         RuleInputs rule_inputs{0.0, 0.f};
-        if (rule_here) rule_inputs = load_rule_inputs(t, tensor, ta);
-        else if constexpr (RULE != kRuleOne) h = uniform_load(t.coef64 + tensor);
+        if constexpr (RULE == kRuleYes) rule_inputs = load_rule_inputs(t, tensor, ta);
+        if constexpr (RULE == kRuleAsk)        // (before the elements: a branch between their loads and their use costs more, where the rule has run)
+            h = rule.ema ? rule_in_update(t, rule, tensor, load_rule_inputs(t, tensor, ta), c.index == 0 && first_tile == 0 && lane == 0)
+                         : uniform_load(t.coef64 + tensor);
+        if constexpr (RULE == kRuleNo) h = uniform_load(t.coef64 + tensor);
         auto evaluate_rule = [&]() __attribute__((always_inline)) {
             if constexpr (RULE == kRuleOne) {
                 const gcbytes chunk = grad_at<BF16G>(ta.grad, first);
@@ -832,7 +834,7 @@ void update_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items, const Step
                     h = one_sums[kWavesPerBlock];
                 }
             }
-            if (rule_here) h = rule_in_update(t, rule, tensor, rule_inputs, c.index == 0 && first_tile == 0 && lane == 0);
+            if constexpr (RULE == kRuleYes) h = rule_in_update(t, rule, tensor, rule_inputs, c.index == 0 && first_tile == 0 && lane == 0);
         };
         const double uc = a.update_clip ? uniform_load(t.ucoef64 + tensor) : 1.0;   // update clipping: scales the direction
         const gcbytes g = grad_at<BF16G>(ta.grad, first);
