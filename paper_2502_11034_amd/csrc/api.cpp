@@ -305,7 +305,7 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
         if (n > most_chunks) most_chunks = n;
     }
     c->stream_grads = c->nontemporal && stream_gradients(c->total_elems, cfg->grad_dtype == ADAGC_GRAD_BF16);
-    c->small_list = tiles <= fused_max_items(cfg->optimizer, c->items_per_chunk) && most_chunks <= kFusedMaxChunks;
+    c->small_list = tiles <= fused_max_items(cfg->optimizer, c->items_per_chunk, cfg->grid_blocks) && most_chunks <= kFusedMaxChunks;
     // (with the library's own choice of work items, a workgroup for each)
     const bool one_launch = c->small_list && tiles <= kOneLaunchItems && cfg->grid_blocks == 0 && cfg->optimizer != ADAGC_OPT_MUON &&
                             c->unroll == default_unroll(cfg->optimizer) && c->items_per_chunk == default_items(c->unroll) && c->nontemporal &&

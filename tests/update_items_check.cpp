@@ -12,7 +12,7 @@ int main()
     while (std::scanf("%d %d %d %d %lld", &optimizer, &unroll, &split, &grid, &elems) == 5) {
         const adagc::UpdateItems u = adagc::update_items(optimizer, unroll, split, grid, elems);
         std::printf("%d %d %lld\n", u.unroll, u.per_chunk,
-                    (long long)(adagc::fused_max_items(optimizer, u.per_chunk) * (adagc::kChunkElems / u.per_chunk)));
+                    (long long)(adagc::fused_max_items(optimizer, u.per_chunk, grid) * (adagc::kChunkElems / u.per_chunk)));
     }
     return 0;
 }
