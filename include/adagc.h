@@ -108,7 +108,7 @@ typedef struct {
                                      norm kernel; a chunk or a part of one in the update kernel) */
     int32_t unroll;               /* 128-bit vectors per lane per array kept in flight by the update kernel:
                                      1, 2 or 4 (default: 2; AdamW 4 with a chosen
-                                     update_split or grid_blocks and on launches of 384 Mi elements
+                                     update_split or grid_blocks and on launches of 200 Mi elements
                                      or more) */
     int32_t nontemporal;          /* streaming (non-temporal) loads and stores of the update kernel, and of the norm kernel
                                      on lists with more than 8 GiB of gradients: 1 = on (default), 2 = off */

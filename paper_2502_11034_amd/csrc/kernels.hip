@@ -7,9 +7,9 @@
 //                           model's norm; "Ablation Study", Sec. 5.6), ZClip
 //   global_rule_kernel / finalize_global_kernel
 //                           those model-wide rules on long lists
-//   update_kernel           per work item (an eighth of a chunk; chunks of up to 512 elements go four to a workgroup):
-//                           clipped gradient into AdamW / Lion  (Alg. 1); small lists with the per-tensor rule inside, the
-//                           smallest with the norms as well
+//   update_kernel           per work item (an eighth of a chunk, a quarter in AdamW's largest launches; chunks of up to 512, 1024,
+//                           elements go four to a workgroup): clipped gradient into AdamW / Lion  (Alg. 1); small lists with the
+//                           per-tensor rule inside, the smallest with the norms as well
 //   tensor_rules_kernel     the per-tensor rule of a group of a large list's tensors
 //   direction_stats_kernel / finalize_update_clip_kernel
 //                           update clipping (AGC and Clippy rows of Table 2): norms of theta and of the
@@ -763,12 +763,13 @@ __device__ __forceinline__ void wait_for_loads()
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// Waves per SIMD that the update kernel may have in flight.  (A single launch, of a round of workgroups at most, has the registers of two.)  With 4 vectors of each array one wave holds 16 loads of 1 KiB, so two
-// are enough to cover the latency, and more only open more DRAM rows at once: AdamW on GPT-2-small shapes 657 us per step with 2, 667
-// with 3, 670 with 4 (Llama-3-8B shapes 10.75, 10.90, 10.87 ms for 4 layers).  With 2 vectors AdamW has 4: 5000 small tensors 94 us with 4, 98
-// with 3; GPT-2-small 616 - 630, 622; 133 M parameters with bf16 gradients and copies 630, 640 (ragged tensors end to end 2085, 2035).  Lion
-// has fewer arrays in flight and wants 3: GPT-2-small shapes 476 us with 2, 448 with 3, 448 with 4; 1500 ragged tensors 1518, 1450,
-// 1495; Llama-3-8B shapes with bf16 gradients and copies 7.10, 6.65, 6.97 ms (5000 small tensors 88, 77, 72 us).
+// Waves per SIMD that the update kernel may have in flight.  With 4 vectors of each array one wave holds 16 loads of 1 KiB, so two are
+// enough to cover the latency, and more only open more DRAM rows at once: AdamW on GPT-2-small shapes 657 us per step with 2, 667 with
+// 3, 670 with 4 (Llama-3-8B shapes 10.75, 10.90, 10.87 ms for 4 layers).  With 2 vectors AdamW has 4: 5000 small tensors 94 us with 4,
+// 98 with 3; GPT-2-small 616 - 630, 622; 133 M parameters with bf16 gradients and copies 630, 640 (ragged tensors end to end 2085,
+// 2035).  Lion has fewer arrays in flight and wants 3: GPT-2-small shapes 476 us with 2, 448 with 3, 448 with 4; 1500 ragged tensors
+// 1518, 1450, 1495; Llama-3-8B shapes with bf16 gradients and copies 7.10, 6.65, 6.97 ms (5000 small tensors 88, 77, 72 us).  A single
+// launch, of a round of workgroups at most, has the registers of two.
 template <int OPT, int U>
 constexpr int kUpdateWaves = OPT == ADAGC_OPT_ADAMW ? (U == 4 ? 2 : 4) : 3;
 
@@ -777,7 +778,8 @@ constexpr int kUpdateWaves = OPT == ADAGC_OPT_ADAMW ? (U == 4 ? 2 : 4) : 3;
 enum RuleHere { kRuleNo, kRuleYes, kRuleAsk, kRuleOne };
 
 template <int OPT, bool BF16G, bool COPY, int U, bool NT, bool TELE, bool LINES, RuleHere RULE>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RULE == kRuleOne ? 2 : kUpdateWaves<OPT, U>, RULE == kRuleOne ? 2 : kUpdateWaves<OPT, U>)))
+__global__ __launch_bounds__(kBlock)
+__attribute__((amdgpu_waves_per_eu(RULE == kRuleOne ? 2 : kUpdateWaves<OPT, U>, RULE == kRuleOne ? 2 : kUpdateWaves<OPT, U>)))
 void update_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items, const StepScalars* device_scalars, FusedRule rule, Exchange exchange)
 {
     static_assert(kVecPerLane % U == 0, "a chunk is a whole number of tiles");
@@ -991,7 +993,8 @@ void update_kernel(DeviceTables t, UpdateArgs a, uint32_t log2_items, const Step
 // Update clipping (AGC and Clippy rows of Table 2).  The coefficient of a tensor's update needs the norms
 // of theta and of the whole tensor's direction Delta, so the direction is evaluated twice: here for its
 // norms (nothing is written but two partial results per work item), then by update_kernel, which scales it.
-// Work items are those of update_kernel, or several of them (log2_stats_items).  LINF selects maxima of |.| (Clippy) instead of sums of squares (AGC).
+// Work items are those of update_kernel, or several of them (log2_stats_items).  LINF selects maxima of |.| (Clippy) instead of sums of
+// squares (AGC).
 
 // All 64 lanes must be active.  Returns the same value in every lane.  Maxima are exact in any order.
 __device__ __forceinline__ double wave_max_f64(double x)
@@ -1031,8 +1034,8 @@ __device__ __forceinline__ void stat_acc(double (&acc)[2], float theta, double d
     }
 }
 
-// Vectors per lane and array in flight.  AdamW: 4, as the update kernel once had; with its 2 and 2048 elements at a time
-// 133 M parameters under AGC take 932 us per step, so 919.
+// Vectors per lane and array in flight.  AdamW: 4 whatever the update kernel has; with 2, and 2048 elements at a time, 133 M
+// parameters under AGC take 932 us per step, so 919.
 template <int OPT>
 constexpr int kStatsUnroll = OPT == ADAGC_OPT_ADAMW ? 4 : 2;
 
@@ -1123,7 +1126,8 @@ __global__ __launch_bounds__(kBlock) void direction_stats_kernel(DeviceTables t,
             }
         }
 
-        // every item writes its two slots; those that a chunk of one item has no item for stay zero from the start
+        // every item writes its two slots, a long chunk's those of the first of the update kernel's items that it covers; the others are
+        // never written and zero since the context's creation, which adds nothing to either norm
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             const double part = LINF ? wave_max_f64(acc[q]) : wave_sum_f64(acc[q]);
@@ -1218,7 +1222,9 @@ UpdateFn select_update_variant(int unroll, int nt, int tele, bool lines, bool ru
     if (one) return update_kernel<OPT, BF16G, COPY, default_unroll(OPT), true, false, false, kRuleOne>;
     static_assert(default_unroll(OPT) == 2, "the kernels below");
     if constexpr (OPT == ADAGC_OPT_ADAMW)
-        if (unroll == 4) return rule ? select_update_flags<OPT, BF16G, COPY, 4, kRuleYes>(nt, tele, lines) : select_update_flags<OPT, BF16G, COPY, 4, kRuleNo>(nt, tele, lines);
+        if (unroll == 4)
+            return rule ? select_update_flags<OPT, BF16G, COPY, 4, kRuleYes>(nt, tele, lines)
+                        : select_update_flags<OPT, BF16G, COPY, 4, kRuleNo>(nt, tele, lines);
     if (unroll == 4) return select_update_flags<OPT, BF16G, COPY, 4, kRuleAsk>(nt, tele, lines);
     if (unroll == 1) return select_update_flags<OPT, BF16G, COPY, 1, kRuleAsk>(nt, tele, lines);
     return rule ? select_update_flags<OPT, BF16G, COPY, 2, kRuleYes>(nt, tele, lines) : select_update_flags<OPT, BF16G, COPY, 2, kRuleNo>(nt, tele, lines);
@@ -1310,8 +1316,8 @@ hipError_t launch_update(const DeviceTables& t, const UpdateArgs& a, int optimiz
                          int with_copy, int unroll, int items_per_chunk, int nt, int tele, int grid,
                          hipStream_t stream, bool device_scalars, const FusedRule& rule, const Exchange& exchange)
 {
-    select_update(optimizer, grad_bf16, with_copy, unroll, nt, tele, t.off_lines != 0, rule.ema != nullptr, exchange.words != nullptr)<<<dim3(grid), dim3(kBlock), 0, stream>>>(
-        t, a, log2_of(items_per_chunk), device_scalars ? t.scalars : nullptr, rule, exchange);
+    const UpdateFn fn = select_update(optimizer, grad_bf16, with_copy, unroll, nt, tele, t.off_lines != 0, rule.ema != nullptr, exchange.words != nullptr);
+    fn<<<dim3(grid), dim3(kBlock), 0, stream>>>(t, a, log2_of(items_per_chunk), device_scalars ? t.scalars : nullptr, rule, exchange);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !tele) return e;
     finalize_telemetry_kernel<<<dim3(t.n_tensors, 3), dim3(kBlock), 0, stream>>>(t, (uint32_t)items_per_chunk);

@@ -4,15 +4,15 @@
 //
 //   muon_momentum_kernel    per chunk:  M <- mu M + h g;  partial sum of squares of U
 //                                       (U = h g + mu M in the Nesterov form, U = M otherwise)
-//   muon_normalise_kernel   per batch:  X0 = bf16(U / (||U||_F + 1e-7)) of every matrix into the zero-padded workspace,
+//   muon_normalise_kernel   per round:  X0 = bf16(U / (||U||_F + 1e-7)) of every matrix into the zero-padded workspace,
 //                                       tall ones transposed
-//   muon_apply_kernel       per batch:  theta <- theta - lr (wd theta + scale O) of every matrix, optional bf16 copy
+//   muon_apply_kernel       per round:  theta <- theta - lr (wd theta + scale O) of every matrix, optional bf16 copy
 //
-// A batch is one launch of each, over all of its matrices: a matrix of a few hundred rows is read in two microseconds,
-// less than a launch takes.  48 hidden matrices of GPT-2-small (85 M parameters, bf16 gradients, three batches): normalise 164 us in
-// all (48 x 7.7 with a launch per matrix; 8 B per parameter, 4.2 TB/s), apply 181 us (48 x 6.0; 12 B, 5.6 TB/s).  872 M parameters at
-// Llama-3-8B shapes, fp32 gradients: normalise 1.65 ms (10 B, 5.3 TB/s; with X and its transpose to write 1.94), apply 1.53 ms (10 B,
-// 5.7 TB/s).
+// A round, all batches that are in the workspace together, is one launch of each over all of its matrices: a matrix of a few hundred
+// rows is read in two microseconds, less than a launch takes.  48 hidden matrices of GPT-2-small (85 M parameters, bf16 gradients, three
+// batches): normalise 119 us (48 x 7.7 with a launch per matrix; 8 B per parameter), apply 177 us (48 x 6.0; 12 B).  872 M
+// parameters at Llama-3-8B shapes, fp32 gradients: normalise 1.65 ms (10 B; with X and its transpose to write 1.94), apply 1.55 ms
+// (10 B).
 //
 // The clip coefficient h of every tensor comes from the same norm and rule kernels as for AdamW and Lion
 // (kernels.hip); the Newton-Schulz products run in muon_gemm.hip.  Arithmetic is double with one rounding per

@@ -229,7 +229,9 @@ extern "C" int adagc_step_static(const adagc_tensor_desc* descs, int64_t n_tenso
     UpdateArgs u;
     host_step_scalars(*hp, step, r, u);
     FusedRule rule{};
-    if (largest <= kFusedMaxChunks * kChunkElems && items <= fused_max_items(cfg->optimizer, items_per_chunk, 0) && !r.warmup && r.mode == ADAGC_MODE_ADAGC) rule = FusedRule{ema_norms, r};
+    if (largest <= kFusedMaxChunks * kChunkElems && items <= fused_max_items(cfg->optimizer, items_per_chunk, 0) && !r.warmup &&
+        r.mode == ADAGC_MODE_ADAGC)
+        rule = FusedRule{ema_norms, r};
     const LaunchShape shape{(int64_t)n_long, (int64_t)n_short, (int64_t)n_tiny, n_full, (largest + kChunkElems - 1) / kChunkElems,
                             largest <= kChunkElems / items_per_chunk};
     const bool one_launch = rule.ema && 2 * n_chunks + (uint64_t)n_tensors <= kMaxWords &&

@@ -12,15 +12,18 @@ namespace adagc {
 // (adagc_config::grid_blocks) below a workgroup for each work item; 0 elements: never.  The kernel that walks lines spends more
 // instructions, and reads and writes up to 37 elements of a tensor one by one: with few workgroups it is bound by those, and in a small
 // list by the chain of accesses of its first and last tiles.  Time per step without / with, equal tensors of 16501 to 1048577
-// elements end to end, by size of the list in 2^20 elements; and lists of 9, 30 and 64 M elements by workgroups:
-//                      1.5         3           4           6          12          160         256         320         640
-//   AdamW, copy        .95 - 1.02  1.01 - 1.07 1.03 - 1.06 1.03 - 1.09 1.07 - 1.11 .97 - 1.07  1.06 - 1.24 1.08 - 1.18 1.07 - 1.20
-//   AdamW, bf16        .95 - 1.00  .99 - 1.06  1.00 - 1.03 1.03 - 1.07 1.04       .90 - .92   .98 - 1.01  1.00 - 1.10 1.06 - 1.11
-//   AdamW, f32         .95 - 1.02  .97 - 1.03  .96 - 1.01  .99 - 1.04 1.02 - 1.04 .83 - .84   .95 - 1.03  1.02 - 1.12 .98 - 1.08
-//   Lion, bf16 + copy  .94 - 1.01  .97 - 1.01  .99 - 1.00  .97 - 1.00 1.01 - 1.02 .82 - .84   .85 - .89   .91 - .99   1.07 - 1.17
-// (Those figures are with AdamW in items of 4096 elements.  In items of 2048 and at four waves per SIMD, sizes 1.5, 3, 4, 6, 12, 32: with the copy .98 - .99, 1.02 - 1.03,
-// 1.02 - 1.06, 1.07 - 1.08, 1.11, 1.12 - 1.14; bf16 .96 - .98, .96 - 1.00, .99 - 1.01, 1.03 - 1.04, 1.06 - 1.07, 1.09 - 1.10; f32 .97, .97 - 1.00, .99 - 1.01, 1.02 - 1.04,
-// 1.06, 1.09 - 1.10: the same lines.)
+// elements end to end, by size of the list in 2^20 elements:
+//                      1.5         3           4           6           12          32
+//   AdamW, copy        .98 - .99   1.02 - 1.03 1.02 - 1.06 1.07 - 1.08 1.11        1.12 - 1.14
+//   AdamW, bf16        .96 - .98   .96 - 1.00  .99 - 1.01  1.03 - 1.04 1.06 - 1.07 1.09 - 1.10
+//   AdamW, f32         .97         .97 - 1.00  .99 - 1.01  1.02 - 1.04 1.06        1.09 - 1.10
+//   Lion, bf16 + copy  .94 - 1.01  .97 - 1.01  .99 - 1.00  .97 - 1.00  1.01 - 1.02
+// and lists of 9, 30 and 64 M elements by workgroups (AdamW then with 4 vectors in flight and items of 4096 elements):
+//                      160         256         320         640
+//   AdamW, copy        .97 - 1.07  1.06 - 1.24 1.08 - 1.18 1.07 - 1.20
+//   AdamW, bf16        .90 - .92   .98 - 1.01  1.00 - 1.10 1.06 - 1.11
+//   AdamW, f32         .83 - .84   .95 - 1.03  1.02 - 1.12 .98 - 1.08
+//   Lion, bf16 + copy  .82 - .84   .85 - .89   .91 - .99   1.07 - 1.17
 // (Lion at 8: 1.00 - 1.02, with 512 workgroups .93 - 1.04.  Fewer, larger work items, adagc_config::update_split 1 or 2: 1.01 - 1.13 at
 // the size where the line lies and twice that.)
 struct LineLimits {

@@ -190,13 +190,13 @@ def test_steps_that_overlap_leave_nothing_behind():
     ctx.close()
 
 
-# The rule's two limits, 64 chunks of a tensor and 1024 work items (4096 elements each with AdamW, 2048 with Lion): at them and one
+# The rule's two limits, 64 chunks of a tensor and 16384 work items of 2048 elements with AdamW, 8192 with Lion: at them and one
 # beyond, in whole chunks and in short ones.
 FUSED = {"64_chunks": [64 * 16384, 5], "65_chunks": [64 * 16384 + 1, 5], "ragged_64th": [63 * 16384 + 1, 16385],
-         "1024_long_adamw": [64 * 16384] * 4, "1025_long_adamw": [64 * 16384] * 4 + [1],
-         "1024_long_lion": [64 * 16384] * 2, "1025_long_lion": [64 * 16384] * 2 + [1],
-         "1024_short_adamw": [4096] * 1024, "1025_short_adamw": [4096] * 1025,
-         "1024_short_lion": [2048] * 1024, "1025_short_lion": [2048] * 1025, "one": [1], "tiny_and_long": [1000] * 300 + [17000]}
+         "16384_long_adamw": [64 * 16384] * 32, "16385_long_adamw": [64 * 16384] * 32 + [1],
+         "8192_long_lion": [64 * 16384] * 16, "8193_long_lion": [64 * 16384] * 16 + [1],
+         "16384_short_adamw": [4096] * 8192, "16385_short_adamw": [4096] * 8192 + [1],
+         "8192_short_lion": [4096] * 4096, "8193_short_lion": [4096] * 4096 + [1], "one": [1], "tiny_and_long": [1000] * 300 + [17000]}
 
 
 @pytest.mark.parametrize("numels", FUSED.values(), ids=FUSED.keys())

@@ -95,8 +95,8 @@ def test_a_chosen_split_or_grid_has_the_vectors_in_flight_that_suit_it(tmp_path)
 
 
 def test_the_largest_launches_have_larger_items(tmp_path):
-    """From 384 Mi elements AdamW has 4 vectors in flight and items of 4096 elements, unless the caller chooses."""
-    at = 384 << 20
+    """From 200 Mi elements AdamW has 4 vectors in flight and items of 4096 elements, unless the caller chooses."""
+    at = 200 << 20
     asked = [(ADAMW, 0, 0, 0, at - 1, 2, 8), (ADAMW, 0, 0, 0, at, 4, 4), (ADAMW, 0, 0, 0, 1 << 34, 4, 4), (ADAMW, 2, 0, 0, at, 2, 8),
              (ADAMW, 0, 2, 0, at, 4, 2), (ADAMW, 1, 0, 0, at, 1, 8), (LION, 0, 0, 0, 1 << 34, 2, 8)]
     assert [x[:2] for x in _update_items(tmp_path, [x[:5] for x in asked])] == [x[5:] for x in asked]
