@@ -144,9 +144,9 @@ constexpr int default_items(int unroll) { return kVecPerLane >= unroll ? kVecPer
 // items of 4096 too, as it fetches one after the other: GPT-2-small with 160, 1024 and 16384 workgroups, 2 and 2048 / 4 and 4096: 906 / 762,
 // 721 / 691, 662 / 657, bf16 and the copy 991 / 774, 694 / 664, 645 / 625 (320: 784 / 827, 770 / 811; lists of 64 M 444 / 446, 475 / 478).
 // The largest launches (elems: the list's, or a group's: see kGroupBytes) have AdamW's 4 vectors and items of 4096.  us per step taken whole, 2 and
-// 2048 / 4 and 4096, several placements of the arrays: f32 124 M parameters 616 / 626, 183 M 922 / 930, 238 M 1200 / 1211 and 1215 / 1224 (under
-// Clippy 1725 / 1694), 271 M 1374 / 1382 and 1449 / 1433, 354 M 1856 / 1832, 374 M 1975 / 1953 and 1936 / 1931, 423 M 2251 / 2229, 536 M 2828 / 2818,
-// 941 M 5300 / 5164; bf16 and the copy 587 / 595, 873 / 880, 1147 / 1157 (1695 / 1661), 1306 / 1312 and 1314 / 1318, 1769 / 1769, 1870 / 1854 and
+// 2048 / 4 and 4096, several placements of the arrays: f32 124 M parameters 616 / 626, 183 M 922 / 930, 238 M 1200 / 1211 and 1215 / 1224,
+// 271 M 1374 / 1382 and 1449 / 1433, 354 M 1856 / 1832, 374 M 1975 / 1953 and 1936 / 1931, 423 M 2251 / 2229, 536 M 2828 / 2818,
+// 941 M 5300 / 5164; bf16 and the copy 587 / 595, 873 / 880, 1147 / 1157, 1306 / 1312 and 1314 / 1318, 1769 / 1769, 1870 / 1854 and
 // 1823 / 1837, 2136 / 2090, 2667 / 2642, 4893 / 4737; in list order (adagc_step_static) 271 M 1351 / 1387, 374 M 1952 / 1947, 423 M 2236 / 2246, 536 M
 // 2979 / 2828, 941 M 5041 / 4887.  The smaller items even out a launch, the larger ones open fewer DRAM rows at once.
 constexpr int64_t kWideItemsElems = (int64_t)200 << 20;
