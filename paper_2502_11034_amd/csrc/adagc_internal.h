@@ -212,6 +212,23 @@ inline bool stream_gradients(int64_t total_elems, bool grad_bf16) { return total
 // 2931 / 2669; Lion fp32 108 M 387 / 390, 133 M 483 / 473, 296 M 1075 / 1057, bf16 and the copy 583 M 2005 / 1883.  Groups of 128, 256, 512 and 1024 MiB:
 // 1500 ragged tensors of 1.6 GB of gradients 1965, 1905, 1994, 2007 (whole 2039), Llama shapes 9.93, 9.86, 9.95, 10.08 ms (10.22).
 constexpr int64_t kGroupBytes = (int64_t)256 << 20, kGroupedBytes = (int64_t)450 << 20;
+// Where the group that begins with tensor `first` ends; most: kGroupBytes in elements.  A small tensor before or after one that (nearly) fills a
+// group by itself goes with it: three launches and the end of each cost some 10 us, and 16 MiB of gradients from the cache save 3.
+// us per step as a whole / small tensors in groups of their own / so, Lion f32: 8 tensors of 70 M elements with one of 4096 after each 2064 / 2073 / 1961,
+// 5 with three each 1270 / 1285 / 1204, two of 71 M with two of 1000 each 519 / 524 / 499; AdamW f32 2755 / 2652 / 2414, 1733 / 1677 / 1556,
+// 701 / 686 / 661.
+inline int64_t group_end(const adagc_tensor_desc* descs, int64_t n_tensors, int64_t first, int64_t most)
+{
+    int64_t elems = descs[first].numel, largest = elems, end = first + 1;
+    for (; end < n_tensors; ++end) {
+        const int64_t next = descs[end].numel;
+        if (next > largest) largest = next;
+        const int64_t with_small = largest + most / 16;
+        if (elems + next > (with_small > most ? with_small : most)) break;
+        elems += next;
+    }
+    return end;
+}
 
 // Small lists evaluate the per-tensor rule (Eq. 3) inside the update kernel, every wave for its own tensor, from the tensor's
 // partial sums and a copy of gamma that the norm kernel makes: one launch less, for one more load per wave.  It needs tensors whose

@@ -286,13 +286,17 @@ extern "C" int adagc_create(adagc_ctx** out, const adagc_tensor_desc* descs, int
             for (int64_t first = 0; rc == ADAGC_OK && first < n_tensors;) {
                 adagc_ctx::TensorGroup g;
                 g.first = first;
-                do {
-                    g.elems += descs[first++].numel;
-                    ++g.count;
-                } while (first < n_tensors && g.elems + descs[first].numel <= most);
+                first = group_end(descs, n_tensors, first, most);
+                g.count = first - g.first;
+                for (int64_t i = g.first; i < first; ++i) g.elems += descs[i].numel;
                 g.update = update_items(cfg->optimizer, cfg->unroll, cfg->update_split, cfg->grid_blocks, g.elems);
                 rc = append_range((size_t)c->chunk_begin[(size_t)g.first], (size_t)c->chunk_begin[(size_t)first], group_work, group_items, g);
                 c->tensor_groups.push_back(g);
+            }
+            if (c->tensor_groups.size() == 1) {           // the list as a whole
+                c->tensor_groups.clear();
+                group_work.clear();
+                group_items.clear();
             }
         }
     } catch (const std::bad_alloc&) { rc = ADAGC_ERR_OOM; }

@@ -100,3 +100,29 @@ def test_the_largest_launches_have_larger_items(tmp_path):
     asked = [(ADAMW, 0, 0, 0, at - 1, 2, 8), (ADAMW, 0, 0, 0, at, 4, 4), (ADAMW, 0, 0, 0, 1 << 34, 4, 4), (ADAMW, 2, 0, 0, at, 2, 8),
              (ADAMW, 0, 2, 0, at, 4, 2), (ADAMW, 1, 0, 0, at, 1, 8), (LION, 0, 0, 0, 1 << 34, 2, 8)]
     assert [x[:2] for x in _update_items(tmp_path, [x[:5] for x in asked])] == [x[5:] for x in asked]
+
+
+MIB = 1 << 20
+GROUP = 64 * MIB              # elements of a full group, f32
+# list, sizes of its groups in tensors
+GROUPS = [([1], [1]), ([GROUP, 1], [2]), ([1, GROUP], [2]), ([GROUP // 2] * 4 + [1], [2, 2, 1]), ([GROUP // 2 + 1] * 3, [1, 1, 1]),
+          ([GROUP + 7, 4096] * 3, [2, 2, 2]), ([4096, 4096, 2 * GROUP, 4096, GROUP + 7, 4096], [4, 2]), ([9 * GROUP] + [1000] * 7, [8]),
+          ([GROUP, GROUP // 16], [2]), ([GROUP, GROUP // 16 + 1], [1, 1]), ([GROUP // 16, GROUP], [2]), ([GROUP // 16 + 1, GROUP], [1, 1]),
+          ([GROUP] + [GROUP // 32] * 3, [3, 1]), ([GROUP * 15 // 16, GROUP // 16, 1], [2, 1]), ([MIB] * 130, [64, 64, 2])]
+
+
+@pytest.fixture(scope="module")
+def groups(tmp_path_factory):
+    exe = _driver(tmp_path_factory.mktemp("groups"), "groups_check")
+
+    def ask(numels):
+        line = " ".join(str(x) for x in [GROUP, len(numels)] + numels)
+        ends = [int(x) for x in subprocess.run([exe], input=line, capture_output=True, text=True, check=True, timeout=60).stdout.split()]
+        assert ends[-1] == len(numels)
+        return [b - a for a, b in zip([0] + ends, ends)]
+    return ask
+
+
+@pytest.mark.parametrize("numels, sizes", GROUPS, ids=range(len(GROUPS)))
+def test_small_tensors_beside_a_large_one_are_no_group_of_their_own(groups, numels, sizes):
+    assert groups(numels) == sizes
